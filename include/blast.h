@@ -28,8 +28,8 @@
  *    compute-unit count, of which kernels have had their dynamic-LDS limit raised
  *    and of the address of the scratch array below (all atomics: host threads may
  *    race on them); one small pinned host buffer per host thread that has called
- *    blast_bsr_pack (hipHostMalloc, never freed); the last HIP error text per
- *    host thread; and, on every GPU the library is loaded on, the device array of
+ *    blast_bsr_pack or blast_bsr_transpose (hipHostMalloc, never freed); the last HIP
+ *    error text per host thread; and, on every GPU the library is loaded on, the device array of
  *    BLAST_STATIC_SCRATCH_BYTES behind blast_sparse_mlp_static.
  *  - Every call returns 0 (BLAST_OK) or a negative error code.  Argument errors
  *    (INVALID_ARG, SHAPE, UNSUPPORTED_BLOCK, WORKSPACE) are found before anything
@@ -299,7 +299,7 @@ int blast_sparse_mlp_e5m2w_workspace(const blast_bsr_view* Wgate, int64_t T, siz
  *   aux_t             out, may be NULL; at least blast_bsr_aux_bytes(cols, rows, b, W->nnz) bytes
  *   max_row_blocks_t_out  HOST, may be NULL: stored blocks of the fullest block column of W (0 without
  *                     aux_t); goes into the view's max_row_blocks.  Asking for it makes the call wait for
- *                     `stream` (one small copy); otherwise the call never synchronises.
+ *                     `stream`; otherwise the call never synchronises.
  * Errors: INVALID_ARG, SHAPE, UNSUPPORTED_BLOCK, WORKSPACE (W->aux missing, aux_t too small), HIP.
  */
 int blast_bsr_transpose(const blast_bsr_view* W, int32_t* row_ptr_t, int32_t* col_idx_t, uint16_t* vals_t,

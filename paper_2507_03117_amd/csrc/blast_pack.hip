@@ -711,6 +711,96 @@ __global__ __launch_bounds__(1024) void k_masks_small(const double* __restrict__
     if (j < per && e0 + j < n) mask[e0 + j] = ((keep_w >> j) & 1u) ? 1 : (((keep_g >> j) & 1u) ? 2 : 0);
 }
 
+// Rows by population, descending, stable: rord (LDS) and row_order get the schedule of nbr <= 1024 rows; run by a
+// workgroup of 1024 threads.  rcnt: 1024 populations in LDS, zero beyond nbr (which never counts).  P threads share
+// a row, each comparing it with a contiguous part of the rows (four populations per LDS read).
+__device__ __forceinline__ void schedule_small(const int* rcnt, int nbr, int* rord, int* __restrict__ row_order) {
+  const int tid = threadIdx.x;
+  const int pl = 31 - __clz(1024 / nbr);         // log2 P, P = largest power of two <= 1024 / nbr ...
+  const int lp = pl > 6 ? 6 : pl, P = 1 << lp;   // ... and <= 64, so that the P threads sit in one wave
+  const int r = tid >> lp, part = tid & (P - 1);
+  const int len = (((nbr + P - 1) >> lp) + 3) & ~3;
+  const int cr = r < nbr ? rcnt[r] : 0;
+  int rank = 0;
+  const int q0 = part * len;
+#pragma unroll 4
+  for (int q = q0; q < q0 + len; q += 4) {
+    const int4 c4 = *reinterpret_cast<const int4*>(&rcnt[q]);
+    rank += (c4.x > cr || (c4.x == cr && q < r)) ? 1 : 0;
+    rank += (c4.y > cr || (c4.y == cr && q + 1 < r)) ? 1 : 0;
+    rank += (c4.z > cr || (c4.z == cr && q + 2 < r)) ? 1 : 0;
+    rank += (c4.w > cr || (c4.w == cr && q + 3 < r)) ? 1 : 0;
+  }
+  for (int d = P >> 1; d > 0; d >>= 1) rank += __shfl_xor(rank, d, kWave);
+  if (r < nbr && part == 0) {
+    rord[rank] = r;
+    row_order[rank] = r;
+  }
+}
+
+// Both chunk plans of nbr <= 1024 rows in schedule order, cut into chunks of at most 16 / 64 blocks (an empty row
+// still gets one chunk: its output has to be written); run by a workgroup of 1024 threads.  rptr, rord: row pointers
+// and schedule in LDS; sh: LDS scratch of 3 ints.  Thread 0 returns with the fullest row's population.
+__device__ __forceinline__ int chunk_plans_small(const int* rptr, const int* rord, int nbr, const PlanOut& narrow,
+                                                 const PlanOut& wide, int* wave_tot, int* sh) {
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    sh[0] = 0;  // fullest row
+    sh[1] = 0;  // chunks of the rows that the first plan cuts
+    sh[2] = 0;  // ... the second plan
+  }
+  wg_barrier<true>();
+  constexpr int ls0 = __builtin_ctz(blast::kChunkBlocks), ls1 = __builtin_ctz(blast::kWideChunkBlocks);
+  int r = 0, kb = 0, ke = 0, n0 = 0, n1 = 0;
+  if (tid < nbr) {
+    r = rord[tid];
+    kb = rptr[r];
+    ke = rptr[r + 1];
+    n0 = (ke - kb + (1 << ls0) - 1) >> ls0;
+    n1 = (ke - kb + (1 << ls1) - 1) >> ls1;
+    n0 = n0 < 1 ? 1 : n0;
+    n1 = n1 < 1 ? 1 : n1;
+    atomicMax(&sh[0], ke - kb);
+    if (n0 > 1) atomicAdd(&sh[1], n0);
+    if (n1 > 1) atomicAdd(&sh[2], n1);
+    narrow.row_slot[r] = n0 > 1 ? tid : -1;
+  }
+  int total;
+  const int first = block_exscan<true>(n0 | (n1 << 16), wave_tot, total);
+  if (tid < nbr) {
+    const int f0 = first & 0xFFFF, f1 = first >> 16;
+    narrow.row_chunk0[r] = n0 > 1 ? f0 : -1;
+    for (int j = 0; j < n0; ++j) {
+      const int e = f0 + j, b0 = kb + (j << ls0);
+      if (e < narrow.cap) {
+        narrow.chunk_row[e] = r | (n0 > 1 ? (int)0x80000000u : 0);
+        narrow.chunk_kb[e] = b0;
+        narrow.chunk_ke[e] = (b0 + (1 << ls0) < ke) ? b0 + (1 << ls0) : ke;
+      }
+    }
+    for (int j = 0; j < n1; ++j) {
+      const int e = f1 + j, b0 = kb + (j << ls1);
+      if (e < wide.cap) {
+        wide.chunk_row[e] = r | (n1 > 1 ? (int)0x80000000u : 0);
+        wide.chunk_kb[e] = b0;
+        wide.chunk_ke[e] = (b0 + (1 << ls1) < ke) ? b0 + (1 << ls1) : ke;
+      }
+    }
+  }
+  const int heavy = sh[0];
+  if (tid == 0) {
+    narrow.hdr[0] = total & 0xFFFF;
+    narrow.hdr[1] = heavy;
+    narrow.hdr[2] = 1 << ls0;
+    narrow.hdr[3] = sh[1];
+    wide.hdr[0] = total >> 16;
+    wide.hdr[1] = heavy;
+    wide.hdr[2] = 1 << ls1;
+    wide.hdr[3] = sh[2];
+  }
+  return heavy;
+}
+
 struct SmallOut {
   int* row_ptr;
   int* col_idx;
@@ -798,91 +888,13 @@ __global__ __launch_bounds__(1024) void k_pack_small(const double* __restrict__ 
       if (!o.col_ptr) o.scalars[1] = 0;
     }
   }
-  // schedule: rows by population, descending, stable.  P threads share a row, each comparing it with a
-  // contiguous part of the rows (four populations per LDS read; the array is zero beyond nbr, which never counts).
-  {
-    const int pl = 31 - __clz(1024 / nbr);         // log2 P, P = largest power of two <= 1024 / nbr ...
-    const int lp = pl > 6 ? 6 : pl, P = 1 << lp;   // ... and <= 64, so that the P threads sit in one wave
-    const int r = tid >> lp, part = tid & (P - 1);
-    const int len = (((nbr + P - 1) >> lp) + 3) & ~3;
-    const int cr = r < nbr ? rcnt[r] : 0;
-    int rank = 0;
-    const int q0 = part * len;
-#pragma unroll 4
-    for (int q = q0; q < q0 + len; q += 4) {
-      const int4 c4 = *reinterpret_cast<const int4*>(&rcnt[q]);
-      rank += (c4.x > cr || (c4.x == cr && q < r)) ? 1 : 0;
-      rank += (c4.y > cr || (c4.y == cr && q + 1 < r)) ? 1 : 0;
-      rank += (c4.z > cr || (c4.z == cr && q + 2 < r)) ? 1 : 0;
-      rank += (c4.w > cr || (c4.w == cr && q + 3 < r)) ? 1 : 0;
-    }
-    for (int d = P >> 1; d > 0; d >>= 1) rank += __shfl_xor(rank, d, kWave);
-    if (r < nbr && part == 0) {
-      rord[rank] = r;
-      o.row_order[rank] = r;
-    }
-  }
+  schedule_small(rcnt, nbr, rord, o.row_order);
   wg_barrier<true>();
   if (!o.col_ptr) return;
 
-  // both chunk plans: rows in schedule order, cut into chunks of at most 16 / 64 blocks (an empty row still gets
-  // one chunk: its output has to be written)
   {
-    if (tid == 0) {
-      sh[0] = 0;  // fullest row
-      sh[1] = 0;  // chunks of the rows that the first plan cuts
-      sh[2] = 0;  // ... the second plan
-    }
-    wg_barrier<true>();
-    constexpr int ls0 = __builtin_ctz(blast::kChunkBlocks), ls1 = __builtin_ctz(blast::kWideChunkBlocks);
-    int r = 0, kb = 0, ke = 0, n0 = 0, n1 = 0;
-    if (tid < nbr) {
-      r = rord[tid];
-      kb = rptr[r];
-      ke = rptr[r + 1];
-      n0 = (ke - kb + (1 << ls0) - 1) >> ls0;
-      n1 = (ke - kb + (1 << ls1) - 1) >> ls1;
-      n0 = n0 < 1 ? 1 : n0;
-      n1 = n1 < 1 ? 1 : n1;
-      atomicMax(&sh[0], ke - kb);
-      if (n0 > 1) atomicAdd(&sh[1], n0);
-      if (n1 > 1) atomicAdd(&sh[2], n1);
-      narrow.row_slot[r] = n0 > 1 ? tid : -1;
-    }
-    int total;
-    const int first = block_exscan<true>(n0 | (n1 << 16), wave_tot, total);
-    if (tid < nbr) {
-      const int f0 = first & 0xFFFF, f1 = first >> 16;
-      narrow.row_chunk0[r] = n0 > 1 ? f0 : -1;
-      for (int j = 0; j < n0; ++j) {
-        const int e = f0 + j, b0 = kb + (j << ls0);
-        if (e < narrow.cap) {
-          narrow.chunk_row[e] = r | (n0 > 1 ? (int)0x80000000u : 0);
-          narrow.chunk_kb[e] = b0;
-          narrow.chunk_ke[e] = (b0 + (1 << ls0) < ke) ? b0 + (1 << ls0) : ke;
-        }
-      }
-      for (int j = 0; j < n1; ++j) {
-        const int e = f1 + j, b0 = kb + (j << ls1);
-        if (e < wide.cap) {
-          wide.chunk_row[e] = r | (n1 > 1 ? (int)0x80000000u : 0);
-          wide.chunk_kb[e] = b0;
-          wide.chunk_ke[e] = (b0 + (1 << ls1) < ke) ? b0 + (1 << ls1) : ke;
-        }
-      }
-    }
-    if (tid == 0) {
-      const int heavy = sh[0];
-      narrow.hdr[0] = total & 0xFFFF;
-      narrow.hdr[1] = heavy;
-      narrow.hdr[2] = 1 << ls0;
-      narrow.hdr[3] = sh[1];
-      wide.hdr[0] = total >> 16;
-      wide.hdr[1] = heavy;
-      wide.hdr[2] = 1 << ls1;
-      wide.hdr[3] = sh[2];
-      o.scalars[1] = heavy;
-    }
+    const int heavy = chunk_plans_small(rptr, rord, nbr, narrow, wide, wave_tot, sh);
+    if (tid == 0) o.scalars[1] = heavy;
   }
 
   // column-grouped index: the same count with the blocks taken in column-major order
@@ -926,19 +938,101 @@ __global__ __launch_bounds__(1024) void k_pack_small(const double* __restrict__ 
   }
 }
 
-// One workgroup per stored block of the transposed matrix: block e of the output is the transpose of
-// block src_blk[e] of the input.  Rows are read and written whole; the turn happens in LDS (row pitch
-// b + 2 elements, so that a column walk does not stay on one bank).
-__global__ __launch_bounds__(256) void k_transpose_blocks(const uint16_t* __restrict__ vals, int b,
-                                                          const int* __restrict__ src_blk,
-                                                          uint16_t* __restrict__ vals_t) {
-  extern __shared__ uint16_t tile[];
-  const int pitch = b + 2;
-  const uint16_t* src = vals + (int64_t)src_blk[blockIdx.x] * b * b;
-  uint16_t* dst = vals_t + (int64_t)blockIdx.x * b * b;
-  for (int idx = threadIdx.x; idx < b * b; idx += blockDim.x) tile[(idx / b) * pitch + idx % b] = src[idx];
+struct TransposeArgs {
+  // the matrix: its column-grouped index (BCSC), row pointers and column indices
+  const int* col_ptr;
+  const int* csc_row;
+  const int* csc_blk;
+  const int* row_ptr;
+  const int* col_idx;
+  const uint16_t* vals;
+  int64_t nbr, nbc, nnz;
+  // its transpose: BSR arrays, and in aux (null pointers without) the column-grouped index
+  int* row_ptr_t;
+  int* col_idx_t;
+  uint16_t* vals_t;
+  int* row_order_t;
+  int* col_ptr_t;
+  int* csc_row_t;
+  int* csc_blk_t;
+  PlanOut narrow, wide;  // aux only
+  int* max_row_out;      // aux only: the fullest row of the transpose
+  int index_job;         // workgroup 0 makes schedule and chunk plans (up to 1024 rows, fewer than 65536 chunks)
+};
+
+// The whole packed transpose in one launch.  Workgroup 0 writes the pointer arrays and, for up to 1024 block rows of
+// the transpose, its schedule and chunk plans; the others turn the blocks, kTransposeElems values each (one block of
+// 128 x 128, four of 64 x 64, ...), and write their entries of the index arrays.  A block of the transpose is read
+// and written in 16-byte pieces, whole lines; the turn happens in LDS (row pitch b + 2 elements, so that a column
+// walk does not stay on one bank).
+// What bounds it: the latency of the index job beside a copy of the blocks.  In a training step of an 8192 x 3072
+// matrix (b = 64, 1229 blocks, 2000 tokens: forward, transpose, dX, dW) the ten launches before it (copies of the
+// four index arrays, schedule, chunk plans, inverse permutation, blocks two bytes at a time, a copy back of one
+// number) were 45 us of kernels and their gaps; the step took 199 us with them and takes 147 us with this one.
+constexpr int kTransposeElems = 16384;
+template <int B>
+__global__ __launch_bounds__(1024) void k_transpose(const TransposeArgs a) {
+  constexpr int NB = kTransposeElems / (B * B);  // blocks per workgroup
+  constexpr int CPR = B / 8, PITCH = B + 2;      // 16-byte pieces per block row; LDS row pitch
+  constexpr int kTile = B * PITCH;
+  __shared__ __attribute__((aligned(16))) uint16_t tile[NB * kTile];
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    for (int64_t i = tid; i <= a.nbc; i += 1024) a.row_ptr_t[i] = a.col_ptr[i];
+    if (a.col_ptr_t)
+      for (int64_t i = tid; i <= a.nbr; i += 1024) a.col_ptr_t[i] = a.row_ptr[i];
+    if (!a.index_job) return;
+    // the index job's LDS lies over the tile
+    struct Sched {
+      int rcnt[1024], rptr[1025], rord[1024], wave_tot[16], sh[3];
+    };
+    static_assert(sizeof(Sched) <= sizeof(tile), "the schedule fits the tile");
+    Sched& s = *reinterpret_cast<Sched*>(tile);
+    const int n = (int)a.nbc;
+    s.rcnt[tid] = tid < n ? a.col_ptr[tid + 1] - a.col_ptr[tid] : 0;
+    if (tid < n) s.rptr[tid] = a.col_ptr[tid];
+    if (tid == 0) s.rptr[n] = a.col_ptr[n];
+    wg_barrier<true>();
+    schedule_small(s.rcnt, n, s.rord, a.row_order_t);
+    wg_barrier<true>();
+    if (!a.max_row_out) return;
+    const int heavy = chunk_plans_small(s.rptr, s.rord, n, a.narrow, a.wide, s.wave_tot, s.sh);
+    if (tid == 0) *a.max_row_out = heavy;
+    return;
+  }
+  const int64_t e0 = (int64_t)(blockIdx.x - 1) * NB;
+  if (tid < NB && e0 + tid < a.nnz) {
+    const int64_t e = e0 + tid;
+    a.col_idx_t[e] = a.csc_row[e];
+    if (a.csc_row_t) {
+      a.csc_row_t[e] = a.col_idx[e];
+      a.csc_blk_t[a.csc_blk[e]] = (int)e;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kTransposeElems / 8 / 1024; ++q) {
+    const int p = q * 1024 + tid, blk = p / (B * CPR), i = p / CPR % B, c = p % CPR;
+    if (e0 + blk < a.nnz) {
+      const uint4 v = *reinterpret_cast<const uint4*>(a.vals + (int64_t)a.csc_blk[e0 + blk] * (B * B) + i * B + c * 8);
+      uint32_t* dst = reinterpret_cast<uint32_t*>(tile + blk * kTile + i * PITCH + c * 8);
+      dst[0] = v.x;
+      dst[1] = v.y;
+      dst[2] = v.z;
+      dst[3] = v.w;
+    }
+  }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < b * b; idx += blockDim.x) dst[idx] = tile[(idx % b) * pitch + idx / b];
+#pragma unroll
+  for (int q = 0; q < kTransposeElems / 8 / 1024; ++q) {
+    const int p = q * 1024 + tid, blk = p / (B * CPR), j = p / CPR % B, c = p % CPR;
+    if (e0 + blk < a.nnz) {
+      const uint16_t* src = tile + blk * kTile + c * 8 * PITCH + j;
+      uint32_t w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] = (uint32_t)src[2 * u * PITCH] | ((uint32_t)src[(2 * u + 1) * PITCH] << 16);
+      *reinterpret_cast<uint4*>(a.vals_t + (e0 + blk) * (B * B) + j * B + c * 8) = uint4{w[0], w[1], w[2], w[3]};
+    }
+  }
 }
 
 // One workgroup per block of the dense matrix: copies the stored block there, or writes zeros where the
@@ -967,18 +1061,6 @@ __global__ __launch_bounds__(256) void k_unpack_blocks(const int* __restrict__ r
     *reinterpret_cast<uint4*>(dst + (int64_t)i * ldw + j8 * 8) =
         src ? *reinterpret_cast<const uint4*>(src + (int64_t)c * 8) : uint4{0u, 0u, 0u, 0u};
   }
-}
-
-// out[i] = in[i]
-__global__ __launch_bounds__(256) void k_copy_i32(const int* __restrict__ in, int64_t n, int* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = in[i];
-}
-
-// inv[perm[e]] = e
-__global__ __launch_bounds__(256) void k_invert_perm(const int* __restrict__ perm, int64_t n, int* __restrict__ inv) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) inv[perm[e]] = (int)e;
 }
 
 struct PackWs {
@@ -1012,6 +1094,30 @@ int check_shape(int64_t rows, int64_t cols, int32_t b) {
   if (rows % b || cols % b) return BLAST_ERR_SHAPE;
   if (rows / b > INT32_MAX / 2 || cols / b > INT32_MAX / 2 || (rows / b) * (cols / b) > (int64_t)INT32_MAX)
     return BLAST_ERR_INVALID_ARG;
+  return BLAST_OK;
+}
+
+// A small pinned buffer per host thread (allocated on first use and kept) through which numbers come back from the
+// device: a copy into pageable memory costs a call tens of microseconds more.  Kernels can store to it themselves.
+// Null when it cannot be had.
+int* pinned_ints() {
+  static thread_local int* pinned = nullptr;
+  if (!pinned) {
+    void* p = nullptr;
+    if (hipHostMalloc(&p, 64, hipHostMallocDefault) == hipSuccess) {
+      pinned = static_cast<int*>(p);
+    } else {
+      (void)hipGetLastError();
+    }
+  }
+  return pinned;
+}
+
+template <int B>
+int launch_transpose(const TransposeArgs& a, hipStream_t stream) {
+  constexpr int NB = kTransposeElems / (B * B);
+  k_transpose<B><<<dim3((unsigned)(1 + (a.nnz + NB - 1) / NB)), dim3(1024), 0, stream>>>(a);
+  BLAST_LAUNCH_CHECK("k_transpose");
   return BLAST_OK;
 }
 
@@ -1185,18 +1291,8 @@ extern "C" int blast_bsr_pack(const uint16_t* W, int64_t ldw, int64_t rows, int6
   if (int rc = pack_enqueue(W, ldw, rows, cols, b, mode, block_mask, sparsity, row_ptr, col_idx, vals, row_order, aux,
                             aux_bytes, nnz_cap, nullptr, ws, ws_bytes, stream, &scalars))
     return rc;
-  // The two scalars come back through a small pinned buffer (one per host thread, allocated on first use
-  // and kept): a copy into pageable memory costs the call tens of microseconds more.
   int host_vals[2] = {0, 0};
-  static thread_local int* pinned = nullptr;
-  if (!pinned) {
-    void* p = nullptr;
-    if (hipHostMalloc(&p, 64, hipHostMallocDefault) == hipSuccess) {
-      pinned = static_cast<int*>(p);
-    } else {
-      (void)hipGetLastError();
-    }
-  }
+  int* pinned = pinned_ints();
   int* landing = pinned ? pinned : host_vals;
   BLAST_HIP_TRY(hipMemcpyAsync(landing, scalars, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
   BLAST_HIP_TRY(hipStreamSynchronize(stream));
@@ -1243,43 +1339,60 @@ extern "C" int blast_bsr_transpose(const blast_bsr_view* W, int32_t* row_ptr_t, 
   const int* col_ptr = reinterpret_cast<const int*>(ab + A.col_ptr_off);
   const int* csc_row = reinterpret_cast<const int*>(ab + A.csc_row_off);
   const int* csc_blk = reinterpret_cast<const int*>(ab + A.csc_blk_off);
-  auto blocks_for = [](int64_t n) { return dim3((unsigned)((n + 255) / 256)); };
-
-  // BSR of the transpose = the column-grouped (BCSC) view of the input, with every block turned
-  k_copy_i32<<<blocks_for(nbc + 1), dim3(256), 0, stream>>>(col_ptr, nbc + 1, row_ptr_t);
-  BLAST_LAUNCH_CHECK("k_copy_i32(row_ptr_t)");
-  if (nnz > 0) {
-    k_copy_i32<<<blocks_for(nnz), dim3(256), 0, stream>>>(csc_row, nnz, col_idx_t);
-    BLAST_LAUNCH_CHECK("k_copy_i32(col_idx_t)");
-    k_transpose_blocks<<<dim3((unsigned)nnz), dim3(256), (size_t)b * (b + 2) * 2, stream>>>(W->vals, b, csc_blk, vals_t);
-    BLAST_LAUNCH_CHECK("k_transpose_blocks");
-  }
-  if (nbc > 0) {
-    k_row_order<<<blocks_for(nbc), dim3(256), 0, stream>>>(row_ptr_t, nullptr, (int)nbc, row_order_t);
-    BLAST_LAUNCH_CHECK("k_row_order(transpose)");
-  }
-  int heavy = 0;
+  // BSR of the transpose = the column-grouped (BCSC) view of the input, with every block turned; the column-grouped
+  // index of the transpose is the row-grouped one of the input
+  TransposeArgs ta{};
+  ta.col_ptr = col_ptr;
+  ta.csc_row = csc_row;
+  ta.csc_blk = csc_blk;
+  ta.row_ptr = W->row_ptr;
+  ta.col_idx = W->col_idx;
+  ta.vals = W->vals;
+  ta.nbr = nbr;
+  ta.nbc = nbc;
+  ta.nnz = nnz;
+  ta.row_ptr_t = row_ptr_t;
+  ta.col_idx_t = col_idx_t;
+  ta.vals_t = vals_t;
+  ta.row_order_t = row_order_t;
+  // (the plans' scan holds two counts in one word: fewer than 65536 chunks)
+  ta.index_job = nbc > 0 && nbc <= 1024 && nbc + nnz / blast::kChunkBlocks < 65536;
+  int* landing = nullptr;
   if (aux_t) {
     char* at = static_cast<char*>(aux_t);
-    int* hdr = reinterpret_cast<int*>(at + At.hdr_off);
-    PlanOut narrow, wide;
-    plan_outputs(at, At, narrow, wide);
-    k_chunk_plan<<<dim3(1), dim3(1024), 0, stream>>>(row_ptr_t, row_order_t, (int)nbc, narrow, wide, hdr + 1);
-    BLAST_LAUNCH_CHECK("k_chunk_plan(transpose)");
-    // the column-grouped index of the transpose is the row-grouped one of the input
-    k_copy_i32<<<blocks_for(nbr + 1), dim3(256), 0, stream>>>(W->row_ptr, nbr + 1,
-                                                              reinterpret_cast<int*>(at + At.col_ptr_off));
-    BLAST_LAUNCH_CHECK("k_copy_i32(col_ptr_t)");
-    if (nnz > 0) {
-      k_copy_i32<<<blocks_for(nnz), dim3(256), 0, stream>>>(W->col_idx, nnz, reinterpret_cast<int*>(at + At.csc_row_off));
-      BLAST_LAUNCH_CHECK("k_copy_i32(csc_row_t)");
-      k_invert_perm<<<blocks_for(nnz), dim3(256), 0, stream>>>(csc_blk, nnz, reinterpret_cast<int*>(at + At.csc_blk_off));
-      BLAST_LAUNCH_CHECK("k_invert_perm");
+    plan_outputs(at, At, ta.narrow, ta.wide);
+    ta.col_ptr_t = reinterpret_cast<int*>(at + At.col_ptr_off);
+    ta.csc_row_t = reinterpret_cast<int*>(at + At.csc_row_off);
+    ta.csc_blk_t = reinterpret_cast<int*>(at + At.csc_blk_off);
+    if (max_row_blocks_t_out) landing = pinned_ints();
+    if (landing) *landing = 0;
+    ta.max_row_out = landing ? landing : ta.narrow.hdr + 1;
+  }
+  int rc;
+  switch (b) {
+    case 16: rc = launch_transpose<16>(ta, stream); break;
+    case 32: rc = launch_transpose<32>(ta, stream); break;
+    case 64: rc = launch_transpose<64>(ta, stream); break;
+    default: rc = launch_transpose<128>(ta, stream); break;
+  }
+  if (rc) return rc;
+  if (!ta.index_job) {  // more rows than one workgroup's schedule holds (or none)
+    if (nbc > 0) {
+      k_row_order<<<dim3((unsigned)((nbc + 255) / 256)), dim3(256), 0, stream>>>(row_ptr_t, nullptr, (int)nbc, row_order_t);
+      BLAST_LAUNCH_CHECK("k_row_order(transpose)");
     }
-    if (max_row_blocks_t_out) {
-      BLAST_HIP_TRY(hipMemcpyAsync(&heavy, hdr + 1, sizeof(int), hipMemcpyDeviceToHost, stream));
-      BLAST_HIP_TRY(hipStreamSynchronize(stream));
+    if (aux_t) {
+      k_chunk_plan<<<dim3(1), dim3(1024), 0, stream>>>(row_ptr_t, row_order_t, (int)nbc, ta.narrow, ta.wide,
+                                                       ta.max_row_out);
+      BLAST_LAUNCH_CHECK("k_chunk_plan(transpose)");
     }
+  }
+  int heavy = 0;
+  if (aux_t && max_row_blocks_t_out) {
+    if (!landing)
+      BLAST_HIP_TRY(hipMemcpyAsync(&heavy, ta.narrow.hdr + 1, sizeof(int), hipMemcpyDeviceToHost, stream));
+    BLAST_HIP_TRY(hipStreamSynchronize(stream));
+    if (landing) heavy = *static_cast<volatile int*>(landing);
   }
   if (max_row_blocks_t_out) *max_row_blocks_t_out = heavy;
   return BLAST_OK;

@@ -219,3 +219,15 @@ def test_backward_llama1b_gate_full_size(api):
     assert want.shape[0] == qs.size
     for n, q in enumerate(qs):
         check_close(dvh[q], want[n], f"1B gate dW block {q}")
+
+
+@pytest.mark.parametrize("M,K,b", [(64, 1024 * 16, 16), (64, 1025 * 16, 16), (1025 * 16, 32, 16), (13 * 32, 7 * 32, 32),
+                                   (5 * 64, 9 * 64, 64), (128, 3 * 128, 128), (128, 128, 128)])
+def test_transpose_at_the_edges_of_its_launches(api, M, K, b):
+    """1024 and 1025 block rows of the transpose (schedule inside the launch, or in launches after it), numbers of
+    blocks that do not fill the last workgroup's 16384 values, a single block; the packed transpose of the transpose
+    is the matrix itself."""
+    rng = np.random.default_rng(M + K)
+    W, mask = _case(rng, M, K, b, 0.4, full_col=True)
+    dt, _ = _check_transpose(api, api.bsr_pack(to_dev(W), b, mask=mask_dev(mask)), W, mask, b)
+    _check_transpose(api, dt, np.ascontiguousarray(W.T), np.ascontiguousarray(mask.T), b)
