@@ -18,6 +18,7 @@
 #include "kern_tile.h"
 #include "kern_stream.h"
 #include "kern_decode.h"
+#include "kern_flat.h"
 #include "kern_b16.h"
 
 using namespace blast_dev;
@@ -1172,7 +1173,7 @@ int launch_decode_w8_ntt(const TileArgs& a, const ChunkPlan& plan, hipStream_t s
   if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_decode<B, DUAL, NTT, CHUNK, XSMALL, false, true>),
                                 C::LDS_BYTES, lds_set))
     return rc;
-  if (CHUNK) {  // rows cut into several chunks are accumulated: clear them first
+  if (CHUNK && !plan.pre_zeroed) {  // rows cut into several chunks are accumulated: clear them first
     StreamArgs sa{a, 0, -1, 0, plan.hdr, plan.chunk_row, plan.chunk_kb, plan.chunk_ke};
     k_zero_shared_rows<B><<<dim3((unsigned)plan.max_chunks, (unsigned)((a.T + 63) / 64)), dim3(256), 0, stream>>>(sa);
     BLAST_LAUNCH_CHECK("k_zero_shared_rows");
@@ -1193,18 +1194,90 @@ int launch_decode_w8_c(const TileArgs& a, const ChunkPlan& plan, hipStream_t str
   return launch_decode_w8_ntt<B, DUAL, 2, 0, CHUNK>(a, plan, stream);
 }
 
+// Large layers: the blocks of many rows as one stream per workgroup (kern_flat.h).
+template <int B, bool DUAL, int XI, bool CHUNK>
+int launch_flat_w8(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream) {
+  using C = FlatCfg<B, DUAL, XI, true>;
+  DecArgs d{};
+  d.m0 = a.m0;
+  d.m1 = a.m1;
+  d.row_order = a.row_order;
+  d.X = a.X;
+  d.sxt = a.sxt;
+  d.Y = a.Y;
+  d.syt = a.syt;
+  d.syi = a.syi;
+  d.y_bf16 = a.y_bf16;
+  d.T = a.T;
+  d.act = a.act;
+  d.hdr = plan.hdr;
+  d.chunk_row = plan.chunk_row;
+  d.chunk_kb = plan.chunk_kb;
+  d.chunk_ke = plan.chunk_ke;
+  d.n_units = a.nbr;
+  if (plan.zero_job && plan.zero_job->hdr && !plan.zero_job->wide) {
+    ZeroJob& z = *plan.zero_job;
+    d.z_blocks = (int)z.max_chunks;
+    d.z_hdr = z.hdr;
+    d.z_chunk_row = z.chunk_row;
+    d.z_chunk_kb = z.chunk_kb;
+    d.z_row_ptr = z.row_ptr;
+    d.z_Y = z.Y;
+    d.z_syt = z.syt;
+    d.z_syi = z.syi;
+    d.z_T = z.T;
+    z.done = true;
+  }
+  static blast::DeviceFlags lds_set;
+  if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_decode_flat<B, DUAL, CHUNK, XI, true>), C::LDS_BYTES,
+                                lds_set))
+    return rc;
+  if (CHUNK && !plan.pre_zeroed) {
+    StreamArgs sa{a, 0, -1, 0, plan.hdr, plan.chunk_row, plan.chunk_kb, plan.chunk_ke};
+    k_zero_shared_rows<B><<<dim3((unsigned)plan.max_chunks, (unsigned)((a.T + 63) / 64)), dim3(256), 0, stream>>>(sa);
+    BLAST_LAUNCH_CHECK("k_zero_shared_rows");
+  }
+  const int slots = cu_count() / (8 * C::SLICES);  // row groups per XCD, one workgroup per CU
+  const int n_slots = slots < 1 ? 1 : (slots > C::MAX_SLOTS ? C::MAX_SLOTS : slots);
+  k_decode_flat<B, DUAL, CHUNK, XI, true><<<dim3((unsigned)(8 * C::SLICES * n_slots)), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(d);
+  BLAST_LAUNCH_CHECK("k_decode_flat");
+  return BLAST_OK;
+}
+
+// One token tile of up to 8 tokens (512 / B copy-instruction rows, or twice that), at most 512 rows or chunks (64 per
+// XCD: one per lane) of at most 512 blocks (`longest`, over both matrices), columns that fit 24 bits, and enough
+// blocks that a CU's share is a stream: 32 slices per CU is a fifth of the 405B-class layer, which gains 25 %; the
+// 8B-shaped one has 11 per CU and would only pay the deal.  (More tokens: a 4 KB activation tile per block leaves
+// sixteen waves a single slot each.)
+template <int B, bool DUAL>
+bool flat_applies(const TileArgs& a, int64_t nnz, int64_t items, int64_t longest) {
+  return a.T <= 8 && items <= 512 && longest > 0 && longest <= FlatCfg<B, DUAL, 1, true>::PM && a.kdim / B < (1 << 24) &&
+         nnz * (B / 16) >= (int64_t)32 * cu_count();
+}
+
+template <int B, bool DUAL, bool CHUNK>
+int launch_flat_w8_t(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream) {
+  if (a.T <= 512 / B) return launch_flat_w8<B, DUAL, 1, CHUNK>(a, plan, stream);
+  return launch_flat_w8<B, DUAL, 8 * B / 512, CHUNK>(a, plan, stream);
+}
+
 // `plan`: the chunk plan of the matrix (single matrix, fp32 output only); taken under the rule of the bf16
 // decode path: when the fullest row, dealt to four waves, is deeper than four times a workgroup slot's share.
 template <int B, bool DUAL>
-int launch_decode_w8(const TileArgs& a, int64_t nnz, const ChunkPlan& plan, hipStream_t stream) {
+int launch_decode_w8(const TileArgs& a, int64_t nnz, int64_t max_row_blocks, const ChunkPlan& plan, hipStream_t stream) {
   if constexpr (!DUAL) {
     if (plan.hdr && !a.y_bf16 && a.T <= kDecodeMaxTokens) {
       double ref = (double)nnz * (B / 16) / (4.0 * 2.0 * cu_count());
       if (ref < blast::kChunkBlocks) ref = blast::kChunkBlocks;
+      if (flat_applies<B, DUAL>(a, nnz, plan.max_chunks, blast::kChunkBlocks))
+        return launch_flat_w8_t<B, false, true>(a, plan, stream);
       if ((double)plan.max_row_blocks / 4.0 > 4.0 * ref) return launch_decode_w8_c<B, false, true>(a, plan, stream);
     }
   }
-  return launch_decode_w8_c<B, DUAL, false>(a, ChunkPlan{}, stream);
+  ChunkPlan side{};  // no chunks; only the side job travels on
+  side.zero_job = plan.zero_job;
+  if (flat_applies<B, DUAL>(a, nnz, a.nbr, max_row_blocks)) return launch_flat_w8_t<B, DUAL, false>(a, side, stream);
+  return launch_decode_w8_c<B, DUAL, false>(a, side, stream);
 }
 
 }  // namespace
@@ -1257,15 +1330,35 @@ extern "C" int blast_sparse_mlp_e5m2w(const blast_bsr_view* Wgate, const uint8_t
   d.nbr = (int)(E / b);
   d.kdim = I;
   d.act = -1;
+  ChunkPlan dplan = plan_of(Wdown, T);
   if (I > 0) {
+    // the rows of Y that the chunked second product accumulates into are cleared on the side by the first launch
+    // (where that is the kernel that can; `done` says whether it has been)
+    ZeroJob zj{};
+    if (dplan.hdr && y_dtype == BLAST_F32 && T <= kDecodeMaxTokens) {
+      zj.hdr = dplan.hdr;
+      zj.chunk_row = dplan.chunk_row;
+      zj.chunk_kb = dplan.chunk_kb;
+      zj.max_chunks = dplan.max_chunks;
+      zj.row_ptr = Wdown->row_ptr;
+      zj.Y = static_cast<float*>(Y);
+      zj.syt = d.syt;
+      zj.syi = d.syi;
+      zj.T = (int)T;
+    }
+    ChunkPlan gplan{};
+    gplan.zero_job = zj.hdr ? &zj : nullptr;
     const int64_t nnz_gu = Wgate->nnz + Wup->nnz;
-    if (int rc = (b == 64) ? launch_decode_w8<64, true>(g, nnz_gu, ChunkPlan{}, stream)
-                           : launch_decode_w8<128, true>(g, nnz_gu, ChunkPlan{}, stream))
+    // (the fullest joint row has at most the sum of the two fullest rows; 0: not known)
+    const int64_t longest = Wgate->max_row_blocks > 0 && Wup->max_row_blocks > 0
+                                ? (int64_t)Wgate->max_row_blocks + Wup->max_row_blocks : 0;
+    if (int rc = (b == 64) ? launch_decode_w8<64, true>(g, nnz_gu, longest, gplan, stream)
+                           : launch_decode_w8<128, true>(g, nnz_gu, longest, gplan, stream))
       return rc;
+    dplan.pre_zeroed = zj.done;
   }
-  const ChunkPlan dplan = plan_of(Wdown, T);
-  return (b == 64) ? launch_decode_w8<64, false>(d, Wdown->nnz, dplan, stream)
-                   : launch_decode_w8<128, false>(d, Wdown->nnz, dplan, stream);
+  return (b == 64) ? launch_decode_w8<64, false>(d, Wdown->nnz, Wdown->max_row_blocks, dplan, stream)
+                   : launch_decode_w8<128, false>(d, Wdown->nnz, Wdown->max_row_blocks, dplan, stream);
 }
 
 extern "C" int blast_sparse_mlp2(const blast_bsr_view* W1, const blast_bsr_view* W2, const uint16_t* X, int64_t ldx,

@@ -76,14 +76,15 @@ struct DecArgs {
   int z_T;
 };
 
-template <int B>
+// (NT threads, thread indices taken modulo NT)
+template <int B, int NT = 256>
 __device__ __forceinline__ void decode_zero_job(const DecArgs& a, int ci) {
   if (ci >= ld_idx(a.z_hdr, 0)) return;
   const int cr = ld_idx(a.z_chunk_row, ci);
   if (cr >= 0) return;  // a single-chunk row is stored, not accumulated
   const int r = cr & 0x7FFFFFFF;
   if (ld_idx(a.z_chunk_kb, ci) != ld_idx(a.z_row_ptr, r)) return;  // only the first chunk of the row clears
-  for (int e = threadIdx.x; e < a.z_T * B; e += 256) {
+  for (int e = threadIdx.x % NT; e < a.z_T * B; e += NT) {
     const int t = e / B, i = e % B;
     a.z_Y[(int64_t)t * a.z_syt + ((int64_t)r * B + i) * a.z_syi] = 0.0f;
   }

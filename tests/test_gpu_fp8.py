@@ -363,3 +363,46 @@ def test_mlp_with_e5m2_weights_and_a_very_long_down_row(api, b, nbi, T):
     yb = api.sparse_mlp_e5m2w(dev[0], dev8[0], dev[1], dev8[1], dev[2], dev8[2], to_dev(x), out_dtype=torch.bfloat16)
     torch.cuda.synchronize()
     assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
+
+
+def _skewed(rng, nbr, nbc, lengths):
+    m = np.zeros((nbr, nbc), dtype=np.uint8)
+    for r, n in enumerate(lengths):
+        m[r, rng.choice(nbc, size=min(n, nbc), replace=False)] = 1
+    return m
+
+
+# (b, block rows of H, block columns, joint lengths of the gate/up rows, T): the layers are large enough for the
+# kernel that deals whole rows to workgroups (8192 slices of 16 rows)
+@pytest.mark.parametrize("b,nbi,nbe,kind,T", [
+    (128, 45, 25, "half", 1), (128, 45, 25, "half", 4), (128, 45, 25, "half", 5), (128, 45, 25, "half", 8),
+    (64, 61, 70, "half", 8), (64, 61, 70, "half", 1),  # 8 row groups per XCD
+    (128, 500, 3, "empty", 8),      # more rows per group than entries: several batches; 250 empty rows
+    (128, 512, 3, "full", 7), (128, 513, 3, "full", 3),  # 64 rows per XCD, and one too many
+    (128, 9, 256, "row", 1), (128, 9, 257, "row", 2),   # a joint row of 512 blocks, and one too long
+])
+def test_mlp_with_e5m2_weights_rows_dealt_to_workgroups(api, b, nbi, nbe, kind, T):
+    import torch
+
+    rng = np.random.default_rng(5500 + nbi + T)
+    E, I = nbe * b, nbi * b
+    if kind == "empty":
+        lens = [nbe if r % 2 else 0 for r in range(nbi)]
+    elif kind in ("full", "row"):
+        lens = [nbe] * nbi
+    else:  # a full row, an empty one, the rest uneven
+        lens = [nbe, 0] + [int(rng.integers(1, nbe + 1)) for _ in range(nbi - 2)]
+    mg, mu = _skewed(rng, nbi, nbe, lens), _skewed(rng, nbi, nbe, lens[::-1] if kind == "half" else lens)
+    md = _skewed(rng, nbe, nbi, [0 if r == 1 else nbi - r % 2 for r in range(nbe)])
+    dev, dev8, ref, ref8 = _w8_layer(api, rng, E, I, b, 0.0, masks=[mg, mu, md])
+    x = synth.gauss_bf16(rng, (T, E), 1.0)
+    want = orc.mlp_e5m2w(ref[0], ref8[0], ref[1], ref8[1], ref[2], ref8[2], x)
+    dev[0] = api.with_joint_row_order(dev[0], dev[1])
+    for _ in range(2):
+        y = api.sparse_mlp_e5m2w(dev[0], dev8[0], dev[1], dev8[1], dev[2], dev8[2], to_dev(x),
+                                 out=torch.full((T, E), float("nan"), device="cuda:0"))
+        torch.cuda.synchronize()
+        check_close(y.cpu().numpy().T, want, f"E5M2-weight mlp, dealt rows b={b} nbi={nbi} T={T}")
+    yb = api.sparse_mlp_e5m2w(dev[0], dev8[0], dev[1], dev8[1], dev[2], dev8[2], to_dev(x), out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
