@@ -47,10 +47,61 @@ int launch_fp8(Fp8Args a, hipStream_t stream) {
   return BLAST_OK;
 }
 
+int cu_count_fp8() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+  return n;
+}
+
+// Many tokens: the streaming kernel of the bf16 product, instantiated for one-byte values.  A wave that copies the
+// weights for its own 64 x 64 tile asks the L1 for 128 bytes per clock at the matrix peak, and the two 64-row halves
+// of a 128-wide block, on different XCDs, each bring the block's activations across the fabric; shared by a workgroup,
+// a 256-token x 128-row tile asks for 47, and the activations come once.  53248 x 16384, 95 % uniform, bf16 output,
+// column groups: 1000 tokens 99.9 -> 85.9 us, 2048 tokens 227.5 -> 143.8 (1.24 PFLOP/s on stored blocks).  Bound there by the
+// fabric: 348 MB read and 112 MB written in 86 us (rows pinned to XCDs instead of token tiles: 98.4).
+template <int B, int TW, int NW>
+int launch_fp8_stream(const Fp8Args& f, hipStream_t stream) {
+  using C = StreamCfg<B, TW, NW, true>;
+  StreamArgs sa{};
+  TileArgs& a = sa.t;
+  a.m0.row_ptr = f.row_ptr;
+  a.m0.col_idx = f.col_idx;
+  a.m0.vals8 = f.vals;
+  a.row_order = f.row_order;
+  a.X = reinterpret_cast<const uint16_t*>(f.X);
+  a.Y = f.Y;
+  a.syt = f.ldy;
+  a.syi = 1;
+  a.y_bf16 = f.y_bf16;
+  a.y_fast = ((int64_t)256 * f.ldy * 4 + f.ldy * 4 < ((int64_t)1 << 31)) ? 1 : 0;
+  a.T = f.T;
+  a.nbr = f.n_units / (B / 64);
+  a.act = -1;
+  a.ntt = (f.T + C::TT - 1) / C::TT;
+  if ((int64_t)a.ntt * a.nbr > INT32_MAX / 2) return BLAST_ERR_INVALID_ARG;
+  sa.x8_col = f.x_cg ? (B / 64) * f.x_cg : B;
+  sa.x8_tok = (uint32_t)f.ldx;
+  sa.x8_half = f.x_cg ? (uint32_t)f.x_cg : 64u;
+  const int64_t slab = ((int64_t)a.ntt + 7) / 8 * C::TT * f.kdim;
+  const int64_t grid = stream_grid<C, B>(sa, a.nbr, cu_count_fp8(), slab);
+  static blast::DeviceFlags lds_set;
+  int dev = 0;
+  BLAST_HIP_TRY(hipGetDevice(&dev));
+  if (!lds_set.test(dev)) {
+    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_spmm_stream<B, false, TW, false, false, NW, false, true>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES));
+    lds_set.set(dev);
+  }
+  k_spmm_stream<B, false, TW, false, false, NW, false, true><<<dim3((unsigned)grid), dim3(64 * NW), C::LDS_BYTES, stream>>>(sa);
+  BLAST_LAUNCH_CHECK("k_spmm_stream (E5M2)");
+  return BLAST_OK;
+}
+
 template <int B>
 int launch_fp8_b(const Fp8Args& a, const blast_bsr_view* W, hipStream_t stream) {
   // up to two token tiles the stages of a row are dealt to the four waves (every wave streams weights);
-  // beyond that a wave owns a token tile of its own and walks the whole row
+  // beyond that the streaming kernel
   if (a.T <= 128) {
     // A row of n blocks is n * (B / 64) / 4 stages deep per wave.  When the fullest row is deeper than four
     // chunks' worth, take the packer's chunk plan (fp32 output only: chunks of a row add atomically).
@@ -70,7 +121,20 @@ int launch_fp8_b(const Fp8Args& a, const blast_bsr_view* W, hipStream_t stream) 
     }
     return launch_fp8<B, true>(a, stream);
   }
-  return launch_fp8<B, false>(a, stream);
+  const int64_t tiles = (a.T + 255) / 256, cus = cu_count_fp8();
+  const bool wide = tiles * (a.n_units / (B / 64)) >= 2 * cus;
+  if constexpr (B == 128) {
+    if (wide) return launch_fp8_stream<128, 4, 8>(a, stream);
+    return launch_fp8_stream<128, 2, 4>(a, stream);
+  } else {
+    // A wave that owns its token tile starts copying two trips to the memory earlier than the streaming kernel with its
+    // table of items, which shows while a workgroup slot (two per CU) has only a few blocks: 8192 x 3072, 1000 tokens, 614 blocks
+    // (4.8 per slot) 11.7 against 13.5 us; 1843 blocks, 300 tokens (7.2) 12.6 against 13.0; 2048 tokens (29) 30.9
+    // against 27.5.
+    if (W->nnz * tiles < 6 * 2 * cus) return launch_fp8<B, false>(a, stream);
+    if (wide) return launch_fp8_stream<64, 4, 4>(a, stream);
+    return launch_fp8_stream<64, 2, 4>(a, stream);
+  }
 }
 
 }  // namespace
@@ -136,6 +200,7 @@ extern "C" int blast_bsr_spmm_e5m2(const blast_bsr_view* W, const uint8_t* vals8
     a.X = X8;
     a.ldx = cg ? 64 : ldx;
     a.x_cg = cg ? T * 64 : 0;
+    a.kdim = W->cols;
     a.Y = Y;
     a.ldy = ldy;
     a.y_bf16 = y_dtype == BLAST_BF16 ? 1 : 0;

@@ -177,13 +177,6 @@ struct ChunkPlan {
   int64_t max_chunks1 = 0;
 };
 
-// An XCD's L2 (4 MB) keeps the slab of activations of the token tiles it works on only while that slab is a
-// few megabytes.  Beyond that every stored block fetches its activation tile from the memory side whatever the
-// schedule does, and what is left to save is the weights: with a block row pinned to one XCD they leave the
-// memory side once instead of once per XCD (measured on the 405B-class layer, 16384 / 53248 features wide: 3.6
-// and 2.2 GB per launch cross the fabric with token tiles pinned, at the 6 - 7.5 TB/s it delivers).
-constexpr int64_t kRowPinnedSlabBytes = (int64_t)6 << 20;
-
 template <int B, bool DUAL, int TW, bool CHUNK, int NW = 4, bool LONG = false>
 int launch_stream_tw(TileArgs a, const ChunkPlan& plan, int64_t k_features, hipStream_t stream) {
   using C = StreamCfg<B, TW, NW>;
@@ -192,21 +185,14 @@ int launch_stream_tw(TileArgs a, const ChunkPlan& plan, int64_t k_features, hipS
   const int64_t n_items = (int64_t)a.ntt * n_rows;
   if (n_items <= 0) return BLAST_OK;
   if (n_items > INT32_MAX / 2) return BLAST_ERR_INVALID_ARG;
-  int shift = -1;
-  for (int q = 0; q < 31; ++q)
-    if ((1 << q) == a.ntt) shift = q;
-  int64_t grid = (n_items + 7) / 8 * 8;
-  const int64_t resident = (int64_t)cu_count() * C::WG_PER_CU / 8 * 8;
-  if (grid > resident) grid = resident;
-  // a workgroup keeps the descriptors of its items one per lane: at most 64 rounds
-  if (grid * 64 < n_items) grid = ((n_items + 63) / 64 + 7) / 8 * 8;
-  // row-pinned schedule: every token tile of a row on one XCD, side by side
-  int row_pinned = 0;
+  StreamArgs sa{};
+  sa.t = a;
+  sa.hdr = plan.hdr;
+  sa.chunk_row = plan.chunk_row;
+  sa.chunk_kb = plan.chunk_kb;
+  sa.chunk_ke = plan.chunk_ke;
   const int64_t slab = ((int64_t)a.ntt + 7) / 8 * C::TT * k_features * 2;
-  if (B == 128 && slab > kRowPinnedSlabBytes && grid == resident && a.ntt <= grid / 8 && (grid / 8) % a.ntt == 0 &&
-      n_rows / 8 + 1 <= 64 * ((grid / 8) / a.ntt))
-    row_pinned = 1;
-  StreamArgs sa{a, (int)n_items, shift, row_pinned, plan.hdr, plan.chunk_row, plan.chunk_kb, plan.chunk_ke};
+  const int64_t grid = stream_grid<C, B>(sa, n_rows, cu_count(), slab);
   if constexpr (LONG) {
     sa.hdr1 = plan.hdr1;
     sa.chunk_row1 = plan.chunk_row1;

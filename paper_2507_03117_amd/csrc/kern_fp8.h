@@ -16,8 +16,9 @@
 //    copy): the eight rows one read cycle touches then cover all banks.
 // One byte per value halves every byte count of the bf16 kernels (HBM, L2 -> LDS, LDS -> registers) per
 // multiply-add, which is what bounds them.
-//  - KSPLIT = false (many tokens): a workgroup owns (block row, 64-row sub-block, 256 tokens), one 64-token
-//    tile per wave; the four waves read the same weight tiles (L1 hits).
+//  - KSPLIT = false (64-wide blocks, many tokens, few blocks per workgroup): a workgroup owns (block row, 64-row
+//    sub-block, 256 tokens), one 64-token tile per wave; the four waves read the same weight tiles (L1 hits).
+//    Everything else beyond 128 tokens runs on the streaming kernel of the bf16 product (kern_stream.h, F8).
 //  - KSPLIT = true (up to a few token tiles): a workgroup owns (block row, sub-block, 64 tokens) and its
 //    four waves deal the stages among themselves; the partial sums are added in LDS in a fixed order.
 //    With CHUNK the unit is a chunk of at most 16 stored blocks from the packer's chunk plan instead of a
@@ -36,6 +37,7 @@ struct Fp8Args {
   const uint8_t* vals;   // [nnz][b][b] E5M2
   const uint8_t* X;      // token-major [T][cols] E5M2, row pitch ldx bytes (multiple of 16); or column groups, see x_cg
   int64_t ldx;
+  int64_t kdim;          // features contracted over; host-side scheduling only
   int64_t x_cg;          // 0: token-major.  Else X is [cols/64][T][64]: bytes between two column groups (ldx = 64)
   void* Y;               // token-major [T][rows], row pitch ldy elements
   int64_t ldy;

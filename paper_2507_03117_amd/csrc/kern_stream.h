@@ -15,9 +15,13 @@
 // 16-byte chunk index with a key derived from the row, applied on the
 // global-address side of the copy.
 #pragma once
+#include <type_traits>
+
 #include "kern_common.h"
 
 namespace blast_dev {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define BLAST_GLDS16(gptr, lptr)                                                                   \
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gptr),          \
@@ -32,7 +36,9 @@ namespace blast_dev {
 // NW = waves of a workgroup (4, or 8 for 128-wide blocks: a 256-token x 128-row output tile, one workgroup
 // per CU, so that a weight slice is copied once per 256 tokens and 85 flop are done per byte copied
 // instead of 64).
-template <int B, int TW, int NW = 4>
+// F8: both operands in E5M2, one byte per value.  A step is then as many BYTES deep as in bf16 (128-byte rows for
+// 128-wide blocks, 64 for 64-wide ones), twice the contraction, on the 64-deep matrix instruction.
+template <int B, int TW, int NW = 4, bool F8 = false>
 struct StreamCfg {
   static_assert(TW == 2 || TW == 4, "two or four waves along tokens");
   static_assert(NW == 4 || NW == 8, "four or eight waves");
@@ -46,10 +52,12 @@ struct StreamCfg {
   static constexpr int TT = TOKW * 64;             // tokens per workgroup tile
   // Contraction slice per step.  The L1 path moves about one cache line per 2.5 clk whatever the
   // line's used fraction, so a row of a stage is a whole 128-byte line wherever the block allows.
-  static constexpr int KS = (B >= 64) ? 64 : 32;
+  static constexpr int EB = F8 ? 1 : 2;            // bytes per value
+  static constexpr int KS = F8 ? (B >= 128 ? 128 : 64) : (B >= 64 ? 64 : 32);
   static constexpr int NSLICE = B / KS;
-  static constexpr int ROW_BYTES = 2 * KS;         // LDS row pitch
-  static constexpr int CPR = KS / 8;               // 16-byte chunks per LDS row
+  static_assert(!F8 || (B >= 64 && NSLICE == 1), "E5M2: a step is a whole block of 64 or 128 columns");
+  static constexpr int ROW_BYTES = EB * KS;        // LDS row pitch
+  static constexpr int CPR = ROW_BYTES / 16;       // 16-byte chunks per LDS row
   static constexpr int RPI = 1024 / ROW_BYTES;     // rows written by one wave-wide copy instruction
   static constexpr int W_BYTES = B * ROW_BYTES;
   static constexpr int X_BYTES = TT * ROW_BYTES;
@@ -64,7 +72,8 @@ struct StreamCfg {
   static constexpr int XQ = X_INSTR / NW;             // (activations)
   static_assert(X_INSTR % NW == 0, "the activation copies divide evenly among the waves");
   static constexpr int LPS = WQ + XQ;              // copies per thread and step
-  static constexpr int KSTEPS = KS / 16;
+  static constexpr int KSTEPS = KS / (F8 ? 64 : 16);
+  static constexpr int CPF = F8 ? 2 : 1;           // 16-byte chunks per operand fragment and lane
   static constexpr int KEY_MOD = (CPR >= 8) ? 8 : CPR;
   static constexpr int KEY_DIV = 8 / KEY_MOD;
   static constexpr size_t LDS_BYTES = (size_t)NSTAGE * STAGE;
@@ -124,9 +133,42 @@ struct StreamArgs {
   const int* chunk_row1;
   const int* chunk_kb1;
   const int* chunk_ke1;
+  // E5M2 activations (F8 instances): bytes between block columns, between tokens, and from the first 64 features of a
+  // token to the next 64 - token-major [T][K] or column groups [K/64][T][64]
+  int64_t x8_col;
+  uint32_t x8_tok, x8_half;
 };
 
 constexpr int kLongChunk = 16;  // blocks per chunk of the plan that the LONG launch works from
+
+// Host side: workgroups and order of a launch over n_rows (block rows or chunks) x a.ntt token tiles, on a device of
+// `cus` CUs with C's number of workgroups on each; `slab_bytes` = activations of the token tiles that one XCD works on.
+//
+// An XCD's L2 (4 MB) keeps the slab of activations of the token tiles it works on only while that slab is a
+// few megabytes.  Beyond that every stored block fetches its activation tile from the memory side whatever the
+// schedule does, and what is left to save is the weights: with a block row pinned to one XCD they leave the
+// memory side once instead of once per XCD (measured on the 405B-class layer, 16384 / 53248 features wide: 3.6
+// and 2.2 GB per launch cross the fabric with token tiles pinned, at the 6 - 7.5 TB/s it delivers).
+constexpr int64_t kRowPinnedSlabBytes = (int64_t)6 << 20;
+
+template <class C, int B>
+inline int64_t stream_grid(StreamArgs& sa, int64_t n_rows, int cus, int64_t slab_bytes) {
+  const int ntt = sa.t.ntt;
+  const int64_t n_items = (int64_t)ntt * n_rows;
+  sa.n_items = (int)n_items;
+  sa.ntt_shift = -1;
+  for (int q = 0; q < 31; ++q)
+    if ((1 << q) == ntt) sa.ntt_shift = q;
+  int64_t grid = (n_items + 7) / 8 * 8;
+  const int64_t resident = (int64_t)cus * C::WG_PER_CU / 8 * 8;
+  if (grid > resident) grid = resident;
+  // a workgroup keeps the descriptors of its items one per lane: at most 64 rounds
+  if (grid * 64 < n_items) grid = ((n_items + 63) / 64 + 7) / 8 * 8;
+  // row-pinned schedule: every token tile of a row on one XCD, side by side
+  sa.row_pinned = B == 128 && slab_bytes > kRowPinnedSlabBytes && grid == resident && ntt <= grid / 8 &&
+                  (grid / 8) % ntt == 0 && n_rows / 8 + 1 <= 64 * ((grid / 8) / ntt);
+  return grid;
+}
 
 // number of chunks of a matrix' cut rows (hdr points at that count, or is null)
 __device__ __forceinline__ int long_chunks(const int* hdr) { return hdr ? ld_idx(hdr, 0) : 0; }
@@ -396,12 +438,14 @@ __device__ __forceinline__ void stream_zero_side(const StreamArgs& sa, int w, in
 // POST: a single-matrix product whose result goes through the activation a.act before it is stored
 // (the first half of a two-matrix MLP).
 // LONG: the gated product with its long rows cut into chunks and finished by a later launch, see StreamArgs.
-template <int B, bool DUAL, int TW, bool CHUNK, bool POST = false, int NW = 4, bool LONG = false>
-__global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) void k_spmm_stream(const StreamArgs sa) {
+// F8: both operands in E5M2 (MatDev::vals8; X bytes).
+template <int B, bool DUAL, int TW, bool CHUNK, bool POST = false, int NW = 4, bool LONG = false, bool F8 = false>
+__global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)) void k_spmm_stream(const StreamArgs sa) {
+  static_assert(!F8 || (!DUAL && !CHUNK && !POST && !LONG), "the E5M2 product is a plain one");
   static_assert(!(DUAL && CHUNK), "the activation needs complete sums: the gated product is never split");
   static_assert(!POST || (!DUAL && !CHUNK), "an activation on the output needs complete sums of a single matrix");
   static_assert(!LONG || (DUAL && !CHUNK), "long rows are a matter of the gated product");
-  using C = StreamCfg<B, TW, NW>;
+  using C = StreamCfg<B, TW, NW, F8>;
   const TileArgs& a = sa.t;
   const int n_items = LONG    ? (long_chunks(sa.hdr) + long_chunks(sa.hdr1) + a.nbr) * a.ntt
                       : CHUNK ? ld_idx(sa.hdr, 0) * a.ntt
@@ -419,9 +463,13 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
   // copy side: lane -> (row inside the instruction, slot); the chunk fetched is slot ^ key(row)
   const int cp_rr = lane / C::CPR, cp_slot = lane % C::CPR;
   // fragment side: byte offset of the chunk for every k-step (same for the A and B operands)
-  int frag_off[C::KSTEPS];
+  // (E5M2: a lane hands over two chunks, 0 and 2 or 1 and 3 of the k-step's four - the same on both operands, so
+  // whatever contraction index the instruction gives a byte, it meets its partner)
+  int frag_off[C::KSTEPS][C::CPF];
 #pragma unroll
-  for (int kk = 0; kk < C::KSTEPS; ++kk) frag_off[kk] = (((2 * kk + lh) ^ C::key(l32)) << 4);
+  for (int kk = 0; kk < C::KSTEPS; ++kk)
+#pragma unroll
+    for (int c = 0; c < C::CPF; ++c) frag_off[kk][c] = (((2 * C::CPF * kk + 2 * c + lh) ^ C::key(l32)) << 4);
   const int a_row0 = (tw * 64 + l32) * C::ROW_BYTES;         // + mi * 32 rows
   const int b_row0 = (rw * C::WT_ROW + l32) * C::ROW_BYTES;  // + ni * 32 rows
 
@@ -435,7 +483,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
   for (int q = 0; q < C::WQ; ++q) {
     winstr[q] = (q * NW + wave) % C::W_INSTR;  // with fewer instructions than waves, waves duplicate each other
     const int row = winstr[q] * C::RPI + cp_rr;
-    woff[q] = (uint32_t)(row * B + ((cp_slot ^ C::key(row)) << 3)) * 2u;
+    woff[q] = (uint32_t)(row * B * C::EB + ((cp_slot ^ C::key(row)) << 4));
   }
   int xoff_tile = -1;
   const uint32_t sxt32 = (uint32_t)a.sxt;
@@ -447,7 +495,11 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
       const int row = (q * NW + wave) * C::RPI + cp_rr;
       int t = tile * C::TT + row;
       t = t < a.T ? t : a.T - 1;  // clamp: rows past T are never stored
-      xoff[q] = ((uint32_t)t * sxt32 + (uint32_t)((cp_slot ^ C::key(row)) << 3)) * 2u;
+      const uint32_t chunk = cp_slot ^ C::key(row);
+      if constexpr (F8)
+        xoff[q] = (uint32_t)t * sa.x8_tok + (chunk >> 2) * sa.x8_half + (chunk & 3) * 16u;
+      else
+        xoff[q] = ((uint32_t)t * sxt32 + chunk * 8u) * 2u;
     }
   };
   if (sa.z_hdr) stream_zero_side<B, 64 * NW>(sa, w, G, lane);
@@ -493,7 +545,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
       }
       if (k < e) {
         ld.rem = e - k;
-        ld.wptr = reinterpret_cast<const unsigned char*>(m->vals) + (int64_t)k * (B * B * 2);
+        ld.wptr = (F8 ? m->vals8 : reinterpret_cast<const unsigned char*>(m->vals)) + (int64_t)k * (B * B * C::EB);
         ld.cptr = m->col_idx + k;
         ld.c_next = ld_idx(ld.cptr, ld.rem > 1 ? 1 : 0);
         set_tile(ld.tile);
@@ -505,11 +557,12 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
   int ahead = 0;  // steps issued whose stage the multiplying side has not entered yet
   auto issue_next = [&]() {
     unsigned char* st = smem + ld.stage_off;
-    const unsigned char* wblk = ld.wptr + ld.slice * (C::KS * 2);
+    const unsigned char* wblk = ld.wptr + ld.slice * C::ROW_BYTES;
 #pragma unroll
     for (int q = 0; q < C::WQ; ++q) BLAST_GLDS16(wblk + woff[q], st + winstr[q] * 1024);
     const unsigned char* xcol =
-        reinterpret_cast<const unsigned char*>(a.X) + (int64_t)ld.c * (B * 2) + ld.slice * (C::KS * 2);
+        reinterpret_cast<const unsigned char*>(a.X) +
+        (F8 ? (int64_t)ld.c * sa.x8_col : (int64_t)ld.c * (B * 2) + ld.slice * C::ROW_BYTES);
 #pragma unroll
     for (int q = 0; q < C::XQ; ++q) BLAST_GLDS16(xcol + xoff[q], st + C::W_BYTES + (q * NW + wave) * 1024);
     ld.stage_off = (ld.stage_off + C::STAGE == (uint32_t)C::LDS_BYTES) ? 0u : ld.stage_off + C::STAGE;
@@ -519,7 +572,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
       ld.slice = 0;
     }
     if (--ld.rem > 0) {
-      ld.wptr += B * B * 2;
+      ld.wptr += B * B * C::EB;
       ++ld.cptr;
       ld.c = ld.c_next;
       ld.c_next = ld_idx(ld.cptr, ld.rem > 1 ? 1 : 0);  // the last block of a run re-reads its own entry
@@ -547,24 +600,40 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
     }
   }
 
-  // Operand fragments of one 16-wide k-step: MI token fragments, NI weight-row fragments.
+  // Operand fragments of one k-step: MI token fragments, NI weight-row fragments.
+  typedef int v8i __attribute__((ext_vector_type(8)));
+  using Operand = std::conditional_t<F8, v8i, bf16x8>;
   struct Frag {
-    bf16x8 x[C::MI], w[C::NI];
+    Operand x[C::MI], w[C::NI];
+  };
+  auto read_operand = [&](const unsigned char* row, int kk) {
+    if constexpr (F8) {
+      struct Pair {
+        i32x4 lo, hi;
+      };
+      return __builtin_bit_cast(v8i, Pair{*reinterpret_cast<const i32x4*>(row + frag_off[kk][0]),
+                                          *reinterpret_cast<const i32x4*>(row + frag_off[kk][C::CPF - 1])});
+    } else {
+      return *reinterpret_cast<const bf16x8*>(row + frag_off[kk][0]);
+    }
   };
   auto read_frag = [&](Frag& f, const unsigned char* st, int kk) {
 #pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi)
-      f.x[mi] = *reinterpret_cast<const bf16x8*>(st + C::W_BYTES + a_row0 + mi * 32 * C::ROW_BYTES + frag_off[kk]);
+    for (int mi = 0; mi < C::MI; ++mi) f.x[mi] = read_operand(st + C::W_BYTES + a_row0 + mi * 32 * C::ROW_BYTES, kk);
 #pragma unroll
-    for (int ni = 0; ni < C::NI; ++ni)
-      f.w[ni] = *reinterpret_cast<const bf16x8*>(st + b_row0 + ni * 32 * C::ROW_BYTES + frag_off[kk]);
+    for (int ni = 0; ni < C::NI; ++ni) f.w[ni] = read_operand(st + b_row0 + ni * 32 * C::ROW_BYTES, kk);
   };
   auto mma = [&](f32x16 (&acc)[C::MI][C::NI], const Frag& f) {
 #pragma unroll
     for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.x[mi], f.w[ni], acc[mi][ni], 0, 0, 0);
+      for (int ni = 0; ni < C::NI; ++ni) {
+        if constexpr (F8)  // format code 1 = E5M2 on both sides, all block scales 2^0
+          acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f.x[mi], f.w[ni], acc[mi][ni], 1, 1, 0, 0x7F7F7F7F,
+                                                                        0, 0x7F7F7F7F);
+        else
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.x[mi], f.w[ni], acc[mi][ni], 0, 0, 0);
+      }
   };
   // A fragment read follows every matrix instruction: the wait for the fragments of this k-step then sits
   // in front of its first matrix instruction, where only reads issued a whole k-step ago are outstanding.
@@ -572,7 +641,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW>::WAVES_PER_SIMD)) vo
 #pragma unroll
     for (int i = 0; i < C::MI * C::NI; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if (i < C::MI + C::NI) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (i < C::MI + C::NI) __builtin_amdgcn_sched_group_barrier(0x100, C::CPF, 0);
     }
   };
 

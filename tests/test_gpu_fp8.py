@@ -406,3 +406,32 @@ def test_mlp_with_e5m2_weights_rows_dealt_to_workgroups(api, b, nbi, nbe, kind, 
     yb = api.sparse_mlp_e5m2w(dev[0], dev8[0], dev[1], dev8[1], dev[2], dev8[2], to_dev(x), out_dtype=torch.bfloat16)
     torch.cuda.synchronize()
     assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
+
+
+@pytest.mark.parametrize("b,nbr,nbc,T,groups", [
+    (128, 9, 7, 130, True), (128, 9, 7, 257, False),   # 128-token tiles, a tile of one and of 129 tokens
+    (128, 130, 9, 1025, True), (128, 130, 9, 1100, False),  # 256-token tiles, five to a row
+    (64, 40, 30, 700, True), (64, 129, 40, 1000, True), (64, 129, 40, 1023, False),  # both tiles of 64-wide blocks
+])
+def test_spmm_e5m2_many_tokens(api, b, nbr, nbc, T, groups):
+    """The streaming kernel on one-byte values, both activation layouts and outputs, empty and full rows."""
+    import torch
+
+    rng = np.random.default_rng(5600 + nbr + T)
+    M, K = nbr * b, nbc * b
+    W = synth.gauss_bf16(rng, (M, K), 0.05)
+    mask = synth.uniform_mask(rng, nbr, nbc, 0.4)
+    mask[1, :], mask[2, :] = 0, 1
+    dev, ref = api.bsr_pack(to_dev(W), b, mask=mask_dev(mask)), orc.pack(W, b, mask)
+    w8 = api.quantize_e5m2(dev.vals[: dev.nnz * b * b].contiguous())
+    x = to_dev(synth.gauss_bf16(rng, (T, K), 1.0))
+    x8 = api.quantize_e5m2_groups(x) if groups else api.quantize_e5m2(x)
+    layout = api.COLUMN_GROUPS_64 if groups else api.TOKEN_MAJOR
+    sel = np.unique(np.r_[0:3, T // 2, T - 130, T - 3:T])  # the tokens of the oracle
+    x_or = api.quantize_e5m2(x[torch.from_numpy(sel).to(x.device)].contiguous()).cpu().numpy()
+    want = orc.spmm_e5m2(ref, orc.e5m2_quantize(_f32(ref.vals)), x_or)
+    y = api.bsr_spmm_e5m2(dev, w8, x8, layout=layout, out=torch.full((T, M), float("nan"), device="cuda:0"))
+    yb = api.bsr_spmm_e5m2(dev, w8, x8, layout=layout, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    check_close(y.cpu().numpy()[sel].T, want, f"E5M2 product b={b} T={T}")
+    assert torch.isfinite(y).all() and torch.equal(y.to(torch.bfloat16), yb)
