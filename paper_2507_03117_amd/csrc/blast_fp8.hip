@@ -157,9 +157,14 @@ extern "C" int blast_quantize_e5m2_groups(const uint16_t* X_bf16, int64_t ldx, i
   if (T < 0 || K < 0 || K % 64 != 0) return BLAST_ERR_INVALID_ARG;
   if (T == 0 || K == 0) return BLAST_OK;
   if (!X_bf16 || !out || ldx < K || !blast::aligned(out, 16)) return BLAST_ERR_INVALID_ARG;
-  const int64_t blocks = (T * (K / 8) + 255) / 256;
+  const int64_t blocks = (T + kQuantTokens - 1) / kQuantTokens;
   if (blocks > INT32_MAX) return BLAST_ERR_INVALID_ARG;
-  k_quantize_e5m2_groups<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(X_bf16, ldx, T, K, out);
+  const int wide = ldx % 8 == 0 && blast::aligned(X_bf16, 16);
+  for (int64_t c = 0; c < K / 64; c += 65535) {  // (gridDim.y holds 65535 column groups)
+    const int64_t n = K / 64 - c < 65535 ? K / 64 - c : 65535;
+    k_quantize_e5m2_groups<<<dim3((unsigned)blocks, (unsigned)n), dim3(256), 0, stream>>>(X_bf16 + c * 64, ldx, T, wide,
+                                                                                          out + c * 64 * T);
+  }
   BLAST_LAUNCH_CHECK("k_quantize_e5m2_groups");
   return BLAST_OK;
 }

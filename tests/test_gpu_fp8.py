@@ -435,3 +435,18 @@ def test_spmm_e5m2_many_tokens(api, b, nbr, nbc, T, groups):
     torch.cuda.synchronize()
     check_close(y.cpu().numpy()[sel].T, want, f"E5M2 product b={b} T={T}")
     assert torch.isfinite(y).all() and torch.equal(y.to(torch.bfloat16), yb)
+
+
+@pytest.mark.parametrize("T,K,pad", [(512, 128, 0), (127, 192, 8), (129, 64, 1), (1, 128, 3)])
+def test_quantize_groups_equals_the_token_major_codes(api, T, K, pad):
+    """Every bf16 pattern (512 x 128 of them) through the column-grouped form, partial workgroups, and rows whose pitch
+    does not allow 16-byte loads: the same codes as the oracle's, regrouped."""
+    import torch
+
+    bits = (np.arange(T * (K + pad), dtype=np.int64) * (1 if pad == 0 else 40503) % 65536).astype(np.uint16).reshape(T, K + pad)
+    x = to_dev(bits)[:, :K]
+    got = api.quantize_e5m2_groups(x).cpu().numpy()
+    want = orc.e5m2_quantize(_f32(np.ascontiguousarray(bits[:, :K])))
+    nan = (want & 0x7F) > 0x7C
+    got_t = got.transpose(1, 0, 2).reshape(T, K)
+    assert np.array_equal(got_t[~nan], want[~nan]) and ((got_t[nan] & 0x7F) > 0x7C).all()
