@@ -294,8 +294,7 @@ def generate_masks(W: torch.Tensor, G: torch.Tensor, b: int, sparsity: float) ->
     ws = torch.empty(max(int(L.blast_generate_masks_workspace(rows, cols, b)), 16), dtype=torch.uint8, device=W.device)
     _check(L.blast_generate_masks(_ptr(W), W.stride(0), _ptr(G), G.stride(0), rows, cols, b, float(sparsity),
                                   _ptr(mask), _ptr(ws), ws.numel(), _stream()), "blast_generate_masks")
-    torch.cuda.current_stream().synchronize()  # ws is released on return
-    return mask
+    return mask  # (ws goes back to the allocator of the stream that uses it: no wait needed)
 
 
 def pooled_topk_mask(S: torch.Tensor, b: int, sparsity: float) -> torch.Tensor:
@@ -307,8 +306,7 @@ def pooled_topk_mask(S: torch.Tensor, b: int, sparsity: float) -> torch.Tensor:
     ws = torch.empty(max(int(L.blast_pooled_topk_mask_workspace(rows, cols, b)), 16), dtype=torch.uint8, device=S.device)
     _check(L.blast_pooled_topk_mask(_ptr(S), S.stride(0), rows, cols, b, float(sparsity), _ptr(mask), _ptr(ws),
                                     ws.numel(), _stream()), "blast_pooled_topk_mask")
-    torch.cuda.current_stream().synchronize()  # ws is released on return
-    return mask
+    return mask  # (ws goes back to the allocator of the stream that uses it: no wait needed)
 
 
 def sparsity_schedule(i: int, m: int, d: int, s_init: float, s_max: float) -> float:
