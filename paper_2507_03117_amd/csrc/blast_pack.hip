@@ -540,15 +540,16 @@ inline void plan_outputs(char* ab, const blast::AuxLayout& A, PlanOut& narrow, P
                  nullptr, nullptr};
 }
 
-// ---- small matrices: selection and every index array in one workgroup ----
+// ---- small matrices: a workgroup per job ----
 //
 // A layer-sized matrix has a few thousand blocks; scored, the rest of the packing is a few thousand integer
 // operations, and as a dozen dependent launches it costs a dozen launch latencies.  For at most kSmallN blocks
-// (and at most 1024 block rows and block columns) one workgroup does it all: a thread owns `per` consecutive
-// blocks in row-major order and keeps their keys in registers; the mask, the position of every stored block and
-// the per-line populations live in LDS.  The workgroup's 16 waves share one compute unit, so what the kernel
-// costs is instructions per thread: no integer division per block, both scans of a pair in one (two 16-bit
-// counts in one word: no sum here exceeds kSmallN + 1024), barriers that do not wait for global stores.
+// (and at most 1024 block rows and block columns) the selection is one workgroup and the rest one launch, in which a
+// workgroup makes the row arrays and another the column arrays: a thread owns `per` consecutive blocks in row-major
+// order; its keys stay in registers, positions and the per-line populations live in LDS.  The workgroup's 16 waves
+// share one compute unit, so what such a job costs is instructions per thread: no integer division per block, both
+// chunk plans' scans in one (two 16-bit counts in one word: no sum here exceeds kSmallN + 1024), barriers that do not
+// wait for global stores.
 constexpr int kSmallPer = 8;
 constexpr int kSmallN = 1024 * kSmallPer;
 static_assert(kSmallN + 1024 < 65536, "two counts share a 32-bit word");
@@ -804,100 +805,175 @@ __device__ __forceinline__ int chunk_plans_small(const int* rptr, const int* ror
 struct SmallOut {
   int* row_ptr;
   int* col_idx;
-  int* blk_row;
   int* row_order;
-  uint8_t* mask_out;  // may be null (the caller's mask is the mask)
   int* col_ptr;       // null without aux
   int* csc_row;       // csc_blk follows at the next 16-byte boundary after nnz entries
   int* scalars;       // {nnz, max_row_blocks}
   int64_t nnz_cap;
 };
 
-template <bool TOPK>
-__global__ __launch_bounds__(1024) void k_pack_small(const double* __restrict__ score,
-                                                     const uint8_t* __restrict__ mask_in, int nbr, int nbc,
-                                                     long long n_keep, SmallOut o, PlanOut narrow, PlanOut wide) {
-  __shared__ int kpos[kSmallN];  // position of a stored block in col_idx / vals, by row-major block index
-  __shared__ uint8_t m[kSmallN];
-  __shared__ __attribute__((aligned(16))) int rcnt[1024];
-  __shared__ int ccnt[1024];
-  __shared__ int rptr[1025];
-  __shared__ int rord[1024];
-  __shared__ SelectShared ssh;
-  __shared__ int sh[3];
-  int* wave_tot = ssh.wave_tot;
+struct GatherArgs {
+  const uint16_t* W;
+  int64_t ldw;
+  int b;
+  uint16_t* vals;
+};
+
+// Flags of the blocks a thread owns (bit j: block tid * per + j is kept).
+__device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask, int n, int per) {
+  const int e0 = threadIdx.x * per;
+  unsigned keep = 0u;
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) keep |= (j < per && e0 + j < n && mask[e0 + j] != 0) ? 1u << j : 0u;
+  return keep;
+}
+
+// Everything that follows the mask, in one launch.  Workgroup 0: row pointers, schedule, chunk plans; workgroup 1 (with
+// aux): the column-grouped index; the others: kGatherSpan candidate blocks each, whose places among the stored blocks
+// they count for themselves - column indices and values.  A block whose mask code is 2 (regrown, BLaST Sec. 3.2) is
+// stored as zeros: it joins the structure without changing the product.
+// What bounds it: the index jobs, a chain of scans and barriers in a workgroup each.  Three 8192 x 2048 matrices, b = 64,
+// 80 % sparse, after a mask update: as one workgroup for all index arrays and a launch for the values 12 + 4.6 us per
+// matrix and 187 us for the update and re-packing together, now 9 us and 163.
+constexpr int kGatherSpan = 16;
+__global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__ mask, int nbr, int nbc, SmallOut o,
+                                                     PlanOut narrow, PlanOut wide, GatherArgs ga) {
+  __shared__ __attribute__((aligned(16))) int cnt[1024];  // populations of the rows, or of the columns
+  __shared__ union {
+    struct {
+      int rptr[1025], rord[1024];
+    } row;
+    struct {
+      int kpos[kSmallN];  // position of a stored block in col_idx / vals, by row-major block index
+      uint8_t m[kSmallN];
+    } col;
+  } sh;
+  __shared__ int wave_tot[16], sh3[3];
   const int tid = threadIdx.x;
   const int n = nbr * nbc;
   const int per = (n + 1023) >> 10;  // blocks per thread (uniform); the loops below are unrolled to kSmallPer
   const int e0 = tid * per;
-  rcnt[tid] = 0;
-  ccnt[tid] = 0;
-  unsigned keep = 0u;  // bit j: block e0 + j is kept
-  if (TOPK) {
-    keep = select_small(score, n, n_keep, per, ssh);
-  } else {
+  const unsigned keep = small_flags(mask, n, per);
+  const int jobs = o.col_ptr ? 2 : 1;
+
+  if ((int)blockIdx.x >= jobs) {
+    // ---- the values of the candidates [c0, c0 + kGatherSpan) -------------------------------------------------------
+    const int c0 = ((int)blockIdx.x - jobs) * kGatherSpan;
+    int before = 0;  // stored blocks before c0
 #pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) keep |= (j < per && e0 + j < n && mask_in[e0 + j] != 0) ? 1u << j : 0u;
+    for (int j = 0; j < kSmallPer; ++j) before += __popcll(__ballot(((keep >> j) & 1u) && e0 + j < c0));
+    if (lane_id() == 0) wave_tot[tid / kWave] = before;
+    const int cand = c0 + lane_id();
+    const int code = lane_id() < kGatherSpan && cand < n ? mask[cand] : 0;
+    const unsigned kept = (unsigned)__ballot(code != 0), zero = (unsigned)__ballot(code == 2);
+    __syncthreads();
+    int first = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) first += wave_tot[w];
+    const int nk = __popc(kept);
+    if (tid < kGatherSpan && (kept >> tid & 1u)) {
+      const int k = first + __popc(kept & ((1u << tid) - 1u));
+      if (k < o.nnz_cap) o.col_idx[k] = (c0 + tid) % nbc;
+    }
+    const int cpr = ga.b / 8, lcpr = __builtin_ctz(cpr), lcpb = __builtin_ctz(ga.b * cpr);  // 16-byte pieces per row, per block
+    const int total = nk << lcpb;
+    constexpr int kAhead = 4;
+    for (int p0 = tid; p0 < total; p0 += kAhead * 1024) {
+      uint4 v[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int p = p0 + u * 1024;
+        v[u] = uint4{0u, 0u, 0u, 0u};
+        if (p < total) {
+          // the (p >> lcpb)-th kept candidate
+          unsigned left = kept;
+          for (int q = p >> lcpb; q > 0; --q) left &= left - 1u;
+          const int c = __builtin_ctz(left);
+          if (!(zero >> c & 1u)) {
+            const int piece = p & ((1 << lcpb) - 1), i = piece >> lcpr, j8 = piece & (cpr - 1);
+            const int br = (c0 + c) / nbc, bc = (c0 + c) - br * nbc;
+            v[u] = *reinterpret_cast<const uint4*>(ga.W + ((int64_t)br * ga.b + i) * ga.ldw + (int64_t)bc * ga.b + j8 * 8);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int p = p0 + u * 1024;
+        if (p < total && first + (p >> lcpb) < o.nnz_cap)
+          *reinterpret_cast<uint4*>(ga.vals + (((int64_t)first << lcpb) + p) * 8) = v[u];
+      }
+    }
+    return;
   }
 
-  // stored blocks in row-major order: the position of a block is the number of kept blocks before it
+  cnt[tid] = 0;
+  if (blockIdx.x == 0) {
+    // ---- rows: pointers, schedule, chunk plans -----------------------------------------------------------------------
+    wg_barrier<true>();
+    {
+      int r = e0 / nbc, c = e0 - r * nbc, run = 0;  // a thread adds its blocks of a row at once
+#pragma unroll
+      for (int j = 0; j < kSmallPer; ++j) {
+        if (j < per && e0 + j < n) {
+          run += (keep >> j) & 1u;
+          if (++c == nbc || j == per - 1 || e0 + j == n - 1) {
+            if (run) atomicAdd(&cnt[r], run);
+            run = 0;
+            if (c == nbc) {
+              c = 0;
+              ++r;
+            }
+          }
+        }
+      }
+    }
+    wg_barrier<true>();
+    int nnz;
+    const int ex = block_exscan<true>(tid < nbr ? cnt[tid] : 0, wave_tot, nnz);
+    if (tid < nbr) {
+      sh.row.rptr[tid] = ex;
+      o.row_ptr[tid] = ex;
+    }
+    if (tid == 0) {
+      sh.row.rptr[nbr] = nnz;
+      o.row_ptr[nbr] = nnz;
+      o.scalars[0] = nnz;
+      if (!o.col_ptr) o.scalars[1] = 0;
+    }
+    schedule_small(cnt, nbr, sh.row.rord, o.row_order);
+    wg_barrier<true>();
+    if (!o.col_ptr) return;
+    const int heavy = chunk_plans_small(sh.row.rptr, sh.row.rord, nbr, narrow, wide, wave_tot, sh3);
+    if (tid == 0) o.scalars[1] = heavy;
+    return;
+  }
+
+  // ---- columns: the position of a stored block is the number of kept blocks before it, in row-major order for
+  // col_idx / vals and in column-major order for the column-grouped index --------------------------------------------
   int nnz;
-  int k = block_exscan<true>(__popc(keep), wave_tot, nnz);  // (its barriers also cover the clearing of rcnt / ccnt)
+  int k = block_exscan<true>(__popc(keep), wave_tot, nnz);  // (its barriers also cover the clearing of cnt)
   {
-    int r = e0 / nbc, c = e0 - r * nbc;
+    int c = e0 % nbc;
 #pragma unroll
     for (int j = 0; j < kSmallPer; ++j) {
       if (j < per && e0 + j < n) {
         const bool kp = (keep >> j) & 1u;
-        m[e0 + j] = kp ? 1 : 0;
-        if (o.mask_out) o.mask_out[e0 + j] = kp ? 1 : 0;
+        sh.col.m[e0 + j] = kp ? 1 : 0;
         if (kp) {
-          kpos[e0 + j] = k;
-          if (k < o.nnz_cap) {
-            o.col_idx[k] = c;
-            o.blk_row[k] = r;
-          }
-          atomicAdd(&rcnt[r], 1);
-          atomicAdd(&ccnt[c], 1);
-          ++k;
+          sh.col.kpos[e0 + j] = k++;
+          atomicAdd(&cnt[c], 1);
         }
-        if (++c == nbc) {
-          c = 0;
-          ++r;
-        }
+        if (++c == nbc) c = 0;
       }
     }
   }
   wg_barrier<true>();
-
-  // row pointers and column pointers: one scan of both populations
   {
-    const int v = (tid < nbr ? rcnt[tid] : 0) | ((tid < nbc ? ccnt[tid] : 0) << 16);
     int total;
-    const int ex = block_exscan<true>(v, wave_tot, total);
-    if (tid < nbr) {
-      rptr[tid] = ex & 0xFFFF;
-      o.row_ptr[tid] = ex & 0xFFFF;
-    }
-    if (o.col_ptr && tid < nbc) o.col_ptr[tid] = ex >> 16;
-    if (tid == 0) {
-      rptr[nbr] = nnz;
-      o.row_ptr[nbr] = nnz;
-      if (o.col_ptr) o.col_ptr[nbc] = nnz;
-      o.scalars[0] = nnz;
-      if (!o.col_ptr) o.scalars[1] = 0;
-    }
+    const int ex = block_exscan<true>(tid < nbc ? cnt[tid] : 0, wave_tot, total);
+    if (tid < nbc) o.col_ptr[tid] = ex;
+    if (tid == 0) o.col_ptr[nbc] = nnz;
   }
-  schedule_small(rcnt, nbr, rord, o.row_order);
-  wg_barrier<true>();
-  if (!o.col_ptr) return;
-
-  {
-    const int heavy = chunk_plans_small(rptr, rord, nbr, narrow, wide, wave_tot, sh);
-    if (tid == 0) o.scalars[1] = heavy;
-  }
-
-  // column-grouped index: the same count with the blocks taken in column-major order
   if (nnz > o.nnz_cap) return;
   {
     int* csc_blk = o.csc_row + (nnz + 3) / 4 * 4;
@@ -908,7 +984,7 @@ __global__ __launch_bounds__(1024) void k_pack_small(const double* __restrict__ 
 #pragma unroll
       for (int j = 0; j < kSmallPer; ++j) {
         if (j < per && e0 + j < n) {
-          keep_c |= m[at] ? 1u << j : 0u;
+          keep_c |= sh.col.m[at] ? 1u << j : 0u;
           at += nbc;
           if (++r == nbr) {
             r = 0;
@@ -925,7 +1001,7 @@ __global__ __launch_bounds__(1024) void k_pack_small(const double* __restrict__ 
       if (j < per && e0 + j < n) {
         if ((keep_c >> j) & 1u) {
           o.csc_row[e] = r;
-          csc_blk[e] = kpos[at];
+          csc_blk[e] = sh.col.kpos[at];
           ++e;
         }
         at += nbc;
@@ -1202,25 +1278,27 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
     BLAST_LAUNCH_CHECK("k_block_scores");
   }
 
-  if (n > 0 && n <= kSmallN && nbr <= 1024 && nbc <= 1024) {
-    // selection, row pointers, column indices, schedule, chunk plans and column-grouped index: one launch
-    const SmallOut o{row_ptr, col_idx, blk_row, row_order, m, col_ptr, csc_row, nnz_dev, nnz_cap};
-    if (mode == BLAST_PACK_TOPK_FROBENIUS)
-      k_pack_small<true><<<dim3(1), dim3(1024), 0, stream>>>(scores, nullptr, (int)nbr, (int)nbc, (long long)n_keep, o,
-                                                             narrow, wide);
-    else
-      k_pack_small<false><<<dim3(1), dim3(1024), 0, stream>>>(nullptr, mask, (int)nbr, (int)nbc, 0ll, o, narrow, wide);
-    BLAST_LAUNCH_CHECK("k_pack_small");
-  } else {
-    if (m && n > 0) {
-      if (!scored) {
-        k_fill_u8<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(m, n, n_keep == n ? 1 : 0);
-        BLAST_LAUNCH_CHECK("k_fill_u8");
-      } else {
-        k_select_topk<<<dim3(1), dim3(1024), 0, stream>>>(scores, n, n_keep, m);
-        BLAST_LAUNCH_CHECK("k_select_topk");
-      }
+  if (m && n > 0) {
+    if (!scored) {
+      k_fill_u8<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(m, n, n_keep == n ? 1 : 0);
+      BLAST_LAUNCH_CHECK("k_fill_u8");
+    } else if (n <= kSmallN) {
+      k_select_small<<<dim3(1), dim3(1024), 0, stream>>>(scores, (int)n, (long long)n_keep, m);
+      BLAST_LAUNCH_CHECK("k_select_small");
+    } else {
+      k_select_topk<<<dim3(1), dim3(1024), 0, stream>>>(scores, n, n_keep, m);
+      BLAST_LAUNCH_CHECK("k_select_topk");
     }
+  }
+  if (n > 0 && n <= kSmallN && nbr <= 1024 && nbc <= 1024) {
+    // every index array and the values: one launch
+    const SmallOut o{row_ptr, col_idx, row_order, col_ptr, csc_row, nnz_dev, nnz_cap};
+    const unsigned spans = nnz_cap > 0 ? (unsigned)((n + kGatherSpan - 1) / kGatherSpan) : 0u;
+    k_pack_small<<<dim3((aux ? 2u : 1u) + spans), dim3(1024), 0, stream>>>(mask, (int)nbr, (int)nbc, o, narrow, wide,
+                                                                          GatherArgs{W, ldw, b, vals});
+    BLAST_LAUNCH_CHECK("k_pack_small");
+    return BLAST_OK;
+  } else {
     if (nbr > 0) {
       k_line_counts<<<dim3((unsigned)((nbr + 3) / 4)), dim3(256), 0, stream>>>(mask, (int)nbr, (int)nbc, nbc, 1, rcnt);
       BLAST_LAUNCH_CHECK("k_line_counts(rows)");

@@ -183,3 +183,32 @@ def test_unpack_is_the_inverse_of_pack(api, b):
     keep = np.kron((mask == 1).astype(np.uint16), np.ones((b, b), dtype=np.uint16))
     assert np.array_equal(got, W * keep)
     assert np.all(big.cpu().numpy()[:, cols:] == -1)  # nothing written past the row width
+
+
+@pytest.mark.parametrize("nbr,nbc,b", [(1, 1, 128), (1024, 8, 16), (8, 1024, 16), (1023, 3, 16), (5, 13, 32), (91, 90, 16),
+                                       (1025, 2, 16), (17, 33, 64)])
+@pytest.mark.parametrize("with_aux", [True, False])
+def test_pack_at_the_edges_of_its_single_launch(api, nbr, nbc, b, with_aux):
+    """The largest and smallest matrices of the single packing launch, counts of blocks that are no multiple of what a
+    gathering workgroup takes, one row too many; regrown blocks (mask code 2) are stored as zeros."""
+    import torch
+
+    rng = np.random.default_rng(700 + nbr + nbc)
+    W = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.05)
+    mask = rng.choice(np.array([0, 0, 1, 2], dtype=np.uint8), size=(nbr, nbc))
+    mask[0, 0] = 1
+    p = api.bsr_pack(to_dev(W), b, mask=mask_dev(mask), with_aux=with_aux)
+    ref = orc.pack(W, b, (mask != 0).astype(np.uint8))
+    assert p.nnz == ref.nnz and p.max_row_blocks == (int(np.diff(ref.row_ptr).max()) if with_aux else 0)
+    assert np.array_equal(p.row_ptr.cpu().numpy(), ref.row_ptr)
+    assert np.array_equal(p.col_idx.cpu().numpy()[: p.nnz], ref.col_idx)
+    assert np.array_equal(p.row_order.cpu().numpy(), ref.row_order)
+    want = ref.vals.copy()
+    want[(mask[mask != 0] == 2)] = 0
+    assert np.array_equal(bits_of(p.vals)[: p.nnz * b * b].reshape(p.nnz, b, b), want)
+    if with_aux:  # the column-grouped index, by way of the transpose
+        t = api.bsr_transpose(p)
+        ref_t = orc.pack(np.ascontiguousarray(W.T), b, np.ascontiguousarray((mask != 0).T.astype(np.uint8)))
+        assert np.array_equal(t.row_ptr.cpu().numpy(), ref_t.row_ptr)
+        assert np.array_equal(t.col_idx.cpu().numpy()[: t.nnz], ref_t.col_idx)
+        assert np.array_equal(t.row_order.cpu().numpy(), ref_t.row_order)
