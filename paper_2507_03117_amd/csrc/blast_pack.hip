@@ -556,160 +556,179 @@ static_assert(kSmallN + 1024 < 65536, "two counts share a 32-bit word");
 static_assert((blast::kChunkBlocks & (blast::kChunkBlocks - 1)) == 0 &&
               (blast::kWideChunkBlocks & (blast::kWideChunkBlocks - 1)) == 0, "chunk sizes are powers of two");
 
-// LDS scratch of select_small.
+// LDS scratch of select_small, one per group.
 struct SelectShared {
   unsigned hist[256];
   int wave_tot[16];
-  unsigned long long prefix, kth;
-  long long remaining;
-  unsigned h;
+  unsigned long long diff, kth;  // bits in which keys differ; the n_keep-th key ...
+  int kth_at;                    // ... and its index: what is kept sorts before it, or is it
+  int rem, eq, digit, fill, open;
+  int cand[kWave];
 };
 
-// Exact selection of the n_keep highest of n <= kSmallN scores by one workgroup of 1024 threads: thread t owns
-// scores t * per ... t * per + per - 1 (per = ceil(n / 1024)) and returns their keep flags (bit j: score
-// t * per + j is kept).  Equal scores are kept in index order.
-__device__ __forceinline__ unsigned select_small(const double* __restrict__ score, int n, long long n_keep, int per,
-                                                 SelectShared& sh) {
-  const int tid = threadIdx.x, lane = lane_id();
-  const int e0 = tid * per;
-  unsigned* hist = sh.hist;
-  int* wave_tot = sh.wave_tot;
-  unsigned long long& s_prefix = sh.prefix;
-  unsigned long long& s_kth = sh.kth;
-  long long& s_remaining = sh.remaining;
-  unsigned& s_h = sh.h;
-  unsigned keep = 0u;
-  {
-    unsigned long long key[kSmallPer];
+// The n_keep-th of n <= kSmallN scores (0 < n_keep < n) under (score descending, index ascending), into sh.kth and
+// sh.kth_at, by a group of NT threads of a workgroup of GROUPS * NT: the caller's groups select side by side (every
+// barrier is the workgroup's; a selection that is through waits for the others).  keys: LDS, n entries, receives the
+// keys of the scores.
+//
+// Most-significant-digit radix select: scores of one matrix share their leading bits (sign, exponent, often the first
+// mantissa bits), and a digit that every key carries would send every count to one LDS word, so the passes start below
+// the bits common to all keys, eight bits at a time; as soon as at most 64 keys carry the selected prefix, a wave ranks
+// those by comparing each with all.
+// What bounds it is not the work but its dependent steps and, in a workgroup that runs every instruction once or
+// twice with caches full of weights, the fetching of instructions: loops are left rolled.  4096 blocks, weight and gradient (timestamps):
+// keys unrolled over registers and passes down to one key, the two selections in turn: 16 us; this: 12.8 us.
+template <int NT, int GROUPS>
+__device__ __forceinline__ void select_small(const double* __restrict__ score, int n, int n_keep, unsigned long long* keys,
+                                             SelectShared* shared) {
+  const int lane = lane_id(), group = GROUPS == 1 ? 0 : threadIdx.x / NT, tid = threadIdx.x - group * NT;
+  SelectShared& sh = shared[group];
+  const unsigned long long* bits = reinterpret_cast<const unsigned long long*>(score);
+  unsigned long long diff = 0ull;
+  const unsigned long long key0 = order_key(bits[0]);
+  if (tid == 0) sh.diff = 0ull;
+#pragma unroll 4
+  for (int i = tid; i < n; i += NT) {
+    const unsigned long long k = order_key(bits[i]);
+    keys[i] = k;
+    diff |= k ^ key0;
+  }
+#pragma unroll 1
+  for (int d = kWave / 2; d > 0; d >>= 1) diff |= __shfl_xor(diff, d, kWave);
+  wg_barrier<true>();
+  if (lane == 0 && diff != 0ull) atomicOr(&sh.diff, diff);
+  wg_barrier<true>();
+  diff = sh.diff;
+  int fixed = diff == 0ull ? 0 : 64 - __clzll(diff);  // bits at and above this position are decided
+  unsigned long long prefix = fixed == 64 ? 0ull : (key0 >> fixed) << fixed;
+  int rem = n_keep, eq = n;  // the rem-th of the eq keys that carry the decided bits is the one
+  auto carries = [&](unsigned long long k) { return fixed == 64 || (k >> fixed) == (prefix >> fixed); };
+#pragma unroll 1
+  for (;;) {
+    const bool active = fixed > 0 && eq > kWave;
+    if (tid == 0) {
+      sh.open = active ? 1 : 0;
+      sh.fill = 0;
+    }
+    if (tid < 256) sh.hist[tid] = 0u;
+    wg_barrier<true>();
+    int open = 0;
 #pragma unroll
-    for (int j = 0; j < kSmallPer; ++j)
-      key[j] = (j < per && e0 + j < n) ? order_key(reinterpret_cast<const unsigned long long*>(score)[e0 + j]) : 0ull;
-    if (n_keep <= 0 || n_keep >= n) {
-#pragma unroll
-      for (int j = 0; j < kSmallPer; ++j) keep |= (j < per && e0 + j < n && n_keep > 0) ? 1u << j : 0u;
-    } else {
-      // Most-significant-digit radix select of the n_keep-th largest key.  Scores of one matrix share their
-      // leading bits (sign, exponent, often the first mantissa bits), and a digit that every key carries would
-      // send every count to one LDS word: the bits above the highest one in which any two keys differ are taken
-      // as they are, the passes start below them, eight bits at a time, and stop as soon as a single key
-      // carries the selected prefix.
-      unsigned long long diff = 0ull;
-      const unsigned long long key0 = order_key(reinterpret_cast<const unsigned long long*>(score)[0]);
-#pragma unroll
-      for (int j = 0; j < kSmallPer; ++j)
-        if (j < per && e0 + j < n) diff |= key[j] ^ key0;
-#pragma unroll
-      for (int d = kWave / 2; d > 0; d >>= 1) diff |= __shfl_xor(diff, d, kWave);
-      if (tid == 0) s_kth = 0ull;
-      wg_barrier<true>();
-      if (lane == 0 && diff != 0ull) atomicOr(&s_kth, diff);
-      wg_barrier<true>();
-      diff = s_kth;
-      int fixed = diff == 0ull ? 0 : 64 - __clzll(diff);  // bits at and above this position are decided
-      unsigned long long prefix = fixed == 64 ? 0ull : (key0 >> fixed) << fixed;
-      long long rem = n_keep;
-      unsigned eq_total = (unsigned)n;  // keys that carry the decided bits
-      while (fixed > 0) {
-        const int sft = fixed > 8 ? fixed - 8 : 0, width = fixed - sft;
-        if (tid < 256) hist[tid] = 0u;
-        wg_barrier<true>();
-#pragma unroll
-        for (int j = 0; j < kSmallPer; ++j) {
-          if (j < per) {
-            const bool in = e0 + j < n && (fixed == 64 || (key[j] >> fixed) == (prefix >> fixed));
-            if (in) atomicAdd(&hist[(unsigned)(key[j] >> sft) & ((1u << width) - 1u)], 1u);
-          }
-        }
-        wg_barrier<true>();
-        if (tid < kWave) {
-          // lane l looks at bins 255 - 4l ... 252 - 4l; `larger` = keys in bins above the one looked at
-          unsigned h4[4], sum = 0u;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            h4[u] = hist[255 - 4 * lane - u];
-            sum += h4[u];
-          }
-          unsigned inc = sum;
-#pragma unroll
-          for (int d = 1; d < kWave; d <<= 1) {
-            const unsigned v = __shfl_up(inc, d, kWave);
-            if (lane >= d) inc += v;
-          }
-          long long larger = (long long)(inc - sum);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const long long h = h4[u];
-            if (larger < rem && rem <= larger + h) {
-              s_remaining = rem - larger;
-              s_prefix = prefix | ((unsigned long long)(255 - 4 * lane - u) << sft);
-              s_h = (unsigned)h;
-            }
-            larger += h;
-          }
-        }
-        wg_barrier<true>();
-        prefix = s_prefix;
-        rem = s_remaining;
-        eq_total = s_h;
-        fixed = sft;
-        if (eq_total == 1u && fixed > 0) {
-#pragma unroll
-          for (int j = 0; j < kSmallPer; ++j)
-            if (j < per && e0 + j < n && (key[j] >> fixed) == (prefix >> fixed)) s_kth = key[j];
-          wg_barrier<true>();
-          prefix = s_kth;
-          break;
-        }
-      }
-      const unsigned long long kth = prefix;
-      if (rem == (long long)eq_total) {
-#pragma unroll
-        for (int j = 0; j < kSmallPer; ++j) keep |= (j < per && e0 + j < n && key[j] >= kth) ? 1u << j : 0u;
-      } else {
-        // of the keys equal to the threshold the first `rem` in index order are kept
-        int neq = 0;
-#pragma unroll
-        for (int j = 0; j < kSmallPer; ++j) neq += (j < per && e0 + j < n && key[j] == kth) ? 1 : 0;
-        int total;
-        long long pos = block_exscan<true>(neq, wave_tot, total);
-#pragma unroll
-        for (int j = 0; j < kSmallPer; ++j) {
-          if (j < per && e0 + j < n) {
-            const bool eq = key[j] == kth;
-            if (key[j] > kth || (eq && pos < rem)) keep |= 1u << j;
-            pos += eq ? 1 : 0;
-          }
-        }
+    for (int q = 0; q < GROUPS; ++q) open |= shared[q].open;
+    if (open == 0) break;
+    const int sft = fixed > 8 ? fixed - 8 : 0, width = fixed - sft;
+    if (active) {
+#pragma unroll 2
+      for (int i = tid; i < n; i += NT) {
+        const unsigned long long k = keys[i];
+        if (carries(k)) atomicAdd(&sh.hist[(unsigned)(k >> sft) & ((1u << width) - 1u)], 1u);
       }
     }
+    wg_barrier<true>();
+    if (active && tid < kWave) {
+      // lane l looks at bins 255 - 4l ... 252 - 4l; `larger` = keys in bins above the one looked at
+      const uint4 h = *reinterpret_cast<const uint4*>(&sh.hist[252 - 4 * lane]);
+      const int h4[4] = {(int)h.w, (int)h.z, (int)h.y, (int)h.x};
+      const int sum = (h4[0] + h4[1]) + (h4[2] + h4[3]);
+      int inc = sum;
+#pragma unroll 1
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int v = __shfl_up(inc, d, kWave);
+        if (lane >= d) inc += v;
+      }
+      int larger = inc - sum;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (larger < rem && rem <= larger + h4[u]) {
+          sh.rem = rem - larger;
+          sh.eq = h4[u];
+          sh.digit = 255 - 4 * lane - u;
+        }
+        larger += h4[u];
+      }
+    }
+    wg_barrier<true>();
+    if (active) {
+      rem = sh.rem;
+      eq = sh.eq;
+      prefix |= (unsigned long long)(unsigned)sh.digit << sft;
+      fixed = sft;
+    }
   }
-  return keep;
+  int eq_mine = 0, eq_before = 0;
+  if (eq <= kWave) {
+#pragma unroll 2
+    for (int i = tid; i < n; i += NT)
+      if (carries(keys[i])) sh.cand[atomicAdd(&sh.fill, 1)] = i;
+  } else {
+    // more than 64 equal keys: a thread counts those in its stretch of the indices
+    const int per = (n + NT - 1) / NT, e0 = tid * per;
+    int mine = 0;
+    for (int i = e0; i < e0 + per && i < n; ++i) mine += keys[i] == prefix ? 1 : 0;
+    int inc = mine;
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int v = __shfl_up(inc, d, kWave);
+      if (lane >= d) inc += v;
+    }
+    if (lane == kWave - 1) sh.wave_tot[tid / kWave] = inc;
+    eq_mine = mine;
+    eq_before = inc - mine;
+  }
+  wg_barrier<true>();
+  if (eq <= kWave) {
+    if (tid < kWave) {
+      const int at = lane < eq ? sh.cand[lane] : 0;
+      const unsigned long long k = lane < eq ? keys[at] : 0ull;
+      int before = 0;
+#pragma unroll 1
+      for (int c = 0; c < eq; ++c) {
+        const unsigned long long kc = __shfl(k, c, kWave);
+        const int ac = __shfl(at, c, kWave);
+        before += (kc > k || (kc == k && ac < at)) ? 1 : 0;
+      }
+      if (lane < eq && before == rem - 1) {
+        sh.kth = k;
+        sh.kth_at = at;
+      }
+    }
+  } else {
+    for (int w = 0; w < tid / kWave; ++w) eq_before += sh.wave_tot[w];
+    if (eq_before < rem && rem <= eq_before + eq_mine) {
+      const int per = (n + NT - 1) / NT;
+      int i = tid * per;
+      for (int c = rem - eq_before;; ++i)
+        if (keys[i] == prefix && --c == 0) break;
+      sh.kth = prefix;
+      sh.kth_at = i;
+    }
+  }
+  wg_barrier<true>();
 }
 
-// One workgroup: mask[i] = 1 for the n_keep highest of n <= kSmallN scores, else 0.
-__global__ __launch_bounds__(1024) void k_select_small(const double* __restrict__ score, int n, long long n_keep,
+__device__ __forceinline__ bool select_keeps(const SelectShared& sh, unsigned long long k, int i) {
+  return k > sh.kth || (k == sh.kth && i <= sh.kth_at);
+}
+
+// One workgroup: mask[i] = 1 for the n_keep highest of n <= kSmallN scores, else 0.  Dynamic LDS: n keys.
+__global__ __launch_bounds__(1024) void k_select_small(const double* __restrict__ score, int n, int n_keep,
                                                        uint8_t* __restrict__ mask) {
-  __shared__ SelectShared ssh;
-  const int per = (n + 1023) >> 10, e0 = threadIdx.x * per;
-  const unsigned keep = select_small(score, n, n_keep, per, ssh);
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j)
-    if (j < per && e0 + j < n) mask[e0 + j] = (keep >> j) & 1u;
+  extern __shared__ __attribute__((aligned(16))) unsigned long long keys[];
+  __shared__ __attribute__((aligned(16))) SelectShared ssh[1];
+  select_small<1024, 1>(score, n, n_keep, keys, ssh);
+  for (int i = threadIdx.x; i < n; i += 1024) mask[i] = select_keeps(ssh[0], keys[i], i) ? 1 : 0;
 }
 
-// One workgroup: the mask update of prune-and-grow on n <= kSmallN blocks - both selections and their merge
-// (1 where the weight's selection keeps the block, 2 where only the gradient's does, else 0).
+// One workgroup: the mask update of prune-and-grow on n <= kSmallN blocks - both selections, side by side, and their
+// merge (1 where the weight's selection keeps the block, 2 where only the gradient's does, else 0).  Dynamic LDS: 2 n keys.
 __global__ __launch_bounds__(1024) void k_masks_small(const double* __restrict__ score_w,
-                                                      const double* __restrict__ score_g, int n, long long n_keep,
+                                                      const double* __restrict__ score_g, int n, int n_keep,
                                                       uint8_t* __restrict__ mask) {
-  __shared__ SelectShared ssh;
-  const int per = (n + 1023) >> 10, e0 = threadIdx.x * per;
-  const unsigned keep_w = select_small(score_w, n, n_keep, per, ssh);
-  wg_barrier<true>();  // the scratch is used again
-  const unsigned keep_g = select_small(score_g, n, n_keep, per, ssh);
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j)
-    if (j < per && e0 + j < n) mask[e0 + j] = ((keep_w >> j) & 1u) ? 1 : (((keep_g >> j) & 1u) ? 2 : 0);
+  extern __shared__ __attribute__((aligned(16))) unsigned long long keys[];
+  __shared__ __attribute__((aligned(16))) SelectShared ssh[2];
+  const bool grad = threadIdx.x >= 512;
+  select_small<512, 2>(grad ? score_g : score_w, n, n_keep, grad ? keys + n : keys, ssh);
+  for (int i = threadIdx.x; i < n; i += 1024)
+    mask[i] = select_keeps(ssh[0], keys[i], i) ? 1 : (select_keeps(ssh[1], keys[n + i], i) ? 2 : 0);
 }
 
 // Rows by population, descending, stable: rord (LDS) and row_order get the schedule of nbr <= 1024 rows; run by a
@@ -1173,6 +1192,27 @@ int check_shape(int64_t rows, int64_t cols, int32_t b) {
   return BLAST_OK;
 }
 
+// mask = the n_keep highest of n <= kSmallN scores (0 < n_keep < n); with scores1 merged with the n_keep highest of those.
+int launch_select_small(const double* scores, const double* scores1, int64_t n, int64_t n_keep, uint8_t* mask,
+                        hipStream_t stream) {
+  static blast::DeviceFlags lds_set;
+  int dev = 0;
+  BLAST_HIP_TRY(hipGetDevice(&dev));
+  if (!lds_set.test(dev)) {
+    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_select_small),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, kSmallN * 8));
+    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_masks_small),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kSmallN * 8));
+    lds_set.set(dev);
+  }
+  if (scores1)
+    k_masks_small<<<dim3(1), dim3(1024), (size_t)n * 16, stream>>>(scores, scores1, (int)n, (int)n_keep, mask);
+  else
+    k_select_small<<<dim3(1), dim3(1024), (size_t)n * 8, stream>>>(scores, (int)n, (int)n_keep, mask);
+  BLAST_LAUNCH_CHECK("k_select_small");
+  return BLAST_OK;
+}
+
 // A small pinned buffer per host thread (allocated on first use and kept) through which numbers come back from the
 // device: a copy into pageable memory costs a call tens of microseconds more.  Kernels can store to it themselves.
 // Null when it cannot be had.
@@ -1283,8 +1323,7 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
       k_fill_u8<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(m, n, n_keep == n ? 1 : 0);
       BLAST_LAUNCH_CHECK("k_fill_u8");
     } else if (n <= kSmallN) {
-      k_select_small<<<dim3(1), dim3(1024), 0, stream>>>(scores, (int)n, (long long)n_keep, m);
-      BLAST_LAUNCH_CHECK("k_select_small");
+      if (int rc = launch_select_small(scores, nullptr, n, n_keep, m, stream)) return rc;
     } else {
       k_select_topk<<<dim3(1), dim3(1024), 0, stream>>>(scores, n, n_keep, m);
       BLAST_LAUNCH_CHECK("k_select_topk");
@@ -1512,9 +1551,7 @@ extern "C" int blast_generate_masks(const uint16_t* W, int64_t ldw, const uint16
   k_block_scores<<<dim3((unsigned)n, 2), dim3(256), 0, stream>>>(W, ldw, (int)nbc, b, scores, G, ldg, scores_g);
   BLAST_LAUNCH_CHECK("k_block_scores(W, G)");
   if (n <= kSmallN) {  // both selections and the merge in one workgroup
-    k_masks_small<<<dim3(1), dim3(1024), 0, stream>>>(scores, scores_g, (int)n, (long long)n_keep, mask_out);
-    BLAST_LAUNCH_CHECK("k_masks_small");
-    return BLAST_OK;
+    return launch_select_small(scores, scores_g, n, n_keep, mask_out, stream);
   }
   k_select_topk<<<dim3(2), dim3(1024), 0, stream>>>(scores, n, n_keep, mw, scores_g, mg);
   BLAST_LAUNCH_CHECK("k_select_topk(W, G)");
@@ -1562,9 +1599,7 @@ extern "C" int blast_pooled_topk_mask(const float* S, int64_t lds, int64_t rows,
   k_pooled_scores<<<dim3((unsigned)n), dim3(256), 0, stream>>>(S, lds, (int)nbc, b, scores);
   BLAST_LAUNCH_CHECK("k_pooled_scores");
   if (n <= kSmallN) {
-    k_select_small<<<dim3(1), dim3(1024), 0, stream>>>(scores, (int)n, (long long)n_keep, mask_out);
-    BLAST_LAUNCH_CHECK("k_select_small(pooled)");
-    return BLAST_OK;
+    return launch_select_small(scores, nullptr, n, n_keep, mask_out, stream);
   }
   k_select_topk<<<dim3(1), dim3(1024), 0, stream>>>(scores, n, n_keep, mask_out);
   BLAST_LAUNCH_CHECK("k_select_topk(pooled)");

@@ -212,3 +212,34 @@ def test_pack_at_the_edges_of_its_single_launch(api, nbr, nbc, b, with_aux):
         assert np.array_equal(t.row_ptr.cpu().numpy(), ref_t.row_ptr)
         assert np.array_equal(t.col_idx.cpu().numpy()[: t.nnz], ref_t.col_idx)
         assert np.array_equal(t.row_order.cpu().numpy(), ref_t.row_order)
+
+
+@pytest.mark.parametrize("nbr,nbc,levels_w,levels_g", [(3, 7, 2, 9), (32, 64, 3, 1), (64, 128, 2, 200), (64, 128, 1, 2),
+                                                       (40, 45, 1000, 3)])
+@pytest.mark.parametrize("s", [0.3, 0.81])
+def test_selection_among_equal_scores(api, nbr, nbc, levels_w, levels_g, s):
+    """Constant blocks of a few values: many equal scores at the threshold (more than a wave ranks by comparing, or
+    fewer), in one of the two rankings of the mask update or in both, and in the packer's; ties by index."""
+    import torch
+
+    rng = np.random.default_rng(900 + nbr + levels_w)
+    b, n = 16, nbr * nbc
+
+    def constant_blocks(levels):
+        v = rng.integers(1, levels + 1, size=n).astype(np.float32)
+        return v, to_dev(synth.f32_to_bf16_bits(np.kron(v.reshape(nbr, nbc), np.ones((b, b), dtype=np.float32))))
+
+    (vw, W), (vg, G) = constant_blocks(levels_w), constant_blocks(levels_g)
+    # (values above 256 are rounded to bf16: rank what the device sees)
+    vw, vg = (synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(v)) for v in (vw, vg))
+    n_keep = api.n_keep(n, s)
+
+    def kept(v):
+        m = np.zeros(n, dtype=bool)
+        m[np.lexsort((np.arange(n), -v))[:n_keep]] = True
+        return m
+
+    want = np.where(kept(vw), 1, np.where(kept(vg), 2, 0)).astype(np.uint8)
+    assert np.array_equal(api.generate_masks(W, G, b, s).cpu().numpy().ravel(), want)
+    p = api.bsr_pack(W, b, sparsity=s)
+    assert p.nnz == n_keep and np.array_equal(p.col_idx.cpu().numpy()[:n_keep], np.nonzero(kept(vw))[0] % nbc)
