@@ -20,14 +20,14 @@ int cu_count_bwd() {
   return n;
 }
 
-template <int B>
+template <int B, int KW, int UPW>
 int launch_sddmm(SddmmArgs a, hipStream_t stream) {
-  using C = SdCfg<B>;
+  using C = SdCfg<B, KW, UPW>;
   static blast::DeviceFlags lds_set;
   int dev = 0;
   BLAST_HIP_TRY(hipGetDevice(&dev));
   if (!lds_set.test(dev)) {
-    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sddmm<B>),
+    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sddmm<B, KW, UPW>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES));
     lds_set.set(dev);
   }
@@ -52,9 +52,27 @@ int launch_sddmm(SddmmArgs a, hipStream_t stream) {
     k_zero_f32<<<dim3((unsigned)((n / 4 + 255) / 256 + 1)), dim3(256), 0, stream>>>(a.dvals, n);
     BLAST_LAUNCH_CHECK("k_zero_f32");
   }
-  k_sddmm<B><<<dim3((unsigned)((units + 7) / 8 * 8)), dim3(256), C::LDS_BYTES, stream>>>(a);
+  k_sddmm<B, KW, UPW><<<dim3((unsigned)((units + 8 * UPW - 1) / (8 * UPW) * 8)), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(a);
   BLAST_LAUNCH_CHECK("k_sddmm");
   return BLAST_OK;
+}
+
+// Which form, by the units (64-wide sub-blocks of the stored blocks) per CU.
+//   fewer than 2: four waves per unit, or most SIMDs would idle (1.6 units, 700 tokens: 11.1 us against 13.1 with one
+//     wave; 2.4 units, 2000 tokens: 28.9 against 26.7).
+//   up to what is resident at once with a wave per workgroup (rings in 128 of a CU's 160 KiB): a wave per unit, dealt
+//     to the CUs one by one; every XCD then streams X once (4.8 units, 2000 tokens: 40 us; four waves per unit 48, four
+//     units per workgroup 53, whose 308 workgroups load some CUs twice).
+//   more: four neighbouring units, blocks of one row or quarters of one block, in a workgroup, so that the tiles they
+//     share are still in the L1 or L2 (11.2 units, 128-wide blocks, 4096 tokens: 144 us; a wave per workgroup 200, four
+//     waves per unit 185).
+template <int B>
+int sddmm_form(const SddmmArgs& a, hipStream_t stream) {
+  using One = SdCfg<B, 1, 1>;
+  const int64_t units = (int64_t)a.nnz * One::SUB * One::SUB, cus = cu_count_bwd();
+  if (units < 2 * cus) return launch_sddmm<B, 4, 1>(a, stream);
+  if (units * (int64_t)One::LDS_BYTES <= cus * (128 << 10)) return launch_sddmm<B, 1, 1>(a, stream);
+  return launch_sddmm<B, 1, 4>(a, stream);
 }
 
 }  // namespace
@@ -97,9 +115,9 @@ extern "C" int blast_bsr_sddmm(const blast_bsr_view* W, const uint16_t* dY, int6
     a.nbr = (int)(W->rows / b);
     a.nnz = (int)W->nnz;
     switch (b) {
-      case 32: return launch_sddmm<32>(a, stream);
-      case 64: return launch_sddmm<64>(a, stream);
-      default: return launch_sddmm<128>(a, stream);
+      case 32: return sddmm_form<32>(a, stream);
+      case 64: return sddmm_form<64>(a, stream);
+      default: return sddmm_form<128>(a, stream);
     }
   }
   SddmmGenericArgs g{};

@@ -10,13 +10,19 @@
 // global -> LDS as they are (LDS-DMA, whole 64/128-byte row segments) and turned on the way into the
 // registers, two reads per 8-token operand fragment.
 //
-// Work decomposition: a workgroup owns a unit = (stored block, SB x SB sub-block, token chunk); its four
-// waves deal the 16-token stages of the chunk among themselves, each accumulating the whole sub-block
-// (64 x 64: 2 x 2 register blocking, every fragment used twice) from a private ring of LDS stages - no
-// barrier inside the loop, the wave's memory counter is the only synchronisation (the scheme of the
-// decode kernel) - and the four partial sums are added in LDS at the end.  When a matrix has too few
-// blocks to fill the chip even so, the tokens are cut into chunks across workgroups as well and those
-// partial sums meet through fp32 atomics on a zeroed output.
+// Work decomposition: a unit = (stored block, SB x SB sub-block, token chunk), accumulated whole by a wave (64 x 64:
+// 2 x 2 register blocking, every fragment used twice) from its private ring of LDS stages of 16 tokens - no barrier
+// inside the loop, the wave's memory counter is the only synchronisation (the scheme of the decode kernel).  KW waves
+// share a unit (four: they deal its stages among themselves and add their sums in LDS at the end; one: nothing to
+// add), UPW units make a workgroup; launch_sddmm's caller says which form when.  When a matrix has too few blocks to
+// fill the chip even so, the tokens are cut into chunks across workgroups as well and those partial sums meet through
+// fp32 atomics on a zeroed output.
+//
+// What bounds it: a stage is 4 KiB for four matrix instructions, 128 bytes per clock and CU at the matrix peak of
+// which an L1 delivers about 54; the floor that leaves is 22 us for 1229 64-wide blocks at 2000 tokens.  There: 49 us
+// with four waves per block (5 blocks per CU are 2.4 rounds of the 2 workgroups that fit, and each round streams all
+// of X across the fabric to every XCD again) and branches on every stage; 40 us with a wave per block, all resident,
+// and a steady state that decides nothing (640 -> 330 clk per stage of a lone wave).
 #pragma once
 #include "kern_common.h"
 #include "kern_stream.h"
@@ -80,7 +86,8 @@ struct SddmmArgs {
   int n_units;         // workgroups with work: nnz * SUB * SUB * tsplit
 };
 
-template <int B>
+// KW = waves that share a unit, UPW = units of a workgroup.
+template <int B, int KW, int UPW>
 struct SdCfg {
   static_assert(B == 32 || B == 64 || B == 128, "block sizes with at least one 32 x 32 matrix tile");
   static constexpr int SB = B < 64 ? B : 64;   // edge of the sub-block one wave accumulates
@@ -93,9 +100,11 @@ struct SdCfg {
   static constexpr int NI = TILE / 1024;       // wave-wide copy instructions per tile
   static constexpr int OPS = 2 * NI;           // per stage (dY tile + X tile)
   static constexpr int STAGE = 2 * TILE;
-  static constexpr int NSTAGE = 4;             // 16 KiB of ring per wave at SB = 64: two workgroups per CU
+  static constexpr int NSTAGE = 4;             // 16 KiB of ring per wave at SB = 64
   static constexpr int WAVE_LDS = NSTAGE * STAGE;
-  static constexpr size_t LDS_BYTES = 4 * (size_t)WAVE_LDS;
+  static_assert(KW == 1 || UPW == 1, "waves that share a unit meet at the workgroup's barrier");
+  static constexpr int NW = KW * UPW;
+  static constexpr size_t LDS_BYTES = NW * (size_t)WAVE_LDS;
   static_assert(TILE % 1024 == 0 && (NSTAGE - 1) * OPS < 64, "copy granularity / counter range");
   // Swizzle key of a tile row: the four token rows that one transposing read touches must land on
   // different banks.  Rows are ROWB bytes apart, so 128 / ROWB rows share a 128-byte bank line.
@@ -121,19 +130,21 @@ __device__ __forceinline__ void sd_wait_vm(int later, int ops) {
   }
 }
 
-template <int B>
-__global__ __launch_bounds__(256) void k_sddmm(const SddmmArgs a) {
-  using C = SdCfg<B>;
+template <int B, int KW, int UPW>
+__global__ __launch_bounds__(64 * KW * UPW) void k_sddmm(const SddmmArgs a) {
+  using C = SdCfg<B, KW, UPW>;
   constexpr int NQ = C::NQ, NI = C::NI, NSTAGE = C::NSTAGE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = KW == 1 ? 0 : wv;  // place among the waves of the unit
   const int lane = threadIdx.x & 63;
   // Workgroup ids are dealt round-robin to the 8 XCDs: consecutive units (blocks of one block row, which
   // read the same columns of dY) are given ids 8 apart, so they run on one XCD and share its L2.
-  const int per_xcd = (a.n_units + 7) >> 3;
-  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (unit >= a.n_units) return;  // whole workgroup, before any barrier
-  unsigned char* ring = smem + wave * C::WAVE_LDS;
+  const int n_groups = (a.n_units + UPW - 1) / UPW;
+  const int per_xcd = (n_groups + 7) >> 3;
+  const int unit = ((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3)) * UPW + (KW == 1 ? wv : 0);
+  if (unit >= a.n_units) return;  // every wave of a unit, before any barrier
+  unsigned char* ring = smem + wv * C::WAVE_LDS;
 
   // unit -> (stored block q, sub-block (si, sj), token chunk tc); token chunks of one sub-block are adjacent
   const int tc = unit % a.tsplit;
@@ -150,9 +161,9 @@ __global__ __launch_bounds__(256) void k_sddmm(const SddmmArgs a) {
   const int t_lo = tc * a.chunk_tokens;
   int t_hi = t_lo + a.chunk_tokens;
   if (t_hi > a.T) t_hi = a.T;
-  // the four waves deal the 16-token stages of the chunk among themselves: wave w takes w, w + 4, ...
+  // the waves of a unit deal the 16-token stages of the chunk among themselves: wave w takes w, w + KW, ...
   const int chunk_stages = t_hi > t_lo ? (t_hi - t_lo + C::KT - 1) / C::KT : 0;
-  const int n_stage = chunk_stages > wave ? (chunk_stages - wave + 3) >> 2 : 0;
+  const int n_stage = chunk_stages > wave ? (chunk_stages - wave + KW - 1) / KW : 0;
 
   // ---- per-lane constants -----------------------------------------------------------------------
   // Copy side: instruction ni of a tile writes LDS bytes [ni*1024 + lane*16, +16) = position p = ni*64 + lane
@@ -202,7 +213,7 @@ __global__ __launch_bounds__(256) void k_sddmm(const SddmmArgs a) {
   }
   auto issue = [&](int s) {
     unsigned char* slot = ring + (s % NSTAGE) * C::STAGE;
-    const int t0 = t_lo + (wave + 4 * s) * C::KT;
+    const int t0 = t_lo + (wave + KW * s) * C::KT;
     const unsigned char* ys = ybase + (int64_t)t0 * a.ldy * 2;
     const unsigned char* xs = xbase + (int64_t)t0 * a.ldx * 2;
     if (t0 + C::KT <= a.T) {
@@ -235,36 +246,7 @@ __global__ __launch_bounds__(256) void k_sddmm(const SddmmArgs a) {
   for (int s = 0; s < NSTAGE - 1; ++s)
     if (s < n_stage) issue(s);
 
-#pragma unroll 1
-  for (int s = 0; s < n_stage; ++s) {
-    // (the fragment reads of stage s - 1 returned inside their block: its slot goes back to the copier)
-    if (s + NSTAGE - 1 < n_stage) issue(s + NSTAGE - 1);
-    // copies retire in issue order: "at most (stages issued after s) * OPS outstanding" = stage s has landed
-    const int later = (n_stage - 1 - s) < (NSTAGE - 1) ? (n_stage - 1 - s) : (NSTAGE - 1);
-    sd_wait_vm(later, C::OPS);
-    asm volatile("" ::: "memory");
-    u32x2 fr[NF];
-    const uint32_t base = ring_addr + (uint32_t)((s % NSTAGE) * C::STAGE);
-    if constexpr (NQ == 2)
-      sd_read_stage2<4 * C::ROWB, C::TILE>(base + foff[0][0], base + foff[1][0], fr);
-    else
-      sd_read_stage1<4 * C::ROWB, C::TILE>(base + foff[0][0], fr);
-    // tokens of this stage that exist: all 16 except in the last stage of the last chunk
-    const int valid = a.T - (t_lo + (wave + 4 * s) * C::KT);
-    if (valid < C::KT) {
-      const int k0 = 8 * (lane >> 5);  // first token of this lane's fragments inside the stage
-#pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const int kf = k0 + 4 * (f & 1);  // half 1 holds tokens k0 + 4 .. k0 + 7
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {  // a register holds two tokens, the even one in its low half
-          uint32_t v = fr[f][w];
-          if (kf + 2 * w >= valid) v &= 0xFFFF0000u;
-          if (kf + 2 * w + 1 >= valid) v &= 0x0000FFFFu;
-          fr[f][w] = v;
-        }
-      }
-    }
+  auto multiply = [&](const u32x2 (&fr)[NF]) {
     bf16x8 fy[NQ], fx[NQ];
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) {
@@ -280,31 +262,79 @@ __global__ __launch_bounds__(256) void k_sddmm(const SddmmArgs a) {
 #pragma unroll
       for (int nj = 0; nj < NQ; ++nj)
         acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[mi], fx[nj], acc[mi][nj], 0, 0, 0);
+  };
+  auto read_stage = [&](u32x2 (&fr)[NF], uint32_t base) {
+    if constexpr (NQ == 2)
+      sd_read_stage2<4 * C::ROWB, C::TILE>(base + foff[0][0], base + foff[1][0], fr);
+    else
+      sd_read_stage1<4 * C::ROWB, C::TILE>(base + foff[0][0], fr);
+  };
+
+  int s = 0;
+  {
+    // Steady state: the stage that is issued lies wholly inside the tokens and the ring is full, so nothing is decided
+    // per stage - running pointers, one constant wait.
+    // the same number of stages for every wave of a unit: those whose last wave's tokens all exist
+    const int n_full = (t_hi - t_lo) / (KW * C::KT);
+    const int64_t t0 = t_lo + (wave + KW * (NSTAGE - 1)) * C::KT;
+    const unsigned char* ys = ybase + t0 * a.ldy * 2;
+    const unsigned char* xs = xbase + t0 * a.ldx * 2;
+    const int64_t ystep = a.ldy * (2 * KW * C::KT), xstep = a.ldx * (2 * KW * C::KT);
+    uint32_t rd = 0, wr = (NSTAGE - 1) * C::STAGE;
+#pragma unroll 1
+    for (; s + NSTAGE - 1 < n_full; ++s) {
+      unsigned char* slot = ring + wr;
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) BLAST_GLDS16(ys + yoff[ni], slot + ni * 1024);
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) BLAST_GLDS16(xs + xoff[ni], slot + C::TILE + ni * 1024);
+      __builtin_amdgcn_s_waitcnt(BLAST_VMCNT((NSTAGE - 1) * C::OPS));
+      asm volatile("" ::: "memory");
+      u32x2 fr[NF];
+      read_stage(fr, ring_addr + rd);
+      multiply(fr);
+      ys += ystep;
+      xs += xstep;
+      wr = rd;
+      rd = rd + C::STAGE == (uint32_t)C::WAVE_LDS ? 0u : rd + C::STAGE;
+    }
+  }
+  // the last stages: the ring drains, and the tokens may end inside a stage
+#pragma unroll 1
+  for (; s < n_stage; ++s) {
+    // (the fragment reads of stage s - 1 returned inside their block: its slot goes back to the copier)
+    if (s + NSTAGE - 1 < n_stage) issue(s + NSTAGE - 1);
+    // copies retire in issue order: "at most (stages issued after s) * OPS outstanding" = stage s has landed
+    const int later = (n_stage - 1 - s) < (NSTAGE - 1) ? (n_stage - 1 - s) : (NSTAGE - 1);
+    sd_wait_vm(later, C::OPS);
+    asm volatile("" ::: "memory");
+    u32x2 fr[NF];
+    const uint32_t base = ring_addr + (uint32_t)((s % NSTAGE) * C::STAGE);
+    read_stage(fr, base);
+    // tokens of this stage that exist: all 16 except in the last stage of the last chunk
+    const int valid = a.T - (t_lo + (wave + KW * s) * C::KT);
+    if (valid < C::KT) {
+      const int k0 = 8 * (lane >> 5);  // first token of this lane's fragments inside the stage
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const int kf = k0 + 4 * (f & 1);  // half 1 holds tokens k0 + 4 .. k0 + 7
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {  // a register holds two tokens, the even one in its low half
+          uint32_t v = fr[f][w];
+          if (kf + 2 * w >= valid) v &= 0xFFFF0000u;
+          if (kf + 2 * w + 1 >= valid) v &= 0x0000FFFFu;
+          fr[f][w] = v;
+        }
+      }
+    }
+    multiply(fr);
   }
 
-  // ---- the four partial sums meet in LDS (the rings are free once every wave has left its loop); wave w
-  // then owns a quarter of the accumulator registers: adds the four copies in a fixed order and stores.
-  constexpr int NACC = NQ * NQ * 16;
-  float (*red)[NACC][64] = reinterpret_cast<float (*)[NACC][64]>(smem);
-  static_assert(sizeof(float) * 4 * NACC * 64 <= C::LDS_BYTES, "the reduction reuses the ring memory");
-  __syncthreads();
-#pragma unroll
-  for (int mi = 0; mi < NQ; ++mi)
-#pragma unroll
-    for (int nj = 0; nj < NQ; ++nj)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) red[wave][(mi * NQ + nj) * 16 + v][lane] = acc[mi][nj][v];
-  __syncthreads();
   // Result layout of a 32x32 tile: lane -> column n = lane % 32, register v -> row m = 8*(v/4) + 4*(lane/32) + v%4:
   // a store instruction writes two 128-byte row segments.
   float* out = a.dvals + (int64_t)q * (B * B) + (int64_t)(si * C::SB) * B + sj * C::SB;
   const int l32 = lane & 31, lh = lane >> 5;
-  constexpr int PER_WAVE = NACC / 4;
-#pragma unroll
-  for (int e = 0; e < PER_WAVE; ++e) {
-    const int id = wave * PER_WAVE + e;  // accumulator register (tile, v)
-    const float sum = ((red[0][id][lane] + red[1][id][lane]) + red[2][id][lane]) + red[3][id][lane];
-    const int tile = id >> 4, v = id & 15;
+  auto store = [&](int tile, int v, float sum) {
     const int mi = tile / NQ, nj = tile % NQ;
     const int m = 32 * mi + 8 * (v >> 2) + 4 * lh + (v & 3);
     float* dst = out + m * B + 32 * nj + l32;
@@ -312,6 +342,35 @@ __global__ __launch_bounds__(256) void k_sddmm(const SddmmArgs a) {
       atomicAdd(dst, sum);
     else
       *dst = sum;
+  };
+  if constexpr (KW == 1) {
+#pragma unroll
+    for (int mi = 0; mi < NQ; ++mi)
+#pragma unroll
+      for (int nj = 0; nj < NQ; ++nj)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) store(mi * NQ + nj, v, acc[mi][nj][v]);
+  } else {
+    // The partial sums meet in LDS (the rings are free once every wave has left its loop); wave w then owns its share
+    // of the accumulator registers: adds the copies in a fixed order and stores.
+    static_assert(KW == 4, "four copies are added below");
+    constexpr int NACC = NQ * NQ * 16;
+    float (*red)[NACC][64] = reinterpret_cast<float (*)[NACC][64]>(smem);
+    static_assert(sizeof(float) * 4 * NACC * 64 <= C::LDS_BYTES, "the reduction reuses the ring memory");
+    __syncthreads();
+#pragma unroll
+    for (int mi = 0; mi < NQ; ++mi)
+#pragma unroll
+      for (int nj = 0; nj < NQ; ++nj)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[wave][(mi * NQ + nj) * 16 + v][lane] = acc[mi][nj][v];
+    __syncthreads();
+    constexpr int PER_WAVE = NACC / 4;
+#pragma unroll
+    for (int e = 0; e < PER_WAVE; ++e) {
+      const int id = wave * PER_WAVE + e;  // accumulator register (tile, v)
+      store(id >> 4, id & 15, ((red[0][id][lane] + red[1][id][lane]) + red[2][id][lane]) + red[3][id][lane]);
+    }
   }
 }
 

@@ -165,6 +165,29 @@ def test_sddmm_feature_major_strided_and_unaligned(api, b):
     _check_sddmm(dv.cpu().numpy(), want, "sddmm unaligned")
 
 
+@pytest.mark.parametrize("T", [1, 47, 64, 129, 330])
+@pytest.mark.parametrize("b,M,K,nnz", [(32, 1024, 1024, 514), (32, 2048, 2304, 4099), (64, 1728, 1280, 513),
+                                       (64, 3072, 2816, 2055), (128, 1664, 1536, 131), (128, 3072, 2944, 517)])
+def test_sddmm_a_wave_per_block(api, b, M, K, nnz, T):
+    """Enough blocks for a wave each, alone in a workgroup or with three neighbours (the last workgroup not full);
+    integer data, so that the fp32 reference and any order of summation give the same numbers."""
+    import torch
+
+    rng = np.random.default_rng(9800 + nnz + T)
+    nbr, nbc = M // b, K // b
+    kept = rng.permutation(nbr * nbc)[:nnz]
+    mask = np.zeros(nbr * nbc, np.uint8)
+    mask[kept] = 1
+    gen = torch.Generator(device="cuda:0").manual_seed(9800 + T)
+    ints = lambda *s: torch.randint(-8, 9, s, generator=gen, device="cuda:0").to(torch.bfloat16)
+    dev = api.bsr_pack(ints(M, K), b, mask=mask_dev(mask.reshape(nbr, nbc)))
+    assert dev.nnz == nnz
+    dY, X = ints(T, M), ints(T, K)
+    dv = api.bsr_sddmm(dev, dY, X)
+    full = (dY.float().t().contiguous() @ X.float()).view(nbr, b, nbc, b).permute(0, 2, 1, 3).reshape(-1, b, b)
+    assert torch.equal(dv.view(nnz, b, b), full[torch.from_numpy(np.sort(kept)).cuda()])
+
+
 def test_sddmm_exact_on_integer_data_and_token_chunks(api):
     """Small integers: every partial sum is exact in fp32, so the device must match the oracle exactly,
     whatever the order of the additions - including the atomic accumulation over token chunks that a
