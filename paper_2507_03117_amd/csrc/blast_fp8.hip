@@ -124,6 +124,8 @@ int launch_fp8_b(const Fp8Args& a, const blast_bsr_view* W, hipStream_t stream) 
   const int64_t tiles = (a.T + 255) / 256, cus = cu_count_fp8();
   const bool wide = tiles * (a.n_units / (B / 64)) >= 2 * cus;
   if constexpr (B == 128) {
+    // (the streaming kernel holds a lane's offset into both column groups of a block in 32 bits: 2^25 tokens)
+    if (a.x_cg > UINT32_MAX / 2) return launch_fp8<B, false>(a, stream);
     if (wide) return launch_fp8_stream<128, 4, 8>(a, stream);
     return launch_fp8_stream<128, 2, 4>(a, stream);
   } else {

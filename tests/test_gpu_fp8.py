@@ -450,3 +450,21 @@ def test_quantize_groups_equals_the_token_major_codes(api, T, K, pad):
     nan = (want & 0x7F) > 0x7C
     got_t = got.transpose(1, 0, 2).reshape(T, K)
     assert np.array_equal(got_t[~nan], want[~nan]) and ((got_t[nan] & 0x7F) > 0x7C).all()
+
+
+def test_spmm_e5m2_column_groups_past_32_bits(api):
+    """Two column groups of 2^25 tokens and a few: the second group's offsets exceed 32 bits.  The first, middle and
+    last tokens against the same product on those tokens alone (same sums in the same order)."""
+    import torch
+
+    b, T = 128, (1 << 25) + 3
+    rng = np.random.default_rng(5700)
+    dev = api.bsr_pack(to_dev(synth.gauss_bf16(rng, (b, b), 0.05)), b, mask=mask_dev(np.ones((1, 1), dtype=np.uint8)))
+    w8 = api.quantize_e5m2(dev.vals[: b * b].contiguous())
+    gen = torch.Generator(device="cuda:0").manual_seed(5700)
+    x8 = torch.randint(0, 0x40, (2, T, 64), generator=gen, device="cuda:0", dtype=torch.uint8)  # finite codes below 2
+    y = api.bsr_spmm_e5m2(dev, w8, x8, layout=api.COLUMN_GROUPS_64, out_dtype=torch.bfloat16)
+    for t in (0, T // 2, T - 200):
+        part = api.bsr_spmm_e5m2(dev, w8, x8[:, t:t + 200].contiguous(), layout=api.COLUMN_GROUPS_64, out_dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        assert torch.allclose(y[t:t + 200].float(), part.float(), rtol=2.0 ** -7, atol=1e-4), t
