@@ -43,6 +43,27 @@ def test_generate_masks_matches_oracle(api, b, rows, cols, s):
         assert (want == 2).any() and (want == 1).any() and (want == 0).any()
 
 
+@pytest.mark.parametrize("b,nbr,nbc,pad_w,pad_g", [(16, 1, 2, 0, 8), (16, 3, 7, 16, 0), (32, 5, 5, 8, 24),
+                                                   (64, 3, 3, 8, 64), (128, 3, 5, 8, 16)])
+def test_generate_masks_scores_a_wave_per_block(api, b, nbr, nbc, pad_w, pad_g):
+    """Counts of blocks that leave the last workgroup partly empty, row pitches beyond the width and unlike each other;
+    the padding holds large values that must not be scored."""
+    import torch
+
+    rng = np.random.default_rng(9780 + b + nbc)
+    W, G = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02), synth.gauss_bf16(rng, (nbr * b, nbc * b), 1e-3)
+    assert _gaps_ok(W, b, 0.5) and _gaps_ok(G, b, 0.5), "selection hangs on rounding: reseed"
+
+    def padded(A, pad):
+        wide = torch.full((nbr * b, nbc * b + pad), 0x4700, dtype=torch.int16, device="cuda:0")
+        wide = wide.view(to_dev(A).dtype)
+        wide[:, :nbc * b] = to_dev(A)
+        return wide[:, :nbc * b]
+
+    m = api.generate_masks(padded(W, pad_w), padded(G, pad_g), b, 0.5)
+    assert np.array_equal(m.cpu().numpy(), orc.generate_masks(W, G, b, 0.5))
+
+
 def test_generate_masks_and_pooled_selection_beyond_one_workgroup(api):
     """26624 blocks: more than one workgroup selects from (8192), so the mask update runs its two selections side
     by side over global memory and merges them in a launch of its own, and the pooled selection takes the same
