@@ -188,6 +188,30 @@ def test_sddmm_a_wave_per_block(api, b, M, K, nnz, T):
     assert torch.equal(dv.view(nnz, b, b), full[torch.from_numpy(np.sort(kept)).cuda()])
 
 
+@pytest.mark.parametrize("T", [2000, 4099])
+@pytest.mark.parametrize("b,M,K,nnz", [(32, 1024, 1024, 400), (32, 2048, 1024, 1200), (32, 4096, 2048, 4200),
+                                       (64, 2048, 1280, 400), (64, 2048, 2048, 700), (64, 4096, 3072, 2100),
+                                       (128, 1664, 1536, 100), (128, 2560, 2560, 250), (128, 3072, 2944, 517)])
+def test_sddmm_adds_in_four_chains(api, b, M, K, nnz, T):
+    """How many terms one fp32 chain holds, in each of the forms: 2^25 in the first of n stages of 16 tokens and a one in
+    each later stage.  A one added to 2^25 is lost (its neighbours are 4 apart), so a quarter of the ones at most may be
+    lost: those in the chain of the large term.  The three additions of the chains round by at most 2 each."""
+    import torch
+
+    rng = np.random.default_rng(9850 + nnz)
+    nbr, nbc = M // b, K // b
+    mask = np.zeros(nbr * nbc, np.uint8)
+    mask[rng.permutation(nbr * nbc)[:nnz]] = 1
+    dev = api.bsr_pack(torch.ones((M, K), dtype=torch.bfloat16, device="cuda:0"), b, mask=mask_dev(mask.reshape(nbr, nbc)))
+    n = (T + 15) // 16
+    column = torch.zeros(T, dtype=torch.bfloat16, device="cuda:0")
+    column[::16] = 1.0
+    dy, x = (column[:, None].repeat(1, w) for w in (M, K))
+    dy[0], x[0] = 2.0 ** 13, 2.0 ** 12
+    dv = api.bsr_sddmm(dev, dy, x).double()
+    assert float((dv - (2.0 ** 25 + n - 1)).abs().max()) <= (n + 3) // 4 + 6
+
+
 def test_sddmm_exact_on_integer_data_and_token_chunks(api):
     """Small integers: every partial sum is exact in fp32, so the device must match the oracle exactly,
     whatever the order of the additions - including the atomic accumulation over token chunks that a
