@@ -32,7 +32,7 @@ int launch_sddmm(SddmmArgs a, hipStream_t stream) {
     lds_set.set(dev);
   }
   const int64_t sub_units = (int64_t)a.nnz * C::SUB * C::SUB;
-  // Token chunks across workgroups (on top of the four waves of a workgroup): only when there are fewer
+  // Token chunks across workgroups (on top of the waves that share a unit): only when there are fewer
   // units than CUs, and never below 512 tokens per chunk - the atomics on the output cost more than
   // idle workgroup slots otherwise.
   const int64_t want = (int64_t)cu_count_bwd();
@@ -59,19 +59,23 @@ int launch_sddmm(SddmmArgs a, hipStream_t stream) {
 
 // Which form, by the units (64-wide sub-blocks of the stored blocks) per CU.
 //   fewer than 2: four waves per unit, or most SIMDs would idle (1.6 units, 700 tokens: 11.1 us against 13.1 with one
-//     wave; 2.4 units, 2000 tokens: 28.9 against 26.7).
+//     wave; 2.4 units, 2000 tokens: 28.9 against 26.7).  Up to a unit more per CU (two more of the small 32-wide ones)
+//     while the token walk is short: a lone wave's start and its last sums weigh on few stages (64-wide, 2.5 units, 700
+//     tokens: 14.8 against 16.4; 32-wide, 3 units, 200 tokens: 5.9 against 6.4; at 1000 tokens, 3 units, 22.3 against 19.8).
 //   up to what is resident at once with a wave per workgroup (rings in 128 of a CU's 160 KiB): a wave per unit, dealt
 //     to the CUs one by one; every XCD then streams X once (4.8 units, 2000 tokens: 40 us; four waves per unit 48, four
-//     units per workgroup 53, whose 308 workgroups load some CUs twice).
+//     units per workgroup 51, whose 308 workgroups load some CUs twice).
 //   more: four neighbouring units, blocks of one row or quarters of one block, in a workgroup, so that the tiles they
-//     share are still in the L1 or L2 (11.2 units, 128-wide blocks, 4096 tokens: 144 us; a wave per workgroup 200, four
-//     waves per unit 185).
+//     share are still in the L1 or L2 (11.2 units, 128-wide blocks, 4096 tokens: 144 us; a wave per workgroup 184, four
+//     waves per unit 172).  From 6 units on for 128-wide blocks, whose quarters share both tiles (6.5 units, 14336 x 4096,
+//     4096 tokens: 104 us, a wave per workgroup 112; 7.8 units 105 and 130; 5.6 units 103 and 102, 2000 tokens 52 and 48).
 template <int B>
 int sddmm_form(const SddmmArgs& a, hipStream_t stream) {
   using One = SdCfg<B, 1, 1>;
   const int64_t units = (int64_t)a.nnz * One::SUB * One::SUB, cus = cu_count_bwd();
-  if (units < 2 * cus) return launch_sddmm<B, 4, 1>(a, stream);
-  if (units * (int64_t)One::LDS_BYTES <= cus * (128 << 10)) return launch_sddmm<B, 1, 1>(a, stream);
+  const bool short_walk = a.T > (B == 32 ? 64 : 300) && a.T <= 800;
+  if (units < 2 * cus || (short_walk && units < (B == 32 ? 4 : 3) * cus)) return launch_sddmm<B, 4, 1>(a, stream);
+  if (units * (int64_t)One::LDS_BYTES <= cus * ((B == 128 ? 96 : 128) << 10)) return launch_sddmm<B, 1, 1>(a, stream);
   return launch_sddmm<B, 1, 4>(a, stream);
 }
 

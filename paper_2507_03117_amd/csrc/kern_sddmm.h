@@ -13,8 +13,8 @@
 // Work decomposition: a unit = (stored block, SB x SB sub-block, token chunk), accumulated whole by a wave (64 x 64:
 // 2 x 2 register blocking, every fragment used twice) from its private ring of LDS stages of 16 tokens - no barrier
 // inside the loop, the wave's memory counter is the only synchronisation (the scheme of the decode kernel).  KW waves
-// share a unit (four: they deal its stages among themselves and add their sums in LDS at the end; one: nothing to
-// add), UPW units make a workgroup; launch_sddmm's caller says which form when.  When a matrix has too few blocks to
+// share a unit (four: they deal its stages among themselves and add their sums in LDS at the end; one: it adds the
+// stages in as many chains), UPW units make a workgroup; launch_sddmm's caller says which form when.  When a matrix has too few blocks to
 // fill the chip even so, the tokens are cut into chunks across workgroups as well and those partial sums meet through
 // fp32 atomics on a zeroed output.
 //
@@ -83,7 +83,7 @@ struct SddmmArgs {
   int nnz;
   int tsplit;          // token chunks per sub-block (> 1: atomic accumulation into zeroed dvals)
   int chunk_tokens;    // tokens per chunk, a multiple of 16
-  int n_units;         // workgroups with work: nnz * SUB * SUB * tsplit
+  int n_units;         // nnz * SUB * SUB * tsplit
 };
 
 // KW = waves that share a unit, UPW = units of a workgroup.
@@ -130,8 +130,10 @@ __device__ __forceinline__ void sd_wait_vm(int later, int ops) {
   }
 }
 
+// (Two waves per SIMD asked for, the rings allow no more than ten per CU: with 256 registers the compiler keeps a lone
+// wave's sums in ordinary ones, where closing a chain is 64 additions instead of three times as many moves.)
 template <int B, int KW, int UPW>
-__global__ __launch_bounds__(64 * KW * UPW) void k_sddmm(const SddmmArgs a) {
+__global__ __launch_bounds__(64 * KW * UPW, KW == 1 ? 2 : 1) void k_sddmm(const SddmmArgs a) {
   using C = SdCfg<B, KW, UPW>;
   constexpr int NQ = C::NQ, NI = C::NI, NSTAGE = C::NSTAGE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -270,10 +272,12 @@ __global__ __launch_bounds__(64 * KW * UPW) void k_sddmm(const SddmmArgs a) {
       sd_read_stage1<4 * C::ROWB, C::TILE>(base + foff[0][0], fr);
   };
 
-  // A lone wave adds its stages in chains of a quarter of them (of four at least), one after the other, and then the
-  // chains: the rounding of an fp32 sum grows with the additions that a term goes through, and so these are no more
-  // than in a unit that four waves share.  (One chain, 2000 tokens: relative error 2.0e-7 against 1.1e-7.)
-  const int chain = n_stage > 16 ? (n_stage + 3) / 4 : 4;
+  // A lone wave adds its stages in up to four chains, one after the other, and then the chains: the rounding of an fp32
+  // sum grows with the additions that its terms go through, and so it is that of four waves that share a unit.  (One
+  // chain, 2000 tokens: relative error 2.0e-7 against 1.1e-7.)  For terms of one size, n of them in k chains collect a
+  // variance of (n^2 + n (k^2 + k - 2)) / 2k units: up to 6, 10 and 14 terms one, two and three chains are no worse.
+  const int chains = n_stage <= 6 ? 1 : n_stage <= 10 ? 2 : n_stage <= 14 ? 3 : 4;
+  const int chain = chains == 4 ? (n_stage + 3) >> 2 : (n_stage + chains - 1) / chains;
   int fold_at = chain;
   f32x16 total[KW == 1 ? NQ : 1][KW == 1 ? NQ : 1];
   if constexpr (KW == 1) {
