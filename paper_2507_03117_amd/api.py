@@ -284,7 +284,8 @@ def with_joint_row_order(gate: PackedBsr, up: PackedBsr) -> PackedBsr:
 
 
 def generate_masks(W: torch.Tensor, G: torch.Tensor, b: int, sparsity: float) -> torch.Tensor:
-    """blast_generate_masks: uint8 [rows/b, cols/b]; 1 = kept by the weight's ranking, 2 = regrown, 0 = dropped."""
+    """blast_generate_masks: uint8 [rows/b, cols/b]; 1 = kept by the weight's ranking, 2 = regrown, 0 = dropped.
+    Waits for the current stream: on return the mask is complete, for readers on every stream."""
     L = lib()
     for t in (W, G):
         assert t.is_cuda and t.dim() == 2 and t.stride(1) == 1 and t.element_size() == 2
@@ -294,11 +295,13 @@ def generate_masks(W: torch.Tensor, G: torch.Tensor, b: int, sparsity: float) ->
     ws = torch.empty(max(int(L.blast_generate_masks_workspace(rows, cols, b)), 16), dtype=torch.uint8, device=W.device)
     _check(L.blast_generate_masks(_ptr(W), W.stride(0), _ptr(G), G.stride(0), rows, cols, b, float(sparsity),
                                   _ptr(mask), _ptr(ws), ws.numel(), _stream()), "blast_generate_masks")
-    return mask  # (ws goes back to the allocator of the stream that uses it: no wait needed)
+    torch.cuda.current_stream().synchronize()  # the mask may be read from any stream, W and G changed
+    return mask
 
 
 def pooled_topk_mask(S: torch.Tensor, b: int, sparsity: float) -> torch.Tensor:
-    """blast_pooled_topk_mask: keep the blocks with the highest mean sensitivity; uint8 [rows/b, cols/b]."""
+    """blast_pooled_topk_mask: keep the blocks with the highest mean sensitivity; uint8 [rows/b, cols/b].
+    Waits for the current stream, like generate_masks."""
     L = lib()
     assert S.is_cuda and S.dim() == 2 and S.stride(1) == 1 and S.dtype == torch.float32
     rows, cols = S.shape
@@ -306,7 +309,8 @@ def pooled_topk_mask(S: torch.Tensor, b: int, sparsity: float) -> torch.Tensor:
     ws = torch.empty(max(int(L.blast_pooled_topk_mask_workspace(rows, cols, b)), 16), dtype=torch.uint8, device=S.device)
     _check(L.blast_pooled_topk_mask(_ptr(S), S.stride(0), rows, cols, b, float(sparsity), _ptr(mask), _ptr(ws),
                                     ws.numel(), _stream()), "blast_pooled_topk_mask")
-    return mask  # (ws goes back to the allocator of the stream that uses it: no wait needed)
+    torch.cuda.current_stream().synchronize()  # the mask may be read from any stream, S changed
+    return mask
 
 
 def sparsity_schedule(i: int, m: int, d: int, s_init: float, s_max: float) -> float:

@@ -87,6 +87,29 @@ def test_generate_masks_and_pooled_selection_beyond_one_workgroup(api):
     assert np.array_equal(m.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("call", ["generate_masks", "pooled_topk_mask"])
+def test_masks_are_complete_on_return(api, call):
+    """A mask is handed to readers on any stream and its inputs may be overwritten at once: however busy the stream,
+    the call returns when its work is done."""
+    import torch
+
+    b, rows, cols = 64, 512, 1024
+    rng = np.random.default_rng(9790)
+    W, G = synth.gauss_bf16(rng, (rows, cols), 0.02), synth.gauss_bf16(rng, (rows, cols), 1e-3)
+    Wd, Gd = to_dev(W), to_dev(G)
+    S = Wd.float()
+    stream, reader = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(20_000_000)  # about ten milliseconds of device time ahead of the call
+        m = api.generate_masks(Wd, Gd, b, 0.5) if call == "generate_masks" else api.pooled_topk_mask(S, b, 0.5)
+        assert stream.query()
+    with torch.cuda.stream(reader):
+        got = m.cpu().numpy()
+    want = orc.generate_masks(W, G, b, 0.5) if call == "generate_masks" else orc.pooled_topk_mask(S.cpu().numpy(), b, 0.5)[0]
+    assert np.array_equal(got, want)
+
+
 def test_generate_masks_ties_and_equal_gradient(api):
     import torch
 
