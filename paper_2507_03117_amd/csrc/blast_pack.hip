@@ -567,8 +567,9 @@ static_assert(kSmallN + 1024 < 65536, "two counts share a 32-bit word");
 static_assert((blast::kChunkBlocks & (blast::kChunkBlocks - 1)) == 0 &&
               (blast::kWideChunkBlocks & (blast::kWideChunkBlocks - 1)) == 0, "chunk sizes are powers of two");
 
-// LDS scratch of select_small, one per group.
-struct SelectShared {
+// LDS scratch of select_small, one per group (an array of them: the bins are read four at a time, so the size keeps the
+// alignment too).
+struct alignas(16) SelectShared {
   unsigned hist[256];
   int wave_tot[16];
   unsigned long long diff, kth;  // bits in which keys differ; the n_keep-th key ...
@@ -576,6 +577,7 @@ struct SelectShared {
   int rem, eq, digit, fill, open;
   int cand[kWave];
 };
+static_assert(sizeof(SelectShared) % 16 == 0 && offsetof(SelectShared, hist) % 16 == 0, "16-byte reads of hist");
 
 // The n_keep-th of n <= kSmallN scores (0 < n_keep < n) under (score descending, index ascending), into sh.kth and
 // sh.kth_at, by a group of NT threads of a workgroup of GROUPS * NT: the caller's groups select side by side (every
@@ -724,7 +726,7 @@ __device__ __forceinline__ bool select_keeps(const SelectShared& sh, unsigned lo
 __global__ __launch_bounds__(1024) void k_select_small(const double* __restrict__ score, int n, int n_keep,
                                                        uint8_t* __restrict__ mask) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long keys[];
-  __shared__ __attribute__((aligned(16))) SelectShared ssh[1];
+  __shared__ SelectShared ssh[1];
   select_small<1024, 1>(score, n, n_keep, keys, ssh);
   for (int i = threadIdx.x; i < n; i += 1024) mask[i] = select_keeps(ssh[0], keys[i], i) ? 1 : 0;
 }
@@ -735,7 +737,7 @@ __global__ __launch_bounds__(1024) void k_masks_small(const double* __restrict__
                                                       const double* __restrict__ score_g, int n, int n_keep,
                                                       uint8_t* __restrict__ mask) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long keys[];
-  __shared__ __attribute__((aligned(16))) SelectShared ssh[2];
+  __shared__ SelectShared ssh[2];
   const bool grad = threadIdx.x >= 512;
   select_small<512, 2>(grad ? score_g : score_w, n, n_keep, grad ? keys + n : keys, ssh);
   for (int i = threadIdx.x; i < n; i += 1024)
