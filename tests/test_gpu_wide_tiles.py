@@ -119,3 +119,36 @@ def test_mlp_wide_tiles(api, nbi, nbe, T):
     fro, mx = check_close(yh[sel].T, y_or, f"wide mlp I={nbi * b} E={nbe * b} T={T}")
     assert not yh[:, 2 * b:3 * b].any()
     print(f"wide mlp {nbi}x{nbe} T={T}: rel_fro={fro:.2e} max_abs/rms={mx:.2e} on {sel.size} tokens")
+
+
+@pytest.mark.parametrize("T", [257, 319, 320, 321, 552, 767])
+@pytest.mark.parametrize("b,nbr,nbc", [(32, 130, 20), (64, 140, 30), (128, 30, 12), (128, 264, 5)])
+def test_tiles_that_the_tokens_end_in(api, b, nbr, nbc, T):
+    """Token counts that fill a wave's 64 tokens wholly, in part (1, 40, 63) and not at all, both outputs of the bf16
+    product and of the E5M2 one: every token is right and nothing is written past the last one."""
+    import torch
+
+    rng = np.random.default_rng(4200 + b + nbr + T)
+    mask = synth.uniform_mask(rng, nbr, nbc, 0.5)
+    mask[1, :] = 0
+    dev, ref = _pack(api, _sparse_weight(rng, mask, b), b, mask)
+    x = synth.gauss_bf16(rng, (T, nbc * b), 1.0)
+    xd = to_dev(x)
+    sel = np.unique(np.r_[0:2, T // 2, T - 70:T:3, T - 2:T])
+    want = orc.spmm(ref, np.ascontiguousarray(x[sel]))
+    runs = [(lambda out: api.bsr_spmm(dev, xd, out=out), want)]
+    if b >= 64:
+        w8 = api.quantize_e5m2(dev.vals[: dev.nnz * b * b].contiguous())
+        x8 = api.quantize_e5m2(xd)
+        w8_or = orc.e5m2_quantize(np.ascontiguousarray(synth.bf16_bits_to_f32(ref.vals)))
+        runs.append((lambda out: api.bsr_spmm_e5m2(dev, w8, x8, out=out),
+                     orc.spmm_e5m2(ref, w8_or, np.ascontiguousarray(x8.cpu().numpy()[sel]))))
+    for run, y_or in runs:
+        whole = torch.full((T + 256, nbr * b), float("nan"), device="cuda:0")
+        half = whole.to(torch.bfloat16)
+        run(whole[:T])
+        run(half[:T])
+        torch.cuda.synchronize()
+        assert torch.isnan(whole[T:]).all() and torch.isnan(half[T:]).all()
+        assert torch.isfinite(whole[:T]).all() and torch.equal(whole[:T].to(torch.bfloat16), half[:T])
+        check_close(whole[:T].cpu().numpy()[sel].T, y_or, f"ragged tiles b={b} T={T}")
