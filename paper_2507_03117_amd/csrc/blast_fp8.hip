@@ -121,11 +121,16 @@ int launch_fp8_b(const Fp8Args& a, const blast_bsr_view* W, hipStream_t stream) 
     }
     return launch_fp8<B, true>(a, stream);
   }
-  const int64_t tiles = (a.T + 255) / 256, cus = cu_count_fp8();
-  const bool wide = tiles * (a.n_units / (B / 64)) >= 2 * cus;
+  const int64_t rows = a.n_units / (B / 64), cus = cu_count_fp8();
+  const int64_t tiles = (a.T + 255) / 256, half_tiles = (a.T + 127) / 128;
+  const bool wide = tiles * rows >= 2 * cus;
   if constexpr (B == 128) {
     // (the streaming kernel holds a lane's offset into both column groups of a block in 32 bits: 2^25 tokens)
     if (a.x_cg > UINT32_MAX / 2) return launch_fp8<B, false>(a, stream);
+    // A second 128-token tile that is hardly begun costs as much as the first; a wave without tokens costs nothing.
+    // It shows where the tiles do not fit the CUs at once (two workgroups each): 53248 x 16384, 129 tokens, 90 % sparse
+    // 35.0 against 37.1 us, 95 % 22.6 against 23.6; 160 tokens 95 % 24.1 against 23.6.
+    if (a.T <= 128 + 16 && half_tiles * rows > 2 * cus) return launch_fp8<B, false>(a, stream);
     if (wide) return launch_fp8_stream<128, 4, 8>(a, stream);
     return launch_fp8_stream<128, 2, 4>(a, stream);
   } else {
@@ -134,6 +139,12 @@ int launch_fp8_b(const Fp8Args& a, const blast_bsr_view* W, hipStream_t stream) 
     // (4.8 per slot) 11.7 against 13.5 us; 1843 blocks, 300 tokens (7.2) 12.6 against 13.0; 2048 tokens (29) 30.9
     // against 27.5.
     if (W->nnz * tiles < 6 * 2 * cus) return launch_fp8<B, false>(a, stream);
+    // Its workgroups (256 tokens of a row) all fit at once and the streaming kernel's 128-token tiles do not: the fuller
+    // the rows, the more the second, partly empty round costs.  14336 x 4096, 512 tokens (448 against 896 workgroups for
+    // 512 places): half the blocks stored 26.6 against 31.8 us, 30 % 20.5 against 21.9; 8192 x 3072, 700 tokens: half 20.6
+    // against 24.1, 30 % 16.7 against 17.5, 20 % 14.8 against 14.4; 4096 x 14336, 1500 tokens, 10 %: 25.5 against 22.7.
+    if (tiles * rows <= 2 * cus && half_tiles * rows > 2 * cus && 4 * W->nnz >= rows * (W->cols / B))
+      return launch_fp8<B, false>(a, stream);
     if (wide) return launch_fp8_stream<64, 4, 4>(a, stream);
     return launch_fp8_stream<64, 2, 4>(a, stream);
   }

@@ -16,8 +16,9 @@
 //    copy): the eight rows one read cycle touches then cover all banks.
 // One byte per value halves every byte count of the bf16 kernels (HBM, L2 -> LDS, LDS -> registers) per
 // multiply-add, which is what bounds them.
-//  - KSPLIT = false (64-wide blocks, many tokens, few blocks per workgroup): a workgroup owns (block row, 64-row
-//    sub-block, 256 tokens), one 64-token tile per wave; the four waves read the same weight tiles (L1 hits).
+//  - KSPLIT = false (many tokens, where the caller of launch_fp8 says so: mostly 64-wide blocks with few blocks per
+//    workgroup): a workgroup owns (block row, 64-row sub-block, 256 tokens), one 64-token tile per wave; the four waves
+//    read the same weight tiles (L1 hits).
 //    Everything else beyond 128 tokens runs on the streaming kernel of the bf16 product (kern_stream.h, F8).
 //  - KSPLIT = true (up to a few token tiles): a workgroup owns (block row, sub-block, 64 tokens) and its
 //    four waves deal the stages among themselves; the partial sums are added in LDS in a fixed order.

@@ -411,10 +411,14 @@ def test_mlp_with_e5m2_weights_rows_dealt_to_workgroups(api, b, nbi, nbe, kind, 
 @pytest.mark.parametrize("b,nbr,nbc,T,groups", [
     (128, 9, 7, 130, True), (128, 9, 7, 257, False),   # 128-token tiles, a tile of one and of 129 tokens
     (128, 130, 9, 1025, True), (128, 130, 9, 1100, False),  # 256-token tiles, five to a row
-    (64, 40, 30, 700, True), (64, 129, 40, 1000, True), (64, 129, 40, 1023, False),  # both tiles of 64-wide blocks
+    (128, 257, 2, 144, True), (128, 257, 2, 145, False),   # one tile per wave up to 144 tokens of many rows, streaming beyond
+    (64, 129, 40, 1000, True), (64, 129, 40, 1023, False),  # 64-wide blocks, 256-token tiles
+    (64, 100, 40, 300, True), (64, 80, 40, 700, False),     # 128-token tiles
+    (64, 40, 30, 700, True),    # one tile per wave: few blocks
+    (64, 200, 24, 500, False),  # one tile per wave: full rows, and the 128-token tiles do not fit at once
 ])
 def test_spmm_e5m2_many_tokens(api, b, nbr, nbc, T, groups):
-    """The streaming kernel on one-byte values, both activation layouts and outputs, empty and full rows."""
+    """The forms of the E5M2 product beyond 128 tokens, both activation layouts and outputs, empty and full rows."""
     import torch
 
     rng = np.random.default_rng(5600 + nbr + T)
