@@ -57,25 +57,35 @@ int launch_sddmm(SddmmArgs a, hipStream_t stream) {
   return BLAST_OK;
 }
 
-// Which form, by the units (64-wide sub-blocks of the stored blocks) per CU.
-//   fewer than 2: four waves per unit, or most SIMDs would idle (1.6 units, 700 tokens: 11.1 us against 13.1 with one
-//     wave; 2.4 units, 2000 tokens: 28.9 against 26.7).  Up to a unit more per CU (two more of the small 32-wide ones)
-//     while the token walk is short: a lone wave's start and its last sums weigh on few stages (64-wide, 2.5 units, 700
-//     tokens: 14.8 against 16.4; 32-wide, 3 units, 200 tokens: 5.9 against 6.4; at 1000 tokens, 3 units, 22.3 against 19.8).
+// Which form, by the units (64-wide sub-blocks of the stored blocks) per CU and the activations' bytes (`features` = rows
+// + columns of the matrix).
+//   up to 2: four waves per unit, or most SIMDs would idle (1.6 units, 700 tokens: 11.1 us against 13.1 with one wave;
+//     exactly 2, the most that are resident at once, 2048 x 2048, 300 tokens: 8.6 against 10.7, 2000: 21.6 against 26.2).
+//     Up to half a unit more per CU while a second round brings the activations in again cheaply (2.5 units, 128-wide
+//     blocks, 4096 x 4096, 2000 tokens: 25.6 against 27.7; 16384 x 16384, 4096 tokens: 55.2 against 47.1), and up to a
+//     unit more (two more of the small 32-wide ones) while the token walk is short: a lone wave's start and its last sums
+//     weigh on few stages (64-wide, 2.5 units, 700 tokens: 14.8 against 16.4; 32-wide, 3 units, 200 tokens: 5.9 against
+//     6.4, 1000 tokens 12.9 against 13.5; 64-wide, 3 units, 1000 tokens 22.3 against 19.8).
 //   up to what is resident at once with a wave per workgroup (rings in 128 of a CU's 160 KiB): a wave per unit, dealt
 //     to the CUs one by one; every XCD then streams X once (4.8 units, 2000 tokens: 40 us; four waves per unit 48, four
-//     units per workgroup 51, whose 308 workgroups load some CUs twice).
+//     units per workgroup 51, whose 308 workgroups load some CUs twice).  Not 32-wide units on a short walk, of which a
+//     workgroup starts four at once (8 units, 512 tokens: 12.9 us against 14.9, four waves per unit 14.1).
 //   more: four neighbouring units, blocks of one row or quarters of one block, in a workgroup, so that the tiles they
 //     share are still in the L1 or L2 (11.2 units, 128-wide blocks, 4096 tokens: 144 us; a wave per workgroup 184, four
 //     waves per unit 172).  From 6 units on for 128-wide blocks, whose quarters share both tiles (6.5 units, 14336 x 4096,
 //     4096 tokens: 104 us, a wave per workgroup 112; 7.8 units 105 and 130; 5.6 units 103 and 102, 2000 tokens 52 and 48).
 template <int B>
-int sddmm_form(const SddmmArgs& a, hipStream_t stream) {
+int sddmm_form(const SddmmArgs& a, int64_t features, hipStream_t stream) {
   using One = SdCfg<B, 1, 1>;
   const int64_t units = (int64_t)a.nnz * One::SUB * One::SUB, cus = cu_count_bwd();
-  const bool short_walk = a.T > (B == 32 ? 64 : 300) && a.T <= 800;
-  if (units < 2 * cus || (short_walk && units < (B == 32 ? 4 : 3) * cus)) return launch_sddmm<B, 4, 1>(a, stream);
-  if (units * (int64_t)One::LDS_BYTES <= cus * ((B == 128 ? 96 : 128) << 10)) return launch_sddmm<B, 1, 1>(a, stream);
+  const bool short_walk = a.T > (B == 32 ? 64 : 300) && a.T <= (B == 32 ? 1200 : 800);
+  const int64_t per_unit = a.T * features * 2 / (One::SUB * One::SUB);  // activations, of which a block's units share a tile
+  const bool cheap_round = (units == 2 * cus && per_unit <= (50 << 20)) ||
+                           (B > 32 && a.T > 300 && 2 * units <= 5 * cus && per_unit <= (20 << 20));
+  if (units < 2 * cus || cheap_round || (short_walk && units < (B == 32 ? 4 : 3) * cus))
+    return launch_sddmm<B, 4, 1>(a, stream);
+  const bool resident = units * (int64_t)One::LDS_BYTES <= cus * ((B == 128 ? 96 : 128) << 10);
+  if (resident && !(B == 32 && short_walk && a.T <= 800)) return launch_sddmm<B, 1, 1>(a, stream);
   return launch_sddmm<B, 1, 4>(a, stream);
 }
 
@@ -119,9 +129,9 @@ extern "C" int blast_bsr_sddmm(const blast_bsr_view* W, const uint16_t* dY, int6
     a.nbr = (int)(W->rows / b);
     a.nnz = (int)W->nnz;
     switch (b) {
-      case 32: return sddmm_form<32>(a, stream);
-      case 64: return sddmm_form<64>(a, stream);
-      default: return sddmm_form<128>(a, stream);
+      case 32: return sddmm_form<32>(a, W->rows + W->cols, stream);
+      case 64: return sddmm_form<64>(a, W->rows + W->cols, stream);
+      default: return sddmm_form<128>(a, W->rows + W->cols, stream);
     }
   }
   SddmmGenericArgs g{};

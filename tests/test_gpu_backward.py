@@ -165,11 +165,15 @@ def test_sddmm_feature_major_strided_and_unaligned(api, b):
     _check_sddmm(dv.cpu().numpy(), want, "sddmm unaligned")
 
 
-@pytest.mark.parametrize("T", [1, 47, 64, 129, 330])
-@pytest.mark.parametrize("b,M,K,nnz", [(32, 1024, 1024, 514), (32, 2048, 2304, 4099), (64, 1728, 1280, 513),
-                                       (64, 3072, 2816, 2055), (128, 1664, 1536, 131), (128, 3072, 2944, 517)])
+@pytest.mark.parametrize("T", [1, 47, 64, 129, 330, 801, 1201])
+@pytest.mark.parametrize("b,M,K,nnz", [(32, 1024, 1024, 514), (32, 2048, 2304, 1023), (32, 2048, 2304, 1025),
+                                       (32, 2048, 2304, 4099), (64, 1728, 1280, 512), (64, 1728, 1280, 513),
+                                       (64, 1728, 1600, 640), (64, 1728, 1600, 641), (64, 3072, 2816, 2055),
+                                       (128, 1664, 1536, 128), (128, 1664, 1664, 160), (128, 1664, 1664, 161),
+                                       (128, 3072, 2944, 517)])
 def test_sddmm_a_wave_per_block(api, b, M, K, nnz, T):
-    """Enough blocks for a wave each, alone in a workgroup or with three neighbours (the last workgroup not full);
+    """Enough blocks for a wave each, alone in a workgroup or with three neighbours (the last workgroup not full), and
+    the numbers of blocks and tokens at which the form changes;
     integer data, so that the fp32 reference and any order of summation give the same numbers."""
     import torch
 
