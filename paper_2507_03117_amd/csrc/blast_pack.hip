@@ -849,6 +849,7 @@ struct GatherArgs {
   int64_t ldw;
   int b;
   uint16_t* vals;
+  int span;  // candidate blocks of a workgroup, at most 32
 };
 
 // Flags of the blocks a thread owns (bit j: block tid * per + j is kept).
@@ -861,13 +862,12 @@ __device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask
 }
 
 // Everything that follows the mask, in one launch.  Workgroup 0: row pointers, schedule, chunk plans; workgroup 1 (with
-// aux): the column-grouped index; the others: kGatherSpan candidate blocks each, whose places among the stored blocks
+// aux): the column-grouped index; the others: ga.span candidate blocks each, whose places among the stored blocks
 // they count for themselves - column indices and values.  A block whose mask code is 2 (regrown, BLaST Sec. 3.2) is
 // stored as zeros: it joins the structure without changing the product.
 // What bounds it: the index jobs, a chain of scans and barriers in a workgroup each.  Three 8192 x 2048 matrices, b = 64,
 // 80 % sparse, after a mask update: as one workgroup for all index arrays and a launch for the values 12 + 4.6 us per
 // matrix and 187 us for the update and re-packing together, now 9 us and 163.
-constexpr int kGatherSpan = 16;
 __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__ mask, int nbr, int nbc, SmallOut o,
                                                      PlanOut narrow, PlanOut wide, GatherArgs ga) {
   __shared__ __attribute__((aligned(16))) int cnt[1024];  // populations of the rows, or of the columns
@@ -889,21 +889,21 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
   const int jobs = o.col_ptr ? 2 : 1;
 
   if ((int)blockIdx.x >= jobs) {
-    // ---- the values of the candidates [c0, c0 + kGatherSpan) -------------------------------------------------------
-    const int c0 = ((int)blockIdx.x - jobs) * kGatherSpan;
+    // ---- the values of the candidates [c0, c0 + ga.span) -----------------------------------------------------------
+    const int c0 = ((int)blockIdx.x - jobs) * ga.span;
     int before = 0;  // stored blocks before c0
 #pragma unroll
     for (int j = 0; j < kSmallPer; ++j) before += __popcll(__ballot(((keep >> j) & 1u) && e0 + j < c0));
     if (lane_id() == 0) wave_tot[tid / kWave] = before;
     const int cand = c0 + lane_id();
-    const int code = lane_id() < kGatherSpan && cand < n ? mask[cand] : 0;
+    const int code = lane_id() < ga.span && cand < n ? mask[cand] : 0;
     const unsigned kept = (unsigned)__ballot(code != 0), zero = (unsigned)__ballot(code == 2);
     __syncthreads();
     int first = 0;
 #pragma unroll
     for (int w = 0; w < 16; ++w) first += wave_tot[w];
     const int nk = __popc(kept);
-    if (tid < kGatherSpan && (kept >> tid & 1u)) {
+    if (tid < ga.span && (kept >> tid & 1u)) {
       const int k = first + __popc(kept & ((1u << tid) - 1u));
       if (k < o.nnz_cap) o.col_idx[k] = (c0 + tid) % nbc;
     }
@@ -1359,9 +1359,13 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
   if (n > 0 && n <= kSmallN && nbr <= 1024 && nbc <= 1024) {
     // every index array and the values: one launch
     const SmallOut o{row_ptr, col_idx, row_order, col_ptr, csc_row, nnz_dev, nnz_cap};
-    const unsigned spans = nnz_cap > 0 ? (unsigned)((n + kGatherSpan - 1) / kGatherSpan) : 0u;
+    // Sixteen candidates are up to 128 KiB of values; of 128-wide blocks four are, and eight still fill the chip when there
+    // are many.  (Sixteen of those, every block kept, eight matrices: 2048 x 2048 255 us, with four 138; 4096 x 14336 388,
+    // with four 375 and with eight 366, at 90 % sparsity 145, 161 and 138.)
+    const int span = b < 128 ? 16 : n < 2048 ? 4 : 8;
+    const unsigned spans = nnz_cap > 0 ? (unsigned)((n + span - 1) / span) : 0u;
     k_pack_small<<<dim3((aux ? 2u : 1u) + spans), dim3(1024), 0, stream>>>(mask, (int)nbr, (int)nbc, o, narrow, wide,
-                                                                          GatherArgs{W, ldw, b, vals});
+                                                                          GatherArgs{W, ldw, b, vals, span});
     BLAST_LAUNCH_CHECK("k_pack_small");
     return BLAST_OK;
   } else {

@@ -219,6 +219,17 @@ def test_pack_single_workgroup_limits(api, nbr, nbc):
     _assert_packed_equal(dev, ref, b)
 
 
+@pytest.mark.parametrize("b,nbr,nbc", [(128, 3, 7), (128, 32, 63), (128, 32, 64), (128, 41, 50), (64, 5, 13), (16, 31, 33)])
+def test_pack_small_spans_of_candidates(api, b, nbr, nbc):
+    """Every block kept, and two of three, in the one-launch packing: the last workgroup's span of candidates is partial,
+    and the span grows at 2048 blocks of 128 x 128."""
+    rng = np.random.default_rng(640 + nbr * nbc)
+    W = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
+    for mask in (np.ones((nbr, nbc), np.uint8), (np.arange(nbr * nbc).reshape(nbr, nbc) % 3 > 0).astype(np.uint8)):
+        dev, ref = pack_both(api, W, b, mask=mask)
+        check_aux(dev, ref)
+
+
 @pytest.mark.parametrize("sparsity", [0.3, 0.75, 0.97])
 def test_pack_single_workgroup_massive_ties(api, sparsity):
     """6400 blocks with three distinct scores: the threshold is a tie that the index order cuts."""
