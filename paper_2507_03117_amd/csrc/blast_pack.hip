@@ -850,21 +850,23 @@ struct GatherArgs {
   int b;
   uint16_t* vals;
   int span;  // candidate blocks of a workgroup, at most 32
+  int code;  // mask code of every block where there is no mask
 };
 
 // Flags of the blocks a thread owns (bit j: block tid * per + j is kept).
-__device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask, int n, int per) {
+__device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask, int code, int n, int per) {
   const int e0 = threadIdx.x * per;
   unsigned keep = 0u;
 #pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) keep |= (j < per && e0 + j < n && mask[e0 + j] != 0) ? 1u << j : 0u;
+  for (int j = 0; j < kSmallPer; ++j)
+    keep |= (j < per && e0 + j < n && (mask ? mask[e0 + j] : code) != 0) ? 1u << j : 0u;
   return keep;
 }
 
 // Everything that follows the mask, in one launch.  Workgroup 0: row pointers, schedule, chunk plans; workgroup 1 (with
 // aux): the column-grouped index; the others: ga.span candidate blocks each, whose places among the stored blocks
 // they count for themselves - column indices and values.  A block whose mask code is 2 (regrown, BLaST Sec. 3.2) is
-// stored as zeros: it joins the structure without changing the product.
+// stored as zeros: it joins the structure without changing the product.  No mask: every block has the code ga.code.
 // What bounds it: the index jobs, a chain of scans and barriers in a workgroup each.  Three 8192 x 2048 matrices, b = 64,
 // 80 % sparse, after a mask update: as one workgroup for all index arrays and a launch for the values 12 + 4.6 us per
 // matrix and 187 us for the update and re-packing together, now 9 us and 163.
@@ -885,7 +887,7 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
   const int n = nbr * nbc;
   const int per = (n + 1023) >> 10;  // blocks per thread (uniform); the loops below are unrolled to kSmallPer
   const int e0 = tid * per;
-  const unsigned keep = small_flags(mask, n, per);
+  const unsigned keep = small_flags(mask, ga.code, n, per);
   const int jobs = o.col_ptr ? 2 : 1;
 
   if ((int)blockIdx.x >= jobs) {
@@ -896,7 +898,7 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
     for (int j = 0; j < kSmallPer; ++j) before += __popcll(__ballot(((keep >> j) & 1u) && e0 + j < c0));
     if (lane_id() == 0) wave_tot[tid / kWave] = before;
     const int cand = c0 + lane_id();
-    const int code = lane_id() < ga.span && cand < n ? mask[cand] : 0;
+    const int code = lane_id() < ga.span && cand < n ? (mask ? mask[cand] : ga.code) : 0;
     const unsigned kept = (unsigned)__ballot(code != 0), zero = (unsigned)__ballot(code == 2);
     __syncthreads();
     int first = 0;
@@ -1345,7 +1347,9 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
     if (int rc = launch_block_scores(b, W, ldw, nbc, n, scores, nullptr, 0, nullptr, stream)) return rc;
   }
 
-  if (m && n > 0) {
+  const bool small = n > 0 && n <= kSmallN && nbr <= 1024 && nbc <= 1024;
+  if (m && small && !scored) mask = nullptr;  // every block has the same code: no launch that writes it n times
+  if (m && n > 0 && mask) {
     if (!scored) {
       k_fill_u8<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(m, n, n_keep == n ? 1 : 0);
       BLAST_LAUNCH_CHECK("k_fill_u8");
@@ -1356,7 +1360,7 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
       BLAST_LAUNCH_CHECK("k_select_topk");
     }
   }
-  if (n > 0 && n <= kSmallN && nbr <= 1024 && nbc <= 1024) {
+  if (small) {
     // every index array and the values: one launch
     const SmallOut o{row_ptr, col_idx, row_order, col_ptr, csc_row, nnz_dev, nnz_cap};
     // Sixteen candidates are up to 128 KiB of values; of 128-wide blocks four are, and eight still fill the chip when there
@@ -1365,7 +1369,7 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
     const int span = b < 128 ? 16 : n < 2048 ? 4 : 8;
     const unsigned spans = nnz_cap > 0 ? (unsigned)((n + span - 1) / span) : 0u;
     k_pack_small<<<dim3((aux ? 2u : 1u) + spans), dim3(1024), 0, stream>>>(mask, (int)nbr, (int)nbc, o, narrow, wide,
-                                                                          GatherArgs{W, ldw, b, vals, span});
+                                                                          GatherArgs{W, ldw, b, vals, span, n_keep == n ? 1 : 0});
     BLAST_LAUNCH_CHECK("k_pack_small");
     return BLAST_OK;
   } else {
