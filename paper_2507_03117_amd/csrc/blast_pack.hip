@@ -567,6 +567,8 @@ static_assert(kSmallN + 1024 < 65536, "two counts share a 32-bit word");
 static_assert((blast::kChunkBlocks & (blast::kChunkBlocks - 1)) == 0 &&
               (blast::kWideChunkBlocks & (blast::kWideChunkBlocks - 1)) == 0, "chunk sizes are powers of two");
 
+constexpr int kRanked = 16;  // candidates that a wave ranks by comparing each with all
+
 // LDS scratch of select_small, one per group (an array of them: the bins are read four at a time, so the size keeps the
 // alignment too).
 struct alignas(16) SelectShared {
@@ -575,7 +577,7 @@ struct alignas(16) SelectShared {
   unsigned long long diff, kth;  // bits in which keys differ; the n_keep-th key ...
   int kth_at;                    // ... and its index: what is kept sorts before it, or is it
   int rem, eq, digit, fill, open;
-  int cand[kWave];
+  int cand[kRanked];
 };
 static_assert(sizeof(SelectShared) % 16 == 0 && offsetof(SelectShared, hist) % 16 == 0, "16-byte reads of hist");
 
@@ -586,11 +588,13 @@ static_assert(sizeof(SelectShared) % 16 == 0 && offsetof(SelectShared, hist) % 1
 //
 // Most-significant-digit radix select: scores of one matrix share their leading bits (sign, exponent, often the first
 // mantissa bits), and a digit that every key carries would send every count to one LDS word, so the passes start below
-// the bits common to all keys, eight bits at a time; as soon as at most 64 keys carry the selected prefix, a wave ranks
-// those by comparing each with all.
+// the bits common to all keys, eight bits at a time; as soon as at most 16 keys carry the selected prefix, a wave ranks
+// those by comparing each with all (40 ns each, a pass a microsecond: mask
+// update with up to 64 ranked that way 11.9 us on 64 blocks of 64 x 64 and 23.5 on 4096, now 8.2 and 20.9).
 // What bounds it is not the work but its dependent steps and, in a workgroup that runs every instruction once or
-// twice with caches full of weights, the fetching of instructions: loops are left rolled.  4096 blocks, weight and gradient (timestamps):
-// keys unrolled over registers and passes down to one key, the two selections in turn: 16 us; this: 12.8 us.
+// twice with caches full of weights, the fetching of instructions: loops are left rolled.  4096 blocks, weight and gradient
+// (timestamps): keys unrolled over registers and passes down to one key, the two selections in turn: 16 us; keys in LDS,
+// side by side, 64 ranked: 12.8 us.
 template <int NT, int GROUPS>
 __device__ __forceinline__ void select_small(const double* __restrict__ score, int n, int n_keep, unsigned long long* keys,
                                              SelectShared* shared) {
@@ -618,7 +622,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
   auto carries = [&](unsigned long long k) { return fixed == 64 || (k >> fixed) == (prefix >> fixed); };
 #pragma unroll 1
   for (;;) {
-    const bool active = fixed > 0 && eq > kWave;
+    const bool active = fixed > 0 && eq > kRanked;
     if (tid == 0) {
       sh.open = active ? 1 : 0;
       sh.fill = 0;
@@ -669,12 +673,12 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
     }
   }
   int eq_mine = 0, eq_before = 0;
-  if (eq <= kWave) {
+  if (eq <= kRanked) {
 #pragma unroll 2
     for (int i = tid; i < n; i += NT)
       if (carries(keys[i])) sh.cand[atomicAdd(&sh.fill, 1)] = i;
   } else {
-    // more than 64 equal keys: a thread counts those in its stretch of the indices
+    // more equal keys than that: a thread counts those in its stretch of the indices
     const int per = (n + NT - 1) / NT, e0 = tid * per;
     int mine = 0;
     for (int i = e0; i < e0 + per && i < n; ++i) mine += keys[i] == prefix ? 1 : 0;
@@ -688,7 +692,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
     eq_before = inc - mine;
   }
   wg_barrier<true>();
-  if (eq <= kWave) {
+  if (eq <= kRanked) {
     if (tid < kWave) {
       const int at = lane < eq ? sh.cand[lane] : 0;
       const unsigned long long k = lane < eq ? keys[at] : 0ull;

@@ -287,3 +287,28 @@ def test_selection_among_equal_scores(api, nbr, nbc, levels_w, levels_g, s):
     assert np.array_equal(api.generate_masks(W, G, b, s).cpu().numpy().ravel(), want)
     p = api.bsr_pack(W, b, sparsity=s)
     assert p.nnz == n_keep and np.array_equal(p.col_idx.cpu().numpy()[:n_keep], np.nonzero(kept(vw))[0] % nbc)
+
+
+@pytest.mark.parametrize("ties", [1, 15, 16, 17, 18, 63, 64, 65, 300])
+def test_selection_cuts_a_group_of_equal_scores(api, ties):
+    """`ties` blocks share the score at which the selection ends, more or fewer than a wave ranks by comparison; 40 blocks
+    lie above, and the cut falls after the first, the middle and the last of the group."""
+    import torch
+
+    rng = np.random.default_rng(9810 + ties)
+    b, nbr, nbc = 16, 25, 20
+    n = nbr * nbc
+    score = np.empty(n, np.float32)
+    order = rng.permutation(n)
+    score[order[:40]] = 2.0 + np.arange(40) / 64
+    score[order[40:40 + ties]] = 1.0
+    score[order[40 + ties:]] = np.arange(n - 40 - ties) / 1024
+    S = np.ascontiguousarray(np.repeat(np.repeat(score.reshape(nbr, nbc), b, 0), b, 1))
+    W = synth.f32_to_bf16_bits(S)
+    for keep in sorted({41, 40 + (ties + 1) // 2, 40 + ties}):
+        sparsity = 1 - keep / n
+        want = orc.pooled_topk_mask(S, b, sparsity)[0]
+        assert int(want.sum()) == keep
+        assert np.array_equal(api.pooled_topk_mask(torch.from_numpy(S).cuda(), b, sparsity).cpu().numpy(), want)
+        got = api.generate_masks(to_dev(W), to_dev(np.ascontiguousarray(W[::-1])), b, sparsity).cpu().numpy()
+        assert np.array_equal(got, orc.generate_masks(W, np.ascontiguousarray(W[::-1]), b, sparsity))
