@@ -166,6 +166,10 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
       t_pos[i] = pos;
     }
     if (lane == 0) *n_rows_at = __builtin_popcountll(mine);
+  } else if (wave == NW - 1 && a.z_blocks > 0) {
+    // the side job (see DecArgs), dealt to the last waves while the first ones deal rows; a workgroup that is dealt no
+    // row has its share of it all the same
+    for (int ci = w; ci < a.z_blocks; ci += G) decode_zero_job<B, 64>(a, ci);
   }
 
   // ---- per-lane constants of the copies and fragments, as in decode_unit --------------------------------------
@@ -260,8 +264,6 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
 #pragma unroll 1
     for (int b = 0; b < NSLOT - 1; ++b)
       if (b < cnt) issue(b);
-    if (r0 == 0 && a.z_blocks > 0 && wave == NW - 1)  // the side job (see DecArgs), dealt to the last waves
-      for (int ci = w; ci < a.z_blocks; ci += G) decode_zero_job<B, 64>(a, ci);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     // (row, matrix) of the block being multiplied; the first one of the piece may have begun in an earlier piece
     int seg = cnt > 0 ? BLAST_LANE(vs, 0) : -1;

@@ -408,6 +408,35 @@ def test_mlp_with_e5m2_weights_rows_dealt_to_workgroups(api, b, nbi, nbe, kind, 
     assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
 
 
+@pytest.mark.parametrize("b,nbe,nbi,T", [(64, 12, 260, 1), (64, 12, 260, 8), (64, 12, 300, 9), (128, 8, 260, 3),
+                                         (128, 8, 260, 8), (128, 3, 513, 4)])
+def test_mlp_with_e5m2_weights_cleared_rows_of_a_large_layer(api, b, nbe, nbi, T):
+    """Layers large enough for the streamed decode whose down projection has rows of more than 256 blocks: the first
+    launch clears the rows that the chunks of the second add into (9 tokens, or more than 512 gate rows: a launch of its
+    own does).  Poisoned fp32 output, twice; whole rows in bf16."""
+    import torch
+
+    rng = np.random.default_rng(5450 + b + nbi + T)
+    E, I = nbe * b, nbi * b
+    mg, mu = (synth.uniform_mask(rng, nbi, nbe, 0.2) for _ in range(2))
+    md = synth.uniform_mask(rng, nbe, nbi, 0.2)
+    md[0, :] = 1
+    md[1, :] = 0
+    md[2, 5:] = 0
+    dev, dev8, ref, ref8 = _w8_layer(api, rng, E, I, b, 0.0, masks=[mg, mu, md])
+    x = synth.gauss_bf16(rng, (T, E), 1.0)
+    want = orc.mlp_e5m2w(ref[0], ref8[0], ref[1], ref8[1], ref[2], ref8[2], x)
+    args = (dev[0], dev8[0], dev[1], dev8[1], dev[2], dev8[2], to_dev(x))
+    for _ in range(2):
+        y = api.sparse_mlp_e5m2w(*args, out=torch.full((T, E), float("nan"), device="cuda:0"))
+        torch.cuda.synchronize()
+        check_close(y.cpu().numpy().T, want, f"E5M2-weight mlp, cleared rows b={b} nbi={nbi} T={T}")
+    assert not y.cpu().numpy()[:, b:2 * b].any()
+    yb = api.sparse_mlp_e5m2w(*args, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
+
+
 @pytest.mark.parametrize("b,nbr,nbc,T,groups", [
     (128, 9, 7, 130, True), (128, 9, 7, 257, False),   # 128-token tiles, a tile of one and of 129 tokens
     (128, 130, 9, 1025, True), (128, 130, 9, 1100, False),  # 256-token tiles, five to a row
