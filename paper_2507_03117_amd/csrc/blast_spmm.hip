@@ -1231,13 +1231,14 @@ int launch_flat_w8(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream)
 }
 
 // One token tile of up to 8 tokens (512 / B copy-instruction rows, or twice that), at most 512 rows or chunks (64 per
-// XCD: one per lane) of at most 512 blocks (`longest`, over both matrices), columns that fit 24 bits, and enough
+// XCD: one per lane) of at most 512 blocks (`longest`, over both matrices: what the kernel's table of a row holds, so
+// never the view's max_row_blocks, which a re-packing may have left behind), columns that fit 24 bits, and enough
 // blocks that a CU's share is a stream: 32 slices per CU is a fifth of the 405B-class layer, which gains 25 %; the
 // 8B-shaped one has 11 per CU and would only pay the deal.  (More tokens: a 4 KB activation tile per block leaves
 // sixteen waves a single slot each.)
 template <int B, bool DUAL>
 bool flat_applies(const TileArgs& a, int64_t nnz, int64_t items, int64_t longest) {
-  return a.T <= 8 && items <= 512 && longest > 0 && longest <= FlatCfg<B, DUAL, 1, true>::PM && a.kdim / B < (1 << 24) &&
+  return a.T <= 8 && items <= 512 && longest <= FlatCfg<B, DUAL, 1, true>::PM && a.kdim / B < (1 << 24) &&
          nnz * (B / 16) >= (int64_t)32 * cu_count();
 }
 
@@ -1250,7 +1251,7 @@ int launch_flat_w8_t(const TileArgs& a, const ChunkPlan& plan, hipStream_t strea
 // `plan`: the chunk plan of the matrix (single matrix, fp32 output only); taken under the rule of the bf16
 // decode path: when the fullest row, dealt to four waves, is deeper than four times a workgroup slot's share.
 template <int B, bool DUAL>
-int launch_decode_w8(const TileArgs& a, int64_t nnz, int64_t max_row_blocks, const ChunkPlan& plan, hipStream_t stream) {
+int launch_decode_w8(const TileArgs& a, int64_t nnz, const ChunkPlan& plan, hipStream_t stream) {
   if constexpr (!DUAL) {
     if (plan.hdr && !a.y_bf16 && a.T <= kDecodeMaxTokens) {
       double ref = (double)nnz * (B / 16) / (4.0 * 2.0 * cu_count());
@@ -1262,7 +1263,8 @@ int launch_decode_w8(const TileArgs& a, int64_t nnz, int64_t max_row_blocks, con
   }
   ChunkPlan side{};  // no chunks; only the side job travels on
   side.zero_job = plan.zero_job;
-  if (flat_applies<B, DUAL>(a, nnz, a.nbr, max_row_blocks)) return launch_flat_w8_t<B, DUAL, false>(a, side, stream);
+  if (flat_applies<B, DUAL>(a, nnz, a.nbr, (DUAL ? 2 : 1) * a.kdim / B))
+    return launch_flat_w8_t<B, DUAL, false>(a, side, stream);
   return launch_decode_w8_c<B, DUAL, false>(a, side, stream);
 }
 
@@ -1335,16 +1337,13 @@ extern "C" int blast_sparse_mlp_e5m2w(const blast_bsr_view* Wgate, const uint8_t
     ChunkPlan gplan{};
     gplan.zero_job = zj.hdr ? &zj : nullptr;
     const int64_t nnz_gu = Wgate->nnz + Wup->nnz;
-    // (the fullest joint row has at most the sum of the two fullest rows; 0: not known)
-    const int64_t longest = Wgate->max_row_blocks > 0 && Wup->max_row_blocks > 0
-                                ? (int64_t)Wgate->max_row_blocks + Wup->max_row_blocks : 0;
-    if (int rc = (b == 64) ? launch_decode_w8<64, true>(g, nnz_gu, longest, gplan, stream)
-                           : launch_decode_w8<128, true>(g, nnz_gu, longest, gplan, stream))
+    if (int rc = (b == 64) ? launch_decode_w8<64, true>(g, nnz_gu, gplan, stream)
+                           : launch_decode_w8<128, true>(g, nnz_gu, gplan, stream))
       return rc;
     dplan.pre_zeroed = zj.done;
   }
-  return (b == 64) ? launch_decode_w8<64, false>(d, Wdown->nnz, Wdown->max_row_blocks, dplan, stream)
-                   : launch_decode_w8<128, false>(d, Wdown->nnz, Wdown->max_row_blocks, dplan, stream);
+  return (b == 64) ? launch_decode_w8<64, false>(d, Wdown->nnz, dplan, stream)
+                   : launch_decode_w8<128, false>(d, Wdown->nnz, dplan, stream);
 }
 
 extern "C" int blast_sparse_mlp2(const blast_bsr_view* W1, const blast_bsr_view* W2, const uint16_t* X, int64_t ldx,

@@ -437,6 +437,29 @@ def test_mlp_with_e5m2_weights_cleared_rows_of_a_large_layer(api, b, nbe, nbi, T
     assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
 
 
+@pytest.mark.parametrize("b,nbe,nbi", [(64, 4, 600), (128, 257, 9)])
+def test_mlp_with_e5m2_weights_and_a_row_fuller_than_the_view_says(api, b, nbe, nbi):
+    """max_row_blocks is the number the packer reported, which a later re-packing into the same arrays can leave behind:
+    it may not bound what a kernel's tables hold.  Rows of more than 512 blocks (of both matrices) under a smaller claim."""
+    import dataclasses
+
+    import torch
+
+    rng = np.random.default_rng(5480 + b)
+    E, I, T = nbe * b, nbi * b, 5
+    ones = [np.ones(s, np.uint8) for s in ((nbi, nbe), (nbi, nbe), (nbe, nbi))]
+    dev, dev8, ref, ref8 = _w8_layer(api, rng, E, I, b, 0.0, masks=ones)
+    dev = [dataclasses.replace(m, max_row_blocks=3) for m in dev]
+    x = synth.gauss_bf16(rng, (T, E), 1.0)
+    want = orc.mlp_e5m2w(ref[0], ref8[0], ref[1], ref8[1], ref[2], ref8[2], x)
+    args = (dev[0], dev8[0], dev[1], dev8[1], dev[2], dev8[2], to_dev(x))
+    y = api.sparse_mlp_e5m2w(*args, out=torch.full((T, E), float("nan"), device="cuda:0"))
+    yb = api.sparse_mlp_e5m2w(*args, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    check_close(y.cpu().numpy().T, want, f"E5M2-weight mlp, full rows b={b}")
+    assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
+
+
 @pytest.mark.parametrize("b,nbr,nbc,T,groups", [
     (128, 9, 7, 130, True), (128, 9, 7, 257, False),   # 128-token tiles, a tile of one and of 129 tokens
     (128, 130, 9, 1025, True), (128, 130, 9, 1100, False),  # 256-token tiles, five to a row
