@@ -1248,24 +1248,29 @@ int launch_flat_w8_t(const TileArgs& a, const ChunkPlan& plan, hipStream_t strea
   return launch_flat_w8<B, DUAL, 8 * B / 512, CHUNK>(a, plan, stream);
 }
 
-// `plan`: the chunk plan of the matrix (single matrix, fp32 output only); taken under the rule of the bf16
-// decode path: when the fullest row, dealt to four waves, is deeper than four times a workgroup slot's share.
+// Whether a single matrix with fp32 output takes its chunk plan, whose chunks add atomically: the rule of the bf16
+// decode path, when the fullest row, dealt to four waves, is deeper than four times a workgroup slot's share.  (Rows
+// that are less full than that are stored once, in a fixed order, by either kernel.)
+bool w8_chunked(int b, const ChunkPlan& plan, int64_t nnz, bool y_bf16, int64_t T) {
+  if (!plan.hdr || y_bf16 || T > kDecodeMaxTokens) return false;
+  double ref = (double)nnz * (b / 16) / (4.0 * 2.0 * cu_count());
+  if (ref < blast::kChunkBlocks) ref = blast::kChunkBlocks;
+  return (double)plan.max_row_blocks / 4.0 > 4.0 * ref;
+}
+
+// `plan`: the chunk plan of the matrix where w8_chunked() says so (single matrix only).
 template <int B, bool DUAL>
 int launch_decode_w8(const TileArgs& a, int64_t nnz, const ChunkPlan& plan, hipStream_t stream) {
   if constexpr (!DUAL) {
-    if (plan.hdr && !a.y_bf16 && a.T <= kDecodeMaxTokens) {
-      double ref = (double)nnz * (B / 16) / (4.0 * 2.0 * cu_count());
-      if (ref < blast::kChunkBlocks) ref = blast::kChunkBlocks;
+    if (plan.hdr) {
       if (flat_applies<B, DUAL>(a, nnz, plan.max_chunks, blast::kChunkBlocks))
         return launch_flat_w8_t<B, false, true>(a, plan, stream);
-      if ((double)plan.max_row_blocks / 4.0 > 4.0 * ref) return launch_decode_w8_c<B, false, true>(a, plan, stream);
+      return launch_decode_w8_c<B, false, true>(a, plan, stream);
     }
   }
-  ChunkPlan side{};  // no chunks; only the side job travels on
-  side.zero_job = plan.zero_job;
   if (flat_applies<B, DUAL>(a, nnz, a.nbr, (DUAL ? 2 : 1) * a.kdim / B))
-    return launch_flat_w8_t<B, DUAL, false>(a, side, stream);
-  return launch_decode_w8_c<B, DUAL, false>(a, side, stream);
+    return launch_flat_w8_t<B, DUAL, false>(a, plan, stream);
+  return launch_decode_w8_c<B, DUAL, false>(a, plan, stream);
 }
 
 }  // namespace
@@ -1319,11 +1324,12 @@ extern "C" int blast_sparse_mlp_e5m2w(const blast_bsr_view* Wgate, const uint8_t
   d.kdim = I;
   d.act = -1;
   ChunkPlan dplan = plan_of(Wdown, T);
+  if (!w8_chunked(b, dplan, Wdown->nnz, y_dtype == BLAST_BF16, T)) dplan = ChunkPlan{};
   if (I > 0) {
     // the rows of Y that the chunked second product accumulates into are cleared on the side by the first launch
     // (where that is the kernel that can; `done` says whether it has been)
     ZeroJob zj{};
-    if (dplan.hdr && y_dtype == BLAST_F32 && T <= kDecodeMaxTokens) {
+    if (dplan.hdr) {
       zj.hdr = dplan.hdr;
       zj.chunk_row = dplan.chunk_row;
       zj.chunk_kb = dplan.chunk_kb;

@@ -437,6 +437,24 @@ def test_mlp_with_e5m2_weights_cleared_rows_of_a_large_layer(api, b, nbe, nbi, T
     assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
 
 
+@pytest.mark.parametrize("b,nbe,nbi", [(128, 12, 200), (64, 12, 256)])
+def test_mlp_with_e5m2_weights_ordinary_rows_are_stored_once(api, b, nbe, nbi):
+    """Down rows of up to 256 blocks are not cut: the fp32 result is the same in every run, and rounds to the bf16 one."""
+    import torch
+
+    rng = np.random.default_rng(5470 + b)
+    E, I, T = nbe * b, nbi * b, 8
+    masks = [synth.uniform_mask(rng, r, c, 0.2) for r, c in ((nbi, nbe), (nbi, nbe), (nbe, nbi))]
+    masks[2][3, :] = 1
+    dev, dev8, _, _ = _w8_layer(api, rng, E, I, b, 0.0, masks=masks)
+    assert dev[2].max_row_blocks == nbi
+    args = (dev[0], dev8[0], dev[1], dev8[1], dev[2], dev8[2], to_dev(synth.gauss_bf16(rng, (T, E), 1.0)))
+    y = api.sparse_mlp_e5m2w(*args)
+    for _ in range(8):
+        assert torch.equal(api.sparse_mlp_e5m2w(*args), y)
+    assert torch.equal(api.sparse_mlp_e5m2w(*args, out_dtype=torch.bfloat16), y.to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("b,nbe,nbi", [(64, 4, 600), (128, 257, 9)])
 def test_mlp_with_e5m2_weights_and_a_row_fuller_than_the_view_says(api, b, nbe, nbi):
     """max_row_blocks is the number the packer reported, which a later re-packing into the same arrays can leave behind:
@@ -457,7 +475,7 @@ def test_mlp_with_e5m2_weights_and_a_row_fuller_than_the_view_says(api, b, nbe, 
     yb = api.sparse_mlp_e5m2w(*args, out_dtype=torch.bfloat16)
     torch.cuda.synchronize()
     check_close(y.cpu().numpy().T, want, f"E5M2-weight mlp, full rows b={b}")
-    assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
+    assert torch.equal(yb, y.to(torch.bfloat16))
 
 
 @pytest.mark.parametrize("b,nbr,nbc,T,groups", [
