@@ -1242,6 +1242,24 @@ bool flat_applies(const TileArgs& a, int64_t nnz, int64_t items, int64_t longest
          nnz * (B / 16) >= (int64_t)32 * cu_count();
 }
 
+// Whether whole rows are better off there than with a workgroup per row and slice (k_decode), by the fullest row (over
+// both matrices; a hint, 0 = not known) and the share of a workgroup slot, both in blocks.  k_decode ends with its fullest
+// row, a quarter of it per wave, or with its share; the streamed kernel pays for the deal and then for the share alone.
+// microseconds, k_decode / streamed, 4 tokens:
+//   b = 128, gated: share 22 10.9 / 11.2, 34 13.6 / 13.5, 56 17.6 / 16.3, 83 23.4 / 19.9, whatever the rows; up to 8
+//     tokens, where k_decode copies twice the activations, share 22 14.3 / 13.3.
+//   b = 64, gated: share 48 12.3 / 14.5, 90 15.8 / 18.3, 134 19.1 / 21.2 with fullest rows of at most 62; share 67 and
+//     fullest row 128 21 / 16, 135 and 128 23 / 21.
+//   one matrix: share 45, fullest row 58 9.7 / 12.6; 44 and 79 12.6 / 13.0; 24 and 74 10.6 / 10.0; 33 and 118 17.0 /
+//     12.6; 67 and 156 22.0 / 15.1; one token: 17 and 45 9.0 / 8.3; 22 and 39 8.4 / 8.9.
+template <int B, bool DUAL>
+bool flat_pays(const TileArgs& a, int64_t nnz, int64_t fullest) {
+  const int64_t share = nnz * (B / 16) / (2 * cu_count());
+  if (B == 128 && DUAL && share >= (a.T > 512 / B ? 20 : 32)) return true;
+  if (B == 64 && DUAL) return fullest > 48 + share / 2;
+  return fullest > (a.T == 1 ? 16 : 33) + share + share / 8;
+}
+
 template <int B, bool DUAL, bool CHUNK>
 int launch_flat_w8_t(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream) {
   if (a.T <= 512 / B) return launch_flat_w8<B, DUAL, 1, CHUNK>(a, plan, stream);
@@ -1260,7 +1278,7 @@ bool w8_chunked(int b, const ChunkPlan& plan, int64_t nnz, bool y_bf16, int64_t 
 
 // `plan`: the chunk plan of the matrix where w8_chunked() says so (single matrix only).
 template <int B, bool DUAL>
-int launch_decode_w8(const TileArgs& a, int64_t nnz, const ChunkPlan& plan, hipStream_t stream) {
+int launch_decode_w8(const TileArgs& a, int64_t nnz, int64_t fullest, const ChunkPlan& plan, hipStream_t stream) {
   if constexpr (!DUAL) {
     if (plan.hdr) {
       if (flat_applies<B, DUAL>(a, nnz, plan.max_chunks, blast::kChunkBlocks))
@@ -1268,7 +1286,7 @@ int launch_decode_w8(const TileArgs& a, int64_t nnz, const ChunkPlan& plan, hipS
       return launch_decode_w8_c<B, false, true>(a, plan, stream);
     }
   }
-  if (flat_applies<B, DUAL>(a, nnz, a.nbr, (DUAL ? 2 : 1) * a.kdim / B))
+  if (flat_applies<B, DUAL>(a, nnz, a.nbr, (DUAL ? 2 : 1) * a.kdim / B) && flat_pays<B, DUAL>(a, nnz, fullest))
     return launch_flat_w8_t<B, DUAL, false>(a, plan, stream);
   return launch_decode_w8_c<B, DUAL, false>(a, plan, stream);
 }
@@ -1343,13 +1361,15 @@ extern "C" int blast_sparse_mlp_e5m2w(const blast_bsr_view* Wgate, const uint8_t
     ChunkPlan gplan{};
     gplan.zero_job = zj.hdr ? &zj : nullptr;
     const int64_t nnz_gu = Wgate->nnz + Wup->nnz;
-    if (int rc = (b == 64) ? launch_decode_w8<64, true>(g, nnz_gu, gplan, stream)
-                           : launch_decode_w8<128, true>(g, nnz_gu, gplan, stream))
+    // (the fullest joint row has at most the sum of the two fullest rows)
+    const int64_t fullest = (int64_t)Wgate->max_row_blocks + Wup->max_row_blocks;
+    if (int rc = (b == 64) ? launch_decode_w8<64, true>(g, nnz_gu, fullest, gplan, stream)
+                           : launch_decode_w8<128, true>(g, nnz_gu, fullest, gplan, stream))
       return rc;
     dplan.pre_zeroed = zj.done;
   }
-  return (b == 64) ? launch_decode_w8<64, false>(d, Wdown->nnz, dplan, stream)
-                   : launch_decode_w8<128, false>(d, Wdown->nnz, dplan, stream);
+  return (b == 64) ? launch_decode_w8<64, false>(d, Wdown->nnz, Wdown->max_row_blocks, dplan, stream)
+                   : launch_decode_w8<128, false>(d, Wdown->nnz, Wdown->max_row_blocks, dplan, stream);
 }
 
 extern "C" int blast_sparse_mlp2(const blast_bsr_view* W1, const blast_bsr_view* W2, const uint16_t* X, int64_t ldx,

@@ -377,6 +377,7 @@ def _skewed(rng, nbr, nbc, lengths):
 @pytest.mark.parametrize("b,nbi,nbe,kind,T", [
     (128, 45, 25, "half", 1), (128, 45, 25, "half", 4), (128, 45, 25, "half", 5), (128, 45, 25, "half", 8),
     (64, 61, 70, "half", 8), (64, 61, 70, "half", 1),  # 8 row groups per XCD
+    (128, 80, 40, "skew", 4), (128, 80, 40, "skew", 8), (64, 100, 70, "skew", 1), (64, 100, 70, "skew", 8),  # down too
     (128, 500, 3, "empty", 8),      # more rows per group than entries: several batches; 250 empty rows
     (128, 512, 3, "full", 7), (128, 513, 3, "full", 3),  # 64 rows per XCD, and one too many
     (128, 9, 256, "row", 1), (128, 9, 257, "row", 2),   # a joint row of 512 blocks, and one too long
@@ -393,7 +394,7 @@ def test_mlp_with_e5m2_weights_rows_dealt_to_workgroups(api, b, nbi, nbe, kind, 
     else:  # a full row, an empty one, the rest uneven
         lens = [nbe, 0] + [int(rng.integers(1, nbe + 1)) for _ in range(nbi - 2)]
     mg, mu = _skewed(rng, nbi, nbe, lens), _skewed(rng, nbi, nbe, lens[::-1] if kind == "half" else lens)
-    md = _skewed(rng, nbe, nbi, [0 if r == 1 else nbi - r % 2 for r in range(nbe)])
+    md = _skewed(rng, nbe, nbi, [0 if r == 1 else nbi // 4 if kind == "skew" and r % 8 else nbi - r % 2 for r in range(nbe)])
     dev, dev8, ref, ref8 = _w8_layer(api, rng, E, I, b, 0.0, masks=[mg, mu, md])
     x = synth.gauss_bf16(rng, (T, E), 1.0)
     want = orc.mlp_e5m2w(ref[0], ref8[0], ref[1], ref8[1], ref[2], ref8[2], x)
@@ -408,18 +409,19 @@ def test_mlp_with_e5m2_weights_rows_dealt_to_workgroups(api, b, nbi, nbe, kind, 
     assert np.abs(yb.float().cpu().numpy().T - want).max() <= 2.0 ** -7 * np.abs(want).max() + 1e-6
 
 
-@pytest.mark.parametrize("b,nbe,nbi,T", [(64, 12, 260, 1), (64, 12, 260, 8), (64, 12, 300, 9), (128, 8, 260, 3),
+@pytest.mark.parametrize("b,nbe,nbi,T", [(64, 40, 260, 1), (64, 40, 260, 8), (64, 12, 300, 9), (128, 8, 260, 3),
                                          (128, 8, 260, 8), (128, 3, 513, 4)])
 def test_mlp_with_e5m2_weights_cleared_rows_of_a_large_layer(api, b, nbe, nbi, T):
-    """Layers large enough for the streamed decode whose down projection has rows of more than 256 blocks: the first
-    launch clears the rows that the chunks of the second add into (9 tokens, or more than 512 gate rows: a launch of its
-    own does).  Poisoned fp32 output, twice; whole rows in bf16."""
+    """Layers large enough (and, with 64-wide blocks, skewed enough) for the streamed decode whose down projection has
+    rows of more than 256 blocks: the first launch clears the rows that the chunks of the second add into (9 tokens, or
+    more than 512 gate rows: a launch of its own does).  Poisoned fp32 output, twice; whole rows in bf16."""
     import torch
 
     rng = np.random.default_rng(5450 + b + nbi + T)
     E, I = nbe * b, nbi * b
-    mg, mu = (synth.uniform_mask(rng, nbi, nbe, 0.2) for _ in range(2))
-    md = synth.uniform_mask(rng, nbe, nbi, 0.2)
+    mg, mu = (synth.uniform_mask(rng, nbi, nbe, 0.85 if nbe == 40 else 0.2) for _ in range(2))
+    mg[5:25], mu[5:25] = 1, 1
+    md = synth.uniform_mask(rng, nbe, nbi, 0.6 if nbe == 40 else 0.2)  # (at most 512 chunks)
     md[0, :] = 1
     md[1, :] = 0
     md[2, 5:] = 0
