@@ -1183,7 +1183,7 @@ int launch_decode_w8_c(const TileArgs& a, const ChunkPlan& plan, hipStream_t str
 // Large layers: the blocks of many rows as one stream per workgroup (kern_flat.h).
 template <int B, bool DUAL, int XI, bool CHUNK>
 int launch_flat_w8(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream) {
-  using C = FlatCfg<B, DUAL, XI, true>;
+  using C = FlatCfg<B, DUAL, XI>;
   DecArgs d{};
   d.m0 = a.m0;
   d.m1 = a.m1;
@@ -1215,7 +1215,7 @@ int launch_flat_w8(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream)
     z.done = true;
   }
   static blast::DeviceFlags lds_set;
-  if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_decode_flat<B, DUAL, CHUNK, XI, true>), C::LDS_BYTES,
+  if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_decode_flat<B, DUAL, CHUNK, XI>), C::LDS_BYTES,
                                 lds_set))
     return rc;
   if (CHUNK && !plan.pre_zeroed) {
@@ -1225,7 +1225,7 @@ int launch_flat_w8(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream)
   }
   const int slots = cu_count() / (8 * C::SLICES);  // row groups per XCD, one workgroup per CU
   const int n_slots = slots < 1 ? 1 : (slots > C::MAX_SLOTS ? C::MAX_SLOTS : slots);
-  k_decode_flat<B, DUAL, CHUNK, XI, true><<<dim3((unsigned)(8 * C::SLICES * n_slots)), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(d);
+  k_decode_flat<B, DUAL, CHUNK, XI><<<dim3((unsigned)(8 * C::SLICES * n_slots)), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(d);
   BLAST_LAUNCH_CHECK("k_decode_flat");
   return BLAST_OK;
 }
@@ -1238,7 +1238,7 @@ int launch_flat_w8(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream)
 // sixteen waves a single slot each.)
 template <int B, bool DUAL>
 bool flat_applies(const TileArgs& a, int64_t nnz, int64_t items, int64_t longest) {
-  return a.T <= 8 && items <= 512 && longest <= FlatCfg<B, DUAL, 1, true>::PM && a.kdim / B < (1 << 24) &&
+  return a.T <= 8 && items <= 512 && longest <= FlatCfg<B, DUAL, 1>::PM && a.kdim / B < (1 << 24) &&
          nnz * (B / 16) >= (int64_t)32 * cu_count();
 }
 

@@ -1,4 +1,4 @@
-// Decode kernel for large layers: the stored blocks of many short rows as one stream.
+// Decode kernel for large layers with one-byte (E5M2) weights: the stored blocks of many short rows as one stream.
 //
 // k_decode gives every (block row, 16-row slice) a workgroup of its own.  On a large, unevenly filled layer that is
 // thousands of workgroups most of which hold one to three blocks for four waves: each pays the chain of index loads,
@@ -14,7 +14,8 @@
 //    waits for another until the end;
 //  - the sums of a row (of one matrix) that a wave starts are left in an LDS entry of that row, the first sums of a
 //    piece that begins inside a row in an entry of the wave; after one barrier the entries of a row are added in the
-//    order of the stream, activated and stored.  No atomics: the sums do not depend on timing.
+//    order of the stream, activated and stored: the sums of a row do not depend on timing.  (With CHUNK a row is what the
+//    chunk plan made of one, and the chunks of a cut row meet through fp32 atomics.)
 // What bounds it (one-byte weights, 16384 x 53248 layer with Zipf rows, 5 tokens, timestamps of every workgroup): the
 // stream runs at 4.3 TB/s of weights, 13 us of the gate/up launch; 6 us pass before it starts (two trips for the rows,
 // the deal, a trip for the columns), and the workgroup that holds the fullest row (256 blocks of 163 on average) ends
@@ -28,9 +29,9 @@
 namespace blast_dev {
 
 // XI: copy instructions per activation tile, i.e. XI * 512 / B token rows.
-template <int B, bool DUAL, int XI, bool W8>
+template <int B, bool DUAL, int XI>
 struct FlatCfg {
-  using D = DecCfg<B, DUAL, 1, XI, false, W8>;
+  using D = DecCfg<B, DUAL, 1, XI, false, true>;
   static constexpr int NW = 16;
   static constexpr int SLICES = B / 16;
   static constexpr int MAX_SLOTS = 32 / SLICES;  // row groups per XCD of 32 CUs
@@ -58,10 +59,10 @@ __device__ __forceinline__ int lanes_scan(int v) {
   return v;
 }
 
-template <int B, bool DUAL, bool CHUNK, int XI, bool W8>
+template <int B, bool DUAL, bool CHUNK, int XI>
 __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
   static_assert(!(DUAL && CHUNK), "the activation needs complete sums: the gated product is never split");
-  using C = FlatCfg<B, DUAL, XI, W8>;
+  using C = FlatCfg<B, DUAL, XI>;
   using D = typename C::D;
   constexpr int KST = D::KST, NI = D::NI, NIX = D::NIX, NSLOT = C::NSLOT, NM = C::NM, NW = C::NW;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -177,13 +178,8 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
 #pragma unroll
   for (int ni = 0; ni < NI; ++ni) {
     const int p = ni * 64 + lane;
-    if (W8) {
-      const int r = p / D::CPRW8, s = p % D::CPRW8;
-      woff[ni] = (uint32_t)(q * D::SLW + r * B + ((s ^ D::key8(r)) << 4));
-    } else {
-      const int r = p / D::CPRW, s = p % D::CPRW;
-      woff[ni] = (uint32_t)(q * D::SLW + r * (B * 2) + ((s ^ D::key(r)) << 4));
-    }
+    const int r = p / D::CPRW8, s = p % D::CPRW8;
+    woff[ni] = (uint32_t)(q * D::SLW + r * B + ((s ^ D::key8(r)) << 4));
   }
 #pragma unroll
   for (int xi = 0; xi < NIX; ++xi) {
@@ -194,8 +190,7 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
   const int xrow = l16 % C::XR;
 #pragma unroll
   for (int s = 0; s < KST; ++s) {
-    foff[s] = W8 ? (uint32_t)(l16 * B + (((2 * s + (g >> 1)) ^ D::key8(l16)) << 4) + ((g & 1) << 3))
-                 : (uint32_t)(l16 * (B * 2) + (((4 * s + g) ^ D::key(l16)) << 4));
+    foff[s] = (uint32_t)(l16 * B + (((2 * s + (g >> 1)) ^ D::key8(l16)) << 4) + ((g & 1) << 3));
     fxoff[s] = (uint32_t)(xrow * (B * 2) + (((4 * s + g) ^ D::key(xrow)) << 4));
   }
 
@@ -252,8 +247,7 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
     auto issue = [&](int b) {
       const int k = BLAST_LANE(vk, b), c = BLAST_LANE(vc, b);
       const MatDev& m = (DUAL && (BLAST_LANE(vs, b) & 1)) ? a.m1 : a.m0;
-      const unsigned char* wblk = W8 ? m.vals8 + (int64_t)k * (B * B)
-                                     : reinterpret_cast<const unsigned char*>(m.vals) + (int64_t)k * (B * B * 2);
+      const unsigned char* wblk = m.vals8 + (int64_t)k * (B * B);
       const unsigned char* xcol = reinterpret_cast<const unsigned char*>(a.X) + (int64_t)c * (B * 2);
       unsigned char* dst = ring + (b % NSLOT) * D::SLOT;
 #pragma unroll
@@ -288,11 +282,7 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
       const unsigned char* st = ring + (b % NSLOT) * D::SLOT;
 #pragma unroll
       for (int s = 0; s < KST; ++s) {
-        bf16x8 wf;
-        if constexpr (W8)
-          wf = e5m2x8_to_bf16x8(*reinterpret_cast<const uint2*>(st + foff[s]));
-        else
-          wf = *reinterpret_cast<const bf16x8*>(st + foff[s]);
+        const bf16x8 wf = e5m2x8_to_bf16x8(*reinterpret_cast<const uint2*>(st + foff[s]));
         const bf16x8 xf = *reinterpret_cast<const bf16x8*>(st + D::SLW + fxoff[s]);
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, wf, acc, 0, 0, 0);
       }
