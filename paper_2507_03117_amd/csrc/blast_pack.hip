@@ -4,12 +4,13 @@
 // storage from which the product kernel derives its work).
 //
 // Everything runs on the device, on the caller's stream:
-//   score  -> one workgroup per block, 16-byte loads, fp64 sum of squares
+//   score  -> one wave per block, 16-byte loads, fp64 sum of squares
 //   select -> exact radix select on the fp64 bit patterns + index-ordered tie-break
 //   count  -> per block-row / block-column populations, exclusive scans
 //   fill   -> ordered compaction of column indices, gather of block values
 //   order  -> rank block rows by population (schedule for load balance)
 //   csc    -> column-grouped index of the same blocks (used by the fused MLP)
+// For matrices of up to a few thousand blocks, select is one workgroup and all that follows it one launch.
 #include "blast_common.h"
 
 namespace {
@@ -557,7 +558,7 @@ inline void plan_outputs(char* ab, const blast::AuxLayout& A, PlanOut& narrow, P
 // operations, and as a dozen dependent launches it costs a dozen launch latencies.  For at most kSmallN blocks
 // (and at most 1024 block rows and block columns) the selection is one workgroup and the rest one launch, in which a
 // workgroup makes the row arrays and another the column arrays: a thread owns `per` consecutive blocks in row-major
-// order; its keys stay in registers, positions and the per-line populations live in LDS.  The workgroup's 16 waves
+// order; the selection's keys, the positions and the per-line populations live in LDS.  The workgroup's 16 waves
 // share one compute unit, so what such a job costs is instructions per thread: no integer division per block, both
 // chunk plans' scans in one (two 16-bit counts in one word: no sum here exceeds kSmallN + 1024), barriers that do not
 // wait for global stores.
@@ -1248,13 +1249,14 @@ int launch_select_small(const double* scores, const double* scores1, int64_t n, 
 }
 
 // A small pinned buffer per host thread (allocated on first use and kept) through which numbers come back from the
-// device: a copy into pageable memory costs a call tens of microseconds more.  Kernels can store to it themselves.
+// device: a copy into pageable memory costs a call tens of microseconds more.  Kernels can store to it themselves, those
+// of every GPU the thread uses.
 // Null when it cannot be had.
 int* pinned_ints() {
   static thread_local int* pinned = nullptr;
   if (!pinned) {
     void* p = nullptr;
-    if (hipHostMalloc(&p, 64, hipHostMallocDefault) == hipSuccess) {
+    if (hipHostMalloc(&p, 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
       pinned = static_cast<int*>(p);
     } else {
       (void)hipGetLastError();
