@@ -167,7 +167,7 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
       t_pos[i] = pos;
     }
     if (lane == 0) *n_rows_at = __builtin_popcountll(mine);
-  } else if (wave == NW - 1 && a.z_blocks > 0) {
+  } else if (DUAL && wave == NW - 1 && a.z_blocks > 0) {
     // the side job (see DecArgs), dealt to the last waves while the first ones deal rows; a workgroup that is dealt no
     // row has its share of it all the same
     for (int ci = w; ci < a.z_blocks; ci += G) decode_zero_job<B, 64>(a, ci);
@@ -280,12 +280,18 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
         __builtin_amdgcn_s_waitcnt(BLAST_VMCNT(0));
       asm volatile("" ::: "memory");
       const unsigned char* st = ring + (b % NSLOT) * D::SLOT;
+      // every fragment of the block is on its way before the first is widened
+      uint2 wc[KST];
+      bf16x8 xf[KST];
 #pragma unroll
       for (int s = 0; s < KST; ++s) {
-        const bf16x8 wf = e5m2x8_to_bf16x8(*reinterpret_cast<const uint2*>(st + foff[s]));
-        const bf16x8 xf = *reinterpret_cast<const bf16x8*>(st + D::SLW + fxoff[s]);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, wf, acc, 0, 0, 0);
+        wc[s] = *reinterpret_cast<const uint2*>(st + foff[s]);
+        xf[s] = *reinterpret_cast<const bf16x8*>(st + D::SLW + fxoff[s]);
       }
+#pragma unroll
+      for (int s = 0; s < KST; ++s)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[s], e5m2x8_to_bf16x8(wc[s]), acc, 0, 0, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2 * KST, 0);
       asm volatile("" ::: "memory");
       if (next_seg != seg) {
         float* const e = head ? heads + wave * entry : entries + seg * entry;
