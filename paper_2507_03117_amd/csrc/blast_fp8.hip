@@ -75,6 +75,7 @@ int launch_fp8_stream(const Fp8Args& f, hipStream_t stream) {
   a.syi = 1;
   a.y_bf16 = f.y_bf16;
   a.y_fast = ((int64_t)256 * f.ldy * 4 + f.ldy * 4 < ((int64_t)1 << 31)) ? 1 : 0;
+  a.y_pairs = (f.ldy % 2 == 0 && blast::aligned(f.Y, f.y_bf16 ? 4 : 8)) ? 1 : 0;
   a.T = f.T;
   a.nbr = f.n_units / (B / 64);
   a.act = -1;

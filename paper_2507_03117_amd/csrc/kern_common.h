@@ -1,5 +1,7 @@
 // Device-side helpers shared by the product kernels.
 #pragma once
+#include <type_traits>
+
 #include "blast_common.h"
 
 namespace blast_dev {
@@ -30,6 +32,7 @@ struct TileArgs {
   int act;               // gated product: the activation of the gate; single matrix: < 0 none, else applied to the output
   int x_vec;             // 1: 16-byte loads of X are legal (sxk == 1, aligned)
   int y_fast;            // 1: syi == 1 and every byte offset inside a 256-token slab of Y fits 31 bits
+  int y_pairs;           // 1: two neighbouring rows of a token may be stored as one value (Y and syt aligned to two values)
   int x_grp16;           // 16-wide blocks only: X is stored in column groups of 16 features, [kdim/16][T][16]
   int y_grp16;           // ... and so is Y, [rows/16][T][16]
 };
@@ -45,6 +48,16 @@ __device__ __forceinline__ int ld_idx(const int* p, int i) {
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   const __bf16 h = static_cast<__bf16>(f);
   return __builtin_bit_cast(uint16_t, h);
+}
+
+// Stores a value of 2, 4 or 8 bytes (naturally aligned) through the L2 of this XCD to the memory side.  An output that no
+// later instruction of the launch reads gains nothing from staying in the L2, and what is dirty there when the launch
+// ends is written back before the next one may start: the output of a short launch then leaves while it still computes.
+template <class T>
+__device__ __forceinline__ void store_through(T* p, T v) {
+  using U = std::conditional_t<sizeof(T) == 2, uint16_t, std::conditional_t<sizeof(T) == 4, uint32_t, unsigned long long>>;
+  static_assert(sizeof(T) == sizeof(U), "two, four or eight bytes");
+  __hip_atomic_store(reinterpret_cast<U*>(p), __builtin_bit_cast(U, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ float apply_act(int act, float g) {

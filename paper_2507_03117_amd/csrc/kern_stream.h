@@ -38,7 +38,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 // instead of 64).
 // F8: both operands in E5M2, one byte per value.  A step is then as many BYTES deep as in bf16 (128-byte rows for
 // 128-wide blocks, 64 for 64-wide ones), twice the contraction, on the 64-deep matrix instruction.
-template <int B, int TW, int NW = 4, bool F8 = false>
+template <int B, int TW, int NW = 4, bool F8 = false, bool PAIRS = true>
 struct StreamCfg {
   static_assert(TW == 2 || TW == 4, "two or four waves along tokens");
   static_assert(NW == 4 || NW == 8, "four or eight waves");
@@ -80,6 +80,13 @@ struct StreamCfg {
   static constexpr int WG_PER_CU = (NW == 4 && 2 * LDS_BYTES <= 160 * 1024) ? 2 : 1;
   static constexpr int WAVES_PER_SIMD = WG_PER_CU * NW / 4;
   __device__ static __forceinline__ int key(int row) { return (row / KEY_DIV) % KEY_MOD; }
+  static constexpr bool PAIR = PAIRS && NI == 2;
+  // Which weight row of a wave's tile is column l32 of matrix tile ni: with two matrix tiles, neighbouring rows, so that a
+  // lane ends up with two neighbouring rows of a token and stores them together (see the epilogue).  Not with chunks,
+  // whose rows are added to by atomics: lanes side by side do better there (405B-class MLP, 2048 tokens: 718 / 737 us).
+  __device__ static __forceinline__ int row_of(int l32, int ni) { return PAIR ? 2 * l32 + ni : ni * 32 + l32; }
+  // The swizzle key of a weight row: that of the lane which reads it, key(l32).
+  __device__ static __forceinline__ int wkey(int row) { return key(PAIR ? row >> 1 : row); }
 };
 
 struct StreamArgs {
@@ -445,7 +452,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
   static_assert(!(DUAL && CHUNK), "the activation needs complete sums: the gated product is never split");
   static_assert(!POST || (!DUAL && !CHUNK), "an activation on the output needs complete sums of a single matrix");
   static_assert(!LONG || (DUAL && !CHUNK), "long rows are a matter of the gated product");
-  using C = StreamCfg<B, TW, NW, F8>;
+  using C = StreamCfg<B, TW, NW, F8, !CHUNK>;
   const TileArgs& a = sa.t;
   const int n_items = LONG    ? (long_chunks(sa.hdr) + long_chunks(sa.hdr1) + a.nbr) * a.ntt
                       : CHUNK ? ld_idx(sa.hdr, 0) * a.ntt
@@ -471,7 +478,8 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
 #pragma unroll
     for (int c = 0; c < C::CPF; ++c) frag_off[kk][c] = (((2 * C::CPF * kk + 2 * c + lh) ^ C::key(l32)) << 4);
   const int a_row0 = (tw * 64 + l32) * C::ROW_BYTES;         // + mi * 32 rows
-  const int b_row0 = (rw * C::WT_ROW + l32) * C::ROW_BYTES;  // + ni * 32 rows
+  const int b_row0 = (rw * C::WT_ROW + C::row_of(l32, 0)) * C::ROW_BYTES;  // + ni * kRowStep
+  constexpr int kRowStep = (C::PAIR ? 1 : 32) * C::ROW_BYTES;
 
   // ---- loader: issues the copies of one step into an LDS stage --------------------------
   // Every copy is addressed as (uniform 64-bit base) + (per-lane 32-bit byte offset).  The
@@ -483,7 +491,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
   for (int q = 0; q < C::WQ; ++q) {
     winstr[q] = (q * NW + wave) % C::W_INSTR;  // with fewer instructions than waves, waves duplicate each other
     const int row = winstr[q] * C::RPI + cp_rr;
-    woff[q] = (uint32_t)(row * B * C::EB + ((cp_slot ^ C::key(row)) << 4));
+    woff[q] = (uint32_t)(row * B * C::EB + ((cp_slot ^ C::wkey(row)) << 4));
   }
   int xoff_tile = -1;
   const uint32_t sxt32 = (uint32_t)a.sxt;
@@ -621,7 +629,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
 #pragma unroll
     for (int mi = 0; mi < C::MI; ++mi) f.x[mi] = read_operand(st + C::W_BYTES + a_row0 + mi * 32 * C::ROW_BYTES, kk);
 #pragma unroll
-    for (int ni = 0; ni < C::NI; ++ni) f.w[ni] = read_operand(st + b_row0 + ni * 32 * C::ROW_BYTES, kk);
+    for (int ni = 0; ni < C::NI; ++ni) f.w[ni] = read_operand(st + b_row0 + ni * kRowStep, kk);
   };
   auto mma = [&](f32x16 (&acc)[C::MI][C::NI], const Frag& f) {
 #pragma unroll
@@ -771,7 +779,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
         const int tokb = t0 + tw * 64 + 4 * lh;
 #pragma unroll
         for (int ni = 0; ni < C::NI; ++ni) {
-          float* p0 = S + (int64_t)tokb * B + rw * C::WT_ROW + ni * 32 + l32;
+          float* p0 = S + (int64_t)tokb * B + rw * C::WT_ROW + C::row_of(l32, ni);
 #pragma unroll
           for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
@@ -836,8 +844,8 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
       }
     }
 
-    // Result layout: lane -> weight row l32 (+32 ni), register j -> token 8*(j/4) + 4*lh + j%4 (+32 mi).
-    // A store instruction therefore writes 32 consecutive rows of one token: full 64/128-byte segments.
+    // Result layout: lane -> weight row row_of(l32, ni), register j -> token 8*(j/4) + 4*lh + j%4 (+32 mi).
+    // A store instruction therefore writes 64 consecutive rows of two tokens (or 32 of them): whole 128-byte lines.
     // Tokens of this wave that exist: its tile is stored whole, in part or not at all, whatever its neighbours' are.
     const int left = a.T - (t0 + tw * 64);
     if (left <= 0) continue;
@@ -846,48 +854,82 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
     // per item and a 32-bit lane offset per store, so that a stored value costs a conversion, an add and the store
     // instead of 64-bit address arithmetic; in a tile that the tokens end in, a comparison as well.  (A tile of 40 of
     // 64 tokens on the general path below: 2 us after everyone else.  1024 x 1024 in E5M2, 200 tokens: 8.2 -> 6.2 us.)
+    // Two neighbouring rows of a token leave as one value where Y allows it: half the store instructions (53248 x 16384 in
+    // E5M2, 1000 tokens, with the quantiser: 95 -> 93 us; the others within 1 %).
+    // How the output leaves, by what was measured (microseconds, ordinary / through the L2 / non-temporal; repeated calls,
+    // then calls on inputs and outputs that no cache holds):
+    //   64-wide blocks and narrower: through.  1B-shaped MLP, 2048 tokens 44.8 / 42.5 / 44.8, cold 66.7 / 64.8 / 65.6; 512
+    //     tokens 27.3 / 26.1 / 26.7; two-matrix MLP of 1600 and 6400 features, 333 tokens 29.2 / 28.6; 3B-shaped MLP at
+    //     70 %, 4096 tokens 249 / 247 / 251; E5M2, 8192 x 3072 at 80 %, 700 tokens 19.1 / 18.4 / 18.6.
+    //   128-wide blocks in bf16: ordinary (405B-class MLP, 2048 tokens: 715 / 722 / 751).
+    //   128-wide blocks in E5M2: non-temporal.  The output is the larger part of what moves, and the last-level cache keeps
+    //     the inputs instead of it: 53248 x 16384, 1000 tokens, with the quantiser 95 / 93 / 78, cold 111 / 109 / 114; 2048
+    //     tokens, fp32 output 210 / 213 / 200; 14336 x 4096 at 80 %, 2048 tokens 43.8 / 41.7 / 40.7, cold 65 / 63.5 / 61.6.
+    enum { kStoreOrdinary, kStoreThrough, kStoreStreaming };
+    constexpr int kStores = B < 128 ? kStoreThrough : F8 ? kStoreStreaming : kStoreOrdinary;
     if (a.y_fast && !(CHUNK && shared_row)) {
       const uint32_t esz = a.y_bf16 ? 2u : 4u;
       unsigned char* base = reinterpret_cast<unsigned char*>(a.Y) + (int64_t)t0 * a.syt * esz;
       const int lane_left = left - 4 * lh;
-      auto store_tile = [&](auto bf16, auto whole) {
-        constexpr uint32_t kEsz = bf16.value ? 2u : 4u;
+      typedef __bf16 Bf16Pair __attribute__((ext_vector_type(2)));
+      typedef float F32Pair __attribute__((ext_vector_type(2)));
+      auto put_at = [](auto* p, auto v) {
+        if constexpr (kStores == kStoreStreaming)
+          __builtin_nontemporal_store(v, p);
+        else if constexpr (kStores == kStoreThrough)
+          store_through(p, v);
+        else
+          *p = v;
+      };
+      auto store_tile = [&](auto bf16, auto whole, auto pairs) {
+        constexpr uint32_t kEsz = bf16.value ? 2u : 4u, kStep = C::PAIR ? 1u : 32u;
         uint32_t pitch = (uint32_t)a.syt * kEsz;
         // opaque to the optimiser: otherwise the 32 multiples of the pitch are computed once before the
         // loop over items and kept (spilled) for the whole kernel
         asm volatile("" : "+s"(pitch));
-        uint32_t off0[C::NI];
-#pragma unroll
-        for (int ni = 0; ni < C::NI; ++ni)
-          off0[ni] = (uint32_t)(r * B + rw * C::WT_ROW + ni * 32 + l32) * kEsz + (uint32_t)(tw * 64 + 4 * lh) * pitch;
+        const uint32_t off0 = (uint32_t)(r * B + rw * C::WT_ROW + C::row_of(l32, 0)) * kEsz + (uint32_t)(tw * 64 + 4 * lh) * pitch;
 #pragma unroll
         for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int dt = mi * 32 + 8 * (j / 4) + (j % 4);
             // the token step goes into the uniform base, the lane offset stays one register
-            unsigned char* bj = base + __builtin_amdgcn_readfirstlane((uint32_t)dt * pitch);
+            unsigned char* p = base + __builtin_amdgcn_readfirstlane((uint32_t)dt * pitch) + off0;
             if (whole.value || dt < lane_left) {
-#pragma unroll
-              for (int ni = 0; ni < C::NI; ++ni) {
+              if constexpr (C::PAIR && pairs.value) {
                 if constexpr (bf16.value)
-                  *reinterpret_cast<uint16_t*>(bj + off0[ni]) = f32_to_bf16_rne(acc0[mi][ni][j]);
+                  put_at(reinterpret_cast<Bf16Pair*>(p),
+                         Bf16Pair{static_cast<__bf16>(acc0[mi][0][j]), static_cast<__bf16>(acc0[mi][1][j])});
                 else
-                  *reinterpret_cast<float*>(bj + off0[ni]) = acc0[mi][ni][j];
+                  put_at(reinterpret_cast<F32Pair*>(p), F32Pair{acc0[mi][0][j], acc0[mi][1][j]});
+              } else {
+#pragma unroll
+                for (int ni = 0; ni < C::NI; ++ni) {
+                  if constexpr (bf16.value)
+                    put_at(reinterpret_cast<uint16_t*>(p + ni * kStep * kEsz), f32_to_bf16_rne(acc0[mi][ni][j]));
+                  else
+                    put_at(reinterpret_cast<float*>(p + ni * kStep * kEsz), acc0[mi][ni][j]);
+                }
               }
             }
           }
       };
+      auto store = [&](auto bf16, auto whole) {
+        if (C::PAIR && a.y_pairs)
+          store_tile(bf16, whole, std::true_type{});
+        else
+          store_tile(bf16, whole, std::false_type{});
+      };
       if (a.y_bf16) {
         if (full)
-          store_tile(std::true_type{}, std::true_type{});
+          store(std::true_type{}, std::true_type{});
         else
-          store_tile(std::true_type{}, std::false_type{});
+          store(std::true_type{}, std::false_type{});
       } else {
         if (full)
-          store_tile(std::false_type{}, std::true_type{});
+          store(std::false_type{}, std::true_type{});
         else
-          store_tile(std::false_type{}, std::false_type{});
+          store(std::false_type{}, std::false_type{});
       }
       continue;
     }
@@ -903,7 +945,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
     const int64_t tok_pitch = a.syt * esz;
 #pragma unroll
     for (int ni = 0; ni < C::NI; ++ni) {
-      const int64_t row = (int64_t)r * B + rw * C::WT_ROW + ni * 32 + l32;
+      const int64_t row = (int64_t)r * B + rw * C::WT_ROW + C::row_of(l32, ni);
       const int tokb = t0 + tw * 64 + 4 * lh;
       unsigned char* p0 = reinterpret_cast<unsigned char*>(a.Y) + (row * a.syi + (int64_t)tokb * a.syt) * esz;
 #pragma unroll

@@ -471,6 +471,35 @@ def test_spmm_strided_operands(api, b, T):
     assert (yh[:, :8] == -3.0).all() and (yh[:, 8 + nbr * b:] == -3.0).all()
 
 
+@pytest.mark.parametrize("path", ["bf16", "e5m2"])
+@pytest.mark.parametrize("b,nbr,nbc,T", [(128, 4, 6, 300), (128, 128, 2, 1100), (64, 40, 3, 3400), (64, 5, 3, 200)])
+@pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
+def test_spmm_output_alignment(api, path, b, nbr, nbc, T, out_dtype):
+    """Outputs whose rows may be stored two at a time (even pitch, aligned) and outputs whose rows may not (odd pitch, a
+    first column that is not aligned to two values): the same bits, and what lies beside the output untouched.  The aligned
+    one against the oracle; sizes on both sides of the choice of tiles, tokens that end inside a tile."""
+    import torch
+
+    w, mask, x = synth.small_case(5100 + b + T, nbr * b, nbc * b, b, 0.5, T, empty_rows=(2,))
+    dev, ref = pack_both(api, w, b, mask=mask)
+    dt, n = (torch.float32 if out_dtype == "f32" else torch.bfloat16), nbr * b
+    if path == "e5m2":
+        w8, x8 = api.quantize_e5m2(dev.vals), api.quantize_e5m2_groups(to_dev(x))
+        run = lambda out: api.bsr_spmm_e5m2(dev, w8, x8, layout=api.COLUMN_GROUPS_64, out_dtype=dt, out=out)
+    else:
+        run = lambda out: api.bsr_spmm(dev, to_dev(x), out_dtype=dt, out=out)
+    whole = run(None)
+    for pitch, first in ((n + 3, 0), (n + 3, 1), (n + 4, 1)):
+        buf = torch.full((T, pitch), -3.0, dtype=dt, device="cuda:0")
+        run(buf[:, first:first + n])
+        torch.cuda.synchronize()
+        assert torch.equal(buf[:, first:first + n], whole)
+        assert (buf[:, :first] == -3.0).all() and (buf[:, first + n:] == -3.0).all()
+    if path == "bf16" and out_dtype == "f32":
+        some = slice(max(0, T - 70), T)  # the tile that the tokens end in
+        check_close(whole[some].cpu().numpy().T, orc.spmm(ref, x[some]), f"aligned b={b} T={T}")
+
+
 @pytest.mark.parametrize("b,nbc,T", [(32, 70, 300), (64, 40, 520), (128, 36, 200), (64, 72, 300),
                                      (32, 70, 9), (32, 70, 40), (64, 72, 1), (64, 72, 7), (64, 72, 16), (64, 72, 100), (128, 66, 3), (128, 66, 20),
                                      # rows long enough for the decode kernel to take the chunk plan as well
