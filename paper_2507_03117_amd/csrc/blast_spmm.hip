@@ -64,14 +64,14 @@ int launch_tile(TileArgs a, hipStream_t stream) {
 // operands straight from global memory.  A wave takes 16, 32 or 64 tokens of one block row.
 int cu_count();
 
-template <bool DUAL, bool POST, int NS, bool SPLIT, int NW = 4>
+template <bool DUAL, bool POST, int NS, bool SPLIT, int NW = 4, bool GROUPED = false>
 int launch_b16_ns(TileArgs a, int y_vec, hipStream_t stream) {
   a.ntt = (a.T + 16 * NS - 1) / (16 * NS);
   const int64_t items = (int64_t)a.ntt * a.nbr;
   const int64_t grid = SPLIT ? items : (items + 3) / 4;
   if (grid <= 0) return BLAST_OK;
   if (grid > INT32_MAX) return BLAST_ERR_INVALID_ARG;
-  k_spmm_b16<DUAL, POST, NS, SPLIT, NW><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(a, y_vec);
+  k_spmm_b16<DUAL, POST, NS, SPLIT, NW, GROUPED><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(a, y_vec);
   BLAST_LAUNCH_CHECK("k_spmm_b16");
   return BLAST_OK;
 }
@@ -87,7 +87,13 @@ int launch_b16_t(const TileArgs& a, int64_t nnz, int y_vec, hipStream_t stream) 
     return launch_b16_ns<DUAL, POST, 1, true>(a, y_vec, stream);
   }
   if (a.T <= 32) return launch_b16_ns<DUAL, POST, 2, true>(a, y_vec, stream);
-  if ((int64_t)((a.T + 63) / 64) * a.nbr < 8 * cu_count()) return launch_b16_ns<DUAL, POST, 4, true>(a, y_vec, stream);
+  const bool split = (int64_t)((a.T + 63) / 64) * a.nbr < 8 * cu_count();
+  // (column groups that 32-bit byte offsets reach, a wave's 64 tokens past the end included)
+  if (a.x_grp16 && ((int64_t)a.kdim / 16 * a.T + 64) * 32 < ((int64_t)1 << 32)) {
+    if (split) return launch_b16_ns<DUAL, POST, 4, true, 4, true>(a, y_vec, stream);
+    return launch_b16_ns<DUAL, POST, 4, false, 4, true>(a, y_vec, stream);
+  }
+  if (split) return launch_b16_ns<DUAL, POST, 4, true>(a, y_vec, stream);
   return launch_b16_ns<DUAL, POST, 4, false>(a, y_vec, stream);
 }
 

@@ -78,6 +78,94 @@ __device__ __forceinline__ void b16_row(const TileArgs& a, const MatDev& m, int 
   }
 }
 
+// ---- activations in column groups of 16 features ---------------------------------------------------------------------
+// There a fragment of 16 tokens is 512 consecutive bytes, and those of the wave's next tokens follow it: both operands are
+// addressed as (descriptor, one 32-bit offset per lane, an immediate), which leaves the registers to the operands of
+// several pairs and takes a column's 64-bit product off every pair.  Reads past the row's values (a row with an odd number
+// of blocks) and past the last group return zeros; tokens past T of an inner group are those of the next group and are
+// never stored.  1B-shaped MLP with 16-wide blocks at 90 %, microseconds a pass, before / now: 64 tokens 17.2 / 15.8, 128
+// 18.4 / 16.9, 1000 49.2 / 42.5, 2048 79.2 / 71.8; at 500, where all waves are resident at once and the three launches'
+// start-up is half of it, 29.0 / 28.4.  (Three or four pairs on their way instead of two: 43.0 and 43.5 at 1000.)
+struct B16Row {
+  int n;                            // pairs of this wave
+  int cols;                         // lane 2 i + h: block column of block h of the wave's i-th pair, i < 32
+  int k0, ke, pair0, pstride;
+  __amdgpu_buffer_rsrc_t w;         // the values of the row's blocks
+};
+
+// Columns of up to 32 pairs from the wave's pair `first` on (a row that ends with a single block repeats it).
+__device__ __forceinline__ int b16_cols(const MatDev& m, const B16Row& q, int first) {
+  const int lane = threadIdx.x & 63;
+  const int kp = q.k0 + 2 * (q.pair0 + (first + (lane >> 1)) * q.pstride), blk = kp + (lane & 1);
+  return kp < q.ke ? m.col_idx[blk < q.ke ? blk : kp] : 0;
+}
+
+__device__ __forceinline__ B16Row b16_begin(const MatDev& m, int r, int pair0, int pstride) {
+  B16Row q;
+  q.k0 = ld_idx(m.row_ptr, r);
+  q.ke = ld_idx(m.row_ptr, r + 1);
+  q.pair0 = pair0;
+  q.pstride = pstride;
+  const int pairs = (q.ke - q.k0 + 1) >> 1;
+  q.n = pairs > pair0 ? (pairs - pair0 + pstride - 1) / pstride : 0;
+  q.cols = b16_cols(m, q, 0);
+  q.w = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(m.vals) + (int64_t)q.k0 * 256, 0, (q.ke - q.k0) * 512, 0x00027000);
+  return q;
+}
+
+// The wave's pairs of a block row: DEPTH of them are on their way while one is multiplied.  x_off: byte offset of this
+// lane's token row and half in a column group, group_bytes: from one group to the next.
+template <int NS>
+__device__ __forceinline__ void b16_walk(const MatDev& m, B16Row& q, __amdgpu_buffer_rsrc_t x, uint32_t x_off,
+                                         uint32_t group_bytes, f32x4_b16 (&acc)[NS]) {
+  constexpr int DEPTH = 2;  // (a wave takes some seven pairs of a row)
+  const int lane = threadIdx.x & 63;
+  const int w_off = (lane >> 5) * 512 + (lane & 15) * 32 + ((lane >> 4) & 1) * 16;
+  auto multiply = [&](const B16Frag<NS>& f) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s) acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.w, f.x[s], acc[s], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);  // the loads that take these registers stay behind: no second set of them
+  };
+#pragma unroll 1
+  for (int done = 0; done < q.n; done += 32) {
+    if (done > 0) q.cols = b16_cols(m, q, done);
+    const int n = q.n - done < 32 ? q.n - done : 32;
+    B16Frag<NS> f[DEPTH];
+    auto load = [&](int i, B16Frag<NS>& d) {
+      const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane(q.cols, 2 * i) * group_bytes;
+      const uint32_t c1 = (uint32_t)__builtin_amdgcn_readlane(q.cols, 2 * i + 1) * group_bytes;
+      const uint32_t off = x_off + (lane < 32 ? c0 : c1);
+      d.w = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                           q.w, w_off + (q.pair0 + (done + i) * q.pstride) * 1024, 0, 0));
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        d.x[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(x, off + s * 512, 0, 0));
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u)
+      if (u < n) load(u, f[u]);
+    int i = 0;
+    // nothing is decided per pair while a whole round of loads lies ahead
+#pragma unroll 1
+    for (; i + 2 * DEPTH <= n; i += DEPTH) {
+#pragma unroll
+      for (int u = 0; u < DEPTH; ++u) {
+        multiply(f[u]);
+        load(i + u + DEPTH, f[u]);
+      }
+    }
+#pragma unroll 1
+    for (; i < n; i += DEPTH) {
+#pragma unroll
+      for (int u = 0; u < DEPTH; ++u) {
+        if (i + u < n) multiply(f[u]);
+        if (i + u + DEPTH < n) load(i + u + DEPTH, f[u]);
+      }
+    }
+  }
+}
+
 // Adds the waves' partial sums; every wave calls it, wave 0 returns with the totals (added in wave order).
 template <int NS, int NW>
 __device__ __forceinline__ void b16_join(f32x4_b16 (&acc)[NS]) {
@@ -103,8 +191,8 @@ __device__ __forceinline__ void b16_join(f32x4_b16 (&acc)[NS]) {
 // SPLIT (decode token counts): the whole workgroup owns one (block row, token tile), its NW waves (4 or 16) deal
 // the row's pairs among themselves and the partial sums meet in LDS - there are too few rows to fill the chip
 // with a wave each, and a row walked by one wave is a chain of dependent loads.
-template <bool DUAL, bool POST, int NS, bool SPLIT = false, int NW = 4>
-__global__ __launch_bounds__(NW * 64) void k_spmm_b16(const TileArgs a, const int y_vec) {
+template <bool DUAL, bool POST, int NS, bool SPLIT = false, int NW = 4, bool GROUPED = false>
+__global__ __launch_bounds__(NW * 64, GROUPED ? 4 : 1) void k_spmm_b16(const TileArgs a, const int y_vec) {
   static_assert(SPLIT || NW == 4, "without SPLIT a workgroup is four independent waves");
   static_assert(!(POST && DUAL), "an activation on the output belongs to the single-matrix product");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -126,12 +214,25 @@ __global__ __launch_bounds__(NW * 64) void k_spmm_b16(const TileArgs a, const in
   f32x4_b16 acc0[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) acc0[s] = f32x4_b16{0.f, 0.f, 0.f, 0.f};
-  b16_row<NS>(a, a.m0, r, xrow, cstride, acc0, SPLIT ? wave : 0, SPLIT ? NW : 1);
-  if (DUAL) {
-    f32x4_b16 acc1[NS];
+  f32x4_b16 acc1[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) acc1[s] = f32x4_b16{0.f, 0.f, 0.f, 0.f};
-    b16_row<NS>(a, a.m1, r, xrow, cstride, acc1, SPLIT ? wave : 0, SPLIT ? NW : 1);
+  for (int s = 0; s < NS; ++s) acc1[s] = f32x4_b16{0.f, 0.f, 0.f, 0.f};
+  const int pair0 = SPLIT ? __builtin_amdgcn_readfirstlane(wave) : 0, pstride = SPLIT ? NW : 1;
+  if constexpr (GROUPED) {
+    const uint32_t group_bytes = (uint32_t)a.T * 32u;
+    const uint32_t x_off = (uint32_t)(t0 + (lane & 15)) * 32u + ((lane >> 4) & 1) * 16u;
+    const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(a.X), 0, (int)((uint32_t)(a.kdim >> 4) * group_bytes), 0x00027000);
+    const int ru = __builtin_amdgcn_readfirstlane(r);
+    B16Row q0 = b16_begin(a.m0, ru, pair0, pstride), q1{};
+    if (DUAL) q1 = b16_begin(a.m1, ru, pair0, pstride);
+    b16_walk<NS>(a.m0, q0, x, x_off, group_bytes, acc0);
+    if (DUAL) b16_walk<NS>(a.m1, q1, x, x_off, group_bytes, acc1);
+  } else {
+    b16_row<NS>(a, a.m0, r, xrow, cstride, acc0, pair0, pstride);
+    if (DUAL) b16_row<NS>(a, a.m1, r, xrow, cstride, acc1, pair0, pstride);
+  }
+  if (DUAL) {
     if (SPLIT) b16_join<NS, NW>(acc1);
     if (SPLIT) __syncthreads();  // the buffer is used again for the first matrix
     if (SPLIT) b16_join<NS, NW>(acc0);
@@ -163,7 +264,7 @@ __global__ __launch_bounds__(NW * 64) void k_spmm_b16(const TileArgs a, const in
         uint2 v;
         v.x = (uint32_t)f32_to_bf16_rne(acc0[s][0]) | ((uint32_t)f32_to_bf16_rne(acc0[s][1]) << 16);
         v.y = (uint32_t)f32_to_bf16_rne(acc0[s][2]) | ((uint32_t)f32_to_bf16_rne(acc0[s][3]) << 16);
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.Y) + off) = v;
+        store_through(reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.Y) + off), v);
       } else {
         *reinterpret_cast<f32x4_b16*>(reinterpret_cast<float*>(a.Y) + off) = acc0[s];
       }

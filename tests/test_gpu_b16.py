@@ -95,6 +95,31 @@ def test_long_rows_at_decode_token_counts(api, T, gated):
     assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -7 + 1e-5 * np.sqrt((want ** 2).mean())).all()
 
 
+@pytest.mark.parametrize("nbc,T", [(300, 40), (80, 9700)])
+@pytest.mark.parametrize("gated", [False, True])
+def test_rows_longer_than_a_waves_column_register(api, nbc, T, gated):
+    """A wave keeps the columns of 32 pairs at a time: rows on both sides of that, dealt to four waves (few tokens) and
+    walked by one (many), with odd and even ends; the tokens end inside a wave's tile.  Some tokens against the oracle."""
+    import torch
+
+    rng = np.random.default_rng(1670 + T)
+    counts = [nbc, 0, nbc - 1, 64, 65, 66, 63, 128 % nbc, 129 % nbc, 3, 4, 5, 1, 2]
+    w = [synth.gauss_bf16(rng, (len(counts) * B, nbc * B), 0.02) for _ in range(2)]
+    x = synth.gauss_bf16(rng, (T, nbc * B), 1.0)
+    (dev, ref), (dev2, ref2) = (_pack(api, m, _rows_with_counts(rng, c, nbc)) for m, c in zip(w, (counts, counts[::-1])))
+    some = np.unique(np.concatenate([np.arange(0, T, max(T // 23, 1)), np.arange(max(T - 70, 0), T)]))
+    if not gated:
+        y = api.bsr_spmm(dev, to_dev(x), out=torch.full((T, len(counts) * B), float("nan"), device="cuda:0"))
+        torch.cuda.synchronize()
+        check_close(y.cpu().numpy()[some].T, orc.spmm(ref, x[some]), f"b=16 nbc={nbc} T={T}")
+        return
+    wd = synth.gauss_bf16(rng, (nbc * B, len(counts) * B), 0.05)
+    down, refd = _pack(api, wd, synth.uniform_mask(rng, nbc, len(counts), 0.5))
+    y = api.sparse_mlp(dev, dev2, down, to_dev(x))  # the intermediate stays in column groups
+    torch.cuda.synchronize()
+    check_close(y.cpu().numpy()[some].T, orc.mlp(ref, ref2, refd, x[some]), f"b=16 MLP nbc={nbc} T={T}")
+
+
 @pytest.mark.parametrize("T", [5, 40, 130])
 def test_spmm_strided_and_unaligned_operands(api, T):
     """Outputs whose row pitch or address rules out the 16-byte stores take the element-wise stores of the same
