@@ -20,6 +20,7 @@
 #include "kern_decode.h"
 #include "kern_flat.h"
 #include "kern_b16.h"
+#include "kern_split.h"
 
 using namespace blast_dev;
 
@@ -310,6 +311,24 @@ int launch_stream(const TileArgs& a, const ChunkPlan& plan, int64_t k_features, 
   return launch_stream_c<B, DUAL, false>(a, side, k_features, stream);
 }
 
+// Few output tiles: a workgroup per (64 rows of a block row, 64 tokens), see kern_split.h.
+template <int B>
+int launch_split(const TileArgs& a, hipStream_t stream) {
+  using C = SplitCfg<B>;
+  const int64_t units = (int64_t)a.nbr * C::SUB, groups = (a.T + C::SB - 1) / C::SB;
+  const int64_t grid = (units + 7) / 8 * 8 * groups;
+  if (grid <= 0) return BLAST_OK;
+  if (grid > INT32_MAX) return BLAST_ERR_INVALID_ARG;
+  auto launch = [&](auto post) {
+    static blast::DeviceFlags lds_set;
+    if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_spmm_split<B, post.value>), C::LDS_BYTES, lds_set)) return rc;
+    k_spmm_split<B, post.value><<<dim3((unsigned)grid), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(a, (int)units, (int)groups);
+    BLAST_LAUNCH_CHECK("k_spmm_split");
+    return (int)BLAST_OK;
+  };
+  return a.act >= 0 ? launch(std::true_type{}) : launch(std::false_type{});
+}
+
 template <int B, bool DUAL, int NTT, bool CHUNK, int XSMALL = 0>
 int launch_decode_ntt(const TileArgs& a, const ChunkPlan& plan, hipStream_t stream) {
   DecArgs d{};
@@ -445,11 +464,41 @@ bool decode_applies(int b, const TileArgs& a, int64_t nnz, int64_t max_row_block
   return reread <= kDecodeMaxRereadBytes;
 }
 
+// Whether a single product is better off on k_spmm_split (64 x 64 tiles, a row's blocks dealt to eight waves) than on the
+// kernel that would take it otherwise.  Microseconds, other kernel / split, uniform masks, bf16 output, graph replay:
+//   streaming (it walks a row in sequence, and leaves CUs idle while its tiles are fewer than those): b = 64, 25 rows of 20
+//     blocks, 384 / 512 / 768 tokens 17.0 / 10.6, 16.9 / 11.1, 17.4 / 15.5; 32 rows of 13, 384 / 768 / 1024 tokens 13.5 / 9.2,
+//     14.5 / 13.9, 14.5 / 15.6; 32 rows of 3, 512 / 768 tokens 6.6 / 5.2, 7.7 / 8.1; 100 rows of 5, 384 tokens 10.5 / 12.7.
+//     b = 128, 16 rows of 6.4, 384 / 768 / 1024 tokens 17.6 / 9.4, 17.7 / 13.2, 17.9 / 15.0; 32 rows of 3.2, 512 / 768 tokens
+//     14.3 / 11.2, 15.1 / 15.0.  So the line: 1.25 tiles per CU with 64-wide blocks, two with 128-wide ones.
+//   decode (33 to 256 tokens; it reads the matrix once per 32 tokens, in many small workgroups): b = 64, 100 rows of 5, 64 /
+//     100 / 160 / 256 tokens 5.2 / 5.4, 7.7 / 5.5, 9.4 / 7.6, 13.6 / 8.8; 32 rows of 13, 128 / 256 tokens 7.3 / 7.4, 10.0 / 8.4;
+//     25 rows of 20, 160 / 256 tokens 7.7 / 9.7, 9.9 / 9.9.  b = 128, 32 rows of 3.2, 64 / 100 / 256 tokens 4.1 / 5.9, 7.0 / 6.1,
+//     13.0 / 7.7.  The two estimates below follow these figures to about 1.5 us.
+// (Two-matrix MLP of 1600 and 6400 features at 80 %: 128 tokens 18.5 -> 14.8, 333 28.8 -> 22.8, 512 28.3 -> 22.9.)
+bool split_applies(int b, const TileArgs& a, int64_t nnz, bool decode) {
+  if ((b != 64 && b != 128) || a.T <= kDecodeAlwaysTokens) return false;
+  const int64_t cus = cu_count(), tiles = (int64_t)a.nbr * (b / 64) * ((a.T + 63) / 64);
+  if (!decode) return tiles * 4 <= (b == 64 ? 5 : 8) * cus;
+  if (tiles > 2 * cus) return false;
+  const double groups = (double)((a.T + 31) / 32), per_wave = (double)nnz / a.nbr * (b / 64) / 8.0;
+  const double stages = per_wave > 0.6 ? per_wave : 0.6;
+  const double decode_us = 3.0 + 0.2e-6 * nnz * b * b * 2 * groups + (double)a.nbr * (b / 16) * groups / 850.0;
+  const double split_us = (tiles > cus ? 7.0 : 4.0) + stages * (1.3 + (double)tiles / cus);
+  return decode_us > split_us + 0.55;
+}
+
 template <bool DUAL>
 int dispatch_tile(int b, const TileArgs& a, int64_t nnz, hipStream_t stream, const ChunkPlan& plan = ChunkPlan{}) {
   // the streaming kernel addresses activations with 32-bit byte offsets inside one column block
   const bool small_x = (int64_t)a.T * a.sxt * 2 < ((int64_t)1 << 32);
-  if (a.x_vec && a.T > 0 && small_x && decode_applies<DUAL>(b, a, nnz, plan.max_row_blocks)) {
+  const bool decode = a.x_vec && a.T > 0 && small_x && decode_applies<DUAL>(b, a, nnz, plan.max_row_blocks);
+  if constexpr (!DUAL) {
+    // (not where rows are cut into chunks, nor where this launch is to clear another one's)
+    if (a.x_vec && small_x && !plan.hdr && !plan.zero_job && split_applies(b, a, nnz, decode))
+      return b == 64 ? launch_split<64>(a, stream) : launch_split<128>(a, stream);
+  }
+  if (decode) {
     // The decode kernel already spreads a block row over b/16 workgroups of four waves each, so a row of n
     // blocks is n/4 block steps deep.  Chunks (a zero-fill launch plus atomics, about 8 us on the 405B-class
     // gate matrix) only pay when that depth exceeds four times the average load of a workgroup slot

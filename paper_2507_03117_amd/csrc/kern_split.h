@@ -1,0 +1,157 @@
+// Product kernel for few output tiles: a few hundred tokens, few block rows (token-major, 16-byte aligned activations).
+//
+// The streaming kernel gives an output tile to one workgroup, which walks the block row in sequence; with fewer tiles
+// than CUs that chain is the whole launch while most of the chip has nothing to do.  Here a workgroup of eight waves
+// shares a tile of 64 rows x 64 tokens by the contraction: the row's stages (64 contraction indices, whole 128-byte lines
+// of a block and of the activations) are dealt to the waves, each accumulates the whole tile from copies of its own, and
+// the eight partial sums meet in LDS, added in wave order.  No barrier before that.
+//  - A wave owns one 16 KiB stage in LDS.  Its fragments go to registers as soon as it has landed (64 of them), so that
+//    the next stage is copied over it while they are multiplied: eight stages are in flight per CU, and one workgroup
+//    fits a CU, which is what there is work for.
+//  - Rows of a wave's tile alternate between the two matrix tiles, so that a lane ends up with two neighbouring rows of a
+//    token, as in the streaming kernel.
+// What bounds it: a tile asks the L1 for a byte per 32 flop, half the matrix peak at 64 bytes a clock; at these sizes the
+// chain (indices, one trip per stage, the sums in LDS) is most of the launch.
+#pragma once
+#include "kern_common.h"
+#include "kern_stream.h"
+
+namespace blast_dev {
+
+template <int B>
+struct SplitCfg {
+  static_assert(B == 64 || B == 128, "a stage is a whole 128-byte line deep");
+  static constexpr int NW = 8;
+  static constexpr int SB = 64;               // rows and tokens of the tile
+  static constexpr int SUB = B / SB;          // tiles per block row
+  static constexpr int KSL = B / 64;          // stages per stored block
+  static constexpr int TILE = SB * 128;       // bytes of one operand of a stage
+  static constexpr int NI = TILE / 1024;      // wave-wide copy instructions per operand
+  static constexpr int STAGE = 2 * TILE;
+  static constexpr size_t LDS_BYTES = (size_t)NW * STAGE;  // (the partial sums are as large)
+  static_assert(sizeof(float) * 64 * 64 == STAGE, "a wave's sums go over its stage");
+};
+
+template <int B, bool POST>
+__global__ __launch_bounds__(512, 2) void k_spmm_split(const TileArgs a, const int n_units, const int groups) {
+  using C = SplitCfg<B>;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  // the token tiles of a unit are 8 workgroup ids apart: one XCD, whose L2 serves the weights to all of them
+  const int blk = blockIdx.x, span = 8 * groups, rem = blk % span;
+  const int unit = (blk / span) * 8 + (rem & 7);
+  if (unit >= n_units) return;  // whole workgroup, before any barrier
+  const int t0 = (rem >> 3) * C::SB;
+  const int rank = unit / C::SUB, si = unit % C::SUB;
+  const int r = a.row_order ? ld_idx(a.row_order, rank) : rank;
+  const int kb = ld_idx(a.m0.row_ptr, r);
+  const int stages = (ld_idx(a.m0.row_ptr, r + 1) - kb) * C::KSL;
+  const int mine = stages > wave ? (stages - wave + C::NW - 1) / C::NW : 0;
+  unsigned char* slot = smem + wave * C::STAGE;
+
+  // Copy side: instruction q of an operand writes LDS bytes [q * 1024 + lane * 16, +16): tile row q * 8 + lane / 8, chunk
+  // lane % 8; it fetches that chunk ^ the key of the lane that reads the row.
+  uint32_t woff[C::NI], xoff[C::NI];
+#pragma unroll
+  for (int q = 0; q < C::NI; ++q) {
+    const int row = q * 8 + (lane >> 3), chunk = lane & 7;
+    woff[q] = (uint32_t)((si * C::SB + row) * (B * 2) + ((chunk ^ ((row >> 1) & 7)) << 4));
+    const int t = t0 + row < a.T ? t0 + row : a.T - 1;  // rows past T are never stored
+    xoff[q] = (uint32_t)t * (uint32_t)a.sxt * 2u + (uint32_t)((chunk ^ (row & 7)) << 4);
+  }
+  auto issue = [&](int s) {
+    const int gs = wave + C::NW * s, q = kb + gs / C::KSL, slice = gs % C::KSL;
+    const unsigned char* w = reinterpret_cast<const unsigned char*>(a.m0.vals) + (int64_t)q * (B * B * 2) + slice * 128;
+    const unsigned char* x = reinterpret_cast<const unsigned char*>(a.X) + (int64_t)ld_idx(a.m0.col_idx, q) * (B * 2) + slice * 128;
+#pragma unroll
+    for (int i = 0; i < C::NI; ++i) BLAST_GLDS16(w + woff[i], slot + i * 1024);
+#pragma unroll
+    for (int i = 0; i < C::NI; ++i) BLAST_GLDS16(x + xoff[i], slot + C::TILE + i * 1024);
+  };
+
+  f32x16 acc[2][2];  // [token half][even / odd rows]
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int nj = 0; nj < 2; ++nj)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[mi][nj][v] = 0.0f;
+  if (mine > 0) issue(0);
+#pragma unroll 1
+  for (int s = 0; s < mine; ++s) {
+    __builtin_amdgcn_s_waitcnt(BLAST_VMCNT(0));
+    asm volatile("" ::: "memory");
+    bf16x8 fw[4][2], fx[4][2];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int chunk = ((2 * kk + lh) ^ (l32 & 7)) << 4;
+        fw[kk][h] = *reinterpret_cast<const bf16x8*>(slot + (2 * l32 + h) * 128 + chunk);
+        fx[kk][h] = *reinterpret_cast<const bf16x8*>(slot + C::TILE + (32 * h + l32) * 128 + chunk);
+      }
+    // the fragments are in registers before the next stage is copied over this one
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    if (s + 1 < mine) issue(s + 1);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int nj = 0; nj < 2; ++nj)
+          acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kk][mi], fw[kk][nj], acc[mi][nj], 0, 0, 0);
+    asm volatile("" ::: "memory");
+  }
+
+  // Every wave's sums go over its own stage (nothing is in flight into it any more); then a wave owns an eighth of the
+  // tile: four tokens per lane, two rows each.
+  float (*red)[64][64] = reinterpret_cast<float (*)[64][64]>(smem);
+#pragma unroll
+  for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+    for (int nj = 0; nj < 2; ++nj)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[wave][(mi * 2 + nj) * 16 + v][lane] = acc[mi][nj][v];
+  __syncthreads();
+  const int mi = wave >> 2, v0 = (wave & 3) * 4;
+  const int64_t row = (int64_t)r * B + si * C::SB + 2 * l32;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    // register v0 + v of a 32 x 32 tile: token 8 * (v0 / 4) + 4 * lh + v
+    const int t = t0 + 32 * mi + 2 * v0 + 4 * lh + v;
+    if (t >= a.T) continue;
+    float y[2];
+#pragma unroll
+    for (int nj = 0; nj < 2; ++nj) {
+      const int id = (mi * 2 + nj) * 16 + v0 + v;
+      float sum = red[0][id][lane];
+#pragma unroll
+      for (int w = 1; w < C::NW; ++w) sum += red[w][id][lane];
+      y[nj] = POST ? apply_act(a.act, sum) : sum;
+    }
+    const int64_t off = (int64_t)t * a.syt + row * a.syi;
+    typedef __bf16 Bf16Pair __attribute__((ext_vector_type(2)));
+    typedef float F32Pair __attribute__((ext_vector_type(2)));
+    if (a.y_bf16) {
+      uint16_t* p = reinterpret_cast<uint16_t*>(a.Y) + off;
+      if (a.y_pairs) {
+        store_through(reinterpret_cast<Bf16Pair*>(p), Bf16Pair{static_cast<__bf16>(y[0]), static_cast<__bf16>(y[1])});
+      } else {
+        p[0] = f32_to_bf16_rne(y[0]);
+        p[a.syi] = f32_to_bf16_rne(y[1]);
+      }
+    } else {
+      float* p = reinterpret_cast<float*>(a.Y) + off;
+      if (a.y_pairs) {
+        store_through(reinterpret_cast<F32Pair*>(p), F32Pair{y[0], y[1]});
+      } else {
+        p[0] = y[0];
+        p[a.syi] = y[1];
+      }
+    }
+  }
+}
+
+}  // namespace blast_dev

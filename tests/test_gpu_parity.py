@@ -471,6 +471,36 @@ def test_spmm_strided_operands(api, b, T):
     assert (yh[:, :8] == -3.0).all() and (yh[:, 8 + nbr * b:] == -3.0).all()
 
 
+@pytest.mark.parametrize("b", [64, 128])
+@pytest.mark.parametrize("T", [100, 191, 256, 257, 320, 383, 384])
+def test_few_output_tiles(api, b, T):
+    """Shapes with fewer output tiles than CUs, whose rows are dealt to the eight waves of a workgroup: rows of 0 to 9, 16,
+    17 and all 40 blocks, so that some waves get nothing and others one stage more; tokens that end a tile and tokens that
+    end inside one.  The plain product in both types and the activated one (first half of a two-matrix MLP)."""
+    import torch
+
+    rng = np.random.default_rng(5300 + b + T)
+    counts, nbc = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 16, 17, 40, 0, 1], 40
+    mask = np.zeros((len(counts), nbc), dtype=np.uint8)
+    for r, c in enumerate(counts):
+        mask[r, rng.choice(nbc, size=c, replace=False)] = 1
+    w = synth.gauss_bf16(rng, (len(counts) * b, nbc * b), 0.02)
+    x = synth.gauss_bf16(rng, (T, nbc * b), 1.0)
+    dev, ref = pack_both(api, w, b, mask=mask)
+    want = orc.spmm(ref, x)
+    y = api.bsr_spmm(dev, to_dev(x), out=torch.full((T, len(counts) * b), float("nan"), device="cuda:0"))
+    yb = api.bsr_spmm(dev, to_dev(x), out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    check_close(y.cpu().numpy().T, want, f"few tiles b={b} T={T}")
+    assert not y[:, :b].any() and not y[:, 13 * b:14 * b].any()  # empty block rows: exact zeros
+    assert torch.equal(yb, y.to(torch.bfloat16))
+    w2 = synth.gauss_bf16(rng, (nbc * b, len(counts) * b), 0.05)
+    dev2, ref2 = pack_both(api, w2, b, mask=synth.uniform_mask(rng, nbc, len(counts), 0.6))
+    z = api.sparse_mlp2(dev, dev2, to_dev(x), act="gelu")
+    torch.cuda.synchronize()
+    check_close(z.cpu().numpy().T, orc.mlp2(ref, ref2, x, activation="gelu"), f"few tiles, two-matrix MLP b={b} T={T}")
+
+
 @pytest.mark.parametrize("path", ["bf16", "e5m2"])
 @pytest.mark.parametrize("b,nbr,nbc,T", [(128, 4, 6, 300), (128, 128, 2, 1100), (64, 40, 3, 3400), (64, 5, 3, 200)])
 @pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
