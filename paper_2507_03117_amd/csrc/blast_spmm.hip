@@ -489,13 +489,15 @@ bool split_applies(int b, const TileArgs& a, int64_t nnz, bool decode) {
 }
 
 template <bool DUAL>
-int dispatch_tile(int b, const TileArgs& a, int64_t nnz, hipStream_t stream, const ChunkPlan& plan = ChunkPlan{}) {
+int dispatch_tile(int b, const TileArgs& a, int64_t nnz, hipStream_t stream, const ChunkPlan& plan = ChunkPlan{},
+                  bool ranged = false) {
   // the streaming kernel addresses activations with 32-bit byte offsets inside one column block
   const bool small_x = (int64_t)a.T * a.sxt * 2 < ((int64_t)1 << 32);
   const bool decode = a.x_vec && a.T > 0 && small_x && decode_applies<DUAL>(b, a, nnz, plan.max_row_blocks);
   if constexpr (!DUAL) {
-    // (not where rows are cut into chunks, nor where this launch is to clear another one's)
-    if (a.x_vec && small_x && !plan.hdr && !plan.zero_job && split_applies(b, a, nnz, decode))
+    // (not where rows are cut into chunks, nor where this launch is to clear another one's, nor for the last tokens of a
+    // longer call, whose rows are summed as the others')
+    if (a.x_vec && small_x && !ranged && !plan.hdr && !plan.zero_job && split_applies(b, a, nnz, decode))
       return b == 64 ? launch_split<64>(a, stream) : launch_split<128>(a, stream);
   }
   if (decode) {
@@ -530,7 +532,7 @@ int dispatch_tile(int b, const TileArgs& a, int64_t nnz, hipStream_t stream, con
         part.T = (int)((a.T - t0 < range) ? a.T - t0 : range);
         part.X = a.X + t0 * a.sxt;
         part.Y = static_cast<char*>(a.Y) + t0 * a.syt * (a.y_bf16 ? 2 : 4);
-        if (int rc = dispatch_tile<DUAL>(b, part, nnz, stream, plan)) return rc;
+        if (int rc = dispatch_tile<DUAL>(b, part, nnz, stream, plan, true)) return rc;
       }
       return BLAST_OK;
     }
