@@ -686,6 +686,10 @@ namespace {
 size_t mlp_h_bytes(int64_t I, int64_t T) { return blast::align_up((size_t)T * (size_t)I * 2, 256); }
 size_t mlp_slot_bytes(int64_t I) { return blast::align_up((size_t)(I / 16) * 8, 256); }
 size_t mlp_workspace_bytes(int64_t I, int64_t T) { return mlp_h_bytes(I, T) + mlp_slot_bytes(I) + kCtlBytes; }
+// The intermediate as tagged words, behind that (a call with a smaller workspace does without).
+size_t tagged_bytes(int32_t b, int64_t I, int64_t T) {
+  return (b == 64 || b == 128) && T <= kTaggedTokens ? (size_t)T * (size_t)I * 8 : 0;
+}
 constexpr size_t kCtlStatusOffset = 16;  // byte offset of the status word inside the control block
 
 // ---- long rows of a gated product ---------------------------------------------------------------------
@@ -755,7 +759,7 @@ extern "C" int blast_sparse_mlp_workspace(const blast_bsr_view* Wgate, const bla
   if (int rc = check_view(Wup)) return rc;
   if (int rc = check_view(Wdown)) return rc;
   if (T < 0 || !ws_bytes) return BLAST_ERR_INVALID_ARG;
-  *ws_bytes = mlp_workspace_bytes(Wgate->rows, T) + mlp_long_bytes(Wgate, Wup, T) +
+  *ws_bytes = mlp_workspace_bytes(Wgate->rows, T) + tagged_bytes(Wgate->b, Wgate->rows, T) + mlp_long_bytes(Wgate, Wup, T) +
               ((Wgate->b == 16 && T >= kGroup16MinTokens) ? group16_bytes(Wgate->cols, T) : 0);
   return BLAST_OK;
 }
@@ -765,7 +769,7 @@ extern "C" int blast_sparse_mlp2_workspace(const blast_bsr_view* W1, const blast
   if (int rc = check_view(W1)) return rc;
   if (int rc = check_view(W2)) return rc;
   if (T < 0 || !ws_bytes) return BLAST_ERR_INVALID_ARG;
-  *ws_bytes = mlp_workspace_bytes(W1->rows, T) +
+  *ws_bytes = mlp_workspace_bytes(W1->rows, T) + tagged_bytes(W1->b, W1->rows, T) +
               ((W1->b == 16 && T >= kGroup16MinTokens) ? group16_bytes(W1->cols, T) : 0);
   return BLAST_OK;
 }
@@ -909,11 +913,25 @@ int launch_mlp_decode(const DecArgs& p, const DecArgs& c, hipStream_t stream) {
   return BLAST_OK;
 }
 
+template <int B, int NTOK, bool GATED>
+int launch_mlp_decode_tagged(const DecArgs& p, const DecArgs& c, hipStream_t stream) {
+  using CP = DecCfg<B, GATED, 1, 1, true>;
+  constexpr size_t kValues = tagged_consumer_lds(B, NTOK), kLds = CP::LDS_BYTES > kValues ? CP::LDS_BYTES : kValues;
+  static blast::DeviceFlags lds_set;
+  if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_mlp_decode_tagged<B, NTOK, GATED>), kLds, lds_set))
+    return rc;
+  const int64_t grid = (int64_t)p.n_units + c.n_units;
+  if (grid > INT32_MAX) return BLAST_ERR_INVALID_ARG;
+  k_mlp_decode_tagged<B, NTOK, GATED><<<dim3((unsigned)grid), dim3(256), kLds, stream>>>(p, c);
+  BLAST_LAUNCH_CHECK("k_mlp_decode_tagged");
+  return BLAST_OK;
+}
+
 // The single-launch form of the MLP for one token tile.  Applies when both products would take the
 // decode kernel's fast path anyway and no row of Wdown is cut into chunks.
 template <int B, bool GATED>
 int enqueue_mlp_decode(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const blast_bsr_view* Wdown,
-                       const TileArgs& g, const TileArgs& d, uint16_t* H, unsigned long long* slots,
+                       const TileArgs& g, const TileArgs& d, uint16_t* H, unsigned long long* words, unsigned long long* slots,
                        unsigned long long* ctl, const HandoverKnobs& knobs, hipStream_t stream) {
   DecArgs p{}, c{};
   p.m0 = g.m0;
@@ -960,6 +978,13 @@ int enqueue_mlp_decode(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, c
     p.ctl_shift = c.ctl_shift = shift;
   }
   (void)Wup;
+  if (words) {
+    p.words = c.words = words;
+    p.words_pitch = c.words_pitch = Wgate->rows;
+    if (g.T == 1) return launch_mlp_decode_tagged<B, 1, GATED>(p, c, stream);
+    if (g.T == 2) return launch_mlp_decode_tagged<B, 2, GATED>(p, c, stream);
+    return launch_mlp_decode_tagged<B, kTaggedTokens, GATED>(p, c, stream);
+  }
   if constexpr (B >= 64) {
     if (g.T <= 512 / B) return launch_mlp_decode<B, 1, true, GATED>(p, c, stream);
   }
@@ -1007,15 +1032,19 @@ int enqueue_mlp(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const bl
     char* wsb = static_cast<char*>(ws);
     unsigned long long* slots = reinterpret_cast<unsigned long long*>(wsb + mlp_h_bytes(I, T));
     unsigned long long* ctl = reinterpret_cast<unsigned long long*>(wsb + mlp_h_bytes(I, T) + mlp_slot_bytes(I));
+    // a few tokens: the intermediate as tagged words, where the caller's workspace has room for them
+    unsigned long long* words = nullptr;
+    if (tagged_bytes(b, I, T) > 0 && ws_bytes >= need + tagged_bytes(b, I, T))
+      words = reinterpret_cast<unsigned long long*>(wsb + need);
     // one kernel does both phases: events[1] falls before it
     if (events) BLAST_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(events[1]), stream));
     int rc;
     if (Wup) {
-      rc = (b == 64) ? enqueue_mlp_decode<64, true>(Wgate, Wup, Wdown, g, d, H, slots, ctl, knobs, stream)
-                     : enqueue_mlp_decode<128, true>(Wgate, Wup, Wdown, g, d, H, slots, ctl, knobs, stream);
+      rc = (b == 64) ? enqueue_mlp_decode<64, true>(Wgate, Wup, Wdown, g, d, H, words, slots, ctl, knobs, stream)
+                     : enqueue_mlp_decode<128, true>(Wgate, Wup, Wdown, g, d, H, words, slots, ctl, knobs, stream);
     } else {
-      rc = (b == 64) ? enqueue_mlp_decode<64, false>(Wgate, Wup, Wdown, g, d, H, slots, ctl, knobs, stream)
-                     : enqueue_mlp_decode<128, false>(Wgate, Wup, Wdown, g, d, H, slots, ctl, knobs, stream);
+      rc = (b == 64) ? enqueue_mlp_decode<64, false>(Wgate, Wup, Wdown, g, d, H, words, slots, ctl, knobs, stream)
+                     : enqueue_mlp_decode<128, false>(Wgate, Wup, Wdown, g, d, H, words, slots, ctl, knobs, stream);
     }
     if (rc) return rc;
     if (events) BLAST_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(events[2]), stream));

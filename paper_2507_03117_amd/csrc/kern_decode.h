@@ -62,6 +62,8 @@ struct DecArgs {
   int ctl_shift;            // log2 of what a launch adds to each arrival counter (a power of two >= the largest group)
   int max_spins;            // polls before a wait gives up (never hang the GPU)
   int withhold;             // diagnostic: producers compute H but do not publish it
+  unsigned long long* words;  // tagged form (kTaggedTokens): H as [T][words_pitch] words, each a value and the launch's tag
+  int64_t words_pitch;
   int* sync_err;            // status word: kHandoverTimedOut / kHandoverInitTimedOut once a wait has given up
   // Side job of a launch (z_blocks > 0): workgroups [main_blocks, main_blocks + z_blocks) clear the fp32
   // rows that a LATER chunked product will accumulate into (the rows of block rows cut into several
@@ -281,11 +283,13 @@ struct DecCfg {
 // producer publishes its slice of H, the consumer waits for the slices of H its blocks will read).
 // POST: a single-matrix product whose sums go through the activation a.act before they are stored (the
 // first half of a two-matrix MLP).
-template <int B, bool DUAL, int NTT, bool CHUNK, int XSMALL, int ROLE, bool POST = false, bool W8 = false>
+// TAGGED: a producer whose consumers read tagged words (see decode_consumer_tagged).
+template <int B, bool DUAL, int NTT, bool CHUNK, int XSMALL, int ROLE, bool POST = false, bool W8 = false, bool TAGGED = false>
 __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, const int t_base, unsigned char* smem) {
   static_assert(!W8 || ROLE == kDecAlone, "one-byte weights run as ordinary launches");
   static_assert(!(DUAL && CHUNK), "the activation needs complete sums: the gated product is never split");
   static_assert(!POST || (!DUAL && !CHUNK), "an activation on the output needs complete sums of a single matrix");
+  static_assert(!TAGGED || ROLE == kDecProducer, "tagged words are written by producers");
   static_assert(ROLE == kDecAlone || (ROLE == kDecProducer && !CHUNK && (DUAL || POST)) ||
                     (ROLE == kDecConsumer && !DUAL && !CHUNK && !POST),
                 "producers compute the activated intermediate, consumers a plain product");
@@ -655,7 +659,12 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
         if (DUAL) v = apply_act(a.act, v) * acc[NM - 1][tt][j];
         if (POST) v = apply_act(a.act, v);
         const int64_t off = (int64_t)tok * a.syt + row * a.syi;
-        if (ROLE == kDecProducer)  // written through to where every XCD sees it
+        if (TAGGED) {  // value and tag in one word: whoever sees the tag has the value
+          if (!a.withhold)
+            __hip_atomic_store(a.words + tok * a.words_pitch + row,
+                               (hand.token & ~0xFFFFull) | (unsigned long long)f32_to_bf16_rne(v), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        } else if (ROLE == kDecProducer)  // written through to where every XCD sees it
           __hip_atomic_store(reinterpret_cast<uint16_t*>(a.Y) + off, f32_to_bf16_rne(v), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
         else if (CHUNK && shared_row)
@@ -666,7 +675,7 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
           reinterpret_cast<float*>(a.Y)[off] = v;
       }
     }
-  if (ROLE == kDecProducer) {
+  if (ROLE == kDecProducer && !TAGGED) {
     // all of this wave's stores have been acknowledged before the slot says so
     __builtin_amdgcn_s_waitcnt(BLAST_VMCNT(0));
     asm volatile("" ::: "memory");
@@ -674,6 +683,133 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
       __hip_atomic_store(a.slots + (int64_t)r * C::SLICES + q, hand.token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (ROLE != kDecAlone) handover_leave(a, hand);
+}
+
+// The consumer of the single-launch MLP at up to kTaggedTokens tokens.  H does not travel as values followed by a slot
+// that says they are there, but as 64-bit words that hold a value and 48 bits of the launch's token: a word is loaded
+// until it carries the tag, and then the value is at hand.  That takes three trips to the memory side off the chain
+// between the last producer's sums and the last consumer's product: the acknowledgement of the values' stores, the slot's
+// own way, and the load of the values after the slot has been seen.  Nothing has to be ordered - a word is written by one
+// 64-bit store and read by one 64-bit load, both past the L2s - and nothing cleared: a word left by another launch or by
+// anyone else carries the tag of this one with probability 2^-48.  A value costs eight bytes instead of two, so this is
+// for a few tokens; the weight fragments, which do not depend on H, are in registers before the first word is asked for.
+// Cold weights, microseconds a layer, slots / words: 1B shape at 1, 2, 4 tokens 9.95 / 8.55, 10.2 / 9.1, 10.7 / 10.1; 8B
+// shape 11.2 / 9.4, 11.3 / 9.8, 11.8 / 11.5.  (128-wide blocks: the registers are held to five waves per SIMD, which is
+// what keeps the 8B-shaped launch resident at once; without that it loses at 2 and 4 tokens, 11.8 and 12.2.)
+constexpr int kTaggedTokens = 4;
+constexpr int tagged_blocks(int b) { return b == 64 ? 4 : 2; }  // blocks of a wave taken at a time
+constexpr size_t tagged_consumer_lds(int b, int ntok) {        // four waves' values, or the partial sums of three
+  const size_t values = (size_t)4 * tagged_blocks(b) * ntok * b * 2, sums = 3 * 4 * 64 * 4;
+  return values > sums ? values : sums;
+}
+
+template <int B, int NTOK>
+__device__ __forceinline__ void decode_consumer_tagged(const DecArgs& a, const int unit, unsigned char* smem) {
+  constexpr int SLICES = B / 16, KST = B / 32, WPL = B / 64, NB = tagged_blocks(B);
+  constexpr int XROW = B * 2, XB = NTOK * XROW;
+  const int q = unit % SLICES, rank = unit / SLICES;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+  const HandoverPeek peek = handover_peek(a);
+  const int r = a.row_order ? ld_idx(a.row_order, rank) : rank;
+  const int kb = ld_idx(a.m0.row_ptr, r), n = ld_idx(a.m0.row_ptr, r + 1) - kb;
+  const int cnt = n > wave ? (n - wave + 3) >> 2 : 0;  // this wave's blocks are wave + 4 j, j < cnt
+  unsigned char* const xt = smem + wave * (NB * XB);   // values of NB blocks, [NB][NTOK][B]
+  const uint32_t woff = (uint32_t)(q * (16 * B * 2) + l16 * (B * 2) + g * 16);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  Handover hand{};
+  bool begun = false, gave_up = false;
+#pragma unroll 1
+  for (int j0 = 0; j0 < cnt; j0 += NB) {
+    bf16x8 w[NB][KST];
+    int64_t at[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const bool have = j0 + u < cnt;
+      const int k = kb + wave + 4 * (have ? j0 + u : j0);
+      at[u] = (int64_t)ld_idx(a.m0.col_idx, k) * B + lane;
+      const unsigned char* wblk = reinterpret_cast<const unsigned char*>(a.m0.vals) + (int64_t)k * (B * B * 2) + woff;
+      const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int s = 0; s < KST; ++s) w[u][s] = have ? *reinterpret_cast<const bf16x8*>(wblk + s * 64) : zero;
+    }
+    asm volatile("" ::: "memory");  // issued here, not later
+    if (!begun) hand = handover_begin(a, peek);
+    begun = true;
+    // (blocks past the wave's last repeat its first of this round and meet zero weights)
+    unsigned long long v[NB][NTOK][WPL];
+    int spins = 0;
+    for (;;) {
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int t = 0; t < NTOK; ++t)
+#pragma unroll
+          for (int i = 0; i < WPL; ++i)
+            if (j0 + u < cnt && t < a.T)
+              v[u][t][i] = __hip_atomic_load(a.words + t * a.words_pitch + at[u] + i * 64, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+            else
+              v[u][t][i] = hand.token & ~0xFFFFull;
+      unsigned long long differ = 0;
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int t = 0; t < NTOK; ++t)
+#pragma unroll
+          for (int i = 0; i < WPL; ++i) differ |= (v[u][t][i] ^ hand.token) >> 16;
+      if (__ballot(differ != 0) == 0) break;
+      if (gave_up || ++spins > a.max_spins) {
+        gave_up = true;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+#pragma unroll
+      for (int t = 0; t < NTOK; ++t)
+#pragma unroll
+        for (int i = 0; i < WPL; ++i)
+          *reinterpret_cast<uint16_t*>(xt + u * XB + t * XROW + (i * 64 + lane) * 2) = (uint16_t)v[u][t][i];
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+#pragma unroll
+      for (int s = 0; s < KST; ++s) {
+        const bf16x8 x = *reinterpret_cast<const bf16x8*>(xt + u * XB + (l16 % NTOK) * XROW + s * 64 + g * 16);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, w[u][s], acc, 0, 0, 0);
+      }
+  }
+  if (!begun) hand = handover_begin(a, peek);
+  if (gave_up) {
+    // the output rows of this unit become NaN instead of plausible numbers, and the status word says why
+    if (lane == 0) __hip_atomic_store(a.sync_err, kHandoverTimedOut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    acc = f32x4{__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf("")};
+  }
+  // the four partial sums meet in LDS, over the values
+  float (*red)[4][64] = reinterpret_cast<float (*)[4][64]>(smem);
+  __syncthreads();
+  if (wave > 0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[wave - 1][j][lane] = acc[j];
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int64_t row = (int64_t)r * B + q * 16 + l16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int tok = 4 * g + j;
+      if (tok < a.T) {
+        const float y = acc[j] + ((red[0][j][lane] + red[1][j][lane]) + red[2][j][lane]);
+        const int64_t off = (int64_t)tok * a.syt + row * a.syi;
+        if (a.y_bf16)
+          reinterpret_cast<uint16_t*>(a.Y)[off] = f32_to_bf16_rne(y);
+        else
+          reinterpret_cast<float*>(a.Y)[off] = y;
+      }
+    }
+  }
+  handover_leave(a, hand);
 }
 
 template <int B, bool DUAL, int NTT, bool CHUNK, int XSMALL, bool POST = false, bool W8 = false>
@@ -708,6 +844,18 @@ __global__ __launch_bounds__(256) void k_mlp_decode(const DecArgs p, const DecAr
     decode_unit<B, GATED, NTT, false, XSMALL, kDecProducer, !GATED>(p, blk, 0, smem);
   } else if (blk - p.n_units < c.n_units) {
     decode_unit<B, false, NTT, false, XSMALL, kDecConsumer>(c, blk - p.n_units, 0, smem);
+  }
+}
+
+// The same with H as tagged words, for up to NTOK tokens.
+template <int B, int NTOK, bool GATED>
+__global__ __launch_bounds__(256, B == 128 ? 5 : 1) void k_mlp_decode_tagged(const DecArgs p, const DecArgs c) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int blk = blockIdx.x;
+  if (blk < p.n_units) {
+    decode_unit<B, GATED, 1, false, 1, kDecProducer, !GATED, false, true>(p, blk, 0, smem);
+  } else if (blk - p.n_units < c.n_units) {
+    decode_consumer_tagged<B, NTOK>(c, blk - p.n_units, smem);
   }
 }
 

@@ -35,7 +35,7 @@ def _layer(api, seed, E, I, b, sparsity):
     return rng, dev, ref, ms_
 
 
-@pytest.mark.parametrize("b,T", [(64, 1), (64, 16), (64, 32), (64, 50), (128, 5), (128, 16), (128, 30)])
+@pytest.mark.parametrize("b,T", [(64, 1), (64, 3), (64, 16), (64, 32), (64, 50), (128, 1), (128, 2), (128, 5), (128, 16), (128, 30)])
 def test_single_launch_form_replays_from_a_graph(api, b, T):
     """One token tile: the call is recorded as ONE kernel and every replay - with new activations, with eager
     calls on the same workspace between the replays - hands over its own H."""
@@ -94,7 +94,49 @@ def test_single_launch_form_at_the_1b_shape_with_changing_activations(api):
         assert api.sparse_mlp_status(dev[0], T, ws[: api.mlp_workspace_bytes(*dev, T)]) == 0
 
 
-@pytest.mark.parametrize("b,T", [(64, 3), (64, 40), (128, 16), (128, 24)])
+@pytest.mark.parametrize("b", [64, 128])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
+def test_tagged_words(api, b, T, out_dtype):
+    """A few tokens: H travels as tagged words where the workspace has room for them, else through slots.  Both forms on a
+    garbage workspace, with rows of the down projection of 0 to 23 blocks (a wave takes four or two at a time), gated and
+    two-matrix; activations change from call to call on one workspace; the two forms agree up to the order of the sums."""
+    import torch
+
+    E, I = 8 * b, 24 * b
+    rng = np.random.default_rng(8250 + b + T)
+    shapes = ((I, E), (I, E), (E, I))
+    ws_ = [synth.gauss_bf16(rng, s, 0.05) for s in shapes]
+    ms_ = [synth.uniform_mask(rng, r // b, c // b, 0.5) for r, c in shapes]
+    for br, count in enumerate((0, 1, 4, 5, 16, 17, 8, 23)):
+        ms_[2][br] = 0
+        ms_[2][br, rng.choice(I // b, size=count, replace=False)] = 1
+    dev = [api.bsr_pack(to_dev(w), b, mask=mask_dev(m)) for w, m in zip(ws_, ms_)]
+    ref = [orc.pack(w, b, m) for w, m in zip(ws_, ms_)]
+    dt = torch.float32 if out_dtype == "f32" else torch.bfloat16
+    tol = 0.0 if out_dtype == "f32" else 2.0 ** -7
+    whole = api.mlp_workspace_bytes(*dev, T)
+    for size in (whole, whole - T * I * 8) if T <= 4 else (whole,):
+        ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device="cuda:0")
+        for rep in range(3):
+            x = synth.gauss_bf16(rng, (T, E), 1.0)
+            out = torch.full((T, E), float("nan"), dtype=dt, device="cuda:0")
+            y = api.sparse_mlp(*dev, to_dev(x), ws=ws, out=out).float()
+            want = orc.mlp(*ref, x)
+            z = api.sparse_mlp2(dev[0], dev[2], to_dev(x), ws=ws, out=torch.empty_like(out)).float()
+            want2 = orc.mlp2(ref[0], ref[2], x)
+            torch.cuda.synchronize()
+            for got, exp in ((y, want), (z, want2)):
+                got = got.cpu().numpy().T
+                if tol == 0.0:
+                    check_close(got, exp, f"tagged b={b} T={T} ws={size} call {rep}")
+                else:  # one rounding to bf16 on top of the sums
+                    assert (np.abs(got - exp) <= np.abs(exp) * tol + 1e-2 * np.sqrt((exp ** 2).mean())).all()
+                assert not got[:b].any()  # an empty block row
+        assert api.sparse_mlp_status(dev[0], T, ws) == 0
+
+
+@pytest.mark.parametrize("b,T", [(64, 3), (128, 1), (64, 40), (128, 16), (128, 24)])
 def test_a_wait_that_expires_gives_nan_rows_and_a_status(api, b, T):
     """Forced from the host: the producers never publish, the consumers poll 20 times and give up.  Every
     workgroup exits normally; the rows of Y that depended on H are NaN, rows of empty block rows are zeros,
