@@ -22,7 +22,9 @@
 // which an L1 delivers about 54; the floor that leaves is 22 us for 1229 64-wide blocks at 2000 tokens.  There: 49 us
 // with four waves per block (5 blocks per CU are 2.4 rounds of the 2 workgroups that fit, and each round streams all
 // of X across the fabric to every XCD again) and branches on every stage; 40 us with a wave per block, all resident,
-// and a steady state that decides nothing (640 -> 330 clk per stage of a lone wave).
+// and a steady state that decides nothing (640 -> 330 clk per stage of a lone wave).  Ordinary / non-temporal stores of the
+// gradient, operands alternating between three sets: 14336 x 4096 at 80 %, 128-wide, 2000 tokens 96 / 80 us, at 70 %, 1000
+// tokens 76 / 68; 8192 x 3072 at 70 %, 64-wide, 4096 tokens 118 / 107; 8192 x 2048 at 80 %, 512 tokens 14.2 / 12.3.
 #pragma once
 #include "kern_common.h"
 #include "kern_stream.h"
@@ -385,8 +387,8 @@ __global__ __launch_bounds__(64 * KW * UPW, KW == 1 ? 2 : 1) void k_sddmm(const 
     float* dst = out + m * B + 32 * nj + l32;
     if (a.tsplit > 1)
       atomicAdd(dst, sum);
-    else
-      *dst = sum;
+    else  // non-temporal: an output as large as the operands need not displace them from the last-level cache
+      __builtin_nontemporal_store(sum, dst);
   };
   if constexpr (KW == 1) {
 #pragma unroll
