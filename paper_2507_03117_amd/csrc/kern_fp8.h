@@ -405,7 +405,8 @@ __global__ __launch_bounds__(256) void k_quantize_e5m2(const uint16_t* __restric
 
 // Token-major bf16 [T][K] (row pitch ld elements) -> E5M2 in column groups of 64: out[(k/64) T + t][k%64].
 // A workgroup turns kQuantTokens tokens of one column group; a thread converts 8 features of a token at a time, so
-// that a wave reads whole 128-byte lines and writes 512 consecutive bytes.
+// that a wave reads whole 128-byte lines and writes 512 consecutive bytes - through the L2, so that the codes are on their
+// way when the launch ends (with the product after it: 2048 x 3072, 30.9 -> 29.8 us; 2048 x 4096, 40.8 -> 39.9).
 constexpr int kQuantTokens = 128;
 __global__ __launch_bounds__(256) void k_quantize_e5m2_groups(const uint16_t* __restrict__ in, int64_t ld, int64_t T,
                                                               int wide, uint8_t* __restrict__ out) {
@@ -428,7 +429,7 @@ __global__ __launch_bounds__(256) void k_quantize_e5m2_groups(const uint16_t* __
 #pragma unroll
   for (int q = 0; q < kQuantTokens / 32; ++q) {
     const int64_t t = t0 + q * 32;
-    if (t < T) *reinterpret_cast<uint2*>(out + (c * T + t) * 64 + k) = bf16x8_to_e5m2x8(v[q]);
+    if (t < T) store_through(reinterpret_cast<uint2*>(out + (c * T + t) * 64 + k), bf16x8_to_e5m2x8(v[q]));
   }
 }
 
