@@ -10,6 +10,9 @@
 //    fits a CU, which is what there is work for.
 //  - Rows of a wave's tile alternate between the two matrix tiles, so that a lane ends up with two neighbouring rows of a
 //    token, as in the streaming kernel.
+// Relative error against 64 bits, other kernel / this one: 1600 x 6400 at 80 %, 333 tokens 2.1e-7 / 0.9e-7; 1024 x 8192 at
+// 80 %, 128-wide, 1000 tokens 2.5e-7 / 1.0e-7; 2048 x 8192 at 90 %, 256 tokens 0.9e-7 / 0.8e-7.
+// Second product of the two-matrix MLP of 1600 and 6400 features at 80 %, 384 tokens: 17.0 us on the streaming kernel, 10.6.
 // What bounds it: a tile asks the L1 for a byte per 32 flop, half the matrix peak at 64 bytes a clock; at these sizes the
 // chain (indices, one trip per stage, the sums in LDS) is most of the launch.
 #pragma once
