@@ -83,7 +83,8 @@ struct StreamCfg {
   static constexpr bool PAIR = PAIRS && NI == 2;
   // Which weight row of a wave's tile is column l32 of matrix tile ni: with two matrix tiles, neighbouring rows, so that a
   // lane ends up with two neighbouring rows of a token and stores them together (see the epilogue).  Not with chunks,
-  // whose rows are added to by atomics: lanes side by side do better there (405B-class MLP, 2048 tokens: 718 / 737 us).
+  // whose rows are added to by atomics, nor where fp32 sums go to scratch value by value: lanes side by side do better
+  // there (405B-class MLP with Zipf rows, 2048 tokens: 718 / 737 us; 512: 288 / 354).
   __device__ static __forceinline__ int row_of(int l32, int ni) { return PAIR ? 2 * l32 + ni : ni * 32 + l32; }
   // The swizzle key of a weight row: that of the lane which reads it, key(l32).
   __device__ static __forceinline__ int wkey(int row) { return key(PAIR ? row >> 1 : row); }
@@ -452,7 +453,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
   static_assert(!(DUAL && CHUNK), "the activation needs complete sums: the gated product is never split");
   static_assert(!POST || (!DUAL && !CHUNK), "an activation on the output needs complete sums of a single matrix");
   static_assert(!LONG || (DUAL && !CHUNK), "long rows are a matter of the gated product");
-  using C = StreamCfg<B, TW, NW, F8, !CHUNK>;
+  using C = StreamCfg<B, TW, NW, F8, !CHUNK && !LONG>;
   const TileArgs& a = sa.t;
   const int n_items = LONG    ? (long_chunks(sa.hdr) + long_chunks(sa.hdr1) + a.nbr) * a.ntt
                       : CHUNK ? ld_idx(sa.hdr, 0) * a.ntt
