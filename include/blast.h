@@ -377,9 +377,11 @@ int blast_bsr_spmm_workspace(const blast_bsr_view* W, int64_t T, size_t* ws_byte
  * stored blocks in the three matrices the whole of Eq. (1) runs as one kernel launch: the workgroups of the second
  * product wait inside the kernel until the slices of H they read have been published by the workgroups of the first
  * (a bounded wait; should it ever expire, their output rows are NaN and blast_sparse_mlp_status reports it).  The
- * hand-over state lives in the workspace and sets itself up: the workspace still needs no initialisation.  The call
- * can be recorded into a HIP graph like any other; replays tell themselves apart through an epoch that the kernel
- * advances in the workspace.
+ * hand-over state lives in the first 8448 bytes of the workspace, at every shape and token count, and sets itself up: the
+ * workspace still needs no initialisation, calls of different shapes and token counts may share one, and what else has
+ * been written over that part between two calls is found out (unless it was confined to less than 512 bytes of it).
+ * The call can be recorded into a HIP graph like any other; replays tell themselves apart through an epoch that the
+ * kernel advances in the workspace.
  * Beyond 64 tokens, when Wgate or Wup carries `aux` and a block row so full that walking it alone would take
  * several times the average share of a workgroup (the load balance Sec. 3.4.1 asks for), the rows of more than
  * 16 blocks are summed chunk by chunk into fp32 scratch behind H and H's rows of those block rows are written by a
@@ -403,11 +405,10 @@ int blast_sparse_mlp_workspace(const blast_bsr_view* Wgate, const blast_bsr_view
 
 /*
  * Status of the in-kernel hand-over of the single-launch form (see blast_sparse_mlp) for the workspace a call
- * used: *status = 0 when every wait ended normally (or no single-launch call has used the workspace at this
- * shape), 1 when a workgroup of the second product gave up waiting for H (its output rows are NaN), 2 when
+ * used: *status = 0 when every wait ended normally (or no single-launch call has used the workspace), 1 when a workgroup of the second product gave up waiting for H (its output rows are NaN), 2 when
  * a wave gave up waiting for the set-up of the control block.  A nonzero status is cleared by the call.
- *   Wgate, T   the first matrix and the token count of the calls in question (they fix where the control
- *              block sits in the workspace)
+ *   Wgate, T   the first matrix and the token count of a call that the workspace is large enough for (the status is
+ *              that of the calls of every shape on this workspace)
  *   ws         the workspace those calls used; NULL = the library's own scratch (blast_sparse_mlp_static)
  *   status     HOST, out
  * Waits for `stream`.  Errors: INVALID_ARG, SHAPE, UNSUPPORTED_BLOCK, WORKSPACE, HIP.
@@ -417,8 +418,8 @@ int blast_sparse_mlp_status(const blast_bsr_view* Wgate, int64_t T, const void* 
 
 /*
  * Diagnostic form of blast_sparse_mlp for testing the failure handling of the hand-over from the host, with
- * every kernel still exiting normally: `spin_limit` (>= 1) replaces the number of polls after which a wait gives
- * up, and a nonzero `withhold_publication` makes the workgroups of the first product compute H without
+ * every kernel still exiting normally: `spin_limit` (>= 1) replaces the number of polls after which a wait for H
+ * gives up, and a nonzero `withhold_publication` makes the workgroups of the first product compute H without
  * publishing it, so that every wait of the second product expires.  Outside the single-launch form the two
  * extra arguments have no effect.  Same arguments, results and errors as blast_sparse_mlp otherwise.
  */
@@ -442,7 +443,8 @@ int blast_sparse_mlp_handover_test(const blast_bsr_view* Wgate, const blast_bsr_
  *           The Llama-3.2-1B-shaped layer (I = 8192) fits up to T = 2048.
  *   sharing every call on one GPU uses that GPU's one array: calls that may overlap in time on the same GPU
  *           (different streams, different host threads) race on it and must be serialised by the caller.
- *           Nothing in the array needs clearing between calls and nothing in it outlives a call.
+ *           Nothing in the array needs clearing between calls; nothing in it outlives a call but the hand-over state at
+ *           its start, which calls of every shape share.
  */
 #define BLAST_STATIC_SCRATCH_BYTES ((size_t)36 << 20)
 int blast_sparse_mlp_static(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const blast_bsr_view* Wdown,

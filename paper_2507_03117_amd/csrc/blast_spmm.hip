@@ -681,17 +681,6 @@ extern "C" int blast_bsr_spmm(const blast_bsr_view* W, const uint16_t* X, int64_
 
 namespace {
 
-// H in bf16, token-major [T][I]; then the publication slots of the single-launch form (one 64-bit word
-// per 16 rows of H) and the control block of the hand-over: signature, epoch, status word, arrival counters
-size_t mlp_h_bytes(int64_t I, int64_t T) { return blast::align_up((size_t)T * (size_t)I * 2, 256); }
-size_t mlp_slot_bytes(int64_t I) { return blast::align_up((size_t)(I / 16) * 8, 256); }
-size_t mlp_workspace_bytes(int64_t I, int64_t T) { return mlp_h_bytes(I, T) + mlp_slot_bytes(I) + kCtlBytes; }
-// The intermediate as tagged words, behind that (a call with a smaller workspace does without).
-size_t tagged_bytes(int32_t b, int64_t I, int64_t T) {
-  return (b == 64 || b == 128) && T <= kTaggedTokens ? (size_t)T * (size_t)I * 8 : 0;
-}
-constexpr size_t kCtlStatusOffset = 16;  // byte offset of the status word inside the control block
-
 // ---- long rows of a gated product ---------------------------------------------------------------------
 // The gated product cannot cut a block row (the activation needs complete sums), so at a few hundred tokens
 // - one to four token tiles per row - the workgroup that walks the fullest joint row alone sets the time of
@@ -951,7 +940,7 @@ int enqueue_mlp_decode(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, c
   p.ctl = ctl;
   p.max_spins = knobs.max_spins;
   p.withhold = knobs.withhold;
-  p.sync_err = reinterpret_cast<int*>(reinterpret_cast<char*>(ctl) + kCtlStatusOffset);
+  p.sync_err = reinterpret_cast<int*>(ctl + kCtlStatusWord);
   c.m0 = d.m0;
   c.row_order = d.row_order;
   c.X = H;
@@ -970,13 +959,7 @@ int enqueue_mlp_decode(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, c
   c.withhold = knobs.withhold;
   c.sync_err = p.sync_err;
   p.groups = c.groups = 1;
-  p.total_waves = c.total_waves = (p.n_units + c.n_units) * 4;
-  {  // a launch adds 2^shift to each of the 64 arrival counters: the smallest power of two >= the largest group
-    const int largest = (p.total_waves + kCtlGroups - 1) / kCtlGroups;
-    int shift = 0;
-    while ((1 << shift) < largest) ++shift;
-    p.ctl_shift = c.ctl_shift = shift;
-  }
+  p.workgroups = c.workgroups = p.n_units + c.n_units;
   (void)Wup;
   if (words) {
     p.words = c.words = words;
@@ -1004,7 +987,8 @@ int enqueue_mlp(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const bl
   if (T == 0 || E == 0) return BLAST_OK;
   const size_t need = mlp_workspace_bytes(I, T);
   if (need > 0 && (!ws || ws_bytes < need || !blast::aligned(ws, 256))) return BLAST_ERR_WORKSPACE;
-  uint16_t* H = static_cast<uint16_t*>(ws);
+  char* const wsb = static_cast<char*>(ws);
+  uint16_t* H = reinterpret_cast<uint16_t*>(wsb + kMlpHOffset);
 
   if (events) BLAST_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(events[0]), stream));
   const int64_t one_tile = (b == 64) ? 64 : 32;  // 64-token units exist for 64-wide blocks only
@@ -1015,7 +999,7 @@ int enqueue_mlp(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const bl
   const bool fused_pays = stored_bytes <= ((int64_t)32 << 20);
   // (b >= 64: a token's slice of one block column of H then fills whole 128-byte lines, so a line is never
   // read by one consumer while the producers of a neighbouring column are still writing the rest of it)
-  if (I > 0 && T <= one_tile && (b == 64 || b == 128) && fused_pays && (I / 16 + E / 16) * 4 < INT32_MAX / 2 &&
+  if (I > 0 && T <= one_tile && (b == 64 || b == 128) && fused_pays && I / 16 + E / 16 <= kCtlMaxWorkgroups &&
       x_layout == BLAST_TOKEN_MAJOR && ldx % 8 == 0 &&
       blast::aligned(X, 16) && T * ldx * 2 < ((int64_t)1 << 32) && !plan_of(Wdown, T).hdr) {
     TileArgs g{}, d{};
@@ -1029,13 +1013,12 @@ int enqueue_mlp(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const bl
     d.row_order = Wdown->row_order;
     set_y(d, Y, ldy, x_layout, y_dtype);
     d.T = (int)T;
-    char* wsb = static_cast<char*>(ws);
-    unsigned long long* slots = reinterpret_cast<unsigned long long*>(wsb + mlp_h_bytes(I, T));
-    unsigned long long* ctl = reinterpret_cast<unsigned long long*>(wsb + mlp_h_bytes(I, T) + mlp_slot_bytes(I));
+    unsigned long long* slots = reinterpret_cast<unsigned long long*>(wsb + mlp_slot_offset(I, T));
+    unsigned long long* ctl = reinterpret_cast<unsigned long long*>(wsb + kMlpCtlOffset);
     // a few tokens: the intermediate as tagged words, where the caller's workspace has room for them
     unsigned long long* words = nullptr;
     if (tagged_bytes(b, I, T) > 0 && ws_bytes >= need + tagged_bytes(b, I, T))
-      words = reinterpret_cast<unsigned long long*>(wsb + need);
+      words = reinterpret_cast<unsigned long long*>(wsb + tagged_offset(I, T));
     // one kernel does both phases: events[1] falls before it
     if (events) BLAST_HIP_TRY(hipEventRecord(static_cast<hipEvent_t>(events[1]), stream));
     int rc;
@@ -1092,14 +1075,14 @@ int enqueue_mlp(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const bl
     const size_t extra = Wup ? mlp_long_bytes(Wgate, Wup, T) : 0;
     const bool have_ls = extra > 0 && ws_bytes >= need + extra;
     if (have_ls) {
-      ls.S0 = reinterpret_cast<float*>(static_cast<char*>(ws) + need);
-      ls.S1 = reinterpret_cast<float*>(static_cast<char*>(ws) + need + long_scratch_bytes(Wgate, T));
+      ls.S0 = reinterpret_cast<float*>(wsb + need);
+      ls.S1 = reinterpret_cast<float*>(wsb + need + long_scratch_bytes(Wgate, T));
     }
     // 16-wide blocks at many tokens: X is regrouped by block column behind the workspace proper (where the
     // caller left room for it), and H is written and read in the same form
     const uint16_t* Xg16 = nullptr;
     if (group16_applies(b, x_layout, X, ldx, T) && ws_bytes >= need + extra + group16_bytes(E, T)) {
-      uint16_t* xg = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + need + extra);
+      uint16_t* xg = reinterpret_cast<uint16_t*>(wsb + need + extra);
       if (int rc = enqueue_group16(X, ldx, T, E, xg, stream)) return rc;
       Xg16 = xg;
       d.x_grp16 = 1;
@@ -1196,19 +1179,18 @@ extern "C" int blast_sparse_mlp_status(const blast_bsr_view* Wgate, int64_t T, c
     have = kStaticScratchBytes;
   }
   if (have < mlp_workspace_bytes(I, T) || !blast::aligned(base, 256)) return BLAST_ERR_WORKSPACE;
-  const char* ctl = static_cast<const char*>(base) + mlp_h_bytes(I, T) + mlp_slot_bytes(I);
+  const char* ctl = static_cast<const char*>(base) + kMlpCtlOffset;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   BLAST_HIP_TRY(hipStreamSynchronize(stream));
-  unsigned long long sig = 0;
-  BLAST_HIP_TRY(hipMemcpy(&sig, ctl, sizeof(sig), hipMemcpyDeviceToHost));
-  // the signature carries the wave count of the launch shape in its low bits
-  if ((sig ^ kCtlReady) >> 32) return BLAST_OK;  // no single-launch call has used this workspace at this shape
-  int32_t word = 0;
-  BLAST_HIP_TRY(hipMemcpy(&word, ctl + kCtlStatusOffset, sizeof(word), hipMemcpyDeviceToHost));
-  *status = word;
-  if (word != 0) {
+  uint64_t block[kCtlWords];
+  BLAST_HIP_TRY(hipMemcpy(block, ctl, sizeof(block), hipMemcpyDeviceToHost));
+  bool whole = ctl_is_signature(block[0]);
+  for (int i = 0; i < kCtlMarks; ++i) whole = whole && block[ctl_mark(i)] == ctl_mark_value(block[0], i);
+  if (!whole) return BLAST_OK;  // no single-launch call has used this workspace, or its block has been written over since
+  *status = (int32_t)(uint32_t)block[kCtlStatusWord];
+  if (*status != 0) {
     const int32_t zero = 0;
-    BLAST_HIP_TRY(hipMemcpy(const_cast<char*>(ctl) + kCtlStatusOffset, &zero, sizeof(zero), hipMemcpyHostToDevice));
+    BLAST_HIP_TRY(hipMemcpy(const_cast<char*>(ctl) + kCtlStatusWord * 8, &zero, sizeof(zero), hipMemcpyHostToDevice));
   }
   return BLAST_OK;
 }

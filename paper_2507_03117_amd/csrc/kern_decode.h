@@ -27,6 +27,7 @@
 // Same arithmetic as the tile kernels: bf16 products, fp32 accumulation,
 // activation on the fp32 sums, one rounding to bf16 where the output is bf16.
 #pragma once
+#include "handover.h"
 #include "kern_common.h"
 #include "kern_stream.h"
 
@@ -53,13 +54,12 @@ struct DecArgs {
   const int* chunk_ke;   // one past its last stored block
   // single-launch MLP only: one 64-bit slot per (block row of H, 16-row slice); the producer of that
   // slice stores the launch's token there once its part of H is visible device-wide, consumers wait for it.
-  // The token is `token` (drawn on the host, one per call) mixed with the epoch kept in ctl[1], see
-  // handover_token(): a replay of a captured call differs from the previous replay in the epoch.
+  // The token is `token` (drawn on the host, one per call) mixed with the epoch of the control block, see
+  // handover_begin(): a replay of a captured call differs from the previous replay in the epoch.
   unsigned long long* slots;
   unsigned long long token;
-  unsigned long long* ctl;  // control block in the workspace (kCtlBytes): signature, epoch, status, arrival counters
-  int total_waves;          // waves of the whole launch
-  int ctl_shift;            // log2 of what a launch adds to each arrival counter (a power of two >= the largest group)
+  unsigned long long* ctl;  // control block of the workspace (handover.h)
+  int workgroups;           // of the whole launch, at most kCtlMaxWorkgroups
   int max_spins;            // polls before a wait gives up (never hang the GPU)
   int withhold;             // diagnostic: producers compute H but do not publish it
   unsigned long long* words;  // tagged form (kTaggedTokens): H as [T][words_pitch] words, each a value and the launch's tag
@@ -112,105 +112,106 @@ __device__ __forceinline__ bf16x8 e5m2x8_to_bf16x8(uint2 raw) {
 
 enum DecRole { kDecAlone = 0, kDecProducer = 1, kDecConsumer = 2 };
 constexpr int kDecMaxSpins = 1 << 19;  // polls of ~0.3 us each before a consumer gives up (never hang the GPU)
-constexpr unsigned long long kCtlReady = 0xB1A57C7100D0C0DEull;  // the control block has been set up
-constexpr unsigned long long kCtlBusy = 0xB1A57C71B0057EEDull;   // a wave is setting it up right now
 constexpr int kHandoverTimedOut = 1, kHandoverInitTimedOut = 2;
 
-constexpr int kCtlGroups = 64;        // arrival counters, each in a 128-byte line of its own
-constexpr int kCtlLineWords = 16;     // 64-bit words per line
-// Control block of the single-launch form, in 64-bit words (kCtlBytes bytes of the workspace):
-//   [0] signature  [2] status (low 32 bits)  [(2 + g) * kCtlLineWords], g < kCtlGroups: arrival counters
-constexpr int kCtlGroupWord0 = 2 * kCtlLineWords;
-constexpr int kCtlBytes = (2 + kCtlGroups) * kCtlLineWords * 8;
-
-// Every wave of a single-launch MLP calls handover_peek first thing, handover_begin once it needs the token
-// and handover_leave as its last act.
+// Every wave of a single-launch MLP calls handover_peek first thing and handover_begin once it needs the token, before
+// the first barrier of its workgroup; the wave that stores the workgroup's results calls handover_leave as its last act.
 //
 // The token of a launch is the call's host-drawn token mixed with an epoch that must change from launch to
 // launch on the same workspace (a call recorded into a graph is replayed with the same arguments).  The
-// epoch is not stored anywhere: it is read off an arrival counter.  Wave number n belongs to group n % 64
-// and, when it leaves, adds 1 to its group's counter - the group's first wave adds the rest up to a power
-// of two P as well, so that a launch adds exactly P to every counter.  A counter therefore stays inside
-// [epoch * P, (epoch + 1) * P) from the first to the last wave of a launch, whichever waves have already
-// left, and counter >> log2(P) is the same number for every wave of the launch and one more for the next
-// launch.  Nobody waits for anybody, no addition returns a value, and no address takes more than a few dozen
+// epoch is not stored anywhere: it is read off an arrival counter.  Workgroup number n belongs to group n % 16
+// and, when it leaves, adds 1 to its group's counter - the group's first workgroup adds the rest up to 2^20 as
+// well, so that a launch of any shape adds exactly 2^20 to every counter.  A counter therefore stays inside
+// [epoch * 2^20, (epoch + 1) * 2^20) until the last workgroup of its group leaves, by when all of them have read it,
+// and counter >> 20 is the same number for every wave of the launch and one more for the next launch.
+// Nobody waits for anybody, no addition returns a value, and no address takes more than a few dozen
 // additions per launch.  Launches on one workspace are ordered by their stream (overlapping calls need
 // different workspaces), and what a launch added is visible when the next one starts.
 //
-// The control block needs no initialisation by the caller: a wave that does not find the signature of its
-// launch shape (the number of waves is part of it) claims the set-up with a compare-and-swap on whatever it
-// found there; the winner clears the counters and the status word, waits for those stores to be
-// acknowledged and writes the signature; every other wave polls for the signature (the winner is running
-// and waits for nothing, so that wait ends; it is bounded besides).
+// The control block needs no initialisation by the caller: a wave that does not find it whole (handover.h) claims
+// the set-up with a compare-and-swap on the signature word it found; the winner writes the block, waits for those
+// stores to be acknowledged and writes the new signature; every other wave polls for a block that is whole (the
+// winner is running and waits for nothing, so that wait ends; it is bounded besides).
+// The block lies at the start of the workspace in every call, and no call writes into it but by the rules above.
 struct HandoverPeek {
-  unsigned long long sig, count;
+  unsigned long long sig, mark, count;
 };
 struct Handover {
   unsigned long long token;  // of this launch, the same in every wave
-  unsigned long long add;    // what this wave adds to its group's counter when it leaves
-  int group;
 };
-__device__ __forceinline__ int handover_group() { return (blockIdx.x * 4 + (threadIdx.x >> 6)) % kCtlGroups; }
+__device__ __forceinline__ unsigned long long handover_load(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
-// The signature as the scalar cache sees it (a stale value only sends the wave down the slow path of
-// handover_begin) and this wave's counter read past the caches (a value from any moment of this launch
-// gives the same epoch; one cached before the set-up of the control block would not).  Issued first thing
-// in a wave, used later.
+// The mark that this lane looks at, and whether all that the lanes hold fit the signature.
+__device__ __forceinline__ int handover_lane() { return threadIdx.x % 32 < kCtlMarks ? threadIdx.x % 32 : 0; }
+__device__ __forceinline__ bool handover_whole(unsigned long long sig, unsigned long long mark) {
+  static_assert(kCtlMarks <= 32, "a mark per lane");
+  return ctl_is_signature(sig) && __ballot(mark != ctl_mark_value(sig, handover_lane())) == 0;
+}
+
+// Signature and marks as the caches see them (stale ones only send the wave down the slow path of handover_begin: a
+// signature and marks of different set-ups never fit) and the group's counter read past the caches (a value from any
+// moment of this launch gives the same epoch; one cached before the set-up would not).  Issued first thing in a wave,
+// used later.  (The marks as scalar loads: the row's indices then wait for them too, 0.2 us a layer.)
 __device__ __forceinline__ HandoverPeek handover_peek(const DecArgs& a) {
   const __attribute__((address_space(4))) unsigned long long* c =
       reinterpret_cast<const __attribute__((address_space(4))) unsigned long long*>(reinterpret_cast<uintptr_t>(a.ctl));
-  return HandoverPeek{c[0], __hip_atomic_load(a.ctl + kCtlGroupWord0 + handover_group() * kCtlLineWords, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT)};
+  return HandoverPeek{c[0], __hip_atomic_load(a.ctl + ctl_mark(handover_lane()), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT),
+                      handover_load(a.ctl + ctl_counter(ctl_group(blockIdx.x)))};
+}
+
+// Returns once the block is whole, by this wave's doing or another's.  Never held to a small number of polls: a wave that
+// went on without the block would spoil its counters for the launches to come.
+__device__ __forceinline__ void handover_set_up(const DecArgs& a) {
+  const int lane = threadIdx.x & 63;
+  for (int spins = 0; spins <= kDecMaxSpins; ++spins) {
+    const unsigned long long found = handover_load(a.ctl);
+    if (found != kCtlBusy) {
+      asm volatile("" ::: "memory");  // the marks are read after the signature
+      if (handover_whole(found, handover_load(a.ctl + ctl_mark(handover_lane())))) return;
+      unsigned long long expected = found;
+      bool won = false;
+      if (lane == 0)
+        won = __hip_atomic_compare_exchange_strong(a.ctl, &expected, kCtlBusy, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+      if (__ballot(won) != 0) {
+        const unsigned long long sig = ctl_signature(__builtin_amdgcn_s_memrealtime());
+        for (int i = lane; i < kCtlWords; i += 64)
+          if (i > 0) __hip_atomic_store(a.ctl + i, ctl_initial(i, sig), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(BLAST_VMCNT(0));  // all acknowledged before the signature appears
+        asm volatile("" ::: "memory");
+        if (lane == 0) __hip_atomic_store(a.ctl, sig, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+      }
+    }
+    __builtin_amdgcn_s_sleep(2);
+  }
+  if (lane == 0) __hip_atomic_store(a.sync_err, kHandoverInitTimedOut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ Handover handover_begin(const DecArgs& a, const HandoverPeek& pk) {
   Handover h{};
-  const int wave_id = blockIdx.x * 4 + (threadIdx.x >> 6);
-  h.group = wave_id % kCtlGroups;
-  const int group_size = a.total_waves / kCtlGroups + (h.group < a.total_waves % kCtlGroups ? 1 : 0);
-  h.add = wave_id < kCtlGroups ? (1ull << a.ctl_shift) - (unsigned long long)group_size + 1ull : 1ull;
-  const unsigned long long ready = kCtlReady ^ (unsigned long long)(unsigned)a.total_waves;
   unsigned long long count = pk.count;
-  if (pk.sig != ready) {
-    if ((threadIdx.x & 63) == 0) {
-      unsigned long long m = __hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (m != ready) {
-        bool won = false;
-        if (m != kCtlBusy)
-          won = __hip_atomic_compare_exchange_strong(a.ctl, &m, kCtlBusy, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-        if (won) {
-          for (int i = 1; i < kCtlBytes / 8; i += (i < kCtlLineWords ? 1 : kCtlLineWords))
-            __hip_atomic_store(a.ctl + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __builtin_amdgcn_s_waitcnt(BLAST_VMCNT(0));  // all acknowledged before the signature appears
-          asm volatile("" ::: "memory");
-          __hip_atomic_store(a.ctl, ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-          int spins = 0;
-          while (__hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ready) {
-            if (++spins > a.max_spins) {
-              __hip_atomic_store(a.sync_err, kHandoverInitTimedOut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-          }
-        }
-      }
-    }
-    // the counter has just been cleared (waves that have left since may have added to it): read it afresh
-    count = __hip_atomic_load(a.ctl + kCtlGroupWord0 + h.group * kCtlLineWords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!handover_whole(pk.sig, pk.mark)) {
+    handover_set_up(a);
+    // the counter has just been set up (workgroups that have left since may have added to it): read it afresh
+    count = handover_load(a.ctl + ctl_counter(ctl_group(blockIdx.x)));
   }
-  const unsigned long long epoch = count >> a.ctl_shift;
+  const unsigned long long epoch = ctl_epoch(count);
   const unsigned elo = __builtin_amdgcn_readfirstlane((unsigned)epoch);
   const unsigned ehi = __builtin_amdgcn_readfirstlane((unsigned)(epoch >> 32));
   h.token = (a.token ^ ((((unsigned long long)ehi << 32) | elo) * 0x9E3779B97F4A7C15ull)) | 1ull;
   return h;
 }
 
-__device__ __forceinline__ void handover_leave(const DecArgs& a, const Handover& h) {
-  if ((threadIdx.x & 63) == 0)
-    (void)__hip_atomic_fetch_add(a.ctl + kCtlGroupWord0 + h.group * kCtlLineWords, h.add, __ATOMIC_RELAXED,
+__device__ __forceinline__ void handover_leave(const DecArgs& a) {
+  const int lane = threadIdx.x & 63, wg = blockIdx.x;
+  if (lane == 0)
+    (void)__hip_atomic_fetch_add(a.ctl + ctl_counter(ctl_group(wg)), ctl_arrival(wg, a.workgroups), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
+  if (wg == 0 && lane >= a.workgroups && lane < kCtlGroups)
+    (void)__hip_atomic_fetch_add(a.ctl + ctl_counter(lane), kCtlArrivalOfNone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // XSMALL > 0: the activation tile of a block holds only as many token rows as XSMALL copy instructions
@@ -305,7 +306,8 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
   bool shared_row = false;
   Handover hand{};  // single-launch MLP only
   HandoverPeek peek{};
-  if (ROLE != kDecAlone) peek = handover_peek(a);
+  // (of a producer only the wave that publishes needs the token, and not before it publishes)
+  if (ROLE == kDecConsumer || (ROLE == kDecProducer && wave == 0)) peek = handover_peek(a);
   if (CHUNK) {
     const int ci = unit / C::SLICES;
     if (ci >= ld_idx(a.hdr, 0)) return;  // the grid is sized by an upper bound of the number of chunks
@@ -459,7 +461,6 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
     asm volatile("" ::: "memory");
   };
 
-  // a producer draws the launch's token while its first copies are in flight; it needs it only to publish
   if constexpr (C::WREG) {
     // Fragment (k-step s, lane group g) of weight row l16 = bytes [(4 s + g) * 16, +16) of that row.  Two
     // register sets take turns: the fragments of the next block are on their way while one block is
@@ -479,7 +480,6 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
     if (cnt > 1) load_w(w1s, 1);
     wait_for_h();
     if (cnt > 0) issue_x(0);
-    if (ROLE == kDecProducer) hand = handover_begin(a, peek);
     // Requests retire in issue order: W 0, W 1, X 0, and then per block j: X j+1, W j+2.  When block j
     // starts, the only requests younger than its activation tile are the KST loads of W j+1 (j >= 1).
     auto block = [&](bf16x8 (&wcur)[KST], int j) {
@@ -525,7 +525,6 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
     if (cnt > 0) issue_w(0);
     wait_for_h();
     if (cnt > 0) issue_x(0);
-    if (ROLE == kDecProducer) hand = handover_begin(a, peek);
 #pragma unroll 1
     for (int j = 0; j < cnt; ++j) {
       const bool more = j + 1 < cnt;
@@ -580,7 +579,6 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
     for (int j = 0; j < NSLOT - 1; ++j)
       if (j < cnt) issue(j);
   }
-  if (ROLE == kDecProducer) hand = handover_begin(a, peek);
 
 #pragma unroll 1
   for (int j = 0; j < cnt; ++j) {
@@ -635,10 +633,7 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
         for (int j = 0; j < 4; ++j) red[wave - 1][m][tt][j][lane] = acc[m][tt][j];
   }
   __syncthreads();
-  if (wave > 0) {
-    if (ROLE != kDecAlone) handover_leave(a, hand);
-    return;
-  }
+  if (wave > 0) return;
 #pragma unroll
   for (int m = 0; m < NM; ++m)
 #pragma unroll
@@ -646,6 +641,8 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         acc[m][tt][j] += (red[0][m][tt][j][lane] + red[1][m][tt][j][lane]) + red[2][m][tt][j][lane];
+
+  if (ROLE == kDecProducer) hand = handover_begin(a, peek);
 
   // ---- epilogue.  Result layout of the 16x16 tile: lane -> weight row l16, register j -> token 4*g + j.
   const int64_t row = (int64_t)r * B + q * 16 + l16;
@@ -682,7 +679,7 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
     if (lane == 0 && !a.withhold)
       __hip_atomic_store(a.slots + (int64_t)r * C::SLICES + q, hand.token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (ROLE != kDecAlone) handover_leave(a, hand);
+  if (ROLE != kDecAlone) handover_leave(a);
 }
 
 // The consumer of the single-launch MLP at up to kTaggedTokens tokens.  H does not travel as values followed by a slot
@@ -696,7 +693,6 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
 // Cold weights, microseconds a layer, slots / words: 1B shape at 1, 2, 4 tokens 9.95 / 8.55, 10.2 / 9.1, 10.7 / 10.1; 8B
 // shape 11.2 / 9.4, 11.3 / 9.8, 11.8 / 11.5.  (128-wide blocks: the registers are held to five waves per SIMD, which is
 // what keeps the 8B-shaped launch resident at once; without that it loses at 2 and 4 tokens, 11.8 and 12.2.)
-constexpr int kTaggedTokens = 4;
 constexpr int tagged_blocks(int b) { return b == 64 ? 4 : 2; }  // blocks of a wave taken at a time
 constexpr size_t tagged_consumer_lds(int b, int ntok) {        // four waves' values, or the partial sums of three
   const size_t values = (size_t)4 * tagged_blocks(b) * ntok * b * 2, sums = 3 * 4 * 64 * 4;
@@ -808,8 +804,8 @@ __device__ __forceinline__ void decode_consumer_tagged(const DecArgs& a, const i
           reinterpret_cast<float*>(a.Y)[off] = y;
       }
     }
+    handover_leave(a);
   }
-  handover_leave(a, hand);
 }
 
 template <int B, bool DUAL, int NTT, bool CHUNK, int XSMALL, bool POST = false, bool W8 = false>

@@ -136,6 +136,54 @@ def test_tagged_words(api, b, T, out_dtype):
         assert api.sparse_mlp_status(dev[0], T, ws) == 0
 
 
+@pytest.mark.parametrize("b,I", [(64, 512), (64, 2048), (64, 4096), (128, 1024)])
+def test_token_counts_and_widths_change_on_one_workspace(api, b, I):
+    """A decoding program whose batch changes from call to call, and two layers of different width, on one workspace and on
+    the library's own array: eager calls of both MLP forms, and graphs captured at one and two tokens replayed in turn
+    between them, with new activations each time.  Every wait ends normally."""
+    import torch
+
+    E = 4 * b
+    rng, dev, ref, _ = _layer(api, 8400 + b + I, E, I, b, 0.6)
+    _, dev2, ref2, _ = _layer(api, 8500 + b + I, E, I + 6 * b, b, 0.6)
+    size = max(api.mlp_workspace_bytes(*d, T) for d in (dev, dev2) for T in (1, 2, 3, 4, 5, 8))
+    ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device="cuda:0")
+    graphs = {}
+    for T in (1, 2):
+        xs, y = torch.zeros((T, E), dtype=torch.bfloat16, device="cuda:0"), torch.empty((T, E), device="cuda:0")
+        torch.cuda.synchronize()
+        graphs[T] = (torch.cuda.CUDAGraph(), xs, y)
+        with torch.cuda.graph(graphs[T][0]):
+            api.sparse_mlp(*dev, xs, out=y, ws=ws)
+
+    def replay(T, what):
+        graph, xs, y = graphs[T]
+        x = synth.gauss_bf16(rng, (T, E), 1.0)
+        xs.copy_(to_dev(x))
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        check_close(y.cpu().numpy().T, orc.mlp(*ref, x), f"{what}, replay T={T}")
+
+    for n, T in enumerate((1, 2, 1, 4, 3, 5, 2, 8, 1)):
+        for layer, (d, r) in enumerate(((dev, ref), (dev2, ref2))):
+            what = f"b={b} I={I} call {n} T={T} layer {layer}"
+            x = synth.gauss_bf16(rng, (T, E), 1.0)
+            want = orc.mlp(*r, x)
+            y = api.sparse_mlp(*d, to_dev(x), ws=ws)
+            y_static = api.sparse_mlp_static(*d, to_dev(x), torch.full_like(y, float("nan")))
+            z = api.sparse_mlp2(d[0], d[2], to_dev(x), ws=ws)
+            torch.cuda.synchronize()
+            check_close(y.cpu().numpy().T, want, what)
+            check_close(y_static.cpu().numpy().T, want, what + " static")
+            check_close(z.cpu().numpy().T, orc.mlp2(r[0], r[2], x), what + " two-matrix")
+        replay(2 if n % 2 else 1, what)
+        replay(1 if n % 2 else 2, what)
+    for T in (1, 2, 3, 4, 5, 8):
+        assert api.sparse_mlp_status(dev[0], T, ws) == 0
+        assert api.sparse_mlp_status(dev[0], T, None) == 0
+
+
 @pytest.mark.parametrize("b,T", [(64, 3), (128, 1), (64, 40), (128, 16), (128, 24)])
 def test_a_wait_that_expires_gives_nan_rows_and_a_status(api, b, T):
     """Forced from the host: the producers never publish, the consumers poll 20 times and give up.  Every
