@@ -31,7 +31,9 @@ constexpr uint64_t kCtlEpochMask = (uint64_t(1) << kCtlEpochBits) - 1;
 constexpr uint64_t kCtlMagic = 0xB1A57;                  // top 20 bits of a signature
 constexpr uint64_t kCtlBusy = 0xB1A58B0057EED00Dull;     // in the place of a signature: a wave is setting the block up
 static_assert(kCtlMagic >> (64 - kCtlEpochBits) == 0 && kCtlBusy >> kCtlEpochBits != kCtlMagic, "a signature is never busy");
-// `clock`: a counter of 100 MHz; between two set-ups lies a launch, more than 640 ns.
+// `clock`: a counter of 100 MHz.  A launch takes longer than one of the ticks of 640 ns that a signature counts, so that the
+// epoch, which begins at the time of the set-up and advances by one per launch, stays behind the clock: no epoch comes back
+// when the block is set up again, and a word or slot that was left by another launch of a recorded call never fits.
 constexpr uint64_t ctl_signature(uint64_t clock) { return (kCtlMagic << kCtlEpochBits) | ((clock >> 6) & kCtlEpochMask); }
 constexpr bool ctl_is_signature(uint64_t word) { return word >> kCtlEpochBits == kCtlMagic; }
 // (time in the low bits, position in the top ones: fits neither another mark nor another set-up's)
@@ -52,11 +54,13 @@ constexpr uint64_t ctl_arrival(int workgroup, int workgroups) {
 // Groups without a member, [n, kCtlGroups) of a launch of n < kCtlGroups workgroups: workgroup 0 adds for them.
 constexpr uint64_t kCtlArrivalOfNone = uint64_t(1) << kCtlShift;
 constexpr uint64_t ctl_epoch(uint64_t counter) { return counter >> kCtlShift; }
+// Whether a counter can be one of the block with this signature (of any age that occurs), not what stood there before.
+constexpr bool ctl_epoch_fits(uint64_t epoch, uint64_t signature) { return ((epoch - signature) & kCtlEpochMask) >> 32 == 0; }
 // What the set-up writes into word `i` > 0 of the block.
 constexpr uint64_t ctl_initial(int i, uint64_t signature) {
   if (i % kCtlMarkWords == 0) return ctl_mark_value(signature, i / kCtlMarkWords - 1);
   if (i == kCtlWords - 1) return ctl_mark_value(signature, kCtlMarks - 1);
-  return 0;
+  return i % kCtlLineWords == 8 ? signature << kCtlShift : 0;  // (the counters, and two words that nobody reads)
 }
 
 // ---- workspace -----------------------------------------------------------------------------------------------------

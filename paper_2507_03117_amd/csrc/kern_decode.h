@@ -123,7 +123,8 @@ constexpr int kHandoverTimedOut = 1, kHandoverInitTimedOut = 2;
 // and, when it leaves, adds 1 to its group's counter - the group's first workgroup adds the rest up to 2^20 as
 // well, so that a launch of any shape adds exactly 2^20 to every counter.  A counter therefore stays inside
 // [epoch * 2^20, (epoch + 1) * 2^20) until the last workgroup of its group leaves, by when all of them have read it,
-// and counter >> 20 is the same number for every wave of the launch and one more for the next launch.
+// and counter >> 20 is the same number for every wave of the launch and one more for the next launch; it begins at the
+// time of the set-up, so that no epoch ever comes back.
 // Nobody waits for anybody, no addition returns a value, and no address takes more than a few dozen
 // additions per launch.  Launches on one workspace are ordered by their stream (overlapping calls need
 // different workspaces), and what a launch added is visible when the next one starts.
@@ -192,16 +193,18 @@ __device__ __forceinline__ void handover_set_up(const DecArgs& a) {
 
 __device__ __forceinline__ Handover handover_begin(const DecArgs& a, const HandoverPeek& pk) {
   Handover h{};
-  unsigned long long count = pk.count;
-  if (!handover_whole(pk.sig, pk.mark)) {
+  auto epoch_of = [](unsigned long long count) {
+    const unsigned long long e = ctl_epoch(count);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)e), hi = __builtin_amdgcn_readfirstlane((unsigned)(e >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+  };
+  unsigned long long epoch = epoch_of(pk.count);
+  if (!handover_whole(pk.sig, pk.mark) || !ctl_epoch_fits(epoch, pk.sig)) {
     handover_set_up(a);
     // the counter has just been set up (workgroups that have left since may have added to it): read it afresh
-    count = handover_load(a.ctl + ctl_counter(ctl_group(blockIdx.x)));
+    epoch = epoch_of(handover_load(a.ctl + ctl_counter(ctl_group(blockIdx.x))));
   }
-  const unsigned long long epoch = ctl_epoch(count);
-  const unsigned elo = __builtin_amdgcn_readfirstlane((unsigned)epoch);
-  const unsigned ehi = __builtin_amdgcn_readfirstlane((unsigned)(epoch >> 32));
-  h.token = (a.token ^ ((((unsigned long long)ehi << 32) | elo) * 0x9E3779B97F4A7C15ull)) | 1ull;
+  h.token = (a.token ^ (epoch * 0x9E3779B97F4A7C15ull)) | 1ull;
   return h;
 }
 
@@ -687,8 +690,9 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
 // until it carries the tag, and then the value is at hand.  That takes three trips to the memory side off the chain
 // between the last producer's sums and the last consumer's product: the acknowledgement of the values' stores, the slot's
 // own way, and the load of the values after the slot has been seen.  Nothing has to be ordered - a word is written by one
-// 64-bit store and read by one 64-bit load, both past the L2s - and nothing cleared: a word left by another launch or by
-// anyone else carries the tag of this one with probability 2^-48.  A value costs eight bytes instead of two, so this is
+// 64-bit store and read by one 64-bit load, both past the L2s - and nothing cleared: no other launch has had this token
+// (calls differ in the host's, launches of a recorded call in the epoch), and a word left by another launch or by anyone
+// else carries its upper 48 bits with probability 2^-48.  A value costs eight bytes instead of two, so this is
 // for a few tokens; the weight fragments, which do not depend on H, are in registers before the first word is asked for.
 // Cold weights, microseconds a layer, slots / words: 1B shape at 1, 2, 4 tokens 9.95 / 8.55, 10.2 / 9.1, 10.7 / 10.1; 8B
 // shape 11.2 / 9.4, 11.3 / 9.8, 11.8 / 11.5.  (128-wide blocks: the registers are held to five waves per SIMD, which is

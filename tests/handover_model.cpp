@@ -5,11 +5,14 @@
 // stdin: one sequence per line, calls "form:I:E:T[:base]" separated by blanks; the workspace begins `base` bytes into the
 // memory (0).  Forms: slots, words (single-launch forms), plain (two launches: H only), low (another use of the memory: 2 T I
 // bytes from the base on, as the MLP on E5M2 weights), pieces (another use: 512-byte pieces I to I + T of the memory).
+// A call that is written twice stands for a recorded one: it carries the same host token each time, and no two launches of it
+// may see the same epoch, whatever happened in between.
 // stdout: one line per sequence, "ok" or what went wrong first.
 #include <algorithm>
 #include <cstdio>
 #include <iostream>
 #include <random>
+#include <set>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -28,6 +31,7 @@ static std::string play(const std::vector<Call>& calls, std::mt19937_64& rng) {
   for (const Call& c : calls) bytes = std::max(bytes, c.base + tagged_offset(c.I, c.T) + (size_t)(c.T * c.I * 8));
   std::vector<uint64_t> mem(bytes / 8);
   uint64_t clock = rng() >> 8;
+  std::set<std::pair<std::string, uint64_t>> seen;  // (call, epoch)
   for (auto& w : mem) w = rng();
   auto fill = [&](size_t byte, size_t bytes) {
     for (size_t i = byte / 8; i < (byte + bytes + 7) / 8; ++i) mem.at(i) = rng();
@@ -81,6 +85,9 @@ static std::string play(const std::vector<Call>& calls, std::mt19937_64& rng) {
     }
     for (int w = 0; w < wgs; ++w)
       if (epoch[w] != epoch[0]) return fail("the workgroups of the launch read different epochs");
+    std::ostringstream name;
+    name << c.form << ":" << c.I << ":" << c.E << ":" << c.T << ":" << c.base;
+    if (!seen.insert({name.str(), epoch[0]}).second) return fail("an earlier launch of the same call had this epoch");
     // what the launch writes
     if (c.form == "words") {
       fill(c.base + tagged_offset(c.I, c.T), (size_t)(c.T * c.I * 8));

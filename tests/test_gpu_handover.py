@@ -184,6 +184,32 @@ def test_token_counts_and_widths_change_on_one_workspace(api, b, I):
         assert api.sparse_mlp_status(dev[0], T, None) == 0
 
 
+@pytest.mark.parametrize("b,T", [(64, 1), (64, 4), (64, 16), (128, 2), (128, 16)])
+def test_replays_after_the_control_block_was_written_over(api, b, T):
+    """Something else is written over the start of the workspace between two replays of a recorded call, so that the
+    hand-over state is set up afresh, while the words or slots and H of the replay before stay: no replay takes them."""
+    import torch
+
+    E, I = 4 * b, 16 * b
+    rng, dev, ref, _ = _layer(api, 8600 + b + T, E, I, b, 0.5)
+    ws = torch.randint(0, 256, (api.mlp_workspace_bytes(*dev, T),), dtype=torch.uint8, device="cuda:0")
+    xs = to_dev(synth.gauss_bf16(rng, (T, E), 1.0))
+    y = torch.empty((T, E), device="cuda:0")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        api.sparse_mlp(*dev, xs, out=y, ws=ws)
+    for rep, written in enumerate((0, 8, 512, 2048, 8448, 0, 8, 8, 4096)):
+        ws[:written].random_(0, 256)
+        x = synth.gauss_bf16(rng, (T, E), 1.0)
+        xs.copy_(to_dev(x))
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        check_close(y.cpu().numpy().T, orc.mlp(*ref, x), f"replay {rep} after {written} bytes, b={b} T={T}")
+        assert api.sparse_mlp_status(dev[0], T, ws) == 0
+
+
 @pytest.mark.parametrize("b,T", [(64, 3), (128, 1), (64, 40), (128, 16), (128, 24)])
 def test_a_wait_that_expires_gives_nan_rows_and_a_status(api, b, T):
     """Forced from the host: the producers never publish, the consumers poll 20 times and give up.  Every

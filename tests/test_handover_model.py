@@ -34,7 +34,7 @@ def _check(model, sequences):
 
 @pytest.mark.parametrize("I", [64, 512, 1024, 2048, 4096, 8192])
 def test_token_counts_on_one_workspace(model, I):
-    """Every pair of (form, tokens) in turn, and all orders of three of the smallest: all workgroups of each launch see one epoch."""
+    """Every pair of (form, tokens) in turn, and all orders of three of the smallest: all workgroups of each launch see one epoch, and no other launch of the call did."""
     forms = [("words", T) for T in (1, 2, 3, 4)] + [("slots", T) for T in (1, 2, 3, 4, 5, 8, 13, 16, 32, 64)] + [("plain", 65)]
     pairs = [[_call(*x) for x in ((a, I, s), (b, I, t), (a, I, s), (a, I, s))] for (a, s), (b, t) in itertools.permutations(forms, 2)]
     triples = [[_call(a, I, t) for a, t in order] * 2 for order in itertools.permutations(forms[:4] + [("slots", 5)], 3)]
