@@ -390,7 +390,8 @@ int blast_bsr_spmm_workspace(const blast_bsr_view* W, int64_t T, size_t* ws_byte
  * scratch exactly when the path applies, and a call handed the smaller workspace of the plain path takes the
  * plain path.
  * With 64- and 128-wide blocks at up to 4 tokens it also includes room for the intermediate as 64-bit words, by which
- * the single-launch form hands it over faster (8 T I bytes); a call handed the smaller workspace does without.
+ * the single-launch form hands it over faster (8 T I bytes; beyond 4 tokens what 4 need, so that the size for the largest
+ * batch serves the smaller ones); a call handed the smaller workspace does without.
  * With 16 x 16 blocks, from 33 tokens on, blast_sparse_mlp_workspace() also includes room for X regrouped by
  * block column (see blast_bsr_spmm); H is then kept in the same form.  A call handed the smaller workspace reads
  * X as it lies.

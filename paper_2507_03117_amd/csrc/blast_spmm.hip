@@ -748,7 +748,7 @@ extern "C" int blast_sparse_mlp_workspace(const blast_bsr_view* Wgate, const bla
   if (int rc = check_view(Wup)) return rc;
   if (int rc = check_view(Wdown)) return rc;
   if (T < 0 || !ws_bytes) return BLAST_ERR_INVALID_ARG;
-  *ws_bytes = mlp_workspace_bytes(Wgate->rows, T) + tagged_bytes(Wgate->b, Wgate->rows, T) + mlp_long_bytes(Wgate, Wup, T) +
+  *ws_bytes = mlp_query_bytes(Wgate->b, Wgate->rows, T) + mlp_long_bytes(Wgate, Wup, T) +
               ((Wgate->b == 16 && T >= kGroup16MinTokens) ? group16_bytes(Wgate->cols, T) : 0);
   return BLAST_OK;
 }
@@ -758,7 +758,7 @@ extern "C" int blast_sparse_mlp2_workspace(const blast_bsr_view* W1, const blast
   if (int rc = check_view(W1)) return rc;
   if (int rc = check_view(W2)) return rc;
   if (T < 0 || !ws_bytes) return BLAST_ERR_INVALID_ARG;
-  *ws_bytes = mlp_workspace_bytes(W1->rows, T) + tagged_bytes(W1->b, W1->rows, T) +
+  *ws_bytes = mlp_query_bytes(W1->b, W1->rows, T) +
               ((W1->b == 16 && T >= kGroup16MinTokens) ? group16_bytes(W1->cols, T) : 0);
   return BLAST_OK;
 }

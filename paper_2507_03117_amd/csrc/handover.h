@@ -80,5 +80,12 @@ constexpr size_t tagged_offset(int64_t I, int64_t T) { return mlp_workspace_byte
 constexpr size_t tagged_bytes(int32_t b, int64_t I, int64_t T) {
   return (b == 64 || b == 128) && T <= kTaggedTokens ? (size_t)T * (size_t)I * 8 : 0;
 }
+// What the queries ask for: enough for every smaller call as well, so that a program that asks once, for its largest batch,
+// has the words at the smaller ones.
+constexpr size_t mlp_query_bytes(int32_t b, int64_t I, int64_t T) {
+  const int64_t few = T < kTaggedTokens ? T : kTaggedTokens;
+  const size_t own = mlp_workspace_bytes(I, T), smaller = mlp_workspace_bytes(I, few) + tagged_bytes(b, I, few);
+  return own > smaller ? own : smaller;
+}
 
 }  // namespace blast_dev

@@ -158,3 +158,20 @@ def test_spmm_and_mlp_argument_errors_return_before_any_launch():
     # pack: null outputs / bad ld are rejected up front
     nnz = C.c_int64(0)
     assert L.blast_bsr_pack(None, 128, 128, 128, 64, 0, None, 0.0, None, None, None, None, None, 0, 4, C.byref(nnz), None, None, 0, None) == -1
+
+
+@pytest.mark.parametrize("b", [32, 64, 128])
+@pytest.mark.parametrize("I", [128, 4096, 14336])
+def test_mlp_workspace_for_the_largest_batch_serves_the_smaller_ones(b, I):
+    """A program that asks once takes every token count up to that one at full speed: the size never shrinks with T."""
+    L = api.lib()
+    ptr = C.cast((C.c_int32 * 4)(), C.c_void_p)
+    g, d = api.BsrView(I, 128, b, 0, 0, ptr, None, None, None, None), api.BsrView(128, I, b, 0, 0, ptr, None, None, None, None)
+    ws = C.c_size_t(0)
+    sizes = []
+    for T in range(0, 130):
+        assert L.blast_sparse_mlp_workspace(C.byref(g), C.byref(g), C.byref(d), T, C.byref(ws)) == 0
+        sizes.append(ws.value)
+        assert L.blast_sparse_mlp2_workspace(C.byref(g), C.byref(d), T, C.byref(ws)) == 0
+        assert ws.value == sizes[-1]
+    assert sizes == sorted(sizes)
