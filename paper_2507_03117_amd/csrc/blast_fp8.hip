@@ -86,17 +86,24 @@ int launch_fp8_stream(const Fp8Args& f, hipStream_t stream) {
   sa.x8_half = f.x_cg ? (uint32_t)f.x_cg : 64u;
   const int64_t slab = ((int64_t)a.ntt + 7) / 8 * C::TT * f.kdim;
   const int64_t grid = stream_grid<C, B>(sa, a.nbr, cu_count_fp8(), slab);
-  static blast::DeviceFlags lds_set;
-  int dev = 0;
-  BLAST_HIP_TRY(hipGetDevice(&dev));
-  if (!lds_set.test(dev)) {
-    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_spmm_stream<B, false, TW, false, false, NW, false, true>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES));
-    lds_set.set(dev);
+  auto launch = [&](auto pairs) -> int {
+    constexpr auto kernel = &k_spmm_stream<B, false, TW, false, false, NW, false, true, pairs.value>;
+    static blast::DeviceFlags lds_set;
+    int dev = 0;
+    BLAST_HIP_TRY(hipGetDevice(&dev));
+    if (!lds_set.test(dev)) {
+      BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)C::LDS_BYTES));
+      lds_set.set(dev);
+    }
+    kernel<<<dim3((unsigned)grid), dim3(64 * NW), C::LDS_BYTES, stream>>>(sa);
+    BLAST_LAUNCH_CHECK("k_spmm_stream (E5M2)");
+    return BLAST_OK;
+  };
+  if constexpr (C::PAIR) {
+    if (!a.y_fast || !a.y_pairs) return launch(std::false_type{});
   }
-  k_spmm_stream<B, false, TW, false, false, NW, false, true><<<dim3((unsigned)grid), dim3(64 * NW), C::LDS_BYTES, stream>>>(sa);
-  BLAST_LAUNCH_CHECK("k_spmm_stream (E5M2)");
-  return BLAST_OK;
+  return launch(std::true_type{});
 }
 
 template <int B>

@@ -231,23 +231,27 @@ int launch_stream_tw(TileArgs a, const ChunkPlan& plan, int64_t k_features, hipS
     k_zero_shared_rows<B><<<dim3((unsigned)plan.max_chunks, (unsigned)((a.T + 63) / 64)), dim3(256), 0, stream>>>(sa);
     BLAST_LAUNCH_CHECK("k_zero_shared_rows");
   }
-  if constexpr (!DUAL && !CHUNK && !LONG) {
-    if (a.act >= 0) {  // single matrix with an activation on the output
-      static blast::DeviceFlags lds_set_post;
-      if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_spmm_stream<B, false, TW, false, true, NW>),
-                                    C::LDS_BYTES, lds_set_post))
-        return rc;
-      k_spmm_stream<B, false, TW, false, true, NW><<<dim3((unsigned)grid), dim3(64 * NW), C::LDS_BYTES, stream>>>(sa);
-      BLAST_LAUNCH_CHECK("k_spmm_stream");
-      return BLAST_OK;
+  // (two rows to a store: only where Y allows it, and only instances whose waves hold two rows side by side)
+  auto launch = [&](auto post, auto pairs) -> int {
+    constexpr auto kernel = &k_spmm_stream<B, DUAL, TW, CHUNK, post.value, NW, LONG, false, pairs.value>;
+    static blast::DeviceFlags lds_set;
+    if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(kernel), C::LDS_BYTES, lds_set)) return rc;
+    kernel<<<dim3((unsigned)grid), dim3(64 * NW), C::LDS_BYTES, stream>>>(sa);
+    BLAST_LAUNCH_CHECK("k_spmm_stream");
+    return BLAST_OK;
+  };
+  auto launch_post = [&](auto pairs) -> int {
+    if constexpr (!DUAL && !CHUNK && !LONG) {
+      if (a.act >= 0) return launch(std::true_type{}, pairs);  // single matrix with an activation on the output
     }
-  }
-  static blast::DeviceFlags lds_set;
-  if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_spmm_stream<B, DUAL, TW, CHUNK, false, NW, LONG>),
-                                C::LDS_BYTES, lds_set))
-    return rc;
-  k_spmm_stream<B, DUAL, TW, CHUNK, false, NW, LONG><<<dim3((unsigned)grid), dim3(64 * NW), C::LDS_BYTES, stream>>>(sa);
-  BLAST_LAUNCH_CHECK("k_spmm_stream");
+    return launch(std::false_type{}, pairs);
+  };
+  int rc;
+  if constexpr (C::PAIR && !CHUNK && !LONG)
+    rc = a.y_fast && a.y_pairs ? launch_post(std::true_type{}) : launch_post(std::false_type{});
+  else
+    rc = launch_post(std::true_type{});
+  if (rc) return rc;
   if constexpr (LONG) {
     k_long_finish<B><<<dim3((unsigned)((a.nbr + kLongFinishRows - 1) / kLongFinishRows),
                             (unsigned)((a.T + kLongFinishTokens - 1) / kLongFinishTokens)),

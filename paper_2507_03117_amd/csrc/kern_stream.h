@@ -82,8 +82,8 @@ struct StreamCfg {
   __device__ static __forceinline__ int key(int row) { return (row / KEY_DIV) % KEY_MOD; }
   static constexpr bool PAIR = PAIRS && NI == 2;
   // Which weight row of a wave's tile is column l32 of matrix tile ni: with two matrix tiles, neighbouring rows, so that a
-  // lane ends up with two neighbouring rows of a token and stores them together (see the epilogue).  Not with chunks,
-  // whose rows are added to by atomics, nor where fp32 sums go to scratch value by value: lanes side by side do better
+  // lane ends up with two neighbouring rows of a token and stores them together (see the epilogue).  Not in the instances
+  // (PAIRS = false) for outputs that do not allow it, where lanes hold neighbouring rows instead, nor with chunks, whose rows are added to by atomics, nor where fp32 sums go to scratch value by value: lanes side by side do better
   // there (405B-class MLP with Zipf rows, 2048 tokens: 718 / 737 us; 512: 288 / 354).
   __device__ static __forceinline__ int row_of(int l32, int ni) { return PAIR ? 2 * l32 + ni : ni * 32 + l32; }
   // The swizzle key of a weight row: that of the lane which reads it, key(l32).
@@ -447,13 +447,14 @@ __device__ __forceinline__ void stream_zero_side(const StreamArgs& sa, int w, in
 // (the first half of a two-matrix MLP).
 // LONG: the gated product with its long rows cut into chunks and finished by a later launch, see StreamArgs.
 // F8: both operands in E5M2 (MatDev::vals8; X bytes).
-template <int B, bool DUAL, int TW, bool CHUNK, bool POST = false, int NW = 4, bool LONG = false, bool F8 = false>
+// PAIRS: Y allows it that a lane stores two neighbouring rows as one value (y_fast and y_pairs; where StreamCfg::PAIR).
+template <int B, bool DUAL, int TW, bool CHUNK, bool POST = false, int NW = 4, bool LONG = false, bool F8 = false, bool PAIRS = true>
 __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)) void k_spmm_stream(const StreamArgs sa) {
   static_assert(!F8 || (!DUAL && !CHUNK && !POST && !LONG), "the E5M2 product is a plain one");
   static_assert(!(DUAL && CHUNK), "the activation needs complete sums: the gated product is never split");
   static_assert(!POST || (!DUAL && !CHUNK), "an activation on the output needs complete sums of a single matrix");
   static_assert(!LONG || (DUAL && !CHUNK), "long rows are a matter of the gated product");
-  using C = StreamCfg<B, TW, NW, F8, !CHUNK && !LONG>;
+  using C = StreamCfg<B, TW, NW, F8, PAIRS && !CHUNK && !LONG>;
   const TileArgs& a = sa.t;
   const int n_items = LONG    ? (long_chunks(sa.hdr) + long_chunks(sa.hdr1) + a.nbr) * a.ntt
                       : CHUNK ? ld_idx(sa.hdr, 0) * a.ntt
@@ -855,7 +856,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
     // per item and a 32-bit lane offset per store, so that a stored value costs a conversion, an add and the store
     // instead of 64-bit address arithmetic; in a tile that the tokens end in, a comparison as well.  (A tile of 40 of
     // 64 tokens on the general path below: 2 us after everyone else.  1024 x 1024 in E5M2, 200 tokens: 8.2 -> 6.2 us.)
-    // Two neighbouring rows of a token leave as one value where Y allows it: half the store instructions (53248 x 16384 in
+    // Two neighbouring rows of a token leave as one value in the instances that hold them side by side: half the store instructions (53248 x 16384 in
     // E5M2, 1000 tokens, with the quantiser: 95 -> 93 us; the others within 1 %).
     // How the output leaves, by what was measured (microseconds, ordinary / through the L2 / non-temporal; repeated calls,
     // then calls on inputs and outputs that no cache holds):
@@ -863,9 +864,12 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
     //     tokens 27.3 / 26.1 / 26.7; two-matrix MLP of 1600 and 6400 features, 333 tokens 29.2 / 28.6; 3B-shaped MLP at
     //     70 %, 4096 tokens 249 / 247 / 251; E5M2, 8192 x 3072 at 80 %, 700 tokens 19.1 / 18.4 / 18.6.
     //   128-wide blocks in bf16: ordinary (405B-class MLP, 2048 tokens: 715 / 722 / 751).
-    //   128-wide blocks in E5M2: non-temporal.  The output is the larger part of what moves, and the last-level cache keeps
-    //     the inputs instead of it: 53248 x 16384, 1000 tokens, with the quantiser 95 / 93 / 78, cold 111 / 109 / 114; 2048
-    //     tokens, fp32 output 210 / 213 / 200; 14336 x 4096 at 80 %, 2048 tokens 43.8 / 41.7 / 40.7, cold 65 / 63.5 / 61.6.
+    //   128-wide blocks in E5M2: non-temporal.  The output is the
+    //     larger part of what moves, and the last-level cache keeps the inputs instead of it: 53248 x 16384, 1000 tokens, with
+    //     the quantiser 95 / 93 / 78, cold 111 / 109 / 114; 2048 tokens, fp32 output 180 / 182 / 157, cold 183 / 183 / 171.
+    //   An output whose rows may not be stored in pairs: ordinary, so that the L2 puts lines together that are written in
+    //     parts.  (Through or past it with rows two apart: up to 1.9 times as long; 8192 x 3072 at 70 %, 64-wide, 2048 tokens,
+    //     odd pitch, fp32 47.0 / 61.5 us, in E5M2 with 14336 x 4096 at 90 %, 128-wide, bf16 29.3 / 56.0.)
     enum { kStoreOrdinary, kStoreThrough, kStoreStreaming };
     constexpr int kStores = B < 128 ? kStoreThrough : F8 ? kStoreStreaming : kStoreOrdinary;
     if (a.y_fast && !(CHUNK && shared_row)) {
@@ -874,16 +878,16 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
       const int lane_left = left - 4 * lh;
       typedef __bf16 Bf16Pair __attribute__((ext_vector_type(2)));
       typedef float F32Pair __attribute__((ext_vector_type(2)));
-      auto put_at = [](auto* p, auto v) {
-        if constexpr (kStores == kStoreStreaming)
+      auto put_at = [](auto policy, auto* p, auto v) {
+        if constexpr (policy.value == kStoreStreaming)
           __builtin_nontemporal_store(v, p);
-        else if constexpr (kStores == kStoreThrough)
+        else if constexpr (policy.value == kStoreThrough)
           store_through(p, v);
         else
           *p = v;
       };
-      auto store_tile = [&](auto bf16, auto whole, auto pairs) {
-        constexpr uint32_t kEsz = bf16.value ? 2u : 4u, kStep = C::PAIR ? 1u : 32u;
+      auto store_tile = [&](auto bf16, auto whole, auto policy) {
+        constexpr uint32_t kEsz = bf16.value ? 2u : 4u;
         uint32_t pitch = (uint32_t)a.syt * kEsz;
         // opaque to the optimiser: otherwise the 32 multiples of the pitch are computed once before the
         // loop over items and kept (spilled) for the whole kernel
@@ -897,29 +901,29 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
             // the token step goes into the uniform base, the lane offset stays one register
             unsigned char* p = base + __builtin_amdgcn_readfirstlane((uint32_t)dt * pitch) + off0;
             if (whole.value || dt < lane_left) {
-              if constexpr (C::PAIR && pairs.value) {
+              if constexpr (C::PAIR) {
                 if constexpr (bf16.value)
-                  put_at(reinterpret_cast<Bf16Pair*>(p),
+                  put_at(policy, reinterpret_cast<Bf16Pair*>(p),
                          Bf16Pair{static_cast<__bf16>(acc0[mi][0][j]), static_cast<__bf16>(acc0[mi][1][j])});
                 else
-                  put_at(reinterpret_cast<F32Pair*>(p), F32Pair{acc0[mi][0][j], acc0[mi][1][j]});
+                  put_at(policy, reinterpret_cast<F32Pair*>(p), F32Pair{acc0[mi][0][j], acc0[mi][1][j]});
               } else {
 #pragma unroll
                 for (int ni = 0; ni < C::NI; ++ni) {
                   if constexpr (bf16.value)
-                    put_at(reinterpret_cast<uint16_t*>(p + ni * kStep * kEsz), f32_to_bf16_rne(acc0[mi][ni][j]));
+                    put_at(policy, reinterpret_cast<uint16_t*>(p + ni * 32 * kEsz), f32_to_bf16_rne(acc0[mi][ni][j]));
                   else
-                    put_at(reinterpret_cast<float*>(p + ni * kStep * kEsz), acc0[mi][ni][j]);
+                    put_at(policy, reinterpret_cast<float*>(p + ni * 32 * kEsz), acc0[mi][ni][j]);
                 }
               }
             }
           }
       };
       auto store = [&](auto bf16, auto whole) {
-        if (C::PAIR && a.y_pairs)
-          store_tile(bf16, whole, std::true_type{});
-        else
-          store_tile(bf16, whole, std::false_type{});
+        if (PAIRS || a.y_pairs)
+          store_tile(bf16, whole, std::integral_constant<int, kStores>{});
+        else  // lines in parts: the L2 puts them together
+          store_tile(bf16, whole, std::integral_constant<int, kStoreOrdinary>{});
       };
       if (a.y_bf16) {
         if (full)
