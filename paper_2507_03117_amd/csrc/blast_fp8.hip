@@ -101,7 +101,10 @@ int launch_fp8_stream(const Fp8Args& f, hipStream_t stream) {
     return BLAST_OK;
   };
   if constexpr (C::PAIR) {
-    if (!a.y_fast || !a.y_pairs) return launch(std::false_type{});
+    // With 64-wide blocks, rows two apart at 64 bytes of pitch put eight neighbouring lanes of a fragment read on four 16-byte
+    // positions instead of eight.  Fewer, wider stores are worth it in bf16 (8192 x 3072 at 90 %, 2048 tokens, neighbouring
+    // rows / pairs 14.4 / 13.3 us; 14336 x 4096 at 70 %, 4096 tokens 100 / 96), not in fp32 (17.4 / 17.7; 107 / 112).
+    if (!a.y_fast || !a.y_pairs || (B == 64 && !a.y_bf16)) return launch(std::false_type{});
   }
   return launch(std::true_type{});
 }
