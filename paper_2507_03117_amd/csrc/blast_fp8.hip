@@ -100,6 +100,15 @@ int launch_fp8_stream(const Fp8Args& f, hipStream_t stream) {
     BLAST_LAUNCH_CHECK("k_spmm_stream (E5M2)");
     return BLAST_OK;
   };
+  // An fp32 output of 64 to 256 MiB, between a quarter of the last-level cache and all of it, with few blocks per row, so that
+  // the stores are what the launch does, is written through the L2.  Microseconds, non-temporal / through, the same buffers
+  // again and again, then buffers that no cache holds: 4096 x 4096 at 90 %, 4096 tokens 22.0 / 18.2, 23.2 / 22.9; 8192 tokens
+  // 40.2 / 32.1, 43.9 / 42.7; 14336 x 4096 at 90 %, 2048 tokens 34.3 / 30.8, 35.7 / 35.7; 4096 tokens 60.4 / 51.6, 62.8 / 63.8;
+  // 53248 x 16384 at 95 % (6.4 blocks), 1000 tokens 84.2 / 81.1, 101.7 / 99.9.  Smaller: 14336 x 4096 at 90 %, 512 tokens 11.9 /
+  // 11.1, 13.4 / 15.8; larger: 8192 tokens 113 / 126, 124 / 125; more blocks: at 70 % (9.6), 2048 tokens 53.9 / 53.2, 57.0 / 63.9.
+  const int64_t y_bytes = (int64_t)f.T * a.nbr * B * 4;
+  a.y_keep = B == 128 && !f.y_bf16 && a.y_pairs && y_bytes >= ((int64_t)64 << 20) && y_bytes <= ((int64_t)256 << 20) &&
+             f.nnz < 8 * (int64_t)a.nbr;
   if constexpr (C::PAIR) {
     // With 64-wide blocks, rows two apart at 64 bytes of pitch put eight neighbouring lanes of a fragment read on four 16-byte
     // positions instead of eight.  Fewer, wider stores are worth it in bf16 (8192 x 3072 at 90 %, 2048 tokens, neighbouring
@@ -230,6 +239,7 @@ extern "C" int blast_bsr_spmm_e5m2(const blast_bsr_view* W, const uint8_t* vals8
     a.ldx = cg ? 64 : ldx;
     a.x_cg = cg ? T * 64 : 0;
     a.kdim = W->cols;
+    a.nnz = W->nnz;
     a.Y = Y;
     a.ldy = ldy;
     a.y_bf16 = y_dtype == BLAST_BF16 ? 1 : 0;

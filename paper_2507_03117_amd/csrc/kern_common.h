@@ -32,6 +32,7 @@ struct TileArgs {
   int act;               // gated product: the activation of the gate; single matrix: < 0 none, else applied to the output
   int x_vec;             // 1: 16-byte loads of X are legal (sxk == 1, aligned)
   int y_fast;            // 1: syi == 1 and every byte offset inside a 256-token slab of Y fits 31 bits
+  int y_keep;            // E5M2 product with 128-wide blocks: 1: the output is written through the L2, else past the caches
   int y_pairs;           // 1: two neighbouring rows of a token may be stored as one value (Y and syt aligned to two values)
   int x_grp16;           // 16-wide blocks only: X is stored in column groups of 16 features, [kdim/16][T][16]
   int y_grp16;           // ... and so is Y, [rows/16][T][16]

@@ -38,7 +38,7 @@ struct Fp8Args {
   const uint8_t* vals;   // [nnz][b][b] E5M2
   const uint8_t* X;      // token-major [T][cols] E5M2, row pitch ldx bytes (multiple of 16); or column groups, see x_cg
   int64_t ldx;
-  int64_t kdim;          // features contracted over; host-side scheduling only
+  int64_t kdim, nnz;     // features contracted over, stored blocks; host-side scheduling only
   int64_t x_cg;          // 0: token-major.  Else X is [cols/64][T][64]: bytes between two column groups (ldx = 64)
   void* Y;               // token-major [T][rows], row pitch ldy elements
   int64_t ldy;

@@ -864,7 +864,7 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
     //     tokens 27.3 / 26.1 / 26.7; two-matrix MLP of 1600 and 6400 features, 333 tokens 29.2 / 28.6; 3B-shaped MLP at
     //     70 %, 4096 tokens 249 / 247 / 251; E5M2, 8192 x 3072 at 80 %, 700 tokens 19.1 / 18.4 / 18.6.
     //   128-wide blocks in bf16: ordinary (405B-class MLP, 2048 tokens: 715 / 722 / 751).
-    //   128-wide blocks in E5M2: non-temporal.  The output is the
+    //   128-wide blocks in E5M2: non-temporal, or through where the launch says so (y_keep, see there).  The output is the
     //     larger part of what moves, and the last-level cache keeps the inputs instead of it: 53248 x 16384, 1000 tokens, with
     //     the quantiser 95 / 93 / 78, cold 111 / 109 / 114; 2048 tokens, fp32 output 180 / 182 / 157, cold 183 / 183 / 171.
     //   An output whose rows may not be stored in pairs: ordinary, so that the L2 puts lines together that are written in
@@ -920,7 +920,9 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
           }
       };
       auto store = [&](auto bf16, auto whole) {
-        if (PAIRS || a.y_pairs)
+        if (kStores == kStoreStreaming && !bf16.value && a.y_keep)
+          store_tile(bf16, whole, std::integral_constant<int, kStores == kStoreStreaming && !bf16.value ? kStoreThrough : kStores>{});
+        else if (PAIRS || a.y_pairs)
           store_tile(bf16, whole, std::integral_constant<int, kStores>{});
         else  // lines in parts: the L2 puts them together
           store_tile(bf16, whole, std::integral_constant<int, kStoreOrdinary>{});
