@@ -65,14 +65,14 @@ int launch_tile(TileArgs a, hipStream_t stream) {
 // operands straight from global memory.  A wave takes 16, 32 or 64 tokens of one block row.
 int cu_count();
 
-template <bool DUAL, bool POST, int NS, bool SPLIT, int NW = 4, bool GROUPED = false>
+template <bool DUAL, bool POST, int NS, bool SPLIT, int NW = 4, int DEPTH = 0>
 int launch_b16_ns(TileArgs a, int y_vec, hipStream_t stream) {
   a.ntt = (a.T + 16 * NS - 1) / (16 * NS);
   const int64_t items = (int64_t)a.ntt * a.nbr;
   const int64_t grid = SPLIT ? items : (items + 3) / 4;
   if (grid <= 0) return BLAST_OK;
   if (grid > INT32_MAX) return BLAST_ERR_INVALID_ARG;
-  k_spmm_b16<DUAL, POST, NS, SPLIT, NW, GROUPED><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(a, y_vec);
+  k_spmm_b16<DUAL, POST, NS, SPLIT, NW, DEPTH><<<dim3((unsigned)grid), dim3(NW * 64), 0, stream>>>(a, y_vec);
   BLAST_LAUNCH_CHECK("k_spmm_b16");
   return BLAST_OK;
 }
@@ -91,8 +91,18 @@ int launch_b16_t(const TileArgs& a, int64_t nnz, int y_vec, hipStream_t stream) 
   const bool split = (int64_t)((a.T + 63) / 64) * a.nbr < 8 * cu_count();
   // (column groups that 32-bit byte offsets reach, a wave's 64 tokens past the end included)
   if (a.x_grp16 && ((int64_t)a.kdim / 16 * a.T + 64) * 32 < ((int64_t)1 << 32)) {
-    if (split) return launch_b16_ns<DUAL, POST, 4, true, 4, true>(a, y_vec, stream);
-    return launch_b16_ns<DUAL, POST, 4, false, 4, true>(a, y_vec, stream);
+    // Two pairs in flight, or one.  While 64-token tiles divide the 32 that the eight XCDs take in four-wave workgroups, the
+    // workgroups of an XCD keep to the same tokens, whose activations stay in its L2, and what is left is latency: two.
+    // Otherwise every XCD goes over all tokens, and more in flight only pushes activations out of the L2 before the next row
+    // reads them: one, unless there are few tokens or, with shared rows, no second workgroup on a CU.  Microseconds, walk of `b16_row` / two / one: 2048 x 8192 at 70 %, 1024
+    // tokens 56.9 / 44.0 / 46.5, 2048: 79.7 / 78.0 / 83.3; 1280: 66.8 / 76.2 / 72.1, 2500: 135 / 145 / 100, 4096: 157 / 167 /
+    // 146; 4096 x 4096 at 90 %, 1280: 34.5 / 38.7 / 35.0; 1024 x 16384 at 70 %, 700 tokens (split) 53.6 / 63.0 / 54.2, 2500: 149
+    // / 181 / 165; 512 x 8192 at 70 %, 300 (split) 21.2 / 16.5 / 18.6; MLP of 2048 and 8192 features at 90 %, 333 tokens 29.9 / 27.9 / 28.8, 500: 31.9 / 30.5 / 32.3.
+    const int tiles = (a.T + 63) / 64;
+    const bool two = (tiles <= 32 && 32 % tiles == 0) || (split ? (int64_t)tiles * a.nbr <= cu_count() : tiles <= 8);
+    if (split)
+      return two ? launch_b16_ns<DUAL, POST, 4, true, 4, 2>(a, y_vec, stream) : launch_b16_ns<DUAL, POST, 4, true, 4, 1>(a, y_vec, stream);
+    return two ? launch_b16_ns<DUAL, POST, 4, false, 4, 2>(a, y_vec, stream) : launch_b16_ns<DUAL, POST, 4, false, 4, 1>(a, y_vec, stream);
   }
   if (split) return launch_b16_ns<DUAL, POST, 4, true>(a, y_vec, stream);
   return launch_b16_ns<DUAL, POST, 4, false>(a, y_vec, stream);

@@ -113,12 +113,11 @@ __device__ __forceinline__ B16Row b16_begin(const MatDev& m, int r, int pair0, i
   return q;
 }
 
-// The wave's pairs of a block row: DEPTH of them are on their way while one is multiplied.  x_off: byte offset of this
+// The wave's pairs of a block row, DEPTH of them on their way at a time (which number: see launch_b16_t).  x_off: byte offset of this
 // lane's token row and half in a column group, group_bytes: from one group to the next.
-template <int NS>
+template <int NS, int DEPTH>
 __device__ __forceinline__ void b16_walk(const MatDev& m, B16Row& q, __amdgpu_buffer_rsrc_t x, uint32_t x_off,
                                          uint32_t group_bytes, f32x4_b16 (&acc)[NS]) {
-  constexpr int DEPTH = 2;  // (a wave takes some seven pairs of a row)
   const int lane = threadIdx.x & 63;
   const int w_off = (lane >> 5) * 512 + (lane & 15) * 32 + ((lane >> 4) & 1) * 16;
   auto multiply = [&](const B16Frag<NS>& f) {
@@ -191,8 +190,9 @@ __device__ __forceinline__ void b16_join(f32x4_b16 (&acc)[NS]) {
 // SPLIT (decode token counts): the whole workgroup owns one (block row, token tile), its NW waves (4 or 16) deal
 // the row's pairs among themselves and the partial sums meet in LDS - there are too few rows to fill the chip
 // with a wave each, and a row walked by one wave is a chain of dependent loads.
-template <bool DUAL, bool POST, int NS, bool SPLIT = false, int NW = 4, bool GROUPED = false>
-__global__ __launch_bounds__(NW * 64, GROUPED ? 4 : 1) void k_spmm_b16(const TileArgs a, const int y_vec) {
+// DEPTH > 0: X in column groups, b16_walk with that many pairs in flight; 0: either layout of X, b16_row.
+template <bool DUAL, bool POST, int NS, bool SPLIT = false, int NW = 4, int DEPTH = 0>
+__global__ __launch_bounds__(NW * 64, DEPTH ? 4 : 1) void k_spmm_b16(const TileArgs a, const int y_vec) {
   static_assert(SPLIT || NW == 4, "without SPLIT a workgroup is four independent waves");
   static_assert(!(POST && DUAL), "an activation on the output belongs to the single-matrix product");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(NW * 64, GROUPED ? 4 : 1) void k_spmm_b16(const Til
 #pragma unroll
   for (int s = 0; s < NS; ++s) acc1[s] = f32x4_b16{0.f, 0.f, 0.f, 0.f};
   const int pair0 = SPLIT ? __builtin_amdgcn_readfirstlane(wave) : 0, pstride = SPLIT ? NW : 1;
-  if constexpr (GROUPED) {
+  if constexpr (DEPTH > 0) {
     const uint32_t group_bytes = (uint32_t)a.T * 32u;
     const uint32_t x_off = (uint32_t)(t0 + (lane & 15)) * 32u + ((lane >> 4) & 1) * 16u;
     const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
@@ -226,8 +226,8 @@ __global__ __launch_bounds__(NW * 64, GROUPED ? 4 : 1) void k_spmm_b16(const Til
     const int ru = __builtin_amdgcn_readfirstlane(r);
     B16Row q0 = b16_begin(a.m0, ru, pair0, pstride), q1{};
     if (DUAL) q1 = b16_begin(a.m1, ru, pair0, pstride);
-    b16_walk<NS>(a.m0, q0, x, x_off, group_bytes, acc0);
-    if (DUAL) b16_walk<NS>(a.m1, q1, x, x_off, group_bytes, acc1);
+    b16_walk<NS, DEPTH>(a.m0, q0, x, x_off, group_bytes, acc0);
+    if (DUAL) b16_walk<NS, DEPTH>(a.m1, q1, x, x_off, group_bytes, acc1);
   } else {
     b16_row<NS>(a, a.m0, r, xrow, cstride, acc0, pair0, pstride);
     if (DUAL) b16_row<NS>(a, a.m1, r, xrow, cstride, acc1, pair0, pstride);

@@ -120,6 +120,23 @@ def test_rows_longer_than_a_waves_column_register(api, nbc, T, gated):
     check_close(y.cpu().numpy()[some].T, orc.mlp(ref, ref2, refd, x[some]), f"b=16 MLP nbc={nbc} T={T}")
 
 
+@pytest.mark.parametrize("rows,nbc,T", [(1, 70, 128), (20, 70, 320), (2, 70, 700), (10, 70, 1000), (40, 70, 320), (20, 70, 700)])
+def test_one_and_two_pairs_in_flight(api, rows, nbc, T):
+    """Activations in column groups, rows shared by four waves and not, token tiles that divide 32 and that do not: row lengths
+    at both ends of a wave's round of one or two pairs, odd and even, some tokens against the oracle."""
+    import torch
+
+    rng = np.random.default_rng(1690 + T + rows)
+    counts = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 16, 17, 63, 64, 65, nbc] * rows
+    w = synth.gauss_bf16(rng, (len(counts) * B, nbc * B), 0.02)
+    x = synth.gauss_bf16(rng, (T, nbc * B), 1.0)
+    dev, ref = _pack(api, w, _rows_with_counts(rng, counts, nbc))
+    some = np.unique(np.concatenate([np.arange(0, T, max(T // 23, 1)), np.arange(max(T - 70, 0), T)]))
+    y = api.bsr_spmm(dev, to_dev(x), out=torch.full((T, len(counts) * B), float("nan"), device="cuda:0"))
+    torch.cuda.synchronize()
+    check_close(y.cpu().numpy()[some].T, orc.spmm(ref, x[some]), f"b=16 rows={len(counts)} T={T}")
+
+
 @pytest.mark.parametrize("T", [5, 40, 130])
 def test_spmm_strided_and_unaligned_operands(api, T):
     """Outputs whose row pitch or address rules out the 16-byte stores take the element-wise stores of the same
