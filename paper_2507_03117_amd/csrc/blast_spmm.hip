@@ -13,6 +13,7 @@
 #include "blast_common.h"
 
 #include <atomic>
+#include <cmath>
 
 #include "kern_common.h"
 #include "kern_tile.h"
@@ -174,6 +175,7 @@ struct ChunkPlan {
   const int* w_chunk_ke = nullptr;
   int64_t w_max_chunks = 0;
   int max_row_blocks = 0;  // stored blocks of the fullest block row
+  int64_t fullest = 0;     // the same of a single matrix, also where there is no plan (a hint; 0: not known)
   ZeroJob* zero_job = nullptr;  // a side job this launch may take along (decode launches: the first plan's only)
   bool pre_zeroed = false;      // the shared rows of the output have been cleared by an earlier launch ...
   bool zeroed_wide = false;     // ... those of the wide plan only (a subset of the other plan's)
@@ -484,22 +486,36 @@ bool decode_applies(int b, const TileArgs& a, int64_t nnz, int64_t max_row_block
 //     blocks, 384 / 512 / 768 tokens 17.0 / 10.6, 16.9 / 11.1, 17.4 / 15.5; 32 rows of 13, 384 / 768 / 1024 tokens 13.5 / 9.2,
 //     14.5 / 13.9, 14.5 / 15.6; 32 rows of 3, 512 / 768 tokens 6.6 / 5.2, 7.7 / 8.1; 100 rows of 5, 384 tokens 10.5 / 12.7.
 //     b = 128, 16 rows of 6.4, 384 / 768 / 1024 tokens 17.6 / 9.4, 17.7 / 13.2, 17.9 / 15.0; 32 rows of 3.2, 512 / 768 tokens
-//     14.3 / 11.2, 15.1 / 15.0.  So the line: 1.25 tiles per CU with 64-wide blocks, two with 128-wide ones.
+//     14.3 / 11.2, 15.1 / 15.0.  So the line: 1.25 tiles per CU with 64-wide blocks (one where no wave has a whole stage: 64
+//     rows of 1.6, fullest 4, 300 tokens 5.8 / 6.9), two with 128-wide ones.
 //   decode (33 to 256 tokens; it reads the matrix once per 32 tokens, in many small workgroups): b = 64, 100 rows of 5, 64 /
 //     100 / 160 / 256 tokens 5.2 / 5.4, 7.7 / 5.5, 9.4 / 7.6, 13.6 / 8.8; 32 rows of 13, 128 / 256 tokens 7.3 / 7.4, 10.0 / 8.4;
-//     25 rows of 20, 160 / 256 tokens 7.7 / 9.7, 9.9 / 9.9.  b = 128, 32 rows of 3.2, 64 / 100 / 256 tokens 4.1 / 5.9, 7.0 / 6.1,
-//     13.0 / 7.7.  The two estimates below follow these figures to about 1.5 us.
+//     32 rows of 26, 192 tokens 9.5 / 11.3.  b = 128, 32 rows of 3.2, 64 / 100 / 256 tokens 4.1 / 5.9, 7.0 / 6.1, 13.0 / 7.7.
+//     A full row among the others is a chain in either kernel, dealt to four waves of each 16 of its rows by decode, to eight
+//     of each 64 by split: b = 128, 32 rows of 4.1, one of 32, 64 / 160 / 256 tokens 6.8 / 14.9, 9.3 / 15.6, 12.0 / 16.1; 32 rows
+//     of 5.6, fullest 58, 100 / 256 tokens 11.6 / 25.8, 17.5 / 27.4.  The two estimates below were fitted to 1400 such
+//     calls (uniform rows, Zipf rows, one or four full rows; 33 to 256 tokens) for the choice between them: of the calls that
+//     they send here, none with 128-wide blocks and four with 64-wide ones are more than 5 % slower than on decode.
 // (Two-matrix MLP of 1600 and 6400 features at 80 %: 128 tokens 18.5 -> 14.8, 333 28.8 -> 22.8, 512 28.3 -> 22.9.)
-bool split_applies(int b, const TileArgs& a, int64_t nnz, bool decode) {
+bool split_applies(int b, const TileArgs& a, int64_t nnz, int64_t fullest, bool decode) {
   if ((b != 64 && b != 128) || a.T <= kDecodeAlwaysTokens) return false;
   const int64_t cus = cu_count(), tiles = (int64_t)a.nbr * (b / 64) * ((a.T + 63) / 64);
-  if (!decode) return tiles * 4 <= (b == 64 ? 5 : 8) * cus;
+  const double mean = (double)nnz / a.nbr;
+  const double row = fullest > 0 ? (double)fullest : mean + 2.0 * std::sqrt(mean);  // (rows of a uniform mask vary by that)
+  if (!decode) return tiles * 4 <= (b == 128 ? 8 : row < 8.0 ? 4 : 5) * cus;
   if (tiles > 2 * cus) return false;
-  const double groups = (double)((a.T + 31) / 32), per_wave = (double)nnz / a.nbr * (b / 64) / 8.0;
-  const double stages = per_wave > 0.6 ? per_wave : 0.6;
-  const double decode_us = 3.0 + 0.2e-6 * nnz * b * b * 2 * groups + (double)a.nbr * (b / 16) * groups / 850.0;
-  const double split_us = (tiles > cus ? 7.0 : 4.0) + stages * (1.3 + (double)tiles / cus);
-  return decode_us > split_us + 0.55;
+  const double groups = (double)((a.T + 31) / 32), mbytes = nnz * 1e-6 * b * b * 2 * groups, units = a.nbr * (b / 16) * groups * 1e-3;
+  // stages of a wave: in the fullest row, and on average for every CU
+  const double chain = std::ceil(row * (b / 64) / 8.0), load = mean * (b / 64) / 8.0 * tiles / cus;
+  double decode_us, split_us;
+  if (b == 64) {
+    decode_us = 3.30 + 0.162 * mbytes + 1.68 * units + 0.149 * row / 4;
+    split_us = (tiles > cus ? 3.06 : 3.68) + 1.65 * chain + 0.77 * load;
+  } else {
+    decode_us = 3.33 + 0.128 * mbytes + 2.03 * units + 0.291 * row / 4;
+    split_us = (tiles > cus ? 5.44 : 3.86) + 1.39 * chain + 0.89 * load;
+  }
+  return decode_us > split_us + 0.3;
 }
 
 template <bool DUAL>
@@ -509,9 +525,10 @@ int dispatch_tile(int b, const TileArgs& a, int64_t nnz, hipStream_t stream, con
   const bool small_x = (int64_t)a.T * a.sxt * 2 < ((int64_t)1 << 32);
   const bool decode = a.x_vec && a.T > 0 && small_x && decode_applies<DUAL>(b, a, nnz, plan.max_row_blocks);
   if constexpr (!DUAL) {
-    // (not where rows are cut into chunks, nor where this launch is to clear another one's, nor for the last tokens of a
-    // longer call, whose rows are summed as the others')
-    if (a.x_vec && small_x && !ranged && !plan.hdr && !plan.zero_job && split_applies(b, a, nnz, decode))
+    // (not where rows may be cut into chunks - fp32 output without an activation -, nor where this launch is to clear another
+    // one's, nor for the last tokens of a longer call, whose rows are summed as the others')
+    const bool chunks = plan.hdr && !a.y_bf16 && a.act < 0;
+    if (a.x_vec && small_x && !ranged && !chunks && !plan.zero_job && split_applies(b, a, nnz, plan.fullest, decode))
       return b == 64 ? launch_split<64>(a, stream) : launch_split<128>(a, stream);
   }
   if (decode) {
@@ -625,6 +642,7 @@ MatDev mat_of(const blast_bsr_view* v) { return MatDev{v->row_ptr, v->col_idx, v
 // chunks): then that row is the critical path of the launch by a wide margin.
 ChunkPlan plan_of(const blast_bsr_view* v, int64_t T) {
   ChunkPlan p;
+  p.fullest = v->max_row_blocks;
   if (!v->aux || v->max_row_blocks <= blast::kChunkBlocks) return p;
   const int64_t nbr = v->rows / v->b, nbc = v->cols / v->b;
   const int64_t tiles = (T + 255) / 256;
@@ -866,6 +884,7 @@ int enqueue_gated(const blast_bsr_view* Wgate, const blast_bsr_view* Wup, const 
   side.zero_job = side_job;
   // upper bound of the fullest joint row (exact when the same row is the fullest of both matrices)
   side.max_row_blocks = Wgate->max_row_blocks + (Wup ? Wup->max_row_blocks : 0);
+  side.fullest = Wgate->max_row_blocks;
   TileArgs g{};
   g.m0 = mat_of(Wgate);
   if (Wup) g.m1 = mat_of(Wup);

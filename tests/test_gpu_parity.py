@@ -474,9 +474,10 @@ def test_spmm_strided_operands(api, b, T):
 @pytest.mark.parametrize("b", [64, 128])
 @pytest.mark.parametrize("T", [100, 191, 256, 257, 320, 383, 384])
 def test_few_output_tiles(api, b, T):
-    """Shapes with fewer output tiles than CUs, whose rows are dealt to the eight waves of a workgroup: rows of 0 to 9, 16,
-    17 and all 40 blocks, so that some waves get nothing and others one stage more; tokens that end a tile and tokens that
-    end inside one.  The plain product in both types and the activated one (first half of a two-matrix MLP)."""
+    """Shapes with fewer output tiles than CUs, which beyond 256 tokens are shared by the eight waves of a workgroup (up to 256
+    the full row sends them to the decode kernel): rows of 0 to 9, 16, 17 and all 40 blocks, so that some waves get nothing and
+    others one stage more; tokens that end a tile and tokens that end inside one.  The plain product in both types and the
+    activated one (first half of a two-matrix MLP)."""
     import torch
 
     rng = np.random.default_rng(5300 + b + T)
@@ -499,6 +500,34 @@ def test_few_output_tiles(api, b, T):
     z = api.sparse_mlp2(dev, dev2, to_dev(x), act="gelu")
     torch.cuda.synchronize()
     check_close(z.cpu().numpy().T, orc.mlp2(ref, ref2, x, activation="gelu"), f"few tiles, two-matrix MLP b={b} T={T}")
+
+
+@pytest.mark.parametrize("b,nbr,per_row,full,T", [
+    (64, 100, 5, 0, 100), (64, 100, 5, 0, 160), (64, 100, 5, 0, 255), (64, 64, 3, 0, 193), (64, 64, 2, 0, 300),
+    (128, 32, 4, 0, 100), (128, 32, 4, 0, 161), (128, 32, 4, 0, 256), (128, 16, 6, 0, 255),
+    (64, 100, 5, 130, 160), (128, 32, 4, 130, 160), (64, 20, 5, 130, 300), (128, 16, 4, 130, 400), (128, 16, 4, 60, 400)])
+def test_few_output_tiles_by_rows(api, b, nbr, per_row, full, T):
+    """Both sides of the choice between the kernels for few output tiles: rows of one length (shared by eight waves also at
+    decode token counts), one row of `full` blocks among them (fewer tokens: the decode kernel; 130 blocks carry a chunk plan,
+    which only an fp32 output without an activation follows)."""
+    import torch
+
+    rng = np.random.default_rng(5400 + b + T + full)
+    nbc = 140
+    mask = np.zeros((nbr, nbc), dtype=np.uint8)
+    for r in range(nbr):
+        mask[r, rng.choice(nbc, size=full if full and r == 3 else max(per_row - (r % 3 == 1), 1), replace=False)] = 1
+    w = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
+    x = synth.gauss_bf16(rng, (T, nbc * b), 1.0)
+    dev, ref = pack_both(api, w, b, mask=mask)
+    some = np.unique(np.r_[0:T:13, max(T - 66, 0):T])
+    want = orc.spmm(ref, x[some])
+    y = api.bsr_spmm(dev, to_dev(x), out=torch.full((T, nbr * b), float("nan"), device="cuda:0"))
+    yb = api.bsr_spmm(dev, to_dev(x), out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    check_close(y.cpu().numpy()[some].T, want, f"b={b} {nbr} rows of {per_row}, one of {full}, T={T}")
+    got = yb.float().cpu().numpy()[some].T
+    assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -8 + 1e-5 * np.sqrt((want ** 2).mean())).all()  # one rounding
 
 
 @pytest.mark.parametrize("path", ["bf16", "e5m2"])
