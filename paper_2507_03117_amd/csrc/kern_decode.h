@@ -694,18 +694,21 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
 // (calls differ in the host's, launches of a recorded call in the epoch), and a word left by another launch or by anyone
 // else carries its upper 48 bits with probability 2^-48.  A value costs eight bytes instead of two, so this is
 // for a few tokens; the weight fragments, which do not depend on H, are in registers before the first word is asked for.
-// Cold weights, microseconds a layer, slots / words: 1B shape at 1, 2, 4 tokens 9.95 / 8.55, 10.2 / 9.1, 10.7 / 10.1; 8B
-// shape 11.2 / 9.4, 11.3 / 9.8, 11.8 / 11.5.  (128-wide blocks: the registers are held to five waves per SIMD, which is
-// what keeps the 8B-shaped launch resident at once; without that it loses at 2 and 4 tokens, 11.8 and 12.2.)
-constexpr int tagged_blocks(int b) { return b == 64 ? 4 : 2; }  // blocks of a wave taken at a time
+// Cold weights, microseconds a layer from a graph, slots / words: 1B shape at 1, 2, 3, 4 tokens 9.1 / 7.7, 9.5 / 8.1, 9.7 / 8.8,
+// 10.0 / 9.1; 8B shape 10.9 / 9.2, 11.2 / 9.7, 11.2 / 10.5, 11.3 / 10.9: what is gained shrinks with every token.  (128-wide
+// blocks: the registers are held to five waves per SIMD, which is what keeps the 8B-shaped launch resident at once; without
+// that it lost at 2 and 4 tokens.)
+// Blocks of a wave taken at a time.  (128-wide blocks at four tokens: two spill 11 registers under the bound on them; one / two,
+// microseconds a layer, 2048 x 8192 at 90 % 9.7 / 10.0, at three tokens 9.3 / 9.7, 8B shape 10.9 / 10.9, 10.5 / 10.7.)
+constexpr int tagged_blocks(int b, int ntok) { return b == 64 ? 4 : ntok > 2 ? 1 : 2; }
 constexpr size_t tagged_consumer_lds(int b, int ntok) {        // four waves' values, or the partial sums of three
-  const size_t values = (size_t)4 * tagged_blocks(b) * ntok * b * 2, sums = 3 * 4 * 64 * 4;
+  const size_t values = (size_t)4 * tagged_blocks(b, ntok) * ntok * b * 2, sums = 3 * 4 * 64 * 4;
   return values > sums ? values : sums;
 }
 
 template <int B, int NTOK>
 __device__ __forceinline__ void decode_consumer_tagged(const DecArgs& a, const int unit, unsigned char* smem) {
-  constexpr int SLICES = B / 16, KST = B / 32, WPL = B / 64, NB = tagged_blocks(B);
+  constexpr int SLICES = B / 16, KST = B / 32, WPL = B / 64, NB = tagged_blocks(B, NTOK);
   constexpr int XROW = B * 2, XB = NTOK * XROW;
   const int q = unit % SLICES, rank = unit / SLICES;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
