@@ -141,14 +141,11 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()  # (every pointer argument is declared: ctypes converts the number)
 
 
-_device_index, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
-
-
 def _stream() -> int:
     """The current stream of the current device, without the objects that torch.cuda.current_stream() makes on the way
-    (0.1 against 2.8 us).  A small call's time is the host's: 1024 x 4096 in 32-wide blocks, 64 tokens, 9.9 us a call with
+    (0.2 against 2.8 us; looked up here, since an installation without GPU support has neither function).  A small call's time is the host's: 1024 x 4096 in 32-wide blocks, 64 tokens, 9.9 us a call with
     them and with the query of a workspace that only 16-wide blocks have, 6.5 without."""
-    return _raw_stream(_device_index())
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def n_keep(n_blocks: int, sparsity: float) -> int:

@@ -175,3 +175,18 @@ def test_mlp_workspace_for_the_largest_batch_serves_the_smaller_ones(b, I):
         assert L.blast_sparse_mlp2_workspace(C.byref(g), C.byref(d), T, C.byref(ws)) == 0
         assert ws.value == sizes[-1]
     assert sizes == sorted(sizes)
+
+
+def test_the_binding_imports_without_gpu_support(monkeypatch):
+    """An installation of torch that has no GPU functions can import the binding (and query sizes with it)."""
+    import importlib.util
+
+    import torch
+
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("paper_2507_03117_amd.api_without_gpu", api.__file__)
+    mod = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(__import__("sys").modules, spec.name, mod)  # (a dataclass looks its module up)
+    spec.loader.exec_module(mod)
+    assert mod.n_keep(10, 0.5) == 5
