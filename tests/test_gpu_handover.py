@@ -99,7 +99,7 @@ def test_single_launch_form_at_the_1b_shape_with_changing_activations(api):
 @pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
 def test_tagged_words(api, b, T, out_dtype):
     """A few tokens: H travels as tagged words where the workspace has room for them, else through slots.  Both forms on a
-    garbage workspace, with rows of the down projection of 0 to 23 blocks (a wave takes four or two at a time), gated and
+    garbage workspace, with rows of the down projection of 0 to 23 blocks (a wave takes four, two or one at a time), gated and
     two-matrix; activations change from call to call on one workspace; the two forms agree up to the order of the sums."""
     import torch
 
@@ -116,10 +116,11 @@ def test_tagged_words(api, b, T, out_dtype):
     dt = torch.float32 if out_dtype == "f32" else torch.bfloat16
     tol = 0.0 if out_dtype == "f32" else 2.0 ** -7
     whole = api.mlp_workspace_bytes(*dev, T)
+    xs = [synth.gauss_bf16(rng, (T, E), 1.0) for _ in range(3)]
+    words = {}  # results of the first form, by call
     for size in (whole, whole - T * I * 8) if T <= 4 else (whole,):
         ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device="cuda:0")
-        for rep in range(3):
-            x = synth.gauss_bf16(rng, (T, E), 1.0)
+        for rep, x in enumerate(xs):
             out = torch.full((T, E), float("nan"), dtype=dt, device="cuda:0")
             y = api.sparse_mlp(*dev, to_dev(x), ws=ws, out=out).float()
             want = orc.mlp(*ref, x)
@@ -133,6 +134,10 @@ def test_tagged_words(api, b, T, out_dtype):
                 else:  # one rounding to bf16 on top of the sums
                     assert (np.abs(got - exp) <= np.abs(exp) * tol + 1e-2 * np.sqrt((exp ** 2).mean())).all()
                 assert not got[:b].any()  # an empty block row
+            for first, got in zip(words.setdefault(rep, (y, z)), (y, z)):
+                # the same H; fp32 sums of at most 8 blocks of a wave and four waves, in whatever order, and one rounding of them
+                slack = 64 * 2.0 ** -24 * float(first.abs().max()) + tol * first.abs()
+                assert ((got - first).abs() <= slack).all(), f"words and slots differ, b={b} T={T} call {rep}"
         assert api.sparse_mlp_status(dev[0], T, ws) == 0
 
 
