@@ -130,7 +130,7 @@ def zipf_mask(rng: np.random.Generator, nbr: int, nbc: int, sparsity: float, alp
 
 @dataclass
 class Workload:
-    """One configuration of the benchmark spec `configs`, parameterised."""
+    """One workload: the shapes, block size and sparsity of a block-sparse MLP or of one matrix."""
 
     name: str
     config_id: int

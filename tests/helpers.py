@@ -41,7 +41,7 @@ def stratified_tokens(T, n_sample, tile=128, boundary=256):
     return np.array(sorted(sel))
 
 
-# the benchmark spec tolerances: relative Frobenius error <= 1e-3, max elementwise error <= 1e-2 * RMS(oracle)
+# Tolerances: relative Frobenius error <= 1e-3, max elementwise error <= 1e-2 * RMS(oracle)
 REL_FRO = 1e-3
 MAX_ABS_RMS = 1e-2
 

@@ -1,4 +1,4 @@
-"""Two checks of the checker itself (CPU only).
+"""Two checks of the oracle itself (CPU only).
 
 1. The C oracle built with AddressSanitizer + UndefinedBehaviorSanitizer passes its pins: no out-of-bounds
    access, no signed overflow, no misaligned access behind the numbers the GPU path is compared with.
