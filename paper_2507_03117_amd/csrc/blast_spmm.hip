@@ -243,7 +243,6 @@ int launch_stream_tw(TileArgs a, const ChunkPlan& plan, int64_t k_features, hipS
     k_zero_shared_rows<B><<<dim3((unsigned)plan.max_chunks, (unsigned)((a.T + 63) / 64)), dim3(256), 0, stream>>>(sa);
     BLAST_LAUNCH_CHECK("k_zero_shared_rows");
   }
-  // (two rows to a store: only where Y allows it, and only instances whose waves hold two rows side by side)
   auto launch = [&](auto post, auto pairs) -> int {
     constexpr auto kernel = &k_spmm_stream<B, DUAL, TW, CHUNK, post.value, NW, LONG, false, pairs.value>;
     static blast::DeviceFlags lds_set;
@@ -252,17 +251,15 @@ int launch_stream_tw(TileArgs a, const ChunkPlan& plan, int64_t k_features, hipS
     BLAST_LAUNCH_CHECK("k_spmm_stream");
     return BLAST_OK;
   };
-  auto launch_post = [&](auto pairs) -> int {
-    if constexpr (!DUAL && !CHUNK && !LONG) {
-      if (a.act >= 0) return launch(std::true_type{}, pairs);  // single matrix with an activation on the output
-    }
-    return launch(std::false_type{}, pairs);
-  };
+  if constexpr (!DUAL && !CHUNK && !LONG) {
+    // single matrix with an activation on the output: the intermediate of a two-matrix MLP, which takes row pairs
+    if (a.act >= 0) return launch(std::true_type{}, std::true_type{});
+  }
   int rc;
-  if constexpr (C::PAIR && !CHUNK && !LONG)
-    rc = a.y_fast && a.y_pairs ? launch_post(std::true_type{}) : launch_post(std::false_type{});
+  if constexpr (C::PAIR && !CHUNK && !LONG)  // two rows to a store: only where Y allows it
+    rc = a.y_fast && a.y_pairs ? launch(std::false_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{});
   else
-    rc = launch_post(std::true_type{});
+    rc = launch(std::false_type{}, std::true_type{});
   if (rc) return rc;
   if constexpr (LONG) {
     k_long_finish<B><<<dim3((unsigned)((a.nbr + kLongFinishRows - 1) / kLongFinishRows),

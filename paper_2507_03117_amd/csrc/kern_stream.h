@@ -447,7 +447,7 @@ __device__ __forceinline__ void stream_zero_side(const StreamArgs& sa, int w, in
 // (the first half of a two-matrix MLP).
 // LONG: the gated product with its long rows cut into chunks and finished by a later launch, see StreamArgs.
 // F8: both operands in E5M2 (MatDev::vals8; X bytes).
-// PAIRS: Y allows it that a lane stores two neighbouring rows as one value (y_fast and y_pairs; where StreamCfg::PAIR).
+// PAIRS: the lanes hold row pairs (StreamCfg::PAIR), for outputs that take them (y_pairs); false: the instance for others.
 template <int B, bool DUAL, int TW, bool CHUNK, bool POST = false, int NW = 4, bool LONG = false, bool F8 = false, bool PAIRS = true>
 __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)) void k_spmm_stream(const StreamArgs sa) {
   static_assert(!F8 || (!DUAL && !CHUNK && !POST && !LONG), "the E5M2 product is a plain one");

@@ -559,6 +559,30 @@ def test_spmm_output_alignment(api, path, b, nbr, nbc, T, out_dtype):
         check_close(whole[some].cpu().numpy().T, orc.spmm(ref, x[some]), f"aligned b={b} T={T}")
 
 
+@pytest.mark.parametrize("b,nbr,nbc,T", [(128, 4, 6, 300), (128, 128, 2, 1100), (64, 40, 3, 3400), (64, 5, 3, 200)])
+def test_gated_output_alignment(api, b, nbr, nbc, T):
+    """The same for the gated product: H with an odd pitch, and with a first column that is not aligned to two values."""
+    import torch
+
+    n = nbr * b
+    w, mask, x = synth.small_case(5200 + b + T, n, nbc * b, b, 0.5, T, empty_rows=(2,))
+    w2, mask2, _ = synth.small_case(5201 + b + T, n, nbc * b, b, 0.5, 1)
+    (dev, ref), (dev2, ref2) = pack_both(api, w, b, mask=mask), pack_both(api, w2, b, mask=mask2)
+    whole = api.bsr_gated_spmm(dev, dev2, to_dev(x))
+    for pitch, first in ((n + 3, 0), (n + 3, 1), (n + 4, 1)):
+        buf = torch.full((T, pitch), -3.0, dtype=torch.bfloat16, device="cuda:0")
+        api.bsr_gated_spmm(dev, dev2, to_dev(x), out=buf[:, first:first + n])
+        torch.cuda.synchronize()
+        assert torch.equal(buf[:, first:first + n], whole)
+        assert (buf[:, :first] == -3.0).all() and (buf[:, first + n:] == -3.0).all()
+    some = slice(max(0, T - 70), T)
+    g, u = orc.spmm(ref, x[some]), orc.spmm(ref2, x[some])
+    want = g / (1.0 + np.exp(-g)) * u
+    got = whole[some].float().cpu().numpy().T
+    # one rounding to bf16; the sums and the activation in fp32
+    assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -8 + 1e-5 * np.sqrt((want ** 2).mean())).all()
+
+
 @pytest.mark.parametrize("b,nbc,T", [(32, 70, 300), (64, 40, 520), (128, 36, 200), (64, 72, 300),
                                      (32, 70, 9), (32, 70, 40), (64, 72, 1), (64, 72, 7), (64, 72, 16), (64, 72, 100), (128, 66, 3), (128, 66, 20),
                                      # rows long enough for the decode kernel to take the chunk plan as well
