@@ -256,8 +256,10 @@ int launch_stream_tw(TileArgs a, const ChunkPlan& plan, int64_t k_features, hipS
     if (a.act >= 0) return launch(std::true_type{}, std::true_type{});
   }
   int rc;
-  if constexpr (C::PAIR && !CHUNK && !LONG)  // two rows to a store: only where Y allows it
-    rc = a.y_fast && a.y_pairs ? launch(std::false_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{});
+  if constexpr (C::PAIR && !CHUNK && !LONG)
+    // Two rows to a store: only where Y allows it, and with 128-wide blocks not in fp32, where whole lines leave either way (14336
+    // x 4096 at 90 %, pairs / neighbouring rows, 512 tokens 19.4 / 18.9 us, 2048: 46.0 / 45.0; 53248 x 16384 at 95 %, 300: 64.2 / 62.5).
+    rc = a.y_fast && a.y_pairs && !(B == 128 && !a.y_bf16) ? launch(std::false_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{});
   else
     rc = launch(std::false_type{}, std::true_type{});
   if (rc) return rc;
