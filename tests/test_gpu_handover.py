@@ -189,6 +189,24 @@ def test_token_counts_and_widths_change_on_one_workspace(api, b, I):
         assert api.sparse_mlp_status(dev[0], T, None) == 0
 
 
+def test_workspaces_that_the_allocator_hands_round(api):
+    """Calls without a workspace of the caller's get what the allocator has: memory that earlier workspaces lay in, at the same
+    place or beside it, with small tensors written over parts of it in between."""
+    import torch
+
+    b, E, I = 64, 256, 1024
+    rng, dev, ref, _ = _layer(api, 8700, E, I, b, 0.5)
+    held = []
+    for n in range(60):
+        T = int(rng.integers(1, 9))
+        x = synth.gauss_bf16(rng, (T, E), 1.0)
+        y = api.sparse_mlp(*dev, to_dev(x))
+        torch.cuda.synchronize()
+        check_close(y.cpu().numpy().T, orc.mlp(*ref, x), f"call {n} T={T}")
+        held = [t for t in held if rng.random() < 0.5]
+        held += [torch.randint(0, 1 << 30, (int(rng.integers(1, 2000)),), device="cuda:0") for _ in range(4)]
+
+
 @pytest.mark.parametrize("b,T", [(64, 1), (64, 4), (64, 16), (128, 2), (128, 16)])
 def test_replays_after_the_control_block_was_written_over(api, b, T):
     """Something else is written over the start of the workspace between two replays of a recorded call, so that the
