@@ -61,9 +61,33 @@ __device__ __forceinline__ void store_through(T* p, T v) {
   __hip_atomic_store(reinterpret_cast<U*>(p), __builtin_bit_cast(U, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// g * Phi(g), Phi the normal distribution function, from its tail: Phi(-t) = 2^(t R(t)) / 2 for t = |g|, R a polynomial
+// fitted to (log2 Phi(-t) + 1) / t on [0, 6] so that t times the tail's error is below 2e-9 (least squares, reweighted to
+// equal ripple); its leading coefficient is negative, so the tail goes on falling beyond 6 and is 0 at infinity.  Of the
+// same accuracy as 0.5 g (1 + erf(g / sqrt 2)) with a correctly rounded erf, and better for negative g, where that
+// subtracts (against 64 bits, root mean square over normal g, that with erff / this: standard deviation 0.36 8.2e-9 /
+// 7.9e-9, 1: 2.51e-8 / 2.16e-8, 2: 4.90e-8 / 4.24e-8), in 16 instructions without a branch, where erff has 60 in two arms that a wave nearly
+// always both takes: 64 values a lane are the larger part of a short product's time (two-matrix MLP of 1600 and 6400
+// features at 80 %, 333 tokens: 21.1 -> 20.2 us).
+__device__ __forceinline__ float gelu(float g) {
+  const float t = __builtin_fabsf(g);
+  float r = -5.96657159e-8f;
+  r = __builtin_fmaf(r, t, 1.44687544e-6f);
+  r = __builtin_fmaf(r, t, -1.56093192e-5f);
+  r = __builtin_fmaf(r, t, 9.60514999e-5f);
+  r = __builtin_fmaf(r, t, -3.27383575e-4f);
+  r = __builtin_fmaf(r, t, 6.75653209e-5f);
+  r = __builtin_fmaf(r, t, 6.89349836e-3f);
+  r = __builtin_fmaf(r, t, -5.24200164e-2f);
+  r = __builtin_fmaf(r, t, -4.59224194e-1f);
+  r = __builtin_fmaf(r, t, -1.15110409f);
+  const float tail = 0.5f * __builtin_amdgcn_exp2f(t * r);
+  return g * (g > 0.0f ? 1.0f - tail : tail);
+}
+
 __device__ __forceinline__ float apply_act(int act, float g) {
   if (act == BLAST_ACT_SILU) return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
-  if (act == BLAST_ACT_GELU) return 0.5f * g * (1.0f + erff(g * 0.70710678118654752440f));
+  if (act == BLAST_ACT_GELU) return gelu(g);
   return g > 0.0f ? g : 0.0f;
 }
 

@@ -901,6 +901,27 @@ def test_mlp2_small(api, b, T):
     _mlp2_case(api, 8000 + b + T, 4 * b, 6 * b, b, 0.5, T)
 
 
+@pytest.mark.parametrize("T", [3, 40, 300])
+def test_gelu_values(api, T):
+    """The activation itself, through a two-matrix MLP of identity weights: the output is the activation rounded to bf16 once.
+    Inputs on both sides of zero, around it, in the tails (beyond 5.4 the negative side is below 2e-7) and far out.  Bound: half
+    a unit of bf16, and 5e-7 where the activation is computed (four times the error of a 32-bit formula over these inputs)."""
+    import math
+
+    import torch
+
+    n = 64
+    g = np.concatenate([np.linspace(-9, 9, 37), [0.0, 1e-3, -1e-3, 1e-20, -1e-20, 20.0, -20.0, 1e4, -1e4, 3e37, -3e37],
+                        np.linspace(-1, 1, 16)]).astype(np.float32)
+    x = synth.f32_to_bf16_bits(np.stack([np.roll(g, t) for t in range(T)]))
+    eye, _ = pack_both(api, synth.f32_to_bf16_bits(np.eye(n, dtype=np.float32)), n, mask=np.ones((1, 1), dtype=np.uint8))
+    y = api.sparse_mlp2(eye, eye, to_dev(x), act="gelu").double().cpu()
+    v = to_dev(x).double().cpu()
+    want = 0.5 * v * torch.special.erfc(-v / math.sqrt(2.0))
+    assert torch.isfinite(y).all()
+    assert ((y - want).abs() <= want.abs() * 2.0 ** -8 + 5e-7).all()
+
+
 @pytest.mark.parametrize("act", ["silu", "gelu", "relu"])
 @pytest.mark.parametrize("T", [7, 37, 280])
 def test_mlp2_activations_and_layouts(api, act, T):
