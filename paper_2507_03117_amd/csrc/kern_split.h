@@ -1,13 +1,15 @@
 // Product kernel for few output tiles: a few hundred tokens, few block rows (token-major, 16-byte aligned activations).
 //
 // The streaming kernel gives an output tile to one workgroup, which walks the block row in sequence; with fewer tiles
-// than CUs that chain is the whole launch while most of the chip has nothing to do.  Here a workgroup of eight waves
+// than CUs that chain is the whole launch while most of the chip has nothing to do.  Here a workgroup of eight or four waves
 // shares a tile of 64 rows x 64 tokens by the contraction: the row's stages (64 contraction indices, whole 128-byte lines
 // of a block and of the activations) are dealt to the waves, each accumulates the whole tile from copies of its own, and
-// the eight partial sums meet in LDS, added in wave order.  No barrier before that.
+// the partial sums meet in LDS, added in wave order.  No barrier before that.
 //  - A wave owns one 16 KiB stage in LDS.  Its fragments go to registers as soon as it has landed (64 of them), so that
-//    the next stage is copied over it while they are multiplied: eight stages are in flight per CU, and one workgroup
-//    fits a CU, which is what there is work for.
+//    the next stage is copied over it while they are multiplied: eight stages are in flight per CU.  One workgroup of eight
+//    waves fits a CU, or two of four, for up to twice and three times as many tiles as CUs, of which one is multiplied
+//    while the other adds up or waits for its indices (2048 x 2048 at 90 %, 64-wide, 700 tokens, 352 tiles: 7.2 -> 5.8 us;
+//    4096 x 4096 at 90 %, 128-wide, 500 tokens, 512 tiles: 10.9 -> 9.4).
 //  - Rows of a wave's tile alternate between the two matrix tiles, so that a lane ends up with two neighbouring rows of a
 //    token, as in the streaming kernel.
 // Relative error against 64 bits, other kernel / this one: 1600 x 6400 at 80 %, 333 tokens 2.1e-7 / 0.9e-7; 1024 x 8192 at
@@ -21,10 +23,10 @@
 
 namespace blast_dev {
 
-template <int B>
+template <int B, int NWAVES>
 struct SplitCfg {
   static_assert(B == 64 || B == 128, "a stage is a whole 128-byte line deep");
-  static constexpr int NW = 8;
+  static constexpr int NW = NWAVES;
   static constexpr int SB = 64;               // rows and tokens of the tile
   static constexpr int SUB = B / SB;          // tiles per block row
   static constexpr int KSL = B / 64;          // stages per stored block
@@ -35,9 +37,9 @@ struct SplitCfg {
   static_assert(sizeof(float) * 64 * 64 == STAGE, "a wave's sums go over its stage");
 };
 
-template <int B, bool POST>
-__global__ __launch_bounds__(512, 2) void k_spmm_split(const TileArgs a, const int n_units, const int groups) {
-  using C = SplitCfg<B>;
+template <int B, bool POST, int NWAVES>
+__global__ __launch_bounds__(64 * NWAVES, 2) void k_spmm_split(const TileArgs a, const int n_units, const int groups) {
+  using C = SplitCfg<B, NWAVES>;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
@@ -118,12 +120,13 @@ __global__ __launch_bounds__(512, 2) void k_spmm_split(const TileArgs a, const i
 #pragma unroll
       for (int v = 0; v < 16; ++v) red[wave][(mi * 2 + nj) * 16 + v][lane] = acc[mi][nj][v];
   __syncthreads();
-  const int mi = wave >> 2, v0 = (wave & 3) * 4;
+  constexpr int PER = 32 / C::NW;  // registers of a lane's half of the tile (token half, v) that a wave owns
+  const int mi = wave * PER / 16, v0 = wave * PER % 16;
   const int64_t row = (int64_t)r * B + si * C::SB + 2 * l32;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    // register v0 + v of a 32 x 32 tile: token 8 * (v0 / 4) + 4 * lh + v
-    const int t = t0 + 32 * mi + 2 * v0 + 4 * lh + v;
+  for (int v = 0; v < PER; ++v) {
+    // register v0 + v of a 32 x 32 tile: token 8 * ((v0 + v) / 4) + 4 * lh + v % 4
+    const int t = t0 + 32 * mi + 2 * v0 + 8 * (v / 4) + 4 * lh + v % 4;
     if (t >= a.T) continue;
     float y[2];
 #pragma unroll

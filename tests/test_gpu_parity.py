@@ -530,6 +530,44 @@ def test_few_output_tiles_by_rows(api, b, nbr, per_row, full, T):
     assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -8 + 1e-5 * np.sqrt((want ** 2).mean())).all()  # one rounding
 
 
+@pytest.mark.parametrize("b,nbr,per_row,full,T", [
+    (64, 40, 5, 0, 449), (64, 41, 7, 0, 257), (64, 64, 1, 0, 448), (64, 33, 24, 0, 640), (64, 96, 3, 60, 700),
+    (128, 20, 3, 0, 513), (128, 33, 3, 0, 640), (128, 17, 12, 0, 300), (128, 24, 4, 50, 900), (128, 40, 1, 0, 191)])
+def test_output_tiles_shared_by_four_waves(api, b, nbr, per_row, full, T):
+    """One to three tiles of 64 x 64 per CU, whose stages four waves share: rows shorter than the waves are many and rows of
+    several stages a wave, block rows that do not divide by eight, tokens that end inside a tile; uneven rows with more tiles
+    than that.  The plain product in both types (32-bit sums: 1e-5 of the root mean square; one rounding to bf16) and the
+    activated one, whose output is the intermediate of a two-matrix MLP."""
+    import torch
+
+    rng = np.random.default_rng(5500 + b + T + full)
+    nbc = 62
+    mask = np.zeros((nbr, nbc), dtype=np.uint8)
+    for r in range(nbr):
+        mask[r, rng.choice(nbc, size=full if full and r == 3 else max(per_row - (r % 3 == 1), int(r % 5 > 0)), replace=False)] = 1
+    w = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
+    x = synth.gauss_bf16(rng, (T, nbc * b), 1.0)
+    dev, ref = pack_both(api, w, b, mask=mask)
+    some = np.unique(np.r_[0:T:13, max(T - 66, 0):T])
+    want = orc.spmm(ref, x[some])
+    rms = np.sqrt((want ** 2).mean())
+    y = api.bsr_spmm(dev, to_dev(x), out=torch.full((T, nbr * b), float("nan"), device="cuda:0"))
+    yb = api.bsr_spmm(dev, to_dev(x), out_dtype=torch.bfloat16)
+    odd = torch.full((T, nbr * b + 1), float("nan"), device="cuda:0", dtype=torch.bfloat16)  # rows that take no pairs
+    api.bsr_spmm(dev, to_dev(x), out=odd[:, :nbr * b])
+    torch.cuda.synchronize()
+    assert (np.abs(y.cpu().numpy()[some].T - want) <= 1e-5 * rms).all() or full  # (a full row's sums are larger)
+    check_close(y.cpu().numpy()[some].T, want, f"b={b} {nbr} rows of {per_row}, one of {full}, T={T}")
+    got = yb.float().cpu().numpy()[some].T
+    assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -8 + 1e-5 * rms).all()  # one rounding
+    assert torch.equal(odd[:, :nbr * b], yb) and torch.isnan(odd[:, nbr * b:]).all()
+    w2 = synth.gauss_bf16(rng, (nbc * b, nbr * b), 0.05)
+    dev2, ref2 = pack_both(api, w2, b, mask=synth.uniform_mask(rng, nbc, nbr, 0.8))
+    z = api.sparse_mlp2(dev, dev2, to_dev(x), act="gelu")
+    torch.cuda.synchronize()
+    check_close(z.cpu().numpy()[some].T, orc.mlp2(ref, ref2, x[some], activation="gelu"), f"two-matrix MLP b={b} T={T}")
+
+
 @pytest.mark.parametrize("path", ["bf16", "e5m2"])
 @pytest.mark.parametrize("b,nbr,nbc,T", [(128, 4, 6, 300), (128, 128, 2, 1100), (64, 40, 3, 3400), (64, 5, 3, 200)])
 @pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
