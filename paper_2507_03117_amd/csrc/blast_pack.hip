@@ -575,7 +575,7 @@ constexpr int kRanked = 16;  // candidates that a wave ranks by comparing each w
 struct alignas(16) SelectShared {
   unsigned hist[256];
   int wave_tot[16];
-  unsigned long long diff, kth;  // bits in which keys differ; the n_keep-th key ...
+  unsigned long long low, high, kth;  // the smallest and the largest key; the n_keep-th ...
   int kth_at;                    // ... and its index: what is kept sorts before it, or is it
   int rem, eq, digit, fill, open;
   int cand[kRanked];
@@ -587,40 +587,55 @@ static_assert(sizeof(SelectShared) % 16 == 0 && offsetof(SelectShared, hist) % 1
 // barrier is the workgroup's; a selection that is through waits for the others).  keys: LDS, n entries, receives the
 // keys of the scores.
 //
-// Most-significant-digit radix select: scores of one matrix share their leading bits (sign, exponent, often the first
-// mantissa bits), and a digit that every key carries would send every count to one LDS word, so the passes start below
-// the bits common to all keys, eight bits at a time; as soon as at most 16 keys carry the selected prefix, a wave ranks
+// Most-significant-digit radix select on the keys' distances from the smallest one: scores of one matrix share their
+// leading bits, or differ in all of the exponent's where they lie on both sides of a power of two, and a digit that most keys
+// carry sends their counts to one LDS word.  The passes start at the largest distance's leading bit, eight bits at a time;
+// as soon as at most 16 keys carry the selected prefix, a wave ranks
 // those by comparing each with all (40 ns each, a pass a microsecond: mask
-// update with up to 64 ranked that way 11.9 us on 64 blocks of 64 x 64 and 23.5 on 4096, now 8.2 and 20.9).
+// update with up to 64 ranked that way 11.9 us on 64 blocks of 64 x 64 and 23.5 on 4096, now 8.2 and 20.9).  Lanes of a wave
+// that carry its first lane's digit are counted with one addition: a few scores far from the others leave those one bin.
+// (4096 blocks, scores between 0.1 and 4 times one value: the first pass took 5.6 us while it began at the leading bit in which
+// keys differ, that of the exponent, and every key added to one of two words; 13.0 -> 7.8 us in all.)
 // What bounds it is not the work but its dependent steps and, in a workgroup that runs every instruction once or
 // twice with caches full of weights, the fetching of instructions: loops are left rolled.  4096 blocks, weight and gradient
 // (timestamps): keys unrolled over registers and passes down to one key, the two selections in turn: 16 us; keys in LDS,
-// side by side, 64 ranked: 12.8 us.
+// side by side: 12.8 us, now 7.8.
 template <int NT, int GROUPS>
 __device__ __forceinline__ void select_small(const double* __restrict__ score, int n, int n_keep, unsigned long long* keys,
                                              SelectShared* shared) {
   const int lane = lane_id(), group = GROUPS == 1 ? 0 : threadIdx.x / NT, tid = threadIdx.x - group * NT;
   SelectShared& sh = shared[group];
   const unsigned long long* bits = reinterpret_cast<const unsigned long long*>(score);
-  unsigned long long diff = 0ull;
-  const unsigned long long key0 = order_key(bits[0]);
-  if (tid == 0) sh.diff = 0ull;
+  unsigned long long low = ~0ull, high = 0ull;
+  if (tid == 0) {
+    sh.low = ~0ull;
+    sh.high = 0ull;
+  }
 #pragma unroll 4
   for (int i = tid; i < n; i += NT) {
     const unsigned long long k = order_key(bits[i]);
     keys[i] = k;
-    diff |= k ^ key0;
+    low = k < low ? k : low;
+    high = k > high ? k : high;
   }
 #pragma unroll 1
-  for (int d = kWave / 2; d > 0; d >>= 1) diff |= __shfl_xor(diff, d, kWave);
+  for (int d = kWave / 2; d > 0; d >>= 1) {
+    const unsigned long long l = __shfl_xor(low, d, kWave), h = __shfl_xor(high, d, kWave);
+    low = l < low ? l : low;
+    high = h > high ? h : high;
+  }
   wg_barrier<true>();
-  if (lane == 0 && diff != 0ull) atomicOr(&sh.diff, diff);
+  if (lane == 0) {
+    atomicMin(&sh.low, low);
+    atomicMax(&sh.high, high);
+  }
   wg_barrier<true>();
-  diff = sh.diff;
-  int fixed = diff == 0ull ? 0 : 64 - __clzll(diff);  // bits at and above this position are decided
-  unsigned long long prefix = fixed == 64 ? 0ull : (key0 >> fixed) << fixed;
+  low = sh.low;  // (from here on keys count from the smallest one)
+  high = sh.high;
+  int fixed = high == low ? 0 : 64 - __clzll(high - low);  // bits at and above this position are decided
+  unsigned long long prefix = 0ull;
   int rem = n_keep, eq = n;  // the rem-th of the eq keys that carry the decided bits is the one
-  auto carries = [&](unsigned long long k) { return fixed == 64 || (k >> fixed) == (prefix >> fixed); };
+  auto carries = [&](unsigned long long k) { return fixed == 64 || ((k - low) >> fixed) == (prefix >> fixed); };
 #pragma unroll 1
   for (;;) {
     const bool active = fixed > 0 && eq > kRanked;
@@ -639,7 +654,14 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
 #pragma unroll 2
       for (int i = tid; i < n; i += NT) {
         const unsigned long long k = keys[i];
-        if (carries(k)) atomicAdd(&sh.hist[(unsigned)(k >> sft) & ((1u << width) - 1u)], 1u);
+        if (carries(k)) {
+          const unsigned digit = (unsigned)((k - low) >> sft) & ((1u << width) - 1u);
+          const unsigned long long same = __ballot(digit == (unsigned)__builtin_amdgcn_readfirstlane((int)digit));
+          if (!(same >> lane & 1ull))
+            atomicAdd(&sh.hist[digit], 1u);
+          else if (lane == __builtin_ctzll(same))
+            atomicAdd(&sh.hist[digit], (unsigned)__popcll(same));
+        }
       }
     }
     wg_barrier<true>();
@@ -682,7 +704,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
     // more equal keys than that: a thread counts those in its stretch of the indices
     const int per = (n + NT - 1) / NT, e0 = tid * per;
     int mine = 0;
-    for (int i = e0; i < e0 + per && i < n; ++i) mine += keys[i] == prefix ? 1 : 0;
+    for (int i = e0; i < e0 + per && i < n; ++i) mine += keys[i] - low == prefix ? 1 : 0;
     int inc = mine;
     for (int d = 1; d < kWave; d <<= 1) {
       const int v = __shfl_up(inc, d, kWave);
@@ -715,8 +737,8 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
       const int per = (n + NT - 1) / NT;
       int i = tid * per;
       for (int c = rem - eq_before;; ++i)
-        if (keys[i] == prefix && --c == 0) break;
-      sh.kth = prefix;
+        if (keys[i] - low == prefix && --c == 0) break;
+      sh.kth = prefix + low;
       sh.kth_at = i;
     }
   }
