@@ -582,9 +582,9 @@ struct alignas(16) SelectShared {
 };
 static_assert(sizeof(SelectShared) % 16 == 0 && offsetof(SelectShared, hist) % 16 == 0, "16-byte reads of hist");
 
-// The n_keep-th of n <= kSmallN scores (0 < n_keep < n) under (score descending, index ascending), into sh.kth and
+// The n_keep-th of n scores (0 < n_keep < n) under (score descending, index ascending), into sh.kth and
 // sh.kth_at, by a group of NT threads of a workgroup of GROUPS * NT: the caller's groups select side by side (every
-// barrier is the workgroup's; a selection that is through waits for the others).  keys: LDS, n entries, receives the
+// barrier is the workgroup's; a selection that is through waits for the others).  STAGED: keys, LDS of n entries, receives the
 // keys of the scores.
 //
 // Most-significant-digit radix select on the keys' distances from the smallest one: scores of one matrix share their
@@ -600,12 +600,13 @@ static_assert(sizeof(SelectShared) % 16 == 0 && offsetof(SelectShared, hist) % 1
 // twice with caches full of weights, the fetching of instructions: loops are left rolled.  4096 blocks, weight and gradient
 // (timestamps): keys unrolled over registers and passes down to one key, the two selections in turn: 16 us; keys in LDS,
 // side by side: 12.8 us, now 7.8.
-template <int NT, int GROUPS>
+template <int NT, int GROUPS, bool STAGED = true>
 __device__ __forceinline__ void select_small(const double* __restrict__ score, int n, int n_keep, unsigned long long* keys,
                                              SelectShared* shared) {
   const int lane = lane_id(), group = GROUPS == 1 ? 0 : threadIdx.x / NT, tid = threadIdx.x - group * NT;
   SelectShared& sh = shared[group];
   const unsigned long long* bits = reinterpret_cast<const unsigned long long*>(score);
+  auto key_of = [&](int i) { return STAGED ? keys[i] : order_key(bits[i]); };
   unsigned long long low = ~0ull, high = 0ull;
   if (tid == 0) {
     sh.low = ~0ull;
@@ -614,7 +615,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
 #pragma unroll 4
   for (int i = tid; i < n; i += NT) {
     const unsigned long long k = order_key(bits[i]);
-    keys[i] = k;
+    if (STAGED) keys[i] = k;
     low = k < low ? k : low;
     high = k > high ? k : high;
   }
@@ -653,7 +654,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
     if (active) {
 #pragma unroll 2
       for (int i = tid; i < n; i += NT) {
-        const unsigned long long k = keys[i];
+        const unsigned long long k = key_of(i);
         if (carries(k)) {
           const unsigned digit = (unsigned)((k - low) >> sft) & ((1u << width) - 1u);
           const unsigned long long same = __ballot(digit == (unsigned)__builtin_amdgcn_readfirstlane((int)digit));
@@ -699,12 +700,12 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
   if (eq <= kRanked) {
 #pragma unroll 2
     for (int i = tid; i < n; i += NT)
-      if (carries(keys[i])) sh.cand[atomicAdd(&sh.fill, 1)] = i;
+      if (carries(key_of(i))) sh.cand[atomicAdd(&sh.fill, 1)] = i;
   } else {
     // more equal keys than that: a thread counts those in its stretch of the indices
     const int per = (n + NT - 1) / NT, e0 = tid * per;
     int mine = 0;
-    for (int i = e0; i < e0 + per && i < n; ++i) mine += keys[i] - low == prefix ? 1 : 0;
+    for (int i = e0; i < e0 + per && i < n; ++i) mine += key_of(i) - low == prefix ? 1 : 0;
     int inc = mine;
     for (int d = 1; d < kWave; d <<= 1) {
       const int v = __shfl_up(inc, d, kWave);
@@ -718,7 +719,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
   if (eq <= kRanked) {
     if (tid < kWave) {
       const int at = lane < eq ? sh.cand[lane] : 0;
-      const unsigned long long k = lane < eq ? keys[at] : 0ull;
+      const unsigned long long k = lane < eq ? key_of(at) : 0ull;
       int before = 0;
 #pragma unroll 1
       for (int c = 0; c < eq; ++c) {
@@ -737,7 +738,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
       const int per = (n + NT - 1) / NT;
       int i = tid * per;
       for (int c = rem - eq_before;; ++i)
-        if (keys[i] - low == prefix && --c == 0) break;
+        if (key_of(i) - low == prefix && --c == 0) break;
       sh.kth = prefix + low;
       sh.kth_at = i;
     }
@@ -749,13 +750,25 @@ __device__ __forceinline__ bool select_keeps(const SelectShared& sh, unsigned lo
   return k > sh.kth || (k == sh.kth && i <= sh.kth_at);
 }
 
-// One workgroup: mask[i] = 1 for the n_keep highest of n <= kSmallN scores, else 0.  Dynamic LDS: n keys.
-__global__ __launch_bounds__(1024) void k_select_small(const double* __restrict__ score, int n, int n_keep,
-                                                       uint8_t* __restrict__ mask) {
+// One workgroup: mask[i] = 1 for the n_keep highest of n scores, else 0; workgroup 1 of a launch of two: of a second array
+// (the mask update ranks the weight and the gradient at the same sparsity).  STAGED: the keys in dynamic LDS, n <= kStagedN.
+// Otherwise every pass reads the scores again, which the L2 holds, while that is less than k_select_topk's eight passes over
+// what it has not collected yet: up to kOneWorkgroupN.  Weight and gradient, k_select_topk / this: 16384 blocks 25 / 11.7 us,
+// 43008 blocks 47 / 34; the call with its wait 65536 blocks 121 / 111, 229376 blocks 337 / 356.
+constexpr int kStagedN = 20000, kOneWorkgroupN = 1 << 17;
+template <bool STAGED>
+__global__ __launch_bounds__(1024) void k_select_small(const double* __restrict__ score0, int n, int n_keep,
+                                                       uint8_t* __restrict__ mask0, const double* __restrict__ score1,
+                                                       uint8_t* __restrict__ mask1) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long keys[];
   __shared__ SelectShared ssh[1];
-  select_small<1024, 1>(score, n, n_keep, keys, ssh);
-  for (int i = threadIdx.x; i < n; i += 1024) mask[i] = select_keeps(ssh[0], keys[i], i) ? 1 : 0;
+  static_assert(kStagedN * 8 + sizeof(ssh) <= 160 * 1024, "the keys fit the LDS of a CU");
+  const double* __restrict__ score = blockIdx.x == 0 ? score0 : score1;
+  uint8_t* __restrict__ mask = blockIdx.x == 0 ? mask0 : mask1;
+  select_small<1024, 1, STAGED>(score, n, n_keep, keys, ssh);
+  const unsigned long long* bits = reinterpret_cast<const unsigned long long*>(score);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += 1024) mask[i] = select_keeps(ssh[0], STAGED ? keys[i] : order_key(bits[i]), i) ? 1 : 0;
 }
 
 // One workgroup: the mask update of prune-and-grow on n <= kSmallN blocks - both selections, side by side, and their
@@ -1249,24 +1262,43 @@ int check_shape(int64_t rows, int64_t cols, int32_t b) {
   return BLAST_OK;
 }
 
-// mask = the n_keep highest of n <= kSmallN scores (0 < n_keep < n); with scores1 merged with the n_keep highest of those.
-int launch_select_small(const double* scores, const double* scores1, int64_t n, int64_t n_keep, uint8_t* mask,
-                        hipStream_t stream) {
+// mask = the n_keep highest of n <= kSmallN scores (0 < n_keep < n), merged with the n_keep highest of scores1.
+int launch_masks_small(const double* scores, const double* scores1, int64_t n, int64_t n_keep, uint8_t* mask, hipStream_t stream) {
   static blast::DeviceFlags lds_set;
   int dev = 0;
   BLAST_HIP_TRY(hipGetDevice(&dev));
   if (!lds_set.test(dev)) {
-    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_select_small),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, kSmallN * 8));
     BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_masks_small),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kSmallN * 8));
     lds_set.set(dev);
   }
-  if (scores1)
-    k_masks_small<<<dim3(1), dim3(1024), (size_t)n * 16, stream>>>(scores, scores1, (int)n, (int)n_keep, mask);
-  else
-    k_select_small<<<dim3(1), dim3(1024), (size_t)n * 8, stream>>>(scores, (int)n, (int)n_keep, mask);
-  BLAST_LAUNCH_CHECK("k_select_small");
+  k_masks_small<<<dim3(1), dim3(1024), (size_t)n * 16, stream>>>(scores, scores1, (int)n, (int)n_keep, mask);
+  BLAST_LAUNCH_CHECK("k_masks_small");
+  return BLAST_OK;
+}
+
+// mask = the n_keep highest of n scores (0 < n_keep < n), and mask1 those of scores1 where there is one.
+int launch_select(const double* scores, const double* scores1, int64_t n, int64_t n_keep, uint8_t* mask, uint8_t* mask1,
+                  hipStream_t stream) {
+  static blast::DeviceFlags lds_set;
+  int dev = 0;
+  BLAST_HIP_TRY(hipGetDevice(&dev));
+  if (!lds_set.test(dev)) {
+    BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_select_small<true>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, kStagedN * 8));
+    lds_set.set(dev);
+  }
+  const dim3 grid(scores1 ? 2 : 1);
+  if (n > kOneWorkgroupN) {
+    k_select_topk<<<grid, dim3(1024), 0, stream>>>(scores, n, n_keep, mask, scores1, mask1);
+    BLAST_LAUNCH_CHECK("k_select_topk");
+  } else if (n <= kStagedN) {
+    k_select_small<true><<<grid, dim3(1024), (size_t)n * 8, stream>>>(scores, (int)n, (int)n_keep, mask, scores1, mask1);
+    BLAST_LAUNCH_CHECK("k_select_small");
+  } else {
+    k_select_small<false><<<grid, dim3(1024), 0, stream>>>(scores, (int)n, (int)n_keep, mask, scores1, mask1);
+    BLAST_LAUNCH_CHECK("k_select_small");
+  }
   return BLAST_OK;
 }
 
@@ -1381,11 +1413,8 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
     if (!scored) {
       k_fill_u8<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(m, n, n_keep == n ? 1 : 0);
       BLAST_LAUNCH_CHECK("k_fill_u8");
-    } else if (n <= kSmallN) {
-      if (int rc = launch_select_small(scores, nullptr, n, n_keep, m, stream)) return rc;
     } else {
-      k_select_topk<<<dim3(1), dim3(1024), 0, stream>>>(scores, n, n_keep, m);
-      BLAST_LAUNCH_CHECK("k_select_topk");
+      if (int rc = launch_select(scores, nullptr, n, n_keep, m, nullptr, stream)) return rc;
     }
   }
   if (small) {
@@ -1613,10 +1642,9 @@ extern "C" int blast_generate_masks(const uint16_t* W, int64_t ldw, const uint16
   }
   if (int rc = launch_block_scores(b, W, ldw, nbc, n, scores, G, ldg, scores_g, stream)) return rc;
   if (n <= kSmallN) {  // both selections and the merge in one workgroup
-    return launch_select_small(scores, scores_g, n, n_keep, mask_out, stream);
+    return launch_masks_small(scores, scores_g, n, n_keep, mask_out, stream);
   }
-  k_select_topk<<<dim3(2), dim3(1024), 0, stream>>>(scores, n, n_keep, mw, scores_g, mg);
-  BLAST_LAUNCH_CHECK("k_select_topk(W, G)");
+  if (int rc = launch_select(scores, scores_g, n, n_keep, mw, mg, stream)) return rc;
   k_merge_masks<<<per_elem, dim3(256), 0, stream>>>(mw, mg, n, mask_out);
   BLAST_LAUNCH_CHECK("k_merge_masks");
   return BLAST_OK;
@@ -1660,12 +1688,7 @@ extern "C" int blast_pooled_topk_mask(const float* S, int64_t lds, int64_t rows,
   double* scores = static_cast<double*>(ws);
   k_pooled_scores<<<dim3((unsigned)n), dim3(256), 0, stream>>>(S, lds, (int)nbc, b, scores);
   BLAST_LAUNCH_CHECK("k_pooled_scores");
-  if (n <= kSmallN) {
-    return launch_select_small(scores, nullptr, n, n_keep, mask_out, stream);
-  }
-  k_select_topk<<<dim3(1), dim3(1024), 0, stream>>>(scores, n, n_keep, mask_out);
-  BLAST_LAUNCH_CHECK("k_select_topk(pooled)");
-  return BLAST_OK;
+  return launch_select(scores, nullptr, n, n_keep, mask_out, nullptr, stream);
 }
 
 // The dense form of a packed matrix: W_new of prune_weights() (BLaST Sec. 3.2), zeros outside the stored blocks.

@@ -314,7 +314,7 @@ def test_selection_cuts_a_group_of_equal_scores(api, ties):
         assert np.array_equal(got, orc.generate_masks(W, np.ascontiguousarray(W[::-1]), b, sparsity))
 
 
-@pytest.mark.parametrize("nbr,nbc", [(1, 2), (9, 7), (64, 64), (91, 90), (128, 64), (97, 91), (160, 128), (200, 131), (300, 164)])
+@pytest.mark.parametrize("nbr,nbc", [(1, 2), (9, 7), (64, 64), (91, 90), (128, 64), (97, 91), (159, 126), (200, 131), (300, 164), (400, 330)])
 @pytest.mark.parametrize("kind", ["straddle", "outlier", "signed", "wide", "levels", "equal"])
 def test_selection_by_the_distribution_of_scores(api, nbr, nbc, kind):
     """The selection itself, on scores that are known exactly (a block of equal sensitivities has that mean): on both sides of
