@@ -574,32 +574,55 @@ constexpr int kRanked = 16;  // candidates that a wave ranks by comparing each w
 // alignment too).
 struct alignas(16) SelectShared {
   unsigned hist[256];
+  uint4 wave_keys[16];  // of a wave: the smallest and the largest upper word, differing bits of the lower words
   int wave_tot[16];
-  unsigned long long low, high, kth;  // the smallest and the largest key; the n_keep-th ...
+  unsigned long long kth;        // the n_keep-th key ...
   int kth_at;                    // ... and its index: what is kept sorts before it, or is it
   int rem, eq, digit, fill, open;
   int cand[kRanked];
 };
 static_assert(sizeof(SelectShared) % 16 == 0 && offsetof(SelectShared, hist) % 16 == 0, "16-byte reads of hist");
 
+// Over a row of 16 lanes, and over a wave: every lane has the result.
+template <int CTRL>
+__device__ __forceinline__ unsigned from_lane(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+template <typename F>
+__device__ __forceinline__ unsigned reduce_row(unsigned v, F f) {
+  v = f(v, from_lane<0x121>(v));  // rotations of the row by 1, 2, 4, 8
+  v = f(v, from_lane<0x122>(v));
+  v = f(v, from_lane<0x124>(v));
+  return f(v, from_lane<0x128>(v));
+}
+template <typename F>
+__device__ __forceinline__ unsigned reduce_wave(unsigned v, F f) {
+  v = reduce_row(v, f);
+  auto row = [&](int lane) { return (unsigned)__builtin_amdgcn_readlane((int)v, lane); };
+  return f(f(row(0), row(16)), f(row(32), row(48)));
+}
+
 // The n_keep-th of n scores (0 < n_keep < n) under (score descending, index ascending), into sh.kth and
 // sh.kth_at, by a group of NT threads of a workgroup of GROUPS * NT: the caller's groups select side by side (every
 // barrier is the workgroup's; a selection that is through waits for the others).  STAGED: keys, LDS of n entries, receives the
 // keys of the scores.
 //
-// Most-significant-digit radix select on the keys' distances from the smallest one: scores of one matrix share their
-// leading bits, or differ in all of the exponent's where they lie on both sides of a power of two, and a digit that most keys
-// carry sends their counts to one LDS word.  The passes start at the largest distance's leading bit, eight bits at a time;
-// as soon as at most 16 keys carry the selected prefix, a wave ranks
+// Most-significant-digit radix select on the keys' distances from the smallest one (its upper word: reducing 64 bits takes
+// twice the instructions): scores of one matrix share their leading bits, or differ in all of the exponent's where they lie on
+// both sides of a power of two, and a digit that most keys carry sends their counts to one LDS word.  The passes start at the
+// largest distance's leading bit, eight bits at a time; as soon as at most 16 keys carry the selected prefix, a wave ranks
 // those by comparing each with all (40 ns each, a pass a microsecond: mask
-// update with up to 64 ranked that way 11.9 us on 64 blocks of 64 x 64 and 23.5 on 4096, now 8.2 and 20.9).  Lanes of a wave
-// that carry its first lane's digit are counted with one addition: a few scores far from the others leave those one bin.
-// (4096 blocks, scores between 0.1 and 4 times one value: the first pass took 5.6 us while it began at the leading bit in which
-// keys differ, that of the exponent, and every key added to one of two words; 13.0 -> 7.8 us in all.)
+// update with up to 64 ranked that way 11.9 us on 64 blocks of 64 x 64 and 23.5 on 4096, now 8.2 and 20.9).
+// Weight and gradient, 4096 blocks of 64 x 64, normal: from the leading bit in which keys differ, the exponent's there, the
+// first pass took 5.6 us, every key adding to one of two words, 12.9 us in all; now 6.5.  (Blocks of 32 x 32, whose scores lie
+// between two powers of two: 6.7, now 6.7.)
+// A few scores far from the others still leave those one bin: a wave a quarter of whose first keys share a digit counts the
+// lanes that carry its first lane's with one addition (16384 blocks, one of them 100 times the others: mask update 51 us, 44
+// without; 0.7 us of 4096 normal ones where every wave does).
 // What bounds it is not the work but its dependent steps and, in a workgroup that runs every instruction once or
 // twice with caches full of weights, the fetching of instructions: loops are left rolled.  4096 blocks, weight and gradient
 // (timestamps): keys unrolled over registers and passes down to one key, the two selections in turn: 16 us; keys in LDS,
-// side by side: 12.8 us, now 7.8.
+// side by side: 12.8 us, now 6.5.
 template <int NT, int GROUPS, bool STAGED = true>
 __device__ __forceinline__ void select_small(const double* __restrict__ score, int n, int n_keep, unsigned long long* keys,
                                              SelectShared* shared) {
@@ -607,33 +630,31 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
   SelectShared& sh = shared[group];
   const unsigned long long* bits = reinterpret_cast<const unsigned long long*>(score);
   auto key_of = [&](int i) { return STAGED ? keys[i] : order_key(bits[i]); };
-  unsigned long long low = ~0ull, high = 0ull;
-  if (tid == 0) {
-    sh.low = ~0ull;
-    sh.high = 0ull;
-  }
+  auto lesser = [](unsigned x, unsigned y) { return x < y ? x : y; };
+  auto greater = [](unsigned x, unsigned y) { return x > y ? x : y; };
+  auto either = [](unsigned x, unsigned y) { return x | y; };
+  const unsigned long long key0 = order_key(bits[0]);
+  unsigned least = ~0u, most = 0u, diff = 0u;  // of the keys' upper words; bits in which their lower words differ
 #pragma unroll 4
   for (int i = tid; i < n; i += NT) {
     const unsigned long long k = order_key(bits[i]);
     if (STAGED) keys[i] = k;
-    low = k < low ? k : low;
-    high = k > high ? k : high;
+    least = min(least, (unsigned)(k >> 32));
+    most = max(most, (unsigned)(k >> 32));
+    diff |= (unsigned)k ^ (unsigned)key0;
   }
-#pragma unroll 1
-  for (int d = kWave / 2; d > 0; d >>= 1) {
-    const unsigned long long l = __shfl_xor(low, d, kWave), h = __shfl_xor(high, d, kWave);
-    low = l < low ? l : low;
-    high = h > high ? h : high;
-  }
+  least = reduce_wave(least, lesser);
+  most = reduce_wave(most, greater);
+  diff = reduce_wave(diff, either);
+  if (lane == 0) sh.wave_keys[tid / kWave] = make_uint4(least, most, diff, 0u);
   wg_barrier<true>();
-  if (lane == 0) {
-    atomicMin(&sh.low, low);
-    atomicMax(&sh.high, high);
-  }
-  wg_barrier<true>();
-  low = sh.low;  // (from here on keys count from the smallest one)
-  high = sh.high;
-  int fixed = high == low ? 0 : 64 - __clzll(high - low);  // bits at and above this position are decided
+  const uint4 of_wave = sh.wave_keys[lane % (NT / kWave)];  // (every row of 16 lanes reads the 8 or 16 waves')
+  least = reduce_row(of_wave.x, lesser);
+  most = reduce_row(of_wave.y, greater);
+  diff = reduce_row(of_wave.z, either);
+  // bits at and above `fixed` are decided, in the keys' distance from `low`
+  int fixed = most != least ? 64 - __builtin_clz(most - least) : diff != 0u ? 32 - __builtin_clz(diff) : 0;
+  const unsigned long long low = most != least ? (unsigned long long)least << 32 : fixed == 0 ? key0 : key0 >> fixed << fixed;
   unsigned long long prefix = 0ull;
   int rem = n_keep, eq = n;  // the rem-th of the eq keys that carry the decided bits is the one
   auto carries = [&](unsigned long long k) { return fixed == 64 || ((k - low) >> fixed) == (prefix >> fixed); };
@@ -652,16 +673,26 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
     if (open == 0) break;
     const int sft = fixed > 8 ? fixed - 8 : 0, width = fixed - sft;
     if (active) {
+      auto digit_of = [&](unsigned long long k) { return (unsigned)((k - low) >> sft) & ((1u << width) - 1u); };
+      const unsigned long long k0 = key_of(tid < n ? tid : n - 1);
+      const unsigned sample = carries(k0) ? digit_of(k0) : 256u + lane;
+      if (__popcll(__ballot(sample == (unsigned)__builtin_amdgcn_readfirstlane((int)sample))) <= kWave / 4) {
 #pragma unroll 2
-      for (int i = tid; i < n; i += NT) {
-        const unsigned long long k = key_of(i);
-        if (carries(k)) {
-          const unsigned digit = (unsigned)((k - low) >> sft) & ((1u << width) - 1u);
-          const unsigned long long same = __ballot(digit == (unsigned)__builtin_amdgcn_readfirstlane((int)digit));
-          if (!(same >> lane & 1ull))
-            atomicAdd(&sh.hist[digit], 1u);
-          else if (lane == __builtin_ctzll(same))
-            atomicAdd(&sh.hist[digit], (unsigned)__popcll(same));
+        for (int i = tid; i < n; i += NT) {
+          const unsigned long long k = key_of(i);
+          if (carries(k)) atomicAdd(&sh.hist[digit_of(k)], 1u);
+        }
+      } else {
+        for (int i = tid; i < n; i += NT) {
+          const unsigned long long k = key_of(i);
+          if (carries(k)) {
+            const unsigned digit = digit_of(k);
+            const unsigned long long same = __ballot(digit == (unsigned)__builtin_amdgcn_readfirstlane((int)digit));
+            if (!(same >> lane & 1ull))
+              atomicAdd(&sh.hist[digit], 1u);
+            else if (lane == __builtin_ctzll(same))
+              atomicAdd(&sh.hist[digit], (unsigned)__popcll(same));
+          }
         }
       }
     }
@@ -753,9 +784,10 @@ __device__ __forceinline__ bool select_keeps(const SelectShared& sh, unsigned lo
 // One workgroup: mask[i] = 1 for the n_keep highest of n scores, else 0; workgroup 1 of a launch of two: of a second array
 // (the mask update ranks the weight and the gradient at the same sparsity).  STAGED: the keys in dynamic LDS, n <= kStagedN.
 // Otherwise every pass reads the scores again, which the L2 holds, while that is less than k_select_topk's eight passes over
-// what it has not collected yet: up to kOneWorkgroupN.  Weight and gradient, k_select_topk / this: 16384 blocks 25 / 11.7 us,
-// 43008 blocks 47 / 34; the call with its wait 65536 blocks 121 / 111, 229376 blocks 337 / 356.
-constexpr int kStagedN = 20000, kOneWorkgroupN = 1 << 17;
+// what it has not collected yet: up to kOneWorkgroupN.  Mask update with its wait, k_select_topk / this: 16384 blocks 62 /
+// 44 us, 43008 blocks 105 / 86, and with half of the gradient zero 105 / 107; 65536 blocks 122 / 100 and 122 / 118, 128000
+// blocks 205 / 168 and 204 / 222.
+constexpr int kStagedN = 20000, kOneWorkgroupN = 1 << 16;
 template <bool STAGED>
 __global__ __launch_bounds__(1024) void k_select_small(const double* __restrict__ score0, int n, int n_keep,
                                                        uint8_t* __restrict__ mask0, const double* __restrict__ score1,

@@ -314,19 +314,20 @@ def test_selection_cuts_a_group_of_equal_scores(api, ties):
         assert np.array_equal(got, orc.generate_masks(W, np.ascontiguousarray(W[::-1]), b, sparsity))
 
 
-@pytest.mark.parametrize("nbr,nbc", [(1, 2), (9, 7), (64, 64), (91, 90), (128, 64), (97, 91), (159, 126), (200, 131), (300, 164), (400, 330)])
-@pytest.mark.parametrize("kind", ["straddle", "outlier", "signed", "wide", "levels", "equal"])
+@pytest.mark.parametrize("nbr,nbc", [(1, 2), (9, 7), (64, 64), (91, 90), (128, 64), (97, 91), (159, 126), (200, 131), (300, 164), (256, 256), (257, 256), (400, 330)])
+@pytest.mark.parametrize("kind", ["straddle", "outlier", "signed", "wide", "levels", "near", "equal"])
 def test_selection_by_the_distribution_of_scores(api, nbr, nbc, kind):
     """The selection itself, on scores that are known exactly (a block of equal sensitivities has that mean): on both sides of
-    a power of two, all alike but one, of both signs, over sixty decades, on a few levels, all equal; from two blocks to more
-    than one workgroup's keys.  The highest are kept, the first in index order among equals."""
+    a power of two, all alike but one, of both signs, over sixty decades, on a few levels, apart in the last bits only, all equal; from
+    two blocks to more than one workgroup's keys.  The highest are kept, the first in index order among equals."""
     import torch
 
     rng = np.random.default_rng(9790 + nbr)
     n, b = nbr * nbc, 16
     v = {"straddle": lambda: rng.uniform(0.9, 1.1, n), "outlier": lambda: np.r_[1e30, rng.uniform(1.0, 1.001, n - 1)],
          "signed": lambda: rng.normal(0.0, 1.0, n), "wide": lambda: 10.0 ** rng.uniform(-30, 30, n),
-         "levels": lambda: rng.integers(0, 5, n).astype(float), "equal": lambda: np.full(n, 0.375)}[kind]()
+         "levels": lambda: rng.integers(0, 5, n).astype(float),
+         "near": lambda: 1.0 + rng.integers(0, 8, n) * 2.0 ** -23, "equal": lambda: np.full(n, 0.375)}[kind]()
     v = v.astype(np.float32)
     S = torch.from_numpy(v.reshape(nbr, 1, nbc, 1)).cuda().expand(nbr, b, nbc, b).reshape(nbr * b, nbc * b)
     for s in (0.5, 0.93):
