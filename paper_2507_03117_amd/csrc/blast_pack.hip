@@ -13,6 +13,8 @@
 // For matrices of up to a few thousand blocks, select is one workgroup and all that follows it one launch.
 #include "blast_common.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int kWave = 64;
@@ -925,6 +927,11 @@ struct GatherArgs {
   int code;  // mask code of every block where there is no mask
 };
 
+// More blocks than kSmallN, the index arrays still made by a workgroup each: a thread owns up to kBigPer blocks (a multiple
+// of four), flags in 64 bits, positions in 16.
+constexpr int kBigPer = 48, kBigN = 1024 * kBigPer;
+static_assert(kBigN + 1024 < 65536, "two counts share a 32-bit word, positions 16 bits");
+
 // Flags of the blocks a thread owns (bit j: block tid * per + j is kept).
 __device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask, int code, int n, int per) {
   const int e0 = threadIdx.x * per;
@@ -932,6 +939,24 @@ __device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask
 #pragma unroll
   for (int j = 0; j < kSmallPer; ++j)
     keep |= (j < per && e0 + j < n && (mask ? mask[e0 + j] : code) != 0) ? 1u << j : 0u;
+  return keep;
+}
+__device__ __forceinline__ unsigned long long big_flags(const uint8_t* __restrict__ mask, int code, int n, int per) {
+  const int e0 = threadIdx.x * per;
+  const bool words = mask && (reinterpret_cast<uintptr_t>(mask) & 3u) == 0;
+  unsigned long long keep = 0ull;
+#pragma unroll 4
+  for (int j = 0; j < per; j += 4) {
+    unsigned four = 0u;
+    if (words && e0 + j + 3 < n) {
+      const unsigned v = *reinterpret_cast<const unsigned*>(mask + e0 + j);
+      const unsigned any = ((((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v) >> 7) & 0x01010101u;  // a bit per byte that is not 0
+      four = (any * 0x01020408u) >> 24;
+    } else {
+      for (int u = 0; u < 4; ++u) four |= (e0 + j + u < n && (mask ? mask[e0 + j + u] : code) != 0) ? 1u << u : 0u;
+    }
+    keep |= (unsigned long long)four << j;
+  }
   return keep;
 }
 
@@ -942,32 +967,53 @@ __device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask
 // What bounds it: the index jobs, a chain of scans and barriers in a workgroup each.  Three 8192 x 2048 matrices, b = 64,
 // 80 % sparse, after a mask update: as one workgroup for all index arrays and a launch for the values 12 + 4.6 us per
 // matrix and 187 us for the update and re-packing together, now 9 us and 163.
+// BIG: more than kSmallN blocks, at most kBigN, which took nine launches.  A thread's blocks in two walks, as they do not fit
+// registers; every workgroup of values still counts the flags before its blocks itself, n bytes from the L2.  Packing with its
+// wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 92 / 61, 14336 of 64 x 64
+// 72 / 40, of 128 x 128 93 / 59; none left out, 43008 blocks: 119 / 100.  Three 8192 x 2048 matrices, b = 32, mask update and
+// packing: 320 us before, now 208.
+template <bool BIG>
 __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__ mask, int nbr, int nbc, SmallOut o,
                                                      PlanOut narrow, PlanOut wide, GatherArgs ga) {
   __shared__ __attribute__((aligned(16))) int cnt[1024];  // populations of the rows, or of the columns
-  __shared__ union {
-    struct {
-      int rptr[1025], rord[1024];
-    } row;
-    struct {
-      int kpos[kSmallN];  // position of a stored block in col_idx / vals, by row-major block index
-      uint8_t m[kSmallN];
-    } col;
-  } sh;
+  using Flags = std::conditional_t<BIG, unsigned long long, unsigned>;
+  using Place = std::conditional_t<BIG, uint16_t, int>;
+  struct RowArrays {
+    int rptr[1025], rord[1024];
+  };
+  // rows: these; columns: position of a stored block in col_idx / vals by row-major block index, [n], and flags, [n]
+  __shared__ __attribute__((aligned(16))) char arrays[BIG ? 16 : kSmallN * 5];
+  extern __shared__ __attribute__((aligned(16))) char big_arrays[];
+  char* const scratch = BIG ? big_arrays : arrays;
+  static_assert(sizeof(RowArrays) <= kSmallN * 5, "one or the other");
+  RowArrays& row = *reinterpret_cast<RowArrays*>(scratch);
   __shared__ int wave_tot[16], sh3[3];
   const int tid = threadIdx.x;
   const int n = nbr * nbc;
-  const int per = (n + 1023) >> 10;  // blocks per thread (uniform); the loops below are unrolled to kSmallPer
+  // blocks per thread (uniform); without BIG the loops below are unrolled to kSmallPer
+  const int per = BIG ? (((n + 1023) >> 10) + 3) & ~3 : (n + 1023) >> 10, most = BIG ? per : kSmallPer;
   const int e0 = tid * per;
-  const unsigned keep = small_flags(mask, ga.code, n, per);
+  Flags keep;
+  if constexpr (BIG)
+    keep = big_flags(mask, ga.code, n, per);
+  else
+    keep = small_flags(mask, ga.code, n, per);
+  auto population = [](Flags f) { return BIG ? __popcll(f) : __popc((unsigned)f); };
   const int jobs = o.col_ptr ? 2 : 1;
 
   if ((int)blockIdx.x >= jobs) {
     // ---- the values of the candidates [c0, c0 + ga.span) -----------------------------------------------------------
     const int c0 = ((int)blockIdx.x - jobs) * ga.span;
     int before = 0;  // stored blocks before c0
+    if constexpr (BIG) {
+      const int mine = c0 - e0;  // of this thread's blocks, so many lie before c0
+      before = population(mine >= per ? keep : mine > 0 ? keep & ((1ull << mine) - 1ull) : 0ull);
 #pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) before += __popcll(__ballot(((keep >> j) & 1u) && e0 + j < c0));
+      for (int d = kWave / 2; d > 0; d >>= 1) before += __shfl_xor(before, d, kWave);
+    } else {
+#pragma unroll
+      for (int j = 0; j < kSmallPer; ++j) before += __popcll(__ballot(((keep >> j) & 1u) && e0 + j < c0));
+    }
     if (lane_id() == 0) wave_tot[tid / kWave] = before;
     const int cand = c0 + lane_id();
     const int code = lane_id() < ga.span && cand < n ? (mask ? mask[cand] : ga.code) : 0;
@@ -1019,9 +1065,9 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
     {
       int r = e0 / nbc, c = e0 - r * nbc, run = 0;  // a thread adds its blocks of a row at once
 #pragma unroll
-      for (int j = 0; j < kSmallPer; ++j) {
+      for (int j = 0; j < most; ++j) {
         if (j < per && e0 + j < n) {
-          run += (keep >> j) & 1u;
+          run += (int)((keep >> j) & 1u);
           if (++c == nbc || j == per - 1 || e0 + j == n - 1) {
             if (run) atomicAdd(&cnt[r], run);
             run = 0;
@@ -1037,36 +1083,38 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
     int nnz;
     const int ex = block_exscan<true>(tid < nbr ? cnt[tid] : 0, wave_tot, nnz);
     if (tid < nbr) {
-      sh.row.rptr[tid] = ex;
+      row.rptr[tid] = ex;
       o.row_ptr[tid] = ex;
     }
     if (tid == 0) {
-      sh.row.rptr[nbr] = nnz;
+      row.rptr[nbr] = nnz;
       o.row_ptr[nbr] = nnz;
       o.scalars[0] = nnz;
       if (!o.col_ptr) o.scalars[1] = 0;
     }
-    schedule_small(cnt, nbr, sh.row.rord, o.row_order);
+    schedule_small(cnt, nbr, row.rord, o.row_order);
     wg_barrier<true>();
     if (!o.col_ptr) return;
-    const int heavy = chunk_plans_small(sh.row.rptr, sh.row.rord, nbr, narrow, wide, wave_tot, sh3);
+    const int heavy = chunk_plans_small(row.rptr, row.rord, nbr, narrow, wide, wave_tot, sh3);
     if (tid == 0) o.scalars[1] = heavy;
     return;
   }
 
+  Place* const kpos = reinterpret_cast<Place*>(scratch);
+  uint8_t* const flag = reinterpret_cast<uint8_t*>(kpos + n);
   // ---- columns: the position of a stored block is the number of kept blocks before it, in row-major order for
   // col_idx / vals and in column-major order for the column-grouped index --------------------------------------------
   int nnz;
-  int k = block_exscan<true>(__popc(keep), wave_tot, nnz);  // (its barriers also cover the clearing of cnt)
+  int k = block_exscan<true>(population(keep), wave_tot, nnz);  // (its barriers also cover the clearing of cnt)
   {
     int c = e0 % nbc;
 #pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) {
+    for (int j = 0; j < most; ++j) {
       if (j < per && e0 + j < n) {
-        const bool kp = (keep >> j) & 1u;
-        sh.col.m[e0 + j] = kp ? 1 : 0;
+        const bool kp = (int)((keep >> j) & 1u);
+        flag[e0 + j] = kp ? 1 : 0;
         if (kp) {
-          sh.col.kpos[e0 + j] = k++;
+          kpos[e0 + j] = (Place)k++;
           atomicAdd(&cnt[c], 1);
         }
         if (++c == nbc) c = 0;
@@ -1083,14 +1131,14 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
   if (nnz > o.nnz_cap) return;
   {
     int* csc_blk = o.csc_row + (nnz + 3) / 4 * 4;
-    unsigned keep_c = 0u;
+    Flags keep_c = 0;
     const int c0 = e0 / nbr, r0 = e0 - c0 * nbr;
     {
       int r = r0, at = r0 * nbc + c0;
 #pragma unroll
-      for (int j = 0; j < kSmallPer; ++j) {
+      for (int j = 0; j < most; ++j) {
         if (j < per && e0 + j < n) {
-          keep_c |= sh.col.m[at] ? 1u << j : 0u;
+          keep_c |= flag[at] ? (Flags)1 << j : (Flags)0;
           at += nbc;
           if (++r == nbr) {
             r = 0;
@@ -1100,14 +1148,14 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
       }
     }
     int total;
-    int e = block_exscan<true>(__popc(keep_c), wave_tot, total);
+    int e = block_exscan<true>(population(keep_c), wave_tot, total);
     int r = r0, at = r0 * nbc + c0;
 #pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) {
+    for (int j = 0; j < most; ++j) {
       if (j < per && e0 + j < n) {
         if ((keep_c >> j) & 1u) {
           o.csc_row[e] = r;
-          csc_blk[e] = sh.col.kpos[at];
+          csc_blk[e] = kpos[at];
           ++e;
         }
         at += nbc;
@@ -1439,7 +1487,7 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
     if (int rc = launch_block_scores(b, W, ldw, nbc, n, scores, nullptr, 0, nullptr, stream)) return rc;
   }
 
-  const bool small = n > 0 && n <= kSmallN && nbr <= 1024 && nbc <= 1024;
+  const bool small = n > 0 && n <= kBigN && nbr <= 1024 && nbc <= 1024, big = small && n > kSmallN;
   if (m && small && !scored) mask = nullptr;  // every block has the same code: no launch that writes it n times
   if (m && n > 0 && mask) {
     if (!scored) {
@@ -1455,10 +1503,23 @@ int pack_enqueue(const uint16_t* W, int64_t ldw, int64_t rows, int64_t cols, int
     // Sixteen candidates are up to 128 KiB of values; of 128-wide blocks four are, and eight still fill the chip when there
     // are many.  (Sixteen of those, every block kept, eight matrices: 2048 x 2048 255 us, with four 138; 4096 x 14336 388,
     // with four 375 and with eight 366, at 90 % sparsity 145, 161 and 138.)
-    const int span = b < 128 ? 16 : n < 2048 ? 4 : 8;
+    const int span = b < 64 && big ? 32 : b < 128 ? 16 : n < 2048 ? 4 : 8;
     const unsigned spans = nnz_cap > 0 ? (unsigned)((n + span - 1) / span) : 0u;
-    k_pack_small<<<dim3((aux ? 2u : 1u) + spans), dim3(1024), 0, stream>>>(mask, (int)nbr, (int)nbc, o, narrow, wide,
-                                                                          GatherArgs{W, ldw, b, vals, span, n_keep == n ? 1 : 0});
+    const dim3 grid((aux ? 2u : 1u) + spans);
+    const GatherArgs ga{W, ldw, b, vals, span, n_keep == n ? 1 : 0};
+    if (big) {
+      static blast::DeviceFlags lds_set;
+      int dev = 0;
+      BLAST_HIP_TRY(hipGetDevice(&dev));
+      if (!lds_set.test(dev)) {
+        BLAST_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pack_small<true>),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, kBigN * 3));
+        lds_set.set(dev);
+      }
+      k_pack_small<true><<<grid, dim3(1024), (size_t)n * 3, stream>>>(mask, (int)nbr, (int)nbc, o, narrow, wide, ga);
+    } else {
+      k_pack_small<false><<<grid, dim3(1024), 0, stream>>>(mask, (int)nbr, (int)nbc, o, narrow, wide, ga);
+    }
     BLAST_LAUNCH_CHECK("k_pack_small");
     return BLAST_OK;
   } else {

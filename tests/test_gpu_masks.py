@@ -258,6 +258,49 @@ def test_pack_at_the_edges_of_its_single_launch(api, nbr, nbc, b, with_aux):
         assert np.array_equal(t.row_order.cpu().numpy(), ref_t.row_order)
 
 
+@pytest.mark.parametrize("nbr,nbc,b", [(1024, 9, 16), (9, 1024, 16), (1025, 9, 16), (93, 97, 32), (128, 65, 64), (99, 96, 128),
+                                       (211, 157, 16), (128, 258, 32), (1024, 48, 16), (48, 1024, 16), (49153, 1, 16), (323, 165, 16)])
+@pytest.mark.parametrize("fill", ["some", "none", "all", "one_row", "one_column"])
+def test_pack_in_one_launch_beyond_a_few_thousand_blocks(api, nbr, nbc, b, fill):
+    """From one block above the small matrices to the most that the launch takes, and just beyond each of its limits; masks
+    that start at no multiple of four bytes, regrown blocks, rows and columns without a block, without the column index."""
+    import torch
+
+    rng = np.random.default_rng(800 + nbr + nbc)
+    n = nbr * nbc
+    W = torch.randn((nbr * b, nbc * b), device="cuda", generator=torch.Generator("cuda").manual_seed(n)).to(torch.bfloat16)
+    mask = {"some": lambda: rng.choice(np.array([0, 0, 0, 1, 2, 128, 255], dtype=np.uint8), size=(nbr, nbc)),
+            "none": lambda: np.zeros((nbr, nbc), np.uint8), "all": lambda: np.ones((nbr, nbc), np.uint8),
+            "one_row": lambda: (np.arange(nbr)[:, None] == nbr // 2) * np.ones((nbr, nbc), np.uint8),
+            "one_column": lambda: (np.arange(nbc)[None, :] == nbc - 1) * np.ones((nbr, nbc), np.uint8)}[fill]()
+    mask = np.ascontiguousarray(mask, dtype=np.uint8)
+    keep = mask != 0
+    r, c = np.nonzero(keep)
+    blocks = W.view(nbr, b, nbc, b)[torch.from_numpy(r).cuda(), :, torch.from_numpy(c).cuda(), :]  # [nnz, b, b], row-major order of the blocks
+    blocks[torch.from_numpy(mask[keep] == 2).cuda()] = 0
+    count = keep.sum(1)
+    order = np.argsort(-count, kind="stable")
+    for shift, with_aux in ((0, True), (1, True), (2, False)):
+        raw = torch.empty(n + 4, dtype=torch.uint8, device="cuda")
+        m = raw[shift:shift + n].view(nbr, nbc)
+        m.copy_(torch.from_numpy(mask))
+        p = api.bsr_pack(W, b, mask=m, with_aux=with_aux)
+        assert p.nnz == len(r) and p.max_row_blocks == (int(count.max()) if with_aux else 0)
+        assert np.array_equal(p.row_ptr.cpu().numpy(), np.r_[0, np.cumsum(count)])
+        assert np.array_equal(p.col_idx.cpu().numpy()[: p.nnz], c)
+        assert np.array_equal(p.row_order.cpu().numpy(), order)
+        assert torch.equal(p.vals[: p.nnz * b * b].view(torch.int16).view(-1, b, b), blocks.view(torch.int16))
+        if with_aux:  # the column-grouped index and the chunk plans, by way of the transpose and a product
+            t = api.bsr_transpose(p)
+            assert np.array_equal(t.row_ptr.cpu().numpy(), np.r_[0, np.cumsum(keep.sum(0))])
+            assert np.array_equal(t.col_idx.cpu().numpy()[: t.nnz], np.nonzero(keep.T)[1])
+            if n * b * b <= 1 << 24 and len(r):
+                x = torch.randn((3, nbc * b), device="cuda").to(torch.bfloat16)
+                whole = torch.from_numpy(np.kron((mask != 0) & (mask != 2), np.ones((b, b), np.uint8))).cuda()
+                y, ref = api.bsr_spmm(p, x).float(), x.float() @ (W.float() * whole).T
+                assert (y - ref).abs().max() <= 2.0 ** -8 * ref.abs().max()  # (rounded to bf16: 2^-9 of an element)
+
+
 @pytest.mark.parametrize("nbr,nbc,levels_w,levels_g", [(3, 7, 2, 9), (32, 64, 3, 1), (64, 128, 2, 200), (64, 128, 1, 2),
                                                        (40, 45, 1000, 3)])
 @pytest.mark.parametrize("s", [0.3, 0.81])
