@@ -85,11 +85,20 @@ __device__ __forceinline__ float gelu(float g) {
   return __builtin_fmaf(-__builtin_fminf(t, 3.402823466e38f), tail, g > 0.0f ? g : 0.0f * g);
 }
 
-__device__ __forceinline__ float apply_act(int act, float g) {
+// Activation of the output of a single product.
+__device__ __forceinline__ float post_act(int act, float g) {
   if (act == BLAST_ACT_SILU) return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
   if (act == BLAST_ACT_GELU) return gelu(g);
   return g > 0.0f ? g : 0.0f;
 }
 
+// Activation of a gated product.  It has its GELU from erff: with the shorter one beside the SiLU of its usual calls the
+// kernels are laid out otherwise, and these calls are slower (16384 x 53248 at 95 % Zipf, 128-wide, 2048 tokens: 720 / 724 us;
+// 4096 x 14336, 128-wide, eight layers, at 90 % 27 tokens 179 / 183 us, at 95 % 13 tokens 96 / 100).
+__device__ __forceinline__ float apply_act(int act, float g) {
+  if (act == BLAST_ACT_SILU) return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
+  if (act == BLAST_ACT_GELU) return 0.5f * g * (1.0f + erff(g * 0.70710678118654752440f));
+  return g > 0.0f ? g : 0.0f;
+}
 
 }  // namespace blast_dev

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * NWAVES, 2) void k_spmm_split(const TileArgs a,
       float sum = red[0][id][lane];
 #pragma unroll
       for (int w = 1; w < C::NW; ++w) sum += red[w][id][lane];
-      y[nj] = POST ? apply_act(a.act, sum) : sum;
+      y[nj] = POST ? post_act(a.act, sum) : sum;
     }
     const int64_t off = (int64_t)t * a.syt + row * a.syi;
     typedef __bf16 Bf16Pair __attribute__((ext_vector_type(2)));

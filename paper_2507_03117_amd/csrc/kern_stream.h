@@ -828,21 +828,21 @@ __global__ __launch_bounds__(64 * NW, (StreamCfg<B, TW, NW, F8>::WAVES_PER_SIMD)
 #pragma unroll
           for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = apply_act(BLAST_ACT_GELU, acc0[mi][ni][j]);
+            for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = post_act(BLAST_ACT_GELU, acc0[mi][ni][j]);
       } else if (a.act == BLAST_ACT_SILU) {
 #pragma unroll
         for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
           for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = apply_act(BLAST_ACT_SILU, acc0[mi][ni][j]);
+            for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = post_act(BLAST_ACT_SILU, acc0[mi][ni][j]);
       } else {
 #pragma unroll
         for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
           for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = apply_act(BLAST_ACT_RELU, acc0[mi][ni][j]);
+            for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = post_act(BLAST_ACT_RELU, acc0[mi][ni][j]);
       }
     }
 
