@@ -33,26 +33,19 @@ __device__ __forceinline__ void wg_barrier() {
 
 // Exclusive scan of one int per thread over the whole workgroup (blockDim.x a
 // multiple of 64, at most 1024).  `wave_tot` is LDS scratch of >= 16 ints.
-// Returns the exclusive prefix; `total` receives the workgroup sum.
+// Returns the exclusive prefix; `total` receives the workgroup sum.  A chain of instructions and two barriers: shifts between
+// lanes by the vector unit instead of through LDS, the waves' sums read in one go and scanned by every wave.
 template <bool LDS_ONLY = false>
 __device__ __forceinline__ int block_exscan(int v, int* wave_tot, int& total) {
-  const int lane = lane_id(), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int o = __shfl_up(inc, d, kWave);
-    if (lane >= d) inc += o;
-  }
+  const int lane = lane_id(), nw = blockDim.x / kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int inc = blast::lanes_scan(v);
   wg_barrier<LDS_ONLY>();  // protect wave_tot from the previous use
   if (lane == kWave - 1) wave_tot[wave] = inc;
   wg_barrier<LDS_ONLY>();
-  int base = 0, tot = 0;
-  for (int w = 0; w < nw; ++w) {
-    int t = wave_tot[w];
-    if (w < wave) base += t;
-    tot += t;
-  }
-  total = tot;
+  const int waves = blast::lanes_scan(lane < nw ? wave_tot[lane] : 0);
+  total = __builtin_amdgcn_readlane(waves, 15);
+  const int base = wave > 0 ? __builtin_amdgcn_readlane(waves, wave - 1) : 0;
   return base + inc - v;
 }
 
@@ -847,29 +840,23 @@ __device__ __forceinline__ void schedule_small(const int* rcnt, int nbr, int* ro
 
 // Both chunk plans of nbr <= 1024 rows in schedule order, cut into chunks of at most 16 / 64 blocks (an empty row
 // still gets one chunk: its output has to be written); run by a workgroup of 1024 threads.  rptr, rord: row pointers
-// and schedule in LDS; sh: LDS scratch of 3 ints.  Thread 0 returns with the fullest row's population.
+// and schedule in LDS.  Populations fall along the schedule: the first row is the fullest, the rows that a plan cuts come before
+// the others.  Thread 0 returns with the fullest row's population.
 __device__ __forceinline__ int chunk_plans_small(const int* rptr, const int* rord, int nbr, const PlanOut& narrow,
-                                                 const PlanOut& wide, int* wave_tot, int* sh) {
+                                                 const PlanOut& wide, int* wave_tot) {
   const int tid = threadIdx.x;
-  if (tid == 0) {
-    sh[0] = 0;  // fullest row
-    sh[1] = 0;  // chunks of the rows that the first plan cuts
-    sh[2] = 0;  // ... the second plan
-  }
-  wg_barrier<true>();
   constexpr int ls0 = __builtin_ctz(blast::kChunkBlocks), ls1 = __builtin_ctz(blast::kWideChunkBlocks);
-  int r = 0, kb = 0, ke = 0, n0 = 0, n1 = 0;
+  int r = 0, kb = 0, ke = 0, n0 = 0, n1 = 0, next = 0;  // next: the population of the next row in the schedule
   if (tid < nbr) {
     r = rord[tid];
     kb = rptr[r];
     ke = rptr[r + 1];
+    const int rn = tid + 1 < nbr ? rord[tid + 1] : r;
+    next = tid + 1 < nbr ? rptr[rn + 1] - rptr[rn] : 0;
     n0 = (ke - kb + (1 << ls0) - 1) >> ls0;
     n1 = (ke - kb + (1 << ls1) - 1) >> ls1;
     n0 = n0 < 1 ? 1 : n0;
     n1 = n1 < 1 ? 1 : n1;
-    atomicMax(&sh[0], ke - kb);
-    if (n0 > 1) atomicAdd(&sh[1], n0);
-    if (n1 > 1) atomicAdd(&sh[2], n1);
     narrow.row_slot[r] = n0 > 1 ? tid : -1;
   }
   int total;
@@ -894,18 +881,20 @@ __device__ __forceinline__ int chunk_plans_small(const int* rptr, const int* ror
       }
     }
   }
-  const int heavy = sh[0];
+  // chunks of the rows that a plan cuts: these rows are the first, the last of them knows
+  if (n0 > 1 && next <= 1 << ls0) narrow.hdr[3] = (first & 0xFFFF) + n0;
+  if (n1 > 1 && next <= 1 << ls1) wide.hdr[3] = (first >> 16) + n1;
   if (tid == 0) {
     narrow.hdr[0] = total & 0xFFFF;
-    narrow.hdr[1] = heavy;
+    narrow.hdr[1] = ke - kb;
     narrow.hdr[2] = 1 << ls0;
-    narrow.hdr[3] = sh[1];
+    if (n0 <= 1) narrow.hdr[3] = 0;
     wide.hdr[0] = total >> 16;
-    wide.hdr[1] = heavy;
+    wide.hdr[1] = ke - kb;
     wide.hdr[2] = 1 << ls1;
-    wide.hdr[3] = sh[2];
+    if (n1 <= 1) wide.hdr[3] = 0;
   }
-  return heavy;
+  return ke - kb;
 }
 
 struct SmallOut {
@@ -966,13 +955,14 @@ __device__ __forceinline__ unsigned long long big_flags(const uint8_t* __restric
 // stored as zeros: it joins the structure without changing the product.  No mask: every block has the code ga.code.
 // What bounds it: the index jobs, a chain of scans and barriers in a workgroup each.  Three 8192 x 2048 matrices, b = 64,
 // 80 % sparse, after a mask update: as one workgroup for all index arrays and a launch for the values 12 + 4.6 us per
-// matrix and 187 us for the update and re-packing together, now 9 us and 163.
+// matrix and 187 us for the update and re-packing together, as two and the rest 9 us and 163; the launch takes 6.6 us (4096
+// blocks of 32 x 32; 8.8 before) since the scans shift by the vector unit and the chunk plans add nothing up with atomics, 3.4
+// us of whose 7.7 in the row job these were.
 // BIG: more than kSmallN blocks, at most kBigN, which took nine launches.  A thread's blocks in two walks, as they do not fit
 // registers; every workgroup of values still counts the flags before its blocks itself, n bytes from the L2.  Packing with its
 // wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 92 / 61, 14336 of 64 x 64
 // 72 / 40, of 128 x 128 93 / 59; none left out, 43008 blocks: 119 / 100.  Three 8192 x 2048 matrices, b = 32, mask update and
-// packing: 320 us before, now 208.
-template <bool BIG>
+// packing: 320 us before, packing: 320 us before, then 208, 198 with the scans above.
 __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__ mask, int nbr, int nbc, SmallOut o,
                                                      PlanOut narrow, PlanOut wide, GatherArgs ga) {
   __shared__ __attribute__((aligned(16))) int cnt[1024];  // populations of the rows, or of the columns
@@ -987,7 +977,7 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
   char* const scratch = BIG ? big_arrays : arrays;
   static_assert(sizeof(RowArrays) <= kSmallN * 5, "one or the other");
   RowArrays& row = *reinterpret_cast<RowArrays*>(scratch);
-  __shared__ int wave_tot[16], sh3[3];
+  __shared__ int wave_tot[16];
   const int tid = threadIdx.x;
   const int n = nbr * nbc;
   // blocks per thread (uniform); without BIG the loops below are unrolled to kSmallPer
@@ -1095,7 +1085,7 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
     schedule_small(cnt, nbr, row.rord, o.row_order);
     wg_barrier<true>();
     if (!o.col_ptr) return;
-    const int heavy = chunk_plans_small(row.rptr, row.rord, nbr, narrow, wide, wave_tot, sh3);
+    const int heavy = chunk_plans_small(row.rptr, row.rord, nbr, narrow, wide, wave_tot);
     if (tid == 0) o.scalars[1] = heavy;
     return;
   }
@@ -1214,7 +1204,7 @@ __global__ __launch_bounds__(1024) void k_transpose(const TransposeArgs a) {
     if (!a.index_job) return;
     // the index job's LDS lies over the tile
     struct Sched {
-      int rcnt[1024], rptr[1025], rord[1024], wave_tot[16], sh[3];
+      int rcnt[1024], rptr[1025], rord[1024], wave_tot[16];
     };
     static_assert(sizeof(Sched) <= sizeof(tile), "the schedule fits the tile");
     Sched& s = *reinterpret_cast<Sched*>(tile);
@@ -1226,7 +1216,7 @@ __global__ __launch_bounds__(1024) void k_transpose(const TransposeArgs a) {
     schedule_small(s.rcnt, n, s.rord, a.row_order_t);
     wg_barrier<true>();
     if (!a.max_row_out) return;
-    const int heavy = chunk_plans_small(s.rptr, s.rord, n, a.narrow, a.wide, s.wave_tot, s.sh);
+    const int heavy = chunk_plans_small(s.rptr, s.rord, n, a.narrow, a.wide, s.wave_tot);
     if (tid == 0) *a.max_row_out = heavy;
     return;
   }

@@ -48,17 +48,6 @@ struct FlatCfg {
   static_assert(NSLOT >= 2 && (NSLOT - 1) * OPS < 64, "a block in flight beside the one being multiplied");
 };
 
-// Inclusive prefix sum over the wave: shifts inside rows of 16 lanes, then the rows' totals passed on.
-__device__ __forceinline__ int lanes_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);  // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, true);  // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, true);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
 template <int B, bool DUAL, bool CHUNK, int XI>
 __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
   static_assert(!(DUAL && CHUNK), "the activation needs complete sums: the gated product is never split");
@@ -131,7 +120,7 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
       if (best == slot) mine |= 1ull << k;
     }
     const int rest = lane >= ng ? len : 0;
-    const int incl = lanes_scan(rest);
+    const int incl = blast::lanes_scan(rest);
     const int total = BLAST_LANE(incl, 63);
     if (total > 0) {
       // the rest, of `total` work, is cut where it levels the groups: group s is given what it lacks to `level`
@@ -156,7 +145,7 @@ __global__ __launch_bounds__(1024) void k_decode_flat(const DecArgs a) {
     }
     const bool own = (mine >> lane) & 1ull;
     const int blocks = own ? n0 + n1 : 0;
-    const int pos = lanes_scan(blocks) - blocks;
+    const int pos = blast::lanes_scan(blocks) - blocks;
     if (own) {
       const int i = __builtin_popcountll(mine & ((1ull << lane) - 1ull));
       t_row[i] = row;
