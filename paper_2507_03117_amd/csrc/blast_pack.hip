@@ -962,7 +962,8 @@ __device__ __forceinline__ unsigned long long big_flags(const uint8_t* __restric
 // registers; every workgroup of values still counts the flags before its blocks itself, n bytes from the L2.  Packing with its
 // wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 92 / 61, 14336 of 64 x 64
 // 72 / 40, of 128 x 128 93 / 59; none left out, 43008 blocks: 119 / 100.  Three 8192 x 2048 matrices, b = 32, mask update and
-// packing: 320 us before, packing: 320 us before, then 208, 198 with the scans above.
+// packing: 320 us before, then 208, 198 with the scans above.
+template <bool BIG>
 __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__ mask, int nbr, int nbc, SmallOut o,
                                                      PlanOut narrow, PlanOut wide, GatherArgs ga) {
   __shared__ __attribute__((aligned(16))) int cnt[1024];  // populations of the rows, or of the columns
