@@ -1,11 +1,14 @@
 """GPU parity of the blocked prune-and-grow mask update (Sec. 3.2) and of packing its result: byte-exact masks,
 bit-exact packed arrays, regrown blocks stored as zeros."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 
 from oracle import oracle as orc
 from paper_2507_03117_amd import synth
 from tests.helpers import bits_of, check_close, mask_dev, to_dev
+from tests.test_gpu_parity import check_aux
 
 pytestmark = pytest.mark.gpu
 
@@ -290,7 +293,9 @@ def test_pack_in_one_launch_beyond_a_few_thousand_blocks(api, nbr, nbc, b, fill)
         assert np.array_equal(p.col_idx.cpu().numpy()[: p.nnz], c)
         assert np.array_equal(p.row_order.cpu().numpy(), order)
         assert torch.equal(p.vals[: p.nnz * b * b].view(torch.int16).view(-1, b, b), blocks.view(torch.int16))
-        if with_aux:  # the column-grouped index and the chunk plans, by way of the transpose and a product
+        if with_aux:  # the chunk plans and the column-grouped index, the latter by way of the transpose too
+            check_aux(p, SimpleNamespace(rows=nbr * b, cols=nbc * b, b=b, nnz=len(r), row_order=order, col_idx=c,
+                                         row_ptr=np.r_[0, np.cumsum(count)]))
             t = api.bsr_transpose(p)
             assert np.array_equal(t.row_ptr.cpu().numpy(), np.r_[0, np.cumsum(keep.sum(0))])
             assert np.array_equal(t.col_idx.cpu().numpy()[: t.nnz], np.nonzero(keep.T)[1])
