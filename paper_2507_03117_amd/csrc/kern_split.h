@@ -4,7 +4,7 @@
 // than CUs that chain is the whole launch while most of the chip has nothing to do.  Here a workgroup of eight or four waves
 // shares a tile of 64 rows x 64 tokens by the contraction: the row's stages (64 contraction indices, whole 128-byte lines
 // of a block and of the activations) are dealt to the waves, each accumulates the whole tile from copies of its own, and
-// the partial sums meet in LDS, added in wave order.  No barrier before that.
+// the partial sums meet in LDS.  No barrier before that.
 //  - A wave owns one 16 KiB stage in LDS.  Its fragments go to registers as soon as it has landed (64 of them), so that
 //    the next stage is copied over it while they are multiplied: eight stages are in flight per CU.  One workgroup of eight
 //    waves fits a CU, or two of four, for up to twice and three times as many tiles as CUs, of which one is multiplied
@@ -12,8 +12,13 @@
 //    4096 x 4096 at 90 %, 128-wide, 500 tokens, 512 tiles: 10.9 -> 9.4).
 //  - Rows of a wave's tile alternate between the two matrix tiles, so that a lane ends up with two neighbouring rows of a
 //    token, as in the streaming kernel.
-// Relative error against 64 bits, other kernel / this one: 1600 x 6400 at 80 %, 333 tokens 2.1e-7 / 0.9e-7; 1024 x 8192 at
-// 80 %, 128-wide, 1000 tokens 2.5e-7 / 1.0e-7; 2048 x 8192 at 90 %, 256 tokens 0.9e-7 / 0.8e-7.
+//  - Both forms add up the same eight chains: each of four waves keeps two accumulators, of every other stage it is dealt,
+//    and adds them before the sums meet, as of eight waves 0 and 4, 1 and 5, ... are; so a token's row is the same bits
+//    whichever form the size of a call leads to.  (With one accumulator a wave: 0.1 to 0.6 us slower than with two on rows of
+//    10 to 26 blocks, 459 to 1590 tokens, b = 64, and chains twice as long.)
+// Relative error against 64 bits, one chain (streaming kernel) / four / eight chains: b = 64, 40 rows of 5, 449 tokens 9.7e-8
+// / 6.5e-8 / 6.2e-8; 33 rows of 24, 640 tokens 2.3e-7 / 1.14e-7 / 8.8e-8; b = 128, 24 rows of 4, one of 50, 900 tokens 3.2e-7 /
+// 1.54e-7 / 1.12e-7.  2048 x 8192 at 90 %, 256 tokens, decode kernel / this one: 0.9e-7 / 0.8e-7.
 // Second product of the two-matrix MLP of 1600 and 6400 features at 80 %, 384 tokens: 17.0 us on the streaming kernel, 10.6.
 // What bounds it: a tile asks the L1 for a byte per 32 flop, half the matrix peak at 64 bytes a clock; at these sizes the
 // chain (indices, one trip per stage, the sums in LDS) is most of the launch.
@@ -27,6 +32,7 @@ template <int B, int NWAVES>
 struct SplitCfg {
   static_assert(B == 64 || B == 128, "a stage is a whole 128-byte line deep");
   static constexpr int NW = NWAVES;
+  static constexpr int SETS = 8 / NW;         // chains of a wave
   static constexpr int SB = 64;               // rows and tokens of the tile
   static constexpr int SUB = B / SB;          // tiles per block row
   static constexpr int KSL = B / 64;          // stages per stored block
@@ -75,16 +81,16 @@ __global__ __launch_bounds__(64 * NWAVES, 2) void k_spmm_split(const TileArgs a,
     for (int i = 0; i < C::NI; ++i) BLAST_GLDS16(x + xoff[i], slot + C::TILE + i * 1024);
   };
 
-  f32x16 acc[2][2];  // [token half][even / odd rows]
+  f32x16 acc[C::SETS][2][2];  // [chain][token half][even / odd rows]
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+  for (int set = 0; set < C::SETS; ++set)
 #pragma unroll
-    for (int nj = 0; nj < 2; ++nj)
+    for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[mi][nj][v] = 0.0f;
-  if (mine > 0) issue(0);
-#pragma unroll 1
-  for (int s = 0; s < mine; ++s) {
+      for (int nj = 0; nj < 2; ++nj)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[set][mi][nj][v] = 0.0f;
+  auto multiply = [&](int s, f32x16 (&sum)[2][2]) {
     __builtin_amdgcn_s_waitcnt(BLAST_VMCNT(0));
     asm volatile("" ::: "memory");
     bf16x8 fw[4][2], fx[4][2];
@@ -106,19 +112,37 @@ __global__ __launch_bounds__(64 * NWAVES, 2) void k_spmm_split(const TileArgs a,
       for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
         for (int nj = 0; nj < 2; ++nj)
-          acc[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kk][mi], fw[kk][nj], acc[mi][nj], 0, 0, 0);
+          sum[mi][nj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kk][mi], fw[kk][nj], sum[mi][nj], 0, 0, 0);
     asm volatile("" ::: "memory");
+  };
+  if (mine > 0) issue(0);
+#pragma unroll 1
+  for (int s = 0; s < mine; s += C::SETS) {
+    multiply(s, acc[0]);
+    if constexpr (C::SETS == 2) {
+      if (s + 1 < mine) multiply(s + 1, acc[1]);
+    }
   }
 
-  // Every wave's sums go over its own stage (nothing is in flight into it any more); then a wave owns an eighth of the
-  // tile: four tokens per lane, two rows each.
+  if constexpr (C::SETS == 2) {
+    if (mine > 1) {
+#pragma unroll
+      for (int mh = 0; mh < 2; ++mh)
+#pragma unroll
+        for (int nj = 0; nj < 2; ++nj)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[0][mh][nj][v] += acc[1][mh][nj][v];
+    }
+  }
+  // Every wave's sums go over its own stage (nothing is in flight into it any more); then a wave owns 1 / NW of the tile:
+  // 32 / NW tokens per lane, two rows each.
   float (*red)[64][64] = reinterpret_cast<float (*)[64][64]>(smem);
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+  for (int mh = 0; mh < 2; ++mh)
 #pragma unroll
     for (int nj = 0; nj < 2; ++nj)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) red[wave][(mi * 2 + nj) * 16 + v][lane] = acc[mi][nj][v];
+      for (int v = 0; v < 16; ++v) red[wave][(mh * 2 + nj) * 16 + v][lane] = acc[0][mh][nj][v];
   __syncthreads();
   constexpr int PER = 32 / C::NW;  // registers of a lane's half of the tile (token half, v) that a wave owns
   const int mi = wave * PER / 16, v0 = wave * PER % 16;
@@ -132,9 +156,10 @@ __global__ __launch_bounds__(64 * NWAVES, 2) void k_spmm_split(const TileArgs a,
 #pragma unroll
     for (int nj = 0; nj < 2; ++nj) {
       const int id = (mi * 2 + nj) * 16 + v0 + v;
-      float sum = red[0][id][lane];
+      auto pair = [&](int w) { return C::SETS == 2 ? red[w][id][lane] : red[w][id][lane] + red[(w + 4) % C::NW][id][lane]; };
+      float sum = pair(0);
 #pragma unroll
-      for (int w = 1; w < C::NW; ++w) sum += red[w][id][lane];
+      for (int w = 1; w < 4; ++w) sum += pair(w);
       y[nj] = POST ? post_act(a.act, sum) : sum;
     }
     const int64_t off = (int64_t)t * a.syt + row * a.syi;

@@ -568,6 +568,26 @@ def test_output_tiles_shared_by_four_waves(api, b, nbr, per_row, full, T):
     check_close(z.cpu().numpy()[some].T, orc.mlp2(ref, ref2, x[some], activation="gelu"), f"two-matrix MLP b={b} T={T}")
 
 
+@pytest.mark.parametrize("b,nbr,per_row,few,many", [(64, 24, 9, 300, 800), (64, 40, 2, 280, 512), (64, 21, 17, 449, 800),
+                                                    (128, 12, 5, 300, 830), (128, 20, 8, 330, 513), (128, 15, 1, 290, 1000)])
+def test_a_token_is_summed_alike_by_four_waves_and_by_eight(api, b, nbr, per_row, few, many):
+    """A token's row of the product in a call that leaves every tile of 64 x 64 a CU (eight waves to a tile) and in a larger one
+    (four): the same bits, as both forms add up the same eight chains.  Rows of no stage to seventeen, so that a wave has none, one
+    or several of either chain."""
+    import torch
+
+    rng = np.random.default_rng(7100 + nbr)
+    nbc = 30
+    mask = np.zeros((nbr, nbc), dtype=np.uint8)
+    for r in range(nbr):
+        mask[r, rng.choice(nbc, size=max(per_row - r % 3, int(r % 5 > 0)), replace=False)] = 1
+    w = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
+    x = to_dev(synth.gauss_bf16(rng, (many, nbc * b), 1.0))
+    dev, _ = pack_both(api, w, b, mask=mask)
+    for dt in (torch.float32, torch.bfloat16):
+        assert torch.equal(api.bsr_spmm(dev, x[:few].contiguous(), out_dtype=dt), api.bsr_spmm(dev, x, out_dtype=dt)[:few])
+
+
 @pytest.mark.parametrize("path", ["bf16", "e5m2"])
 @pytest.mark.parametrize("b,nbr,nbc,T", [(128, 4, 6, 300), (128, 128, 2, 1100), (64, 40, 3, 3400), (64, 5, 3, 200)])
 @pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
