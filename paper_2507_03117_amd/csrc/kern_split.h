@@ -25,6 +25,7 @@
 #pragma once
 #include "kern_common.h"
 #include "kern_stream.h"
+#include "split_rule.h"
 
 namespace blast_dev {
 
@@ -44,16 +45,16 @@ struct SplitCfg {
 };
 
 template <int B, bool POST, int NWAVES>
-__global__ __launch_bounds__(64 * NWAVES, 2) void k_spmm_split(const TileArgs a, const int n_units, const int groups) {
+__global__ __launch_bounds__(64 * NWAVES, 2) void k_spmm_split(const TileArgs a, const int n_units, const int groups,
+                                                               const int stride_log2) {
   using C = SplitCfg<B, NWAVES>;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-  // the token tiles of a unit are 8 workgroup ids apart: one XCD, whose L2 serves the weights to all of them
-  const int blk = blockIdx.x, span = 8 * groups, rem = blk % span;
-  const int unit = (blk / span) * 8 + (rem & 7);
+  const SplitTile tile = split_tile(blockIdx.x, stride_log2, groups);
+  const int unit = tile.unit;
   if (unit >= n_units) return;  // whole workgroup, before any barrier
-  const int t0 = (rem >> 3) * C::SB;
+  const int t0 = tile.group * C::SB;
   const int rank = unit / C::SUB, si = unit % C::SUB;
   const int r = a.row_order ? ld_idx(a.row_order, rank) : rank;
   const int kb = ld_idx(a.m0.row_ptr, r);

@@ -1,0 +1,107 @@
+// Which single products take k_spmm_split (kern_split.h), and in which form.  Plain C++: no device code.
+#pragma once
+#include <cmath>
+#include <cstdint>
+
+namespace blast_dev {
+
+// Workgroup ids between the token tiles of a unit (64 output rows); the ids go round the XCDs.  Eight: a unit's tiles are
+// all on one XCD, whose L2 serves its weights to them.  With fewer than eight units, or a few more, that leaves most of the chip
+// idle (one unit: 32 CUs for all tiles), so there the tiles of a unit follow each other, over all XCDs, each of which reads what
+// little weight there is.  Eight waves, eight apart / one, microseconds: b = 64, 2 rows of 8 blocks, 4894 tokens 15.7 / 6.4
+// (streaming kernel 7.6), 3 rows of 8, 2672 tokens 11.3 / 6.1 (7.5), 11 rows of 20, 1031 tokens 15.4 / 11.0 (13.3); b = 128, one row
+// of 8, 5421 tokens 21.3 / 9.1 (15.0).  Eight units are spread as they are (b = 64, 8 rows of 8, 3210 tokens 12.0 / 12.6), and from
+// 12 on what the weights cost more is no longer always less than what was idle (equal rows, time with one over time with eight
+// apart: 12 units 0.90 on average, but up to 1.15; 16, 24, 32 units 1.07, 1.11, 1.15).
+constexpr int split_stride_log2(int64_t units) { return units < 12 && units != 8 ? 0 : 3; }
+
+// Workgroups of a launch, those without a tile included.
+constexpr int64_t split_workgroups(int64_t units, int64_t groups) {
+  const int64_t stride = (int64_t)1 << split_stride_log2(units);
+  return (units + stride - 1) / stride * stride * groups;
+}
+
+// Unit (at or beyond the last: none) and token tile of workgroup `id`.
+struct SplitTile {
+  int unit, group;
+};
+constexpr SplitTile split_tile(int id, int stride_log2, int groups) {
+  const int span = groups << stride_log2, turn = id / span, rem = id - turn * span;
+  return SplitTile{(turn << stride_log2) + (rem & ((1 << stride_log2) - 1)), rem >> stride_log2};
+}
+
+// The waves (4 or 8) of k_spmm_split (64 x 64 tiles, a row's stages dealt to the waves) for a single product that is better
+// off there than on the kernel that would take it otherwise; 0 where it is not.  Microseconds, uniform masks unless said
+// otherwise, bf16 output, graph replay:
+//   streaming / split (the former walks a row in sequence, and leaves CUs idle while its tiles are few): b = 64, 25 rows of
+//     20 blocks, 384 / 768 tokens 17.0 / 10.6, 17.4 / 15.5; 32 rows of 3, 512 tokens 6.6 / 5.2.  b = 128, 16 rows of 6.4, 384
+//     / 1024 tokens 17.6 / 9.4, 17.9 / 15.0.  With four waves, of which a CU takes two workgroups, up to twice as many
+//     tiles as CUs and, with 128-wide blocks that make a wave's chain short against the streaming kernel's, three times:
+//     b = 64, 29 rows of 7.4, 269 tokens (440 tiles) 11.7 / 9.2; 44 rows of 6, 700 tokens (484) 9.2 / 8.0 and (512) 8.0 /
+//     7.6, but (560) 13.4 / 14.9; b = 128, 30 rows of 2, 545 tokens (540) 12.2 / 8.5; 18 rows of 2.8, 546 (720) 14.8 / 11.7;
+//     (1200) 14.4 / 15.1; 11 rows of 2.6, 1921 (682) 11.4 / 12.8.
+//   eight waves / four: while every tile has a CU to itself eight (b = 64, 0.4 tiles per CU, 3 to 8 stages a row 4.6 / 4.9 ...
+//     6.7 / 7.2), unless every row is long (23 blocks 11.4 / 10.9, 31: 12.5 / 11.7); from there on four (1.03 tiles per CU 7.1 /
+//     5.6, 1.25: 9.1 / 8.0, 1.9: 17.3 / 16.1), unless one row among short ones is long (2 .. 4 stages, fullest 26, 1.1
+//     tiles per CU 9.3 / 10.5).  The line is a fit of the difference in 920 products.
+//   A row that is much fuller than the others is a chain in either kernel, walked here by four or eight waves: 4096 x
+//     4096, 128-wide, Zipf rows (5.3 blocks on average, fullest 47), 993 tokens 66 / 25, 384 tokens (42) 59 / 20; beyond the
+//     lines above the two estimates decide (500 products of uniform and Zipf rows, 257 to 2048 tokens, at most six tiles per CU).
+//   decode (33 to 256 tokens; it reads the matrix once per 32 tokens, in many small workgroups) / split: b = 64, 100 rows of 5, 64 /
+//     100 / 160 / 256 tokens 5.2 / 5.4, 7.7 / 5.5, 9.4 / 7.6, 13.6 / 8.8; 32 rows of 13, 128 / 256 tokens 7.3 / 7.4, 10.0 / 8.4;
+//     32 rows of 26, 192 tokens 9.5 / 11.3.  b = 128, 32 rows of 3.2, 64 / 100 / 256 tokens 4.1 / 5.9, 7.0 / 6.1, 13.0 / 7.7.
+//     A full row among the others is dealt to four waves of each 16 of its rows by decode: b = 128, 32 rows of 4.1, one of
+//     32, 64 / 160 / 256 tokens 6.8 / 14.9, 9.3 / 15.6, 12.0 / 16.1.  The two estimates were fitted to 1400 such
+//     calls (uniform rows, Zipf rows, one or four full rows; 33 to 256 tokens) for the choice between them, with eight
+//     waves: of the calls that they send here, none with 128-wide blocks and four with 64-wide ones are more than 5 %
+//     slower than on decode.
+// Over 580 products of 257 to 2048 tokens, before (eight waves only, a line by tiles) and after: uniform rows 4.7 % less time
+// on average, Zipf rows 18 %.
+// b: block width; nbr: block rows of the output; nnz: stored blocks, fullest: of the fullest row (0: not known); decode: whether
+// the decode kernel would take it; cus: compute units.
+inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t fullest, bool decode, int64_t cus) {
+  if (b != 64 && b != 128) return 0;
+  const int64_t units = nbr * (b / 64), groups = (tokens + 63) / 64, tiles = units * groups;
+  const int64_t launched = split_workgroups(units, groups);
+  const double mean = (double)nnz / nbr;
+  const double row = fullest > 0 ? (double)fullest : mean + 2.0 * std::sqrt(mean);  // (rows of a uniform mask vary by that)
+  // stages of the fullest row, of a row on average; of a wave in the fullest row; of a CU; tiles of a CU
+  const double most = row * (b / 64), average = mean * (b / 64), per_cu = (double)launched / cus;
+  const double chain4 = std::ceil(most / 4.0), chain8 = std::ceil(most / 8.0), load = average * tiles / cus;
+  const bool uneven = most > 2.5 * average;
+  const double beyond = per_cu > 1.0 ? per_cu - 1.0 : 0.0;
+  const double four_minus_eight = b == 64 ? 0.458 - 0.083 * chain4 + 0.023 * chain8 - 0.349 * per_cu - 1.445 * beyond + 0.036 * load
+                                          : 0.506 + 0.061 * chain4 - 0.247 * chain8 - 0.184 * per_cu - 1.558 * beyond + 0.034 * load;
+  const int waves = (uneven && most >= 12.0 && per_cu <= 1.5) || four_minus_eight >= 0.0 ? 8 : 4;
+  if (decode) {
+    if (tiles > 2 * cus) return 0;
+    const double groups32 = (double)((tokens + 31) / 32), mbytes = nnz * 1e-6 * b * b * 2 * groups32;
+    const double decode_units = nbr * (b / 16) * groups32 * 1e-3;
+    double decode_us, split_us;
+    if (b == 64) {
+      decode_us = 3.30 + 0.162 * mbytes + 1.68 * decode_units + 0.149 * row / 4;
+      split_us = (tiles > cus ? 3.06 : 3.68) + 1.65 * chain8 + 0.77 * load / 8;
+    } else {
+      decode_us = 3.33 + 0.128 * mbytes + 2.03 * decode_units + 0.291 * row / 4;
+      split_us = (tiles > cus ? 5.44 : 3.86) + 1.39 * chain8 + 0.89 * load / 8;
+    }
+    return decode_us > split_us + 0.3 ? waves : 0;
+  }
+  if (per_cu <= (b == 128 && average >= 2.0 ? (tokens <= 1024 ? 3.0 : 2.5) : 2.0)) return waves;
+  if (row <= mean + 3.0 * std::sqrt(mean) + 1.0 || per_cu > 6.0) return 0;  // (no more than a uniform mask's fullest row)
+  const bool wide = (int64_t)((tokens + 255) / 256) * nbr >= 2 * cus;  // the streaming kernel's tiles, see launch_stream_c
+  if (b == 128 && wide) return 0;
+  const int64_t ntt = wide ? (tokens + 255) / 256 : (tokens + 127) / 128;
+  const double blocks = (double)nnz * ntt / cus, items = (double)nbr * ntt / cus;
+  const double stream_us = b == 128 ? 3.27 + 1.24 * row + 0.490 * blocks + 0.85 * items
+                           : wide   ? 4.14 + 0.71 * row + 0.365 * blocks + 0.20 * items
+                                    : 2.86 + 0.44 * row + 0.231 * blocks + 0.33 * items;
+  double split_us;
+  if (b == 64)
+    split_us = waves == 4 ? 2.97 + 0.551 * chain4 + 0.217 * load + 0.888 * per_cu : 1.85 + 1.036 * chain8 + 0.225 * load + 2.196 * per_cu;
+  else
+    split_us = waves == 4 ? 2.99 + 0.604 * chain4 + 0.223 * load + 0.713 * per_cu : 1.93 + 1.081 * chain8 + 0.239 * load + 1.896 * per_cu;
+  return split_us * 1.1 < stream_us ? waves : 0;
+}
+
+}  // namespace blast_dev

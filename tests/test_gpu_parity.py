@@ -6,7 +6,7 @@ import pytest
 
 from oracle import oracle as orc
 from paper_2507_03117_amd import synth
-from tests.helpers import bits_of, check_close, long_row_case, long_scratch_bytes, mask_dev, to_dev
+from tests.helpers import bits_of, check_close, long_row_case, long_scratch_bytes, mask_dev, stratified_tokens, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -586,6 +586,30 @@ def test_a_token_is_summed_alike_by_four_waves_and_by_eight(api, b, nbr, per_row
     dev, _ = pack_both(api, w, b, mask=mask)
     for dt in (torch.float32, torch.bfloat16):
         assert torch.equal(api.bsr_spmm(dev, x[:few].contiguous(), out_dtype=dt), api.bsr_spmm(dev, x, out_dtype=dt)[:few])
+
+
+@pytest.mark.parametrize("b,nbr,per_row,full,T", [(64, 1, 20, 0, 4100), (64, 2, 3, 22, 2950), (64, 3, 1, 0, 3333), (64, 7, 5, 0, 1400),
+                                                  (64, 8, 5, 9, 1400), (64, 9, 4, 0, 1500), (64, 11, 2, 12, 1300), (64, 12, 2, 0, 1290),
+                                                  (128, 1, 6, 0, 5001), (128, 4, 2, 11, 2000), (128, 5, 3, 0, 1111), (128, 6, 9, 0, 1200)])
+def test_narrow_outputs_of_many_tokens(api, b, nbr, per_row, full, T):
+    """One to a dozen units of 64 output rows, whose tiles are on all XCDs or, from twelve on, on one each: any stretch of the
+    tokens gives the same bits as that stretch alone, and the values are the oracle's."""
+    import torch
+
+    rng = np.random.default_rng(7300 + nbr + b)
+    nbc = 24
+    mask = np.zeros((nbr, nbc), dtype=np.uint8)
+    for r in range(nbr):
+        mask[r, rng.choice(nbc, size=full if full and r == nbr - 1 else per_row, replace=False)] = 1
+    w = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
+    x = synth.gauss_bf16(rng, (T, nbc * b), 1.0)
+    dev, ref = pack_both(api, w, b, mask=mask)
+    xd = to_dev(x)
+    y = api.bsr_spmm(dev, xd, out=torch.full((T, nbr * b), float("nan"), device="cuda:0"))
+    for t0 in list(range(0, T - 320, 777)) + [T - 320]:
+        assert torch.equal(y[t0:t0 + 320], api.bsr_spmm(dev, xd[t0:t0 + 320].contiguous()))
+    some = stratified_tokens(T, 40)
+    check_close(y.cpu().numpy()[some].T, orc.spmm(ref, x[some]), f"b={b} {nbr} rows of {per_row}, one of {full}, T={T}")
 
 
 @pytest.mark.parametrize("path", ["bf16", "e5m2"])

@@ -1,0 +1,42 @@
+"""Which single products take the kernel for few output tiles, and in which form: the rule itself, on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CUS = 256
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("split") / "rule")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Wextra", os.path.join(HERE, "split_rule.cpp"), "-o", exe], check=True)
+
+    def ask(calls):
+        """(b, block rows, tokens, blocks per row, fullest row) -> waves, 0 for the other kernel"""
+        lines = "".join(f"{b} {nbr} {t} {round(nbr * mean)} {full} 0 {CUS}\n" for b, nbr, t, mean, full in calls)
+        res = subprocess.run([exe], input=lines, capture_output=True, text=True, check=True).stdout.split()
+        assert all(once == "1" for once in res[1::2])
+        return [int(w) for w in res[::2]]
+
+    return ask
+
+
+def tiles(call):
+    return call[1] * (call[0] // 64) * ((call[2] + 63) // 64)
+
+
+def test_narrow_outputs(rule):
+    """One to a dozen block rows under many tokens: up to one tile of 64 x 64 per CU (128-wide blocks: two) the tile is shared by
+    waves, whose eight chains of sums are more exact than the streaming kernel's one."""
+    calls = [(b, nbr, t, mean, mean + extra) for b in (64, 128) for nbr in range(1, 13) for t in range(300, 20000, 450)
+             for mean in (1, 3, 8, 20, 60) for extra in (0, 9)]
+    calls = [c for c in calls if tiles(c) <= CUS * (2 if c[0] == 128 else 1)]
+    assert len(calls) > 2000
+    for call, waves in zip(calls, rule(calls)):
+        assert waves in (4, 8), call
+
+
+def test_workgroups_cover_every_tile_once(rule):
+    rule([(64, units, t, 1, 1) for units in range(1, 70) for t in (33, 64, 65, 200, 2100)])
