@@ -30,6 +30,23 @@ constexpr SplitTile split_tile(int id, int stride_log2, int groups) {
   return SplitTile{(turn << stride_log2) + (rem & ((1 << stride_log2) - 1)), rem >> stride_log2};
 }
 
+// Waves to a tile, eight or four (the sums are the same): by the stages of the fullest row and of a row on average, and the
+// workgroups per CU.  A CU takes one workgroup of eight or two of four.  Time with four over time with eight, 7200 products of 33
+// to 32000 tokens, b = 64 / 128:
+//   up to one per CU: fullest row of up to 4 stages 1.03 / 1.04, 5 to 12 1.07 / 1.09, 13 to 20 1.03 / 1.06, 21 to 40 0.97 / 0.98, more
+//     0.91 / 0.91: eight waves are the shorter chain, until copies and not trips are what takes the time.
+//   from there to 1.5: 0.67 / 0.71 at 2 stages, 0.78 / 0.79 at 8, 0.87 / 0.90 at 20, 0.95 / 0.97 at 40, 1.02 / 1.04 beyond; beyond 1.5:
+//     0.69 / 0.73, 0.77 / 0.79, 0.85 / 0.87, 0.89 / 0.90, 0.93 / 0.95: eight waves leave half of the CUs a second round.
+//   rows of which the fullest has 2.5 times the average, 1 to 1.5 per CU: 13 to 20 stages 1.02, 21 to 40 1.07, more 0.97; 1.5 to 2:
+//     0.90, 1.01, 0.99: that row's tiles are a round of their own.
+// Of 3400 products that are better off here than on another kernel, 131 (4 %) take more than 4 % longer than with the other form.
+inline int split_form(double most, double average, double per_cu) {
+  if (per_cu <= 1.0) return most <= 20.0 ? 8 : 4;
+  const bool one_long_row = (per_cu <= 1.5 && most >= 24.0 && most > 1.5 * average) ||
+                            (per_cu <= 1.75 && most >= 14.0 && most > 4.0 * average);
+  return one_long_row ? 8 : 4;
+}
+
 // The waves (4 or 8) of k_spmm_split (64 x 64 tiles, a row's stages dealt to the waves) for a single product that is better
 // off there than on the kernel that would take it otherwise; 0 where it is not.  Microseconds, uniform masks unless said
 // otherwise, bf16 output, graph replay:
@@ -40,10 +57,6 @@ constexpr SplitTile split_tile(int id, int stride_log2, int groups) {
 //     b = 64, 29 rows of 7.4, 269 tokens (440 tiles) 11.7 / 9.2; 44 rows of 6, 700 tokens (484) 9.2 / 8.0 and (512) 8.0 /
 //     7.6, but (560) 13.4 / 14.9; b = 128, 30 rows of 2, 545 tokens (540) 12.2 / 8.5; 18 rows of 2.8, 546 (720) 14.8 / 11.7;
 //     (1200) 14.4 / 15.1; 11 rows of 2.6, 1921 (682) 11.4 / 12.8.
-//   eight waves / four: while every tile has a CU to itself eight (b = 64, 0.4 tiles per CU, 3 to 8 stages a row 4.6 / 4.9 ...
-//     6.7 / 7.2), unless every row is long (23 blocks 11.4 / 10.9, 31: 12.5 / 11.7); from there on four (1.03 tiles per CU 7.1 /
-//     5.6, 1.25: 9.1 / 8.0, 1.9: 17.3 / 16.1), unless one row among short ones is long (2 .. 4 stages, fullest 26, 1.1
-//     tiles per CU 9.3 / 10.5).  The line is a fit of the difference in 920 products.
 //   A row that is much fuller than the others is a chain in either kernel, walked here by four or eight waves: 4096 x
 //     4096, 128-wide, Zipf rows (5.3 blocks on average, fullest 47), 993 tokens 66 / 25, 384 tokens (42) 59 / 20; beyond the
 //     lines above the two estimates decide (500 products of uniform and Zipf rows, 257 to 2048 tokens, at most six tiles per CU).
@@ -65,14 +78,10 @@ inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t 
   const int64_t launched = split_workgroups(units, groups);
   const double mean = (double)nnz / nbr;
   const double row = fullest > 0 ? (double)fullest : mean + 2.0 * std::sqrt(mean);  // (rows of a uniform mask vary by that)
-  // stages of the fullest row, of a row on average; of a wave in the fullest row; of a CU; tiles of a CU
+  // stages of the fullest row, of a row on average; workgroups per CU; stages of a wave in the fullest row, of a CU
   const double most = row * (b / 64), average = mean * (b / 64), per_cu = (double)launched / cus;
   const double chain4 = std::ceil(most / 4.0), chain8 = std::ceil(most / 8.0), load = average * tiles / cus;
-  const bool uneven = most > 2.5 * average;
-  const double beyond = per_cu > 1.0 ? per_cu - 1.0 : 0.0;
-  const double four_minus_eight = b == 64 ? 0.458 - 0.083 * chain4 + 0.023 * chain8 - 0.349 * per_cu - 1.445 * beyond + 0.036 * load
-                                          : 0.506 + 0.061 * chain4 - 0.247 * chain8 - 0.184 * per_cu - 1.558 * beyond + 0.034 * load;
-  const int waves = (uneven && most >= 12.0 && per_cu <= 1.5) || four_minus_eight >= 0.0 ? 8 : 4;
+  const int waves = split_form(most, average, per_cu);
   if (decode) {
     if (tiles > 2 * cus) return 0;
     const double groups32 = (double)((tokens + 31) / 32), mbytes = nnz * 1e-6 * b * b * 2 * groups32;

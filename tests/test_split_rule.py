@@ -38,5 +38,20 @@ def test_narrow_outputs(rule):
         assert waves in (4, 8), call
 
 
+def test_form_by_load(rule):
+    """Eight waves to a tile only where each has a CU to itself and no row is long, or where one row is much longer than the
+    others; evenly long rows on more tiles than CUs are four waves' (there eight are a round more)."""
+    for call, waves in (((128, 30, 768, 26, 36), 4), ((64, 32, 640, 50, 50), 4), ((64, 7, 2084, 5, 12), 8), ((128, 8, 900, 20, 20), 4),
+                        ((64, 25, 384, 20, 20), 8), ((64, 25, 384, 31, 31), 4), ((64, 24, 900, 6, 9), 4), ((128, 10, 960, 4, 30), 8),
+                        ((64, 60, 300, 2, 16), 8), ((64, 60, 300, 2, 9), 4)):
+        assert rule([call])[0] == waves, call
+    calls = [(b, nbr, t, mean, mean) for b in (64, 128) for nbr in range(1, 60) for t in range(300, 3000, 170) for mean in (1, 4, 9, 30)]
+    for call, waves in zip(calls, rule(calls)):
+        units = call[1] * call[0] // 64
+        launched = (units if units < 12 and units != 8 else (units + 7) // 8 * 8) * ((call[2] + 63) // 64)
+        stages = call[3] * call[0] // 64
+        assert waves in ((0, 4) if launched > CUS else (8,) if stages <= 20 else (4,)), call
+
+
 def test_workgroups_cover_every_tile_once(rule):
     rule([(64, units, t, 1, 1) for units in range(1, 70) for t in (33, 64, 65, 200, 2100)])
