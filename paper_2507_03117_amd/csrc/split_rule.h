@@ -50,16 +50,18 @@ inline int split_form(double most, double average, double per_cu) {
 // The waves (4 or 8) of k_spmm_split (64 x 64 tiles, a row's stages dealt to the waves) for a single product that is better
 // off there than on the kernel that would take it otherwise; 0 where it is not.  Microseconds, uniform masks unless said
 // otherwise, bf16 output, graph replay:
-//   streaming / split (the former walks a row in sequence, and leaves CUs idle while its tiles are few): b = 64, 25 rows of
-//     20 blocks, 384 / 768 tokens 17.0 / 10.6, 17.4 / 15.5; 32 rows of 3, 512 tokens 6.6 / 5.2.  b = 128, 16 rows of 6.4, 384
-//     / 1024 tokens 17.6 / 9.4, 17.9 / 15.0.  With four waves, of which a CU takes two workgroups, up to twice as many
-//     tiles as CUs and, with 128-wide blocks that make a wave's chain short against the streaming kernel's, three times:
-//     b = 64, 29 rows of 7.4, 269 tokens (440 tiles) 11.7 / 9.2; 44 rows of 6, 700 tokens (484) 9.2 / 8.0 and (512) 8.0 /
-//     7.6, but (560) 13.4 / 14.9; b = 128, 30 rows of 2, 545 tokens (540) 12.2 / 8.5; 18 rows of 2.8, 546 (720) 14.8 / 11.7;
-//     (1200) 14.4 / 15.1; 11 rows of 2.6, 1921 (682) 11.4 / 12.8.
-//   A row that is much fuller than the others is a chain in either kernel, walked here by four or eight waves: 4096 x
-//     4096, 128-wide, Zipf rows (5.3 blocks on average, fullest 47), 993 tokens 66 / 25, 384 tokens (42) 59 / 20; beyond the
-//     lines above the two estimates decide (500 products of uniform and Zipf rows, 257 to 2048 tokens, at most six tiles per CU).
+//   streaming / split (the former walks a row in sequence, in one chain of sums, and leaves CUs idle while its tiles are few): b =
+//     64, 25 rows of 20 blocks, 384 tokens 17.0 / 10.6; 32 rows of 3, 512 tokens 6.6 / 5.2.  b = 128, 16 rows of 6.4, 384 / 1024 tokens
+//     17.6 / 9.4, 17.9 / 15.0.  So up to 1.25 tiles per CU with 64-wide blocks (one where no wave has a whole stage), two with
+//     128-wide ones, always.  Beyond that by two estimates, fitted to 5600 products of 33 to 32000 tokens on one to six tiles per CU
+//     (off by less than 3 % in the median, by 20 % at the fifth and the 95th percentile): equal rows are sooner better off on the streaming kernel
+//     (b = 64, 56 rows of 2, 498 tokens, 448 tiles 4.5 / 4.8; 33 rows of 4.3, 841 tokens, 462 tiles 7.5 / 9.7; 74 rows of 7, 323 tokens,
+//     444 tiles 8.5 / 8.6; 82 rows of 13, 278 tokens, 410 tiles 11.2 / 11.0; b = 128, 52 rows of 5.7, 326 tokens, 624 tiles 12.9 / 15.3;
+//     52 rows of 22, 261 tokens, 520 tiles 34.6 / 29.2), a row much fuller than the others is a chain there, and here one of four
+//     or eight waves (b = 64, 42 rows of 10, fullest 100, 1185 tokens, 798 tiles 53 / 25; b = 128, 47 rows of 12.8, fullest 64, 332
+//     tokens, 564 tiles 88 / 30).  Narrow outputs have the larger margin, as their tiles share no weights in an L2.
+//     Over 6400 products, against the line by tiles alone: equal rows 2.7 % less time on average, 1.1 % of them more than 4 % slower;
+//     uneven rows 16 %, 1.8 % (up to two or three tiles per CU always: 0.9 %, 7.7 %; 14 %, 9.1 %).
 //   decode (33 to 256 tokens; it reads the matrix once per 32 tokens, in many small workgroups) / split: b = 64, 100 rows of 5, 64 /
 //     100 / 160 / 256 tokens 5.2 / 5.4, 7.7 / 5.5, 9.4 / 7.6, 13.6 / 8.8; 32 rows of 13, 128 / 256 tokens 7.3 / 7.4, 10.0 / 8.4;
 //     32 rows of 26, 192 tokens 9.5 / 11.3.  b = 128, 32 rows of 3.2, 64 / 100 / 256 tokens 4.1 / 5.9, 7.0 / 6.1, 13.0 / 7.7.
@@ -68,8 +70,6 @@ inline int split_form(double most, double average, double per_cu) {
 //     calls (uniform rows, Zipf rows, one or four full rows; 33 to 256 tokens) for the choice between them, with eight
 //     waves: of the calls that they send here, none with 128-wide blocks and four with 64-wide ones are more than 5 %
 //     slower than on decode.
-// Over 580 products of 257 to 2048 tokens, before (eight waves only, a line by tiles) and after: uniform rows 4.7 % less time
-// on average, Zipf rows 18 %.
 // b: block width; nbr: block rows of the output; nnz: stored blocks, fullest: of the fullest row (0: not known); decode: whether
 // the decode kernel would take it; cus: compute units.
 inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t fullest, bool decode, int64_t cus) {
@@ -96,21 +96,23 @@ inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t 
     }
     return decode_us > split_us + 0.3 ? waves : 0;
   }
-  if (per_cu <= (b == 128 && average >= 2.0 ? (tokens <= 1024 ? 3.0 : 2.5) : 2.0)) return waves;
-  if (row <= mean + 3.0 * std::sqrt(mean) + 1.0 || per_cu > 6.0) return 0;  // (no more than a uniform mask's fullest row)
-  const bool wide = (int64_t)((tokens + 255) / 256) * nbr >= 2 * cus;  // the streaming kernel's tiles, see launch_stream_c
+  if (tiles * 4 <= (b == 128 ? 8 : row < 8.0 ? 4 : 5) * cus) return waves;
+  if (per_cu > 6.0) return 0;
+  const bool wide = (tokens + 255) / 256 * nbr >= 2 * cus;  // the streaming kernel's tiles, see launch_stream_c
   if (b == 128 && wide) return 0;
   const int64_t ntt = wide ? (tokens + 255) / 256 : (tokens + 127) / 128;
   const double blocks = (double)nnz * ntt / cus, items = (double)nbr * ntt / cus;
-  const double stream_us = b == 128 ? 3.27 + 1.24 * row + 0.490 * blocks + 0.85 * items
+  const double stream_us = b == 128 ? 3.21 + 1.185 * row + 0.50 * blocks + 1.87 * items
                            : wide   ? 4.14 + 0.71 * row + 0.365 * blocks + 0.20 * items
-                                    : 2.86 + 0.44 * row + 0.231 * blocks + 0.33 * items;
-  double split_us;
-  if (b == 64)
-    split_us = waves == 4 ? 2.97 + 0.551 * chain4 + 0.217 * load + 0.888 * per_cu : 1.85 + 1.036 * chain8 + 0.225 * load + 2.196 * per_cu;
-  else
-    split_us = waves == 4 ? 2.99 + 0.604 * chain4 + 0.223 * load + 0.713 * per_cu : 1.93 + 1.081 * chain8 + 0.239 * load + 1.896 * per_cu;
-  return split_us * 1.1 < stream_us ? waves : 0;
+                                    : 2.53 + 0.396 * row + 0.27 * blocks + 1.17 * items;
+  // stages of a CU of the XCD with the fullest row, where that row's tiles are on one
+  const double others = units > b / 64 ? (average * units - most * (b / 64)) / (units - b / 64) : 0.0;
+  const double of_xcd = split_stride_log2(units) == 0 ? load : groups * (most + ((units + 7) / 8 - 1) * others) * 8.0 / cus;
+  const double beyond = of_xcd > load ? of_xcd - load : 0.0;
+  const double split_us = b == 64 ? 2.62 + 0.327 * chain4 + 0.261 * load + 0.113 * beyond + 1.21 * per_cu
+                                  : 3.37 + 0.254 * chain4 + 0.269 * load + 0.127 * beyond + 1.08 * per_cu;
+  const double margin = split_stride_log2(units) == 0 ? 1.15 : most > 2.0 * average ? 1.0 : 1.05;
+  return split_us * margin < stream_us ? waves : 0;
 }
 
 }  // namespace blast_dev

@@ -530,21 +530,29 @@ def test_few_output_tiles_by_rows(api, b, nbr, per_row, full, T):
     assert (np.abs(got - want) <= np.abs(want) * 2.0 ** -8 + 1e-5 * np.sqrt((want ** 2).mean())).all()  # one rounding
 
 
-@pytest.mark.parametrize("b,nbr,per_row,full,T", [
-    (64, 40, 5, 0, 449), (64, 41, 7, 0, 257), (64, 64, 1, 0, 448), (64, 33, 24, 0, 640), (64, 96, 3, 60, 700),
-    (128, 20, 3, 0, 513), (128, 33, 3, 0, 640), (128, 17, 12, 0, 300), (128, 24, 4, 50, 900), (128, 40, 1, 0, 191)])
+# Products that four waves share a tile of, and some on the other side of the rule's lines (tests/test_split_rule.py asks the rule)
+FOUR_WAVES = [(64, 33, 24, 0, 640), (64, 96, 3, 60, 700), (128, 20, 3, 0, 513), (128, 17, 12, 0, 300), (128, 24, 4, 50, 900),
+              (64, 41, 2, 0, 384), (64, 50, 12, 0, 384), (128, 30, 20, 0, 513), (128, 13, 2, 0, 1111)]
+BESIDE_FOUR_WAVES = [(64, 40, 5, 0, 449), (64, 41, 7, 0, 257), (64, 64, 1, 0, 448), (128, 33, 3, 0, 640), (128, 40, 1, 0, 191)]
+
+
+def rows_of_four_waves(nbr, per_row, full):
+    return [full if full and r == 3 else max(per_row - (r % 3 == 1), int(r % 5 > 0)) for r in range(nbr)]
+
+
+@pytest.mark.parametrize("b,nbr,per_row,full,T", FOUR_WAVES + BESIDE_FOUR_WAVES)
 def test_output_tiles_shared_by_four_waves(api, b, nbr, per_row, full, T):
-    """One to three tiles of 64 x 64 per CU, whose stages four waves share: rows shorter than the waves are many and rows of
+    """About one to three tiles of 64 x 64 per CU, whose stages four waves share: rows shorter than the waves are many and rows of
     several stages a wave, block rows that do not divide by eight, tokens that end inside a tile; uneven rows with more tiles
-    than that.  The plain product in both types (32-bit sums: 1e-5 of the root mean square; one rounding to bf16) and the
-    activated one, whose output is the intermediate of a two-matrix MLP."""
+    than that; and products that eight waves or the streaming kernel take.  The plain product in both types (32-bit sums: 1e-5 of
+    the root mean square; one rounding to bf16) and the activated one, whose output is the intermediate of a two-matrix MLP."""
     import torch
 
     rng = np.random.default_rng(5500 + b + T + full)
     nbc = 62
     mask = np.zeros((nbr, nbc), dtype=np.uint8)
-    for r in range(nbr):
-        mask[r, rng.choice(nbc, size=full if full and r == 3 else max(per_row - (r % 3 == 1), int(r % 5 > 0)), replace=False)] = 1
+    for r, size in enumerate(rows_of_four_waves(nbr, per_row, full)):
+        mask[r, rng.choice(nbc, size=size, replace=False)] = 1
     w = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
     x = synth.gauss_bf16(rng, (T, nbc * b), 1.0)
     dev, ref = pack_both(api, w, b, mask=mask)
@@ -568,8 +576,15 @@ def test_output_tiles_shared_by_four_waves(api, b, nbr, per_row, full, T):
     check_close(z.cpu().numpy()[some].T, orc.mlp2(ref, ref2, x[some], activation="gelu"), f"two-matrix MLP b={b} T={T}")
 
 
-@pytest.mark.parametrize("b,nbr,per_row,few,many", [(64, 24, 9, 300, 800), (64, 40, 2, 280, 512), (64, 21, 17, 449, 800),
-                                                    (128, 12, 5, 300, 830), (128, 20, 8, 330, 513), (128, 15, 1, 290, 1000)])
+EIGHT_AND_FOUR = [(64, 24, 9, 300, 800), (64, 41, 2, 290, 384), (64, 21, 17, 449, 800), (128, 12, 5, 300, 830), (128, 20, 8, 330, 513),
+                  (128, 15, 1, 290, 1000)]
+
+
+def rows_of_eight_and_four(nbr, per_row):
+    return [max(per_row - r % 3, int(r % 5 > 0)) for r in range(nbr)]
+
+
+@pytest.mark.parametrize("b,nbr,per_row,few,many", EIGHT_AND_FOUR)
 def test_a_token_is_summed_alike_by_four_waves_and_by_eight(api, b, nbr, per_row, few, many):
     """A token's row of the product in a call that leaves every tile of 64 x 64 a CU (eight waves to a tile) and in a larger one
     (four): the same bits, as both forms add up the same eight chains.  Rows of no stage to seventeen, so that a wave has none, one
@@ -579,8 +594,8 @@ def test_a_token_is_summed_alike_by_four_waves_and_by_eight(api, b, nbr, per_row
     rng = np.random.default_rng(7100 + nbr)
     nbc = 30
     mask = np.zeros((nbr, nbc), dtype=np.uint8)
-    for r in range(nbr):
-        mask[r, rng.choice(nbc, size=max(per_row - r % 3, int(r % 5 > 0)), replace=False)] = 1
+    for r, size in enumerate(rows_of_eight_and_four(nbr, per_row)):
+        mask[r, rng.choice(nbc, size=size, replace=False)] = 1
     w = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
     x = to_dev(synth.gauss_bf16(rng, (many, nbc * b), 1.0))
     dev, _ = pack_both(api, w, b, mask=mask)

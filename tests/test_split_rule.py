@@ -41,7 +41,7 @@ def test_narrow_outputs(rule):
 def test_form_by_load(rule):
     """Eight waves to a tile only where each has a CU to itself and no row is long, or where one row is much longer than the
     others; evenly long rows on more tiles than CUs are four waves' (there eight are a round more)."""
-    for call, waves in (((128, 30, 768, 26, 36), 4), ((64, 32, 640, 50, 50), 4), ((64, 7, 2084, 5, 12), 8), ((128, 8, 900, 20, 20), 4),
+    for call, waves in (((128, 30, 513, 20, 20), 4), ((64, 32, 640, 50, 50), 4), ((64, 7, 2084, 5, 12), 8), ((128, 8, 900, 20, 20), 4),
                         ((64, 25, 384, 20, 20), 8), ((64, 25, 384, 31, 31), 4), ((64, 24, 900, 6, 9), 4), ((128, 10, 960, 4, 30), 8),
                         ((64, 60, 300, 2, 16), 8), ((64, 60, 300, 2, 9), 4)):
         assert rule([call])[0] == waves, call
@@ -51,6 +51,34 @@ def test_form_by_load(rule):
         launched = (units if units < 12 and units != 8 else (units + 7) // 8 * 8) * ((call[2] + 63) // 64)
         stages = call[3] * call[0] // 64
         assert waves in ((0, 4) if launched > CUS else (8,) if stages <= 20 else (4,)), call
+
+
+def test_line_to_the_streaming_kernel(rule):
+    """Up to the line by tiles always waves; beyond it where they are faster: not for short equal rows, for long ones and for one
+    row much fuller than the others (measured products, each at least 10 % apart)."""
+    calls = [(b, nbr, t, mean, max(mean, full)) for b in (64, 128) for nbr in (1, 3, 4, 9, 16, 25, 50, 90) for t in range(257, 2600, 101)
+             for mean in (1, 5, 30) for full in (0, 7, 40)]
+    for call, waves in zip(calls, rule(calls)):
+        if tiles(call) * 4 <= CUS * (8 if call[0] == 128 else 4 if call[4] < 8 else 5):
+            assert waves in (4, 8), call
+    for call, split in (((64, 25, 1189, 0.8, 1), False), ((64, 18, 1624, 2.3, 3), False), ((64, 33, 841, 4.3, 5), False),
+                        ((64, 32, 1024, 1, 3), False), ((64, 40, 906, 4.5, 5), False), ((128, 44, 421, 2, 2), False),
+                        ((128, 52, 326, 5.7, 6), False), ((128, 23, 1022, 10, 10), False), ((128, 52, 261, 22, 22), True),
+                        ((64, 42, 1185, 10, 100), True), ((64, 79, 401, 5, 100), True), ((128, 47, 332, 12.8, 64), True),
+                        ((128, 10, 2226, 4.8, 16), True)):
+        assert (rule([call])[0] > 0) == split, call
+
+
+def test_what_the_gpu_tests_run(rule):
+    """The products of the GPU tests of either form are the rule's for that form."""
+    from tests import test_gpu_parity as gpu
+
+    for b, nbr, per_row, full, t in gpu.FOUR_WAVES:
+        rows = gpu.rows_of_four_waves(nbr, per_row, full)
+        assert rule([(b, nbr, t, sum(rows) / nbr, max(rows))]) == [4], (b, nbr, t)
+    for b, nbr, per_row, few, many in gpu.EIGHT_AND_FOUR:
+        rows = gpu.rows_of_eight_and_four(nbr, per_row)
+        assert rule([(b, nbr, t, sum(rows) / nbr, max(rows)) for t in (few, many)]) == [8, 4], (b, nbr)
 
 
 def test_workgroups_cover_every_tile_once(rule):
