@@ -331,13 +331,13 @@ template <int B, int NWAVES>
 int launch_split(const TileArgs& a, hipStream_t stream) {
   using C = SplitCfg<B, NWAVES>;
   const int64_t units = (int64_t)a.nbr * C::SUB, groups = (a.T + C::SB - 1) / C::SB;
-  const int64_t grid = split_workgroups(units, groups);
+  const int64_t grid = split_workgroups(units, groups, cu_count());
   if (grid <= 0) return BLAST_OK;
   if (grid > INT32_MAX) return BLAST_ERR_INVALID_ARG;
   auto launch = [&](auto post) {
     static blast::DeviceFlags lds_set;
     if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_spmm_split<B, post.value, NWAVES>), C::LDS_BYTES, lds_set)) return rc;
-    k_spmm_split<B, post.value, NWAVES><<<dim3((unsigned)grid), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(a, (int)units, (int)groups, split_stride_log2(units));
+    k_spmm_split<B, post.value, NWAVES><<<dim3((unsigned)grid), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(a, (int)units, (int)groups, split_stride_log2(units, groups, cu_count()));
     BLAST_LAUNCH_CHECK("k_spmm_split");
     return (int)BLAST_OK;
   };

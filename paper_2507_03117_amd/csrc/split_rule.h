@@ -8,16 +8,19 @@ namespace blast_dev {
 // Workgroup ids between the token tiles of a unit (64 output rows); the ids go round the XCDs.  Eight: a unit's tiles are
 // all on one XCD, whose L2 serves its weights to them.  With fewer than eight units, or a few more, that leaves most of the chip
 // idle (one unit: 32 CUs for all tiles), so there the tiles of a unit follow each other, over all XCDs, each of which reads what
-// little weight there is.  Eight waves, eight apart / one, microseconds: b = 64, 2 rows of 8 blocks, 4894 tokens 15.7 / 6.4
-// (streaming kernel 7.6), 3 rows of 8, 2672 tokens 11.3 / 6.1 (7.5), 11 rows of 20, 1031 tokens 15.4 / 11.0 (13.3); b = 128, one row
-// of 8, 5421 tokens 21.3 / 9.1 (15.0).  Eight units are spread as they are (b = 64, 8 rows of 8, 3210 tokens 12.0 / 12.6), and from
-// 12 on what the weights cost more is no longer always less than what was idle (equal rows, time with one over time with eight
-// apart: 12 units 0.90 on average, but up to 1.15; 16, 24, 32 units 1.07, 1.11, 1.15).
-constexpr int split_stride_log2(int64_t units) { return units < 12 && units != 8 ? 0 : 3; }
+// little weight there is - where an XCD would have more tiles than CUs.  Eight waves, eight apart / one, microseconds: b = 64, 2 rows
+// of 8 blocks, 4894 tokens 15.7 / 6.4 (streaming kernel 7.6), 3 rows of 8, 2672 tokens 11.3 / 6.1 (7.5), 11 rows of 20, 1031 tokens
+// 15.4 / 11.0 (13.3); b = 128, one row of 8, 5421 tokens 21.3 / 9.1 (15.0).  Fewer tiles only read more (b = 64, 7 rows of 20, 269
+// tokens 8.3 / 9.2; b = 128, 5 rows of 8, 823 tokens 8.4 / 9.0).  Eight units are spread as they are (b = 64, 8 rows of 8, 3210
+// tokens 12.0 / 12.6), and from 12 on what the weights cost more is no longer always less than what was idle (equal rows, time with one
+// over time with eight apart: 12 units 0.90 on average, but up to 1.15; 16, 24, 32 units 1.07, 1.11, 1.15).
+constexpr int split_stride_log2(int64_t units, int64_t groups, int64_t cus) {
+  return units < 12 && units != 8 && (units + 7) / 8 * 8 * groups > cus ? 0 : 3;
+}
 
 // Workgroups of a launch, those without a tile included.
-constexpr int64_t split_workgroups(int64_t units, int64_t groups) {
-  const int64_t stride = (int64_t)1 << split_stride_log2(units);
+constexpr int64_t split_workgroups(int64_t units, int64_t groups, int64_t cus) {
+  const int64_t stride = (int64_t)1 << split_stride_log2(units, groups, cus);
   return (units + stride - 1) / stride * stride * groups;
 }
 
@@ -75,7 +78,8 @@ inline int split_form(double most, double average, double per_cu) {
 inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t fullest, bool decode, int64_t cus) {
   if (b != 64 && b != 128) return 0;
   const int64_t units = nbr * (b / 64), groups = (tokens + 63) / 64, tiles = units * groups;
-  const int64_t launched = split_workgroups(units, groups);
+  const int64_t launched = split_workgroups(units, groups, cus);
+  const bool spread = split_stride_log2(units, groups, cus) == 0;
   const double mean = (double)nnz / nbr;
   const double row = fullest > 0 ? (double)fullest : mean + 2.0 * std::sqrt(mean);  // (rows of a uniform mask vary by that)
   // stages of the fullest row, of a row on average; workgroups per CU; stages of a wave in the fullest row, of a CU
@@ -107,11 +111,11 @@ inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t 
                                     : 2.53 + 0.396 * row + 0.27 * blocks + 1.17 * items;
   // stages of a CU of the XCD with the fullest row, where that row's tiles are on one
   const double others = units > b / 64 ? (average * units - most * (b / 64)) / (units - b / 64) : 0.0;
-  const double of_xcd = split_stride_log2(units) == 0 ? load : groups * (most + ((units + 7) / 8 - 1) * others) * 8.0 / cus;
+  const double of_xcd = spread ? load : groups * (most + ((units + 7) / 8 - 1) * others) * 8.0 / cus;
   const double beyond = of_xcd > load ? of_xcd - load : 0.0;
   const double split_us = b == 64 ? 2.62 + 0.327 * chain4 + 0.261 * load + 0.113 * beyond + 1.21 * per_cu
                                   : 3.37 + 0.254 * chain4 + 0.269 * load + 0.127 * beyond + 1.08 * per_cu;
-  const double margin = split_stride_log2(units) == 0 ? 1.15 : most > 2.0 * average ? 1.0 : 1.05;
+  const double margin = spread ? 1.15 : most > 2.0 * average ? 1.0 : 1.05;
   return split_us * margin < stream_us ? waves : 0;
 }
 

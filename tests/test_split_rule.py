@@ -48,7 +48,8 @@ def test_form_by_load(rule):
     calls = [(b, nbr, t, mean, mean) for b in (64, 128) for nbr in range(1, 60) for t in range(300, 3000, 170) for mean in (1, 4, 9, 30)]
     for call, waves in zip(calls, rule(calls)):
         units = call[1] * call[0] // 64
-        launched = (units if units < 12 and units != 8 else (units + 7) // 8 * 8) * ((call[2] + 63) // 64)
+        groups, padded = (call[2] + 63) // 64, (units + 7) // 8 * 8
+        launched = (units if units < 12 and units != 8 and padded * groups > CUS else padded) * groups
         stages = call[3] * call[0] // 64
         assert waves in ((0, 4) if launched > CUS else (8,) if stages <= 20 else (4,)), call
 
