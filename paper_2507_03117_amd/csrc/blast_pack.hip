@@ -10,7 +10,7 @@
 //   fill   -> ordered compaction of column indices, gather of block values
 //   order  -> rank block rows by population (schedule for load balance)
 //   csc    -> column-grouped index of the same blocks (used by the fused MLP)
-// For matrices of up to a few thousand blocks, select is one workgroup and all that follows it one launch.
+// Up to 65536 blocks a selection is one workgroup, and up to 49152 (1024 block rows and columns) all that follows it one launch.
 #include "blast_common.h"
 
 #include <type_traits>
@@ -549,27 +549,29 @@ inline void plan_outputs(char* ab, const blast::AuxLayout& A, PlanOut& narrow, P
 
 // ---- small matrices: a workgroup per job ----
 //
-// A layer-sized matrix has a few thousand blocks; scored, the rest of the packing is a few thousand integer
-// operations, and as a dozen dependent launches it costs a dozen launch latencies.  For at most kSmallN blocks
-// (and at most 1024 block rows and block columns) the selection is one workgroup and the rest one launch, in which a
-// workgroup makes the row arrays and another the column arrays: a thread owns `per` consecutive blocks in row-major
+// A layer-sized matrix has a few thousand to a few ten thousand blocks; scored, the rest of the packing is as many integer
+// operations, and as a dozen dependent launches it costs a dozen launch latencies.  So a selection is one workgroup (up to
+// kOneWorkgroupN blocks; both of a mask update in one up to kSmallN) and the rest one launch (up to kSmallN blocks with what a
+// thread owns in registers, up to kBigN in two walks; at most 1024 block rows and block columns), in which a workgroup makes the
+// row arrays and another the column arrays: a thread owns `per` consecutive blocks in row-major
 // order; the selection's keys, the positions and the per-line populations live in LDS.  The workgroup's 16 waves
 // share one compute unit, so what such a job costs is instructions per thread: no integer division per block, both
-// chunk plans' scans in one (two 16-bit counts in one word: no sum here exceeds kSmallN + 1024), barriers that do not
-// wait for global stores.
+// chunk plans' scans in one (two 16-bit counts in one word: a plan has at most a chunk per 16 blocks and one per row, kBigN / 16 +
+// 1024), barriers that do not wait for global stores.
 constexpr int kSmallPer = 8;
 constexpr int kSmallN = 1024 * kSmallPer;
-static_assert(kSmallN + 1024 < 65536, "two counts share a 32-bit word");
 static_assert((blast::kChunkBlocks & (blast::kChunkBlocks - 1)) == 0 &&
               (blast::kWideChunkBlocks & (blast::kWideChunkBlocks - 1)) == 0, "chunk sizes are powers of two");
 
 constexpr int kRanked = 16;  // candidates that a wave ranks by comparing each with all
+constexpr int kWideBits = 11, kWideBins = 1 << kWideBits;  // a digit where every pass reads the scores again
 
 // LDS scratch of select_small, one per group (an array of them: the bins are read four at a time, so the size keeps the
 // alignment too).
 struct alignas(16) SelectShared {
   unsigned hist[256];
   uint4 wave_keys[16];  // of a wave: the smallest and the largest upper word, differing bits of the lower words
+  uint2 wave_zeros[16];  // of a wave: the smallest upper word of a key that is no zero's, its zeros
   int wave_tot[16];
   unsigned long long kth;        // the n_keep-th key ...
   int kth_at;                    // ... and its index: what is kept sorts before it, or is it
@@ -606,18 +608,21 @@ __device__ __forceinline__ unsigned reduce_wave(unsigned v, F f) {
 // twice the instructions): scores of one matrix share their leading bits, or differ in all of the exponent's where they lie on
 // both sides of a power of two, and a digit that most keys carry sends their counts to one LDS word.  The passes start at the
 // largest distance's leading bit, eight bits at a time; as soon as at most 16 keys carry the selected prefix, a wave ranks
-// those by comparing each with all (40 ns each, a pass a microsecond: mask
-// update with up to 64 ranked that way 11.9 us on 64 blocks of 64 x 64 and 23.5 on 4096, now 8.2 and 20.9).
-// Weight and gradient, 4096 blocks of 64 x 64, normal: from the leading bit in which keys differ, the exponent's there, the
-// first pass took 5.6 us, every key adding to one of two words, 12.9 us in all; now 6.5.  (Blocks of 32 x 32, whose scores lie
-// between two powers of two: 6.7, now 6.7.)
+// those by comparing each with all (40 ns each, a pass a microsecond: mask update with its wait, with up to 64 ranked that way 11.9 us
+// on 64 blocks of 64 x 64 and 23.5 on 4096, with 16 8.2 and 20.9).
+// Kernel of the mask update, 4096 blocks of 64 x 64, normal: from the leading bit in which keys differ, the exponent's there, the
+// first pass took 5.6 us, every key adding to one of two words, 12.9 us in all; from the distance 6.5.  (Blocks of 32 x 32, whose
+// scores lie between two powers of two: 6.7 and 6.7.)
 // A few scores far from the others still leave those one bin: a wave a quarter of whose first keys share a digit counts the
-// lanes that carry its first lane's with one addition (16384 blocks, one of them 100 times the others: mask update 51 us, 44
-// without; 0.7 us of 4096 normal ones where every wave does).
+// lanes that carry its first lane's with one addition (16384 blocks, mask update with its wait: 44 us, one score 100 times the
+// others 51; counting so in every wave costs 0.7 us of 4096 normal ones).
+// Where every pass reads the scores again (not STAGED) a pass that tells nothing is dear, so there digits have eleven bits, which still
+// part the others where one score is a million times theirs, and zeros stay out of the passes, see below; both where
+// select_small<..., false> is launched, with times.
 // What bounds it is not the work but its dependent steps and, in a workgroup that runs every instruction once or
 // twice with caches full of weights, the fetching of instructions: loops are left rolled.  4096 blocks, weight and gradient
 // (timestamps): keys unrolled over registers and passes down to one key, the two selections in turn: 16 us; keys in LDS,
-// side by side: 12.8 us, now 6.5.
+// side by side: 12.8 us; and by the distance, bounds in 32 bits: 6.5.
 template <int NT, int GROUPS, bool STAGED = true>
 __device__ __forceinline__ void select_small(const double* __restrict__ score, int n, int n_keep, unsigned long long* keys,
                                              SelectShared* shared) {
@@ -628,6 +633,8 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
   auto lesser = [](unsigned x, unsigned y) { return x < y ? x : y; };
   auto greater = [](unsigned x, unsigned y) { return x > y ? x : y; };
   auto either = [](unsigned x, unsigned y) { return x | y; };
+  auto plus = [](unsigned x, unsigned y) { return x + y; };
+  constexpr unsigned long long kZero = 1ull << 63;  // the key of a zero
   const unsigned long long key0 = order_key(bits[0]);
   unsigned least = ~0u, most = 0u, diff = 0u;  // of the keys' upper words; bits in which their lower words differ
 #pragma unroll 4
@@ -647,12 +654,52 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
   least = reduce_row(of_wave.x, lesser);
   most = reduce_row(of_wave.y, greater);
   diff = reduce_row(of_wave.z, either);
-  // bits at and above `fixed` are decided, in the keys' distance from `low`
-  int fixed = most != least ? 64 - __builtin_clz(most - least) : diff != 0u ? 32 - __builtin_clz(diff) : 0;
-  const unsigned long long low = most != least ? (unsigned long long)least << 32 : fixed == 0 ? key0 : key0 >> fixed << fixed;
-  unsigned long long prefix = 0ull;
-  int rem = n_keep, eq = n;  // the rem-th of the eq keys that carry the decided bits is the one
+  // No score below zero, some zero, each pass another walk over the scores: the zeros sort after all others and stay out of the
+  // passes, whose first would do no more than tell them from the rest - a key less than `low` carries no prefix (its distance wraps
+  // to 2^63 or more, those of the others stay below).
+  int apart = 0;
+  if constexpr (!STAGED) {
+    static_assert(STAGED || GROUPS == 1, "a barrier that is the group's decision");
+    if (least == (unsigned)(kZero >> 32) && most != least) {
+      unsigned other = ~0u, zeros = 0u;
+#pragma unroll 4
+      for (int i = tid; i < n; i += NT) {
+        const unsigned long long k = key_of(i);
+        other = min(other, k == kZero ? ~0u : (unsigned)(k >> 32));
+        zeros += k == kZero ? 1u : 0u;
+      }
+      other = reduce_wave(other, lesser);
+      zeros = reduce_wave(zeros, plus);
+      if (lane == 0) sh.wave_zeros[tid / kWave] = make_uint2(other, zeros);
+      wg_barrier<true>();
+      const uint2 zeros_of = sh.wave_zeros[lane % (NT / kWave)];
+      other = reduce_row(zeros_of.x, lesser);
+      zeros = reduce_row(lane % 16 < NT / kWave ? zeros_of.y : 0u, plus);
+      if (other > least) {  // (a score whose upper word is zero's stays among them)
+        least = other;
+        apart = (int)zeros;
+      }
+    }
+  }
+  // bits at and above `fixed` are decided, in the keys' distance from `low`; the rem-th of the eq keys that carry the decided bits
+  // is the one
+  int fixed, rem = n_keep, eq = n - apart;
+  unsigned long long low, prefix = 0ull;
+  if (n_keep > n - apart) {
+    fixed = 0;
+    low = kZero;
+    rem -= n - apart;
+    eq = apart;
+  } else if (most != least) {
+    fixed = 64 - __builtin_clz(most - least);
+    low = (unsigned long long)least << 32;
+  } else {
+    fixed = diff != 0u ? 32 - __builtin_clz(diff) : 0;
+    low = ((unsigned long long)least << 32 | (unsigned)key0) >> fixed << fixed;
+  }
   auto carries = [&](unsigned long long k) { return fixed == 64 || ((k - low) >> fixed) == (prefix >> fixed); };
+  constexpr int BITS = STAGED ? 8 : kWideBits, BINS = 1 << BITS;
+  unsigned* const hist = STAGED ? sh.hist : reinterpret_cast<unsigned*>(keys);
 #pragma unroll 1
   for (;;) {
     const bool active = fixed > 0 && eq > kRanked;
@@ -660,22 +707,26 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
       sh.open = active ? 1 : 0;
       sh.fill = 0;
     }
-    if (tid < 256) sh.hist[tid] = 0u;
+    if (STAGED) {
+      if (tid < BINS) hist[tid] = 0u;
+    } else {
+      for (int j = tid; j < BINS; j += NT) hist[j] = 0u;
+    }
     wg_barrier<true>();
     int open = 0;
 #pragma unroll
     for (int q = 0; q < GROUPS; ++q) open |= shared[q].open;
     if (open == 0) break;
-    const int sft = fixed > 8 ? fixed - 8 : 0, width = fixed - sft;
+    const int sft = fixed > BITS ? fixed - BITS : 0, width = fixed - sft;
     if (active) {
       auto digit_of = [&](unsigned long long k) { return (unsigned)((k - low) >> sft) & ((1u << width) - 1u); };
       const unsigned long long k0 = key_of(tid < n ? tid : n - 1);
-      const unsigned sample = carries(k0) ? digit_of(k0) : 256u + lane;
+      const unsigned sample = carries(k0) ? digit_of(k0) : (unsigned)BINS + lane;
       if (__popcll(__ballot(sample == (unsigned)__builtin_amdgcn_readfirstlane((int)sample))) <= kWave / 4) {
 #pragma unroll 2
         for (int i = tid; i < n; i += NT) {
           const unsigned long long k = key_of(i);
-          if (carries(k)) atomicAdd(&sh.hist[digit_of(k)], 1u);
+          if (carries(k)) atomicAdd(&hist[digit_of(k)], 1u);
         }
       } else {
         for (int i = tid; i < n; i += NT) {
@@ -684,17 +735,31 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
             const unsigned digit = digit_of(k);
             const unsigned long long same = __ballot(digit == (unsigned)__builtin_amdgcn_readfirstlane((int)digit));
             if (!(same >> lane & 1ull))
-              atomicAdd(&sh.hist[digit], 1u);
+              atomicAdd(&hist[digit], 1u);
             else if (lane == __builtin_ctzll(same))
-              atomicAdd(&sh.hist[digit], (unsigned)__popcll(same));
+              atomicAdd(&hist[digit], (unsigned)__popcll(same));
           }
         }
       }
     }
     wg_barrier<true>();
-    if (active && tid < kWave) {
-      // lane l looks at bins 255 - 4l ... 252 - 4l; `larger` = keys in bins above the one looked at
-      const uint4 h = *reinterpret_cast<const uint4*>(&sh.hist[252 - 4 * lane]);
+    auto look = [&](int bin, int h, int larger) {  // `larger` = keys in bins above this one
+      if (larger < rem && rem <= larger + h) {
+        sh.rem = rem - larger;
+        sh.eq = h;
+        sh.digit = bin;
+      }
+    };
+    if constexpr (!STAGED) {  // (one group: every thread is here, with an active selection)
+      static_assert(BINS == 2 * NT, "two bins a thread");
+      const uint2 h = *reinterpret_cast<const uint2*>(&hist[BINS - 2 - 2 * tid]);
+      int total;
+      const int larger = block_exscan<true>((int)(h.x + h.y), sh.wave_tot, total);
+      look(BINS - 1 - 2 * tid, (int)h.y, larger);
+      look(BINS - 2 - 2 * tid, (int)h.x, larger + (int)h.y);
+    } else if (active && tid < kWave) {
+      // lane l looks at bins 255 - 4l ... 252 - 4l
+      const uint4 h = *reinterpret_cast<const uint4*>(&hist[252 - 4 * lane]);
       const int h4[4] = {(int)h.w, (int)h.z, (int)h.y, (int)h.x};
       const int sum = (h4[0] + h4[1]) + (h4[2] + h4[3]);
       int inc = sum;
@@ -706,11 +771,7 @@ __device__ __forceinline__ void select_small(const double* __restrict__ score, i
       int larger = inc - sum;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        if (larger < rem && rem <= larger + h4[u]) {
-          sh.rem = rem - larger;
-          sh.eq = h4[u];
-          sh.digit = 255 - 4 * lane - u;
-        }
+        look(255 - 4 * lane - u, h4[u], larger);
         larger += h4[u];
       }
     }
@@ -778,10 +839,12 @@ __device__ __forceinline__ bool select_keeps(const SelectShared& sh, unsigned lo
 
 // One workgroup: mask[i] = 1 for the n_keep highest of n scores, else 0; workgroup 1 of a launch of two: of a second array
 // (the mask update ranks the weight and the gradient at the same sparsity).  STAGED: the keys in dynamic LDS, n <= kStagedN.
-// Otherwise every pass reads the scores again, which the L2 holds, while that is less than k_select_topk's eight passes over
-// what it has not collected yet: up to kOneWorkgroupN.  Mask update with its wait, k_select_topk / this: 16384 blocks 62 /
-// 44 us, 43008 blocks 105 / 86, and with half of the gradient zero 105 / 107; 65536 blocks 122 / 100 and 122 / 118, 128000
-// blocks 205 / 168 and 204 / 222.
+// Otherwise every pass reads the scores again, which the L2 holds: two or three passes, where k_select_topk has eight over what it
+// has not collected yet.  Mask update with its wait, k_select_topk / this, us: 24576 blocks of 32 x 32, normal 74 / 60, half of the
+// gradient zero 74 / 63, half of both 74 / 63, equal scores 112 / 89, a few far above the others 74 / 60; 43008 blocks 104 / 85, 104 /
+// 90, 105 / 90, 170 / 134, 104 / 85, and weights that are zero outside a fifth of the blocks 170 / 88; 65536 of 16 x 16 121 / 99, 121 /
+// 106, 125 / 107, 226 / 192, 121 / 99, 226 / 101.  (With the zeros in the passes and digits of eight bits, 43008 blocks: 85, 107, 116,
+// 159, 105, 187; 128000 blocks 205 / 168, with half of the gradient zero 204 / 222, so the line is at 65536.)
 constexpr int kStagedN = 20000, kOneWorkgroupN = 1 << 16;
 template <bool STAGED>
 __global__ __launch_bounds__(1024) void k_select_small(const double* __restrict__ score0, int n, int n_keep,
@@ -919,7 +982,7 @@ struct GatherArgs {
 // More blocks than kSmallN, the index arrays still made by a workgroup each: a thread owns up to kBigPer blocks (a multiple
 // of four), flags in 64 bits, positions in 16.
 constexpr int kBigPer = 48, kBigN = 1024 * kBigPer;
-static_assert(kBigN + 1024 < 65536, "two counts share a 32-bit word, positions 16 bits");
+static_assert(kBigN < 65536 && kBigN / blast::kChunkBlocks + 1024 < 32768, "positions in 16 bits, two counts in a 32-bit word");
 
 // Flags of the blocks a thread owns (bit j: block tid * per + j is kept).
 __device__ __forceinline__ unsigned small_flags(const uint8_t* __restrict__ mask, int code, int n, int per) {
@@ -1367,7 +1430,7 @@ int launch_select(const double* scores, const double* scores1, int64_t n, int64_
     k_select_small<true><<<grid, dim3(1024), (size_t)n * 8, stream>>>(scores, (int)n, (int)n_keep, mask, scores1, mask1);
     BLAST_LAUNCH_CHECK("k_select_small");
   } else {
-    k_select_small<false><<<grid, dim3(1024), 0, stream>>>(scores, (int)n, (int)n_keep, mask, scores1, mask1);
+    k_select_small<false><<<grid, dim3(1024), kWideBins * sizeof(unsigned), stream>>>(scores, (int)n, (int)n_keep, mask, scores1, mask1);
     BLAST_LAUNCH_CHECK("k_select_small");
   }
   return BLAST_OK;

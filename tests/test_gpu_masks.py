@@ -68,9 +68,9 @@ def test_generate_masks_scores_a_wave_per_block(api, b, nbr, nbc, pad_w, pad_g):
 
 
 def test_generate_masks_and_pooled_selection_beyond_one_workgroup(api):
-    """26624 blocks: more than one workgroup selects from (8192), so the mask update runs its two selections side
-    by side over global memory and merges them in a launch of its own, and the pooled selection takes the same
-    select."""
+    """26624 blocks: more than a workgroup holds the keys of (20000), so that every pass of a selection reads the scores from
+    global memory; the mask update runs its two selections side by side, in a workgroup each, and merges them in a launch of its
+    own, and the pooled selection is one of them."""
     import torch
 
     rng = np.random.default_rng(9750)
@@ -88,6 +88,37 @@ def test_generate_masks_and_pooled_selection_beyond_one_workgroup(api):
     m = api.pooled_topk_mask(torch.from_numpy(S).to("cuda:0"), b, s)
     torch.cuda.synchronize()
     assert np.array_equal(m.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("nbr,nbc", [(64, 128), (90, 100), (125, 160), (59, 339), (256, 256), (257, 256)])
+@pytest.mark.parametrize("kind", ["uneven", "pruned", "half_zero", "equal", "outlier"])
+def test_generate_masks_by_the_number_of_blocks(api, nbr, nbc, kind):
+    """Both sides of each size at which the mask update changes its form: two selections in one workgroup (8192 blocks), in one
+    each with the keys in LDS (20000), with the scores read by every pass (65536), and by the general selection.  Weights that are
+    zero outside a mask, more or fewer non-zero blocks than are kept, gradients of which half is zero, equal scores, one far from
+    the others.  Values of seven bits, so that every sum of squares is exact."""
+    rng = np.random.default_rng(9760 + nbr)
+    b = 16
+
+    def values():
+        strength = rng.integers(20, 128, size=(nbr, nbc)) if kind != "equal" else rng.choice([40, 41], size=(nbr, nbc))
+        v = np.repeat(np.repeat(strength, b, 0), b, 1)
+        if kind != "equal":
+            v = v - rng.integers(0, 19, size=v.shape)
+        return v.reshape(nbr, b, nbc, b).astype(np.float32) / 128
+
+    W, G = values(), values()
+    if kind == "pruned":
+        W *= (rng.random((nbr, nbc)) < 0.2)[:, None, :, None]
+    if kind == "half_zero":
+        G[: nbr // 2] = 0
+    if kind == "outlier":
+        W[0, :, 1] *= 64
+        G[nbr - 1, :, 0] *= 1024
+    W, G = (synth.f32_to_bf16_bits(np.ascontiguousarray(v.reshape(nbr * b, nbc * b))) for v in (W, G))
+    Wd, Gd = to_dev(W), to_dev(G)
+    for s in (0.7, 0.9):
+        assert np.array_equal(api.generate_masks(Wd, Gd, b, s).cpu().numpy(), orc.generate_masks(W, G, b, s)), s
 
 
 @pytest.mark.parametrize("call", ["generate_masks", "pooled_topk_mask"])
@@ -362,12 +393,14 @@ def test_selection_cuts_a_group_of_equal_scores(api, ties):
         assert np.array_equal(got, orc.generate_masks(W, np.ascontiguousarray(W[::-1]), b, sparsity))
 
 
-@pytest.mark.parametrize("nbr,nbc", [(1, 2), (9, 7), (64, 64), (91, 90), (128, 64), (97, 91), (159, 126), (200, 131), (300, 164), (256, 256), (257, 256), (400, 330)])
-@pytest.mark.parametrize("kind", ["straddle", "outlier", "signed", "wide", "levels", "near", "equal"])
+@pytest.mark.parametrize("nbr,nbc", [(1, 2), (9, 7), (64, 64), (91, 90), (128, 64), (97, 91), (125, 160), (159, 126), (200, 131), (300, 164), (256, 256), (257, 256), (400, 330)])
+@pytest.mark.parametrize("kind", ["straddle", "outlier", "signed", "wide", "levels", "near", "equal", "half_zero", "few", "signed_zeros",
+                                  "tiny"])
 def test_selection_by_the_distribution_of_scores(api, nbr, nbc, kind):
     """The selection itself, on scores that are known exactly (a block of equal sensitivities has that mean): on both sides of
-    a power of two, all alike but one, of both signs, over sixty decades, on a few levels, apart in the last bits only, all equal; from
-    two blocks to more than one workgroup's keys.  The highest are kept, the first in index order among equals."""
+    a power of two, all alike but one, of both signs, over sixty decades, on a few levels, apart in the last bits only, all equal, half
+    of them zero, fewer that are not zero than are kept, zeros between both signs, zeros and the smallest numbers; from two blocks to
+    more than one workgroup takes.  The highest are kept, the first in index order among equals."""
     import torch
 
     rng = np.random.default_rng(9790 + nbr)
@@ -375,7 +408,10 @@ def test_selection_by_the_distribution_of_scores(api, nbr, nbc, kind):
     v = {"straddle": lambda: rng.uniform(0.9, 1.1, n), "outlier": lambda: np.r_[1e30, rng.uniform(1.0, 1.001, n - 1)],
          "signed": lambda: rng.normal(0.0, 1.0, n), "wide": lambda: 10.0 ** rng.uniform(-30, 30, n),
          "levels": lambda: rng.integers(0, 5, n).astype(float),
-         "near": lambda: 1.0 + rng.integers(0, 8, n) * 2.0 ** -23, "equal": lambda: np.full(n, 0.375)}[kind]()
+         "near": lambda: 1.0 + rng.integers(0, 8, n) * 2.0 ** -23, "equal": lambda: np.full(n, 0.375),
+         "half_zero": lambda: rng.uniform(1.0, 4.0, n) * (rng.random(n) < 0.5), "few": lambda: rng.uniform(1.0, 4.0, n) * (rng.random(n) < 0.04),
+         "signed_zeros": lambda: rng.normal(0.0, 1.0, n) * (rng.random(n) < 0.6),
+         "tiny": lambda: rng.integers(0, 40, n) * 2.0 ** -149}[kind]()
     v = v.astype(np.float32)
     S = torch.from_numpy(v.reshape(nbr, 1, nbc, 1)).cuda().expand(nbr, b, nbc, b).reshape(nbr * b, nbc * b)
     for s in (0.5, 0.93):

@@ -207,8 +207,8 @@ def _assert_packed_equal(dev, ref, b):
 @pytest.mark.parametrize("nbr,nbc", [(64, 128), (1, 8192), (8192, 1), (1024, 8), (3, 1024), (65, 128), (2, 1100),
                                      (1025, 4)])
 def test_pack_single_workgroup_limits(api, nbr, nbc):
-    """Up to 8192 blocks with at most 1024 block rows and columns one workgroup writes every index array; the cases
-    sit on both sides of each of the three limits."""
+    """Up to 8192 blocks with at most 1024 block rows and columns the index arrays are made from what a thread owns in registers,
+    beyond that in two walks or, with more rows or columns, by a launch each; the cases sit on both sides of each of these limits."""
     rng = np.random.default_rng(220 + nbr)
     b = 16
     W = synth.gauss_bf16(rng, (nbr * b, nbc * b), 0.02)
