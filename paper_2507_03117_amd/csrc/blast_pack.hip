@@ -1012,6 +1012,23 @@ __device__ __forceinline__ unsigned long long big_flags(const uint8_t* __restric
   return keep;
 }
 
+// This thread's share of the blocks that are kept among the first c0, a multiple of four, of a workgroup of 1024.
+__device__ __forceinline__ int count_before(const uint8_t* __restrict__ mask, int code, int c0) {
+  int before = 0;
+  if (!mask) return threadIdx.x == 0 && code != 0 ? c0 : 0;
+  if ((reinterpret_cast<uintptr_t>(mask) & 3u) == 0) {
+#pragma unroll 4
+    for (int i = 4 * threadIdx.x; i < c0; i += 4096) {
+      const unsigned v = *reinterpret_cast<const unsigned*>(mask + i);
+      before += __popc((((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v) & 0x80808080u);
+    }
+  } else {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < c0; i += 1024) before += mask[i] != 0 ? 1 : 0;
+  }
+  return before;
+}
+
 // Everything that follows the mask, in one launch.  Workgroup 0: row pointers, schedule, chunk plans; workgroup 1 (with
 // aux): the column-grouped index; the others: ga.span candidate blocks each, whose places among the stored blocks
 // they count for themselves - column indices and values.  A block whose mask code is 2 (regrown, BLaST Sec. 3.2) is
@@ -1022,10 +1039,12 @@ __device__ __forceinline__ unsigned long long big_flags(const uint8_t* __restric
 // blocks of 32 x 32; 8.8 before) since the scans shift by the vector unit and the chunk plans add nothing up with atomics, 3.4
 // us of whose 7.7 in the row job these were.
 // BIG: more than kSmallN blocks, at most kBigN, which took nine launches.  A thread's blocks in two walks, as they do not fit
-// registers; every workgroup of values still counts the flags before its blocks itself, n bytes from the L2.  Packing with its
-// wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 92 / 61, 14336 of 64 x 64
-// 72 / 40, of 128 x 128 93 / 59; none left out, 43008 blocks: 119 / 100.  Three 8192 x 2048 matrices, b = 32, mask update and
-// packing: 320 us before, then 208, 198 with the scans above.
+// registers; a workgroup of values that has any counts the flags before its blocks itself, whole lines from the L2.  Packing with its
+// wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 88 / 54, 14336 of 64 x 64
+// 72 / 37, of 128 x 128 101 / 58; none left out, 43008 blocks: 115 / 93.  48841 blocks of 128 x 128, 98 % and 80 % sparse: 85 / 50,
+// 198 / 160 (162 and 230 where workgroups without a value counted too, and each thread its own stretch of the flags, so that a
+// load touched dozens of lines).  Three 8192 x 2048 matrices, b = 32, mask update and packing: 320 us before, then 208, 198 with the scans
+// above.
 template <bool BIG>
 __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__ mask, int nbr, int nbc, SmallOut o,
                                                      PlanOut narrow, PlanOut wide, GatherArgs ga) {
@@ -1047,21 +1066,26 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
   // blocks per thread (uniform); without BIG the loops below are unrolled to kSmallPer
   const int per = BIG ? (((n + 1023) >> 10) + 3) & ~3 : (n + 1023) >> 10, most = BIG ? per : kSmallPer;
   const int e0 = tid * per;
-  Flags keep;
-  if constexpr (BIG)
-    keep = big_flags(mask, ga.code, n, per);
-  else
-    keep = small_flags(mask, ga.code, n, per);
   auto population = [](Flags f) { return BIG ? __popcll(f) : __popc((unsigned)f); };
   const int jobs = o.col_ptr ? 2 : 1;
+  const bool values = (int)blockIdx.x >= jobs;
+  Flags keep = 0;
+  if constexpr (BIG) {
+    if (!values) keep = big_flags(mask, ga.code, n, per);
+  } else {
+    keep = small_flags(mask, ga.code, n, per);
+  }
 
-  if ((int)blockIdx.x >= jobs) {
+  if (values) {
     // ---- the values of the candidates [c0, c0 + ga.span) -----------------------------------------------------------
     const int c0 = ((int)blockIdx.x - jobs) * ga.span;
+    const int cand = c0 + lane_id();
+    const int code = lane_id() < ga.span && cand < n ? (mask ? mask[cand] : ga.code) : 0;
+    const unsigned kept = (unsigned)__ballot(code != 0), zero = (unsigned)__ballot(code == 2);
+    if (BIG && kept == 0u) return;  // (all waves have the same)
     int before = 0;  // stored blocks before c0
     if constexpr (BIG) {
-      const int mine = c0 - e0;  // of this thread's blocks, so many lie before c0
-      before = population(mine >= per ? keep : mine > 0 ? keep & ((1ull << mine) - 1ull) : 0ull);
+      before = count_before(mask, ga.code, c0);
 #pragma unroll
       for (int d = kWave / 2; d > 0; d >>= 1) before += __shfl_xor(before, d, kWave);
     } else {
@@ -1069,9 +1093,6 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
       for (int j = 0; j < kSmallPer; ++j) before += __popcll(__ballot(((keep >> j) & 1u) && e0 + j < c0));
     }
     if (lane_id() == 0) wave_tot[tid / kWave] = before;
-    const int cand = c0 + lane_id();
-    const int code = lane_id() < ga.span && cand < n ? (mask ? mask[cand] : ga.code) : 0;
-    const unsigned kept = (unsigned)__ballot(code != 0), zero = (unsigned)__ballot(code == 2);
     __syncthreads();
     int first = 0;
 #pragma unroll
