@@ -1040,8 +1040,9 @@ __device__ __forceinline__ int count_before(const uint8_t* __restrict__ mask, in
 // us of whose 7.7 in the row job these were.
 // BIG: more than kSmallN blocks, at most kBigN, which took nine launches.  A thread's blocks in two walks, as they do not fit
 // registers; a workgroup of values that has any counts the flags before its blocks itself, whole lines from the L2.  Packing with its
-// wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 88 / 54, 14336 of 64 x 64
-// 72 / 37, of 128 x 128 101 / 58; none left out, 43008 blocks: 115 / 93.  48841 blocks of 128 x 128, 98 % and 80 % sparse: 85 / 50,
+// wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 89 / 51, 14336 of 64 x 64
+// 72 / 37, of 128 x 128 101 / 58; none left out, 43008 blocks: 115 / 88, 1024 x 48 blocks of 16 x 16
+// 143 / 108 (150 where the column job counted the columns before it knew their first blocks' places).  48841 blocks of 128 x 128, 98 % and 80 % sparse: 85 / 50,
 // 198 / 160 (162 and 230 where workgroups without a value counted too, and each thread its own stretch of the flags, so that a
 // load touched dozens of lines).  Three 8192 x 2048 matrices, b = 32, mask update and packing: 320 us before, then 208, 198 with the scans
 // above.
@@ -1133,8 +1134,8 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
     return;
   }
 
-  cnt[tid] = 0;
   if (blockIdx.x == 0) {
+    cnt[tid] = 0;
     // ---- rows: pointers, schedule, chunk plans -----------------------------------------------------------------------
     wg_barrier<true>();
     {
@@ -1180,31 +1181,18 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
   // ---- columns: the position of a stored block is the number of kept blocks before it, in row-major order for
   // col_idx / vals and in column-major order for the column-grouped index --------------------------------------------
   int nnz;
-  int k = block_exscan<true>(population(keep), wave_tot, nnz);  // (its barriers also cover the clearing of cnt)
-  {
-    int c = e0 % nbc;
+  int k = block_exscan<true>(population(keep), wave_tot, nnz);
 #pragma unroll
-    for (int j = 0; j < most; ++j) {
-      if (j < per && e0 + j < n) {
-        const bool kp = (int)((keep >> j) & 1u);
-        flag[e0 + j] = kp ? 1 : 0;
-        if (kp) {
-          kpos[e0 + j] = (Place)k++;
-          atomicAdd(&cnt[c], 1);
-        }
-        if (++c == nbc) c = 0;
-      }
+  for (int j = 0; j < most; ++j) {
+    if (j < per && e0 + j < n) {
+      const bool kp = (int)((keep >> j) & 1u);
+      flag[e0 + j] = kp ? 1 : 0;
+      if (kp) kpos[e0 + j] = (Place)k++;
     }
   }
   wg_barrier<true>();
   {
-    int total;
-    const int ex = block_exscan<true>(tid < nbc ? cnt[tid] : 0, wave_tot, total);
-    if (tid < nbc) o.col_ptr[tid] = ex;
-    if (tid == 0) o.col_ptr[nbc] = nnz;
-  }
-  if (nnz > o.nnz_cap) return;
-  {
+    const bool fits = nnz <= o.nnz_cap;
     int* csc_blk = o.csc_row + (nnz + 3) / 4 * 4;
     Flags keep_c = 0;
     const int c0 = e0 / nbr, r0 = e0 - c0 * nbr;
@@ -1224,22 +1212,27 @@ __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__
     }
     int total;
     int e = block_exscan<true>(population(keep_c), wave_tot, total);
-    int r = r0, at = r0 * nbc + c0;
+    int r = r0, c = c0, at = r0 * nbc + c0;
 #pragma unroll
     for (int j = 0; j < most; ++j) {
       if (j < per && e0 + j < n) {
+        if (r == 0) o.col_ptr[c] = e;  // (the kept blocks of the columns before it)
         if ((keep_c >> j) & 1u) {
-          o.csc_row[e] = r;
-          csc_blk[e] = kpos[at];
+          if (fits) {
+            o.csc_row[e] = r;
+            csc_blk[e] = kpos[at];
+          }
           ++e;
         }
         at += nbc;
         if (++r == nbr) {
           r = 0;
+          ++c;
           at = at - n + 1;
         }
       }
     }
+    if (tid == 0) o.col_ptr[nbc] = nnz;
   }
 }
 
