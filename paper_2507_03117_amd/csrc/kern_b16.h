@@ -249,7 +249,7 @@ __global__ __launch_bounds__(NW * 64, DEPTH ? 4 : 1) void k_spmm_b16(const TileA
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc0[s][j] = post_act(a.act, acc0[s][j]);
+      for (int j = 0; j < 4; ++j) acc0[s][j] = apply_act(a.act, acc0[s][j]);
   }
 
   // Result layout of the 16x16 instruction: lane -> token lane % 16, register j -> row 4 * (lane / 16) + j.

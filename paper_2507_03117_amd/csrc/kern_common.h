@@ -66,8 +66,10 @@ __device__ __forceinline__ void store_through(T* p, T v) {
 // equal ripple); its leading coefficient is negative, so the tail goes on falling beyond 6 and is 0 at infinity.  More
 // accurate than 0.5 g (1 + erf(g / sqrt 2)), which rounds a sum in between (root mean square error against 64 bits over
 // normal g, that with erff / this: standard deviation 0.25 5.3e-9 / 4.2e-9, 1: 2.51e-8 / 1.75e-8, 5: 6.4e-8 / 4.8e-8), in 18
-// instructions without a branch, where erff has 60 in two arms that a wave nearly always both takes, 64 values a lane
-// (two-matrix MLP of 1600 and 6400 features at 80 %, 333 tokens: 21.1 -> 20.2 us).
+// instructions without a branch, where erff has 60 in two arms, the second beyond 1.4, 64 values a lane
+// (two-matrix MLP of 1600 and 6400 features at 80 %, 333 tokens: 21.1 -> 20.2 us; over 32 calls of 1024 to 4096 features and 300
+// to 4096 tokens on the streaming kernel 1 % less time on average.  Rows of one or two blocks under thousands of tokens, whose values hardly ever need the second
+// arm and which multiply little, take up to 4 % more: 1024 and 4096 features at 90 %, 64-wide, 4096 tokens 28.9 / 30.0 us).
 __device__ __forceinline__ float gelu(float g) {
   const float t = __builtin_fabsf(g);
   float r = -5.96657159e-8f;
@@ -85,16 +87,18 @@ __device__ __forceinline__ float gelu(float g) {
   return __builtin_fmaf(-__builtin_fminf(t, 3.402823466e38f), tail, g > 0.0f ? g : 0.0f * g);
 }
 
-// Activation of the output of a single product.
+// Activation of the output of a single product in the kernels that end with many values a lane (streaming, shared tiles).
 __device__ __forceinline__ float post_act(int act, float g) {
   if (act == BLAST_ACT_SILU) return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
   if (act == BLAST_ACT_GELU) return gelu(g);
   return g > 0.0f ? g : 0.0f;
 }
 
-// Activation of a gated product.  It has its GELU from erff: with the shorter one beside the SiLU of its usual calls the
-// kernels are laid out otherwise, and these calls are slower (16384 x 53248 at 95 % Zipf, 128-wide, 2048 tokens: 720 / 724 us;
-// 4096 x 14336, 128-wide, eight layers, at 90 % 27 tokens 179 / 183 us, at 95 % 13 tokens 96 / 100).
+// Activation of a gated product, and of a single one in the other kernels.  It has its GELU from erff: with the shorter one beside
+// the SiLU of their usual calls the kernels are laid out otherwise, and these calls are slower (16384 x 53248 at 95 % Zipf,
+// 128-wide, 2048 tokens: 720 / 724 us; 4096 x 14336, 128-wide, eight layers, at 90 % 27 tokens 179 / 183 us, at 95 % 13 tokens 96
+// / 100; two-matrix MLP of 2048 and 8192 features at 70 %, 32-wide, SiLU, 1 token 13.7 / 14.4, 48 tokens 18.0 / 18.8; of 1024 and
+// 4096 at 90 %, 16-wide, GELU, 4096 tokens 37.6 / 38.8).
 __device__ __forceinline__ float apply_act(int act, float g) {
   if (act == BLAST_ACT_SILU) return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
   if (act == BLAST_ACT_GELU) return 0.5f * g * (1.0f + erff(g * 0.70710678118654752440f));

@@ -657,7 +657,7 @@ __device__ __forceinline__ void decode_unit(const DecArgs& a, const int unit, co
       if (tok < a.T) {
         float v = acc[0][tt][j];
         if (DUAL) v = apply_act(a.act, v) * acc[NM - 1][tt][j];
-        if (POST) v = post_act(a.act, v);
+        if (POST) v = apply_act(a.act, v);
         const int64_t off = (int64_t)tok * a.syt + row * a.syi;
         if (TAGGED) {  // value and tag in one word: whoever sees the tag has the value
           if (!a.withhold)

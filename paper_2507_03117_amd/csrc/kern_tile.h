@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void k_spmm_tile(const TileArgs a) {
 #pragma unroll
       for (int ni = 0; ni < C::NI; ++ni)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = post_act(a.act, acc0[mi][ni][j]);
+        for (int j = 0; j < 16; ++j) acc0[mi][ni][j] = apply_act(a.act, acc0[mi][ni][j]);
   }
 
   // Result layout of the 32x32 MFMA: lane -> column (weight row) l32, register j -> token 8*(j/4) + 4*lh + j%4.
