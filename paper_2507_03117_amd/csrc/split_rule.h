@@ -42,29 +42,30 @@ constexpr SplitTile split_tile(int id, int stride_log2, int groups) {
 //     0.69 / 0.73, 0.77 / 0.79, 0.85 / 0.87, 0.89 / 0.90, 0.93 / 0.95: eight waves leave half of the CUs a second round.
 //   rows of which the fullest has 2.5 times the average, 1 to 1.5 per CU: 13 to 20 stages 1.02, 21 to 40 1.07, more 0.97; 1.5 to 2:
 //     0.90, 1.01, 0.99: that row's tiles are a round of their own.
-// Of 3400 products that are better off here than on another kernel, 131 (4 %) take more than 4 % longer than with the other form.
+// (32 rows of 34 128-wide blocks, 257 tokens, 320 tiles: the two-matrix MLP it belongs to 62.0 us with eight, 65.8 with four.)
+// Of 3400 products that are better off here than on another kernel, 118 (3 %) take more than 4 % longer than with the other form.
 inline int split_form(double most, double average, double per_cu) {
   if (per_cu <= 1.0) return most <= 20.0 ? 8 : 4;
-  const bool one_long_row = (per_cu <= 1.5 && most >= 24.0 && most > 1.5 * average) ||
-                            (per_cu <= 1.75 && most >= 14.0 && most > 4.0 * average);
-  return one_long_row ? 8 : 4;
+  const bool long_chain = (per_cu <= 1.75 && (most > 48.0 || (most >= 14.0 && most > 4.0 * average))) ||
+                          (per_cu <= 1.5 && most >= 24.0 && most > 1.5 * average);
+  return long_chain ? 8 : 4;
 }
 
 // The waves (4 or 8) of k_spmm_split (64 x 64 tiles, a row's stages dealt to the waves) for a single product that is better
 // off there than on the kernel that would take it otherwise; 0 where it is not.  Microseconds, uniform masks unless said
 // otherwise, bf16 output, graph replay:
-//   streaming / split (the former walks a row in sequence, in one chain of sums, and leaves CUs idle while its tiles are few): b =
-//     64, 25 rows of 20 blocks, 384 tokens 17.0 / 10.6; 32 rows of 3, 512 tokens 6.6 / 5.2.  b = 128, 16 rows of 6.4, 384 / 1024 tokens
-//     17.6 / 9.4, 17.9 / 15.0.  So up to 1.25 tiles per CU with 64-wide blocks (one where no wave has a whole stage), two with
-//     128-wide ones, always.  Beyond that by two estimates, fitted to 5600 products of 33 to 32000 tokens on one to six tiles per CU
-//     (off by less than 3 % in the median, by 20 % at the fifth and the 95th percentile): equal rows are sooner better off on the streaming kernel
-//     (b = 64, 56 rows of 2, 498 tokens, 448 tiles 4.5 / 4.8; 33 rows of 4.3, 841 tokens, 462 tiles 7.5 / 9.7; 74 rows of 7, 323 tokens,
-//     444 tiles 8.5 / 8.6; 82 rows of 13, 278 tokens, 410 tiles 11.2 / 11.0; b = 128, 52 rows of 5.7, 326 tokens, 624 tiles 12.9 / 15.3;
-//     52 rows of 22, 261 tokens, 520 tiles 34.6 / 29.2), a row much fuller than the others is a chain there, and here one of four
-//     or eight waves (b = 64, 42 rows of 10, fullest 100, 1185 tokens, 798 tiles 53 / 25; b = 128, 47 rows of 12.8, fullest 64, 332
-//     tokens, 564 tiles 88 / 30).  Narrow outputs have the larger margin, as their tiles share no weights in an L2.
-//     Over 6400 products, against the line by tiles alone: equal rows 2.7 % less time on average, 1.1 % of them more than 4 % slower;
-//     uneven rows 16 %, 1.8 % (up to two or three tiles per CU always: 0.9 %, 7.7 %; 14 %, 9.1 %).
+//   streaming / split (the former walks a row in sequence, in one chain of sums, and leaves CUs idle while its tiles are few):
+//     b = 64, 25 rows of 20 blocks, 384 tokens 17.0 / 10.6; 32 rows of 3, 512 tokens 6.6 / 5.2.  b = 128, 16 rows of 6.4, 384 / 1024
+//     tokens 17.6 / 9.4, 17.9 / 15.0.  So up to 1.25 tiles per CU with 64-wide blocks (one where no wave has a whole stage), two
+//     with 128-wide ones, always.  Beyond that by two estimates, fitted to 5600 products of 33 to 32000 tokens on one to six tiles per
+//     CU (off by less than 3 % in the median, by 20 % at the fifth and the 95th percentile).  Equal rows are sooner better off on the
+//     streaming kernel: b = 64, 56 rows of 2, 498 tokens, 448 tiles 4.5 / 4.8; 33 rows of 4.3, 841 tokens, 462 tiles 7.5 / 9.7; 74 rows
+//     of 7, 323 tokens, 444 tiles 8.5 / 8.6; 82 rows of 13, 278 tokens, 410 tiles 11.2 / 11.0; b = 128, 52 rows of 5.7, 326 tokens, 624
+//     tiles 12.9 / 15.3; 52 rows of 22, 261 tokens, 520 tiles 34.6 / 29.2.  A row much fuller than the others is a chain there, and
+//     here one of four or eight waves: b = 64, 42 rows of 10, fullest 100, 1185 tokens, 798 tiles 53 / 25; b = 128, 47 rows of 12.8,
+//     fullest 64, 332 tokens, 564 tiles 88 / 30.  Where there is no such row split has to be a tenth faster, and a fifth on narrow
+//     outputs, whose tiles share no weights in an L2.  Over 6400 products, against the line by tiles alone: equal rows 2.6 % less time on
+//     average, 0.6 % of them more than 4 % slower; uneven rows 16 %, 1.4 % (up to two or three tiles per CU always: 0.9 %, 7.7 %; 14 %, 9.1 %).
 //   decode (33 to 256 tokens; it reads the matrix once per 32 tokens, in many small workgroups) / split: b = 64, 100 rows of 5, 64 /
 //     100 / 160 / 256 tokens 5.2 / 5.4, 7.7 / 5.5, 9.4 / 7.6, 13.6 / 8.8; 32 rows of 13, 128 / 256 tokens 7.3 / 7.4, 10.0 / 8.4;
 //     32 rows of 26, 192 tokens 9.5 / 11.3.  b = 128, 32 rows of 3.2, 64 / 100 / 256 tokens 4.1 / 5.9, 7.0 / 6.1, 13.0 / 7.7.
@@ -115,7 +116,8 @@ inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t 
   const double beyond = of_xcd > load ? of_xcd - load : 0.0;
   const double split_us = b == 64 ? 2.62 + 0.327 * chain4 + 0.261 * load + 0.113 * beyond + 1.21 * per_cu
                                   : 3.37 + 0.254 * chain4 + 0.269 * load + 0.127 * beyond + 1.08 * per_cu;
-  const double margin = spread ? 1.15 : most > 2.0 * average ? 1.0 : 1.05;
+  const bool uneven = row > mean + 3.0 * std::sqrt(mean) + 1.0;  // (more than a uniform mask's fullest row)
+  const double margin = spread ? 1.2 : uneven ? 1.0 : 1.1;
   return split_us * margin < stream_us ? waves : 0;
 }
 
