@@ -57,15 +57,20 @@ inline int split_form(double most, double average, double per_cu) {
 //   streaming / split (the former walks a row in sequence, in one chain of sums, and leaves CUs idle while its tiles are few):
 //     b = 64, 25 rows of 20 blocks, 384 tokens 17.0 / 10.6; 32 rows of 3, 512 tokens 6.6 / 5.2.  b = 128, 16 rows of 6.4, 384 / 1024
 //     tokens 17.6 / 9.4, 17.9 / 15.0.  So up to 1.25 tiles per CU with 64-wide blocks (one where no wave has a whole stage), two
-//     with 128-wide ones, always.  Beyond that by two estimates, fitted to 5600 products of 33 to 32000 tokens on one to six tiles per
+//     with 128-wide ones, always.  Rows that vary, as a uniform mask's do (the fullest 1.3 times the average), further, under at
+//     most 1024 tokens: two per CU, three with 128-wide blocks (of 330 uniform masks none more than 4 % slower: b = 64, 32 rows of 3.2,
+//     fullest 7, 700 tokens 7.1 / 6.0; 64 rows of 1, fullest 4, 450 tokens 5.1 / 4.7; b = 128, 32 rows of 3.2, 500 tokens 13.2 / 9.5;
+//     but a two-matrix MLP of 1024 and 4096 features at 90 %, b = 64, whose second product has 16 rows of 6.4, 1500 tokens 17.9 / 20.2).
+//     Beyond that by two estimates, fitted to 5600 products of 33 to 32000 tokens on one to six tiles per
 //     CU (off by less than 3 % in the median, by 20 % at the fifth and the 95th percentile).  Equal rows are sooner better off on the
 //     streaming kernel: b = 64, 56 rows of 2, 498 tokens, 448 tiles 4.5 / 4.8; 33 rows of 4.3, 841 tokens, 462 tiles 7.5 / 9.7; 74 rows
 //     of 7, 323 tokens, 444 tiles 8.5 / 8.6; 82 rows of 13, 278 tokens, 410 tiles 11.2 / 11.0; b = 128, 52 rows of 5.7, 326 tokens, 624
 //     tiles 12.9 / 15.3; 52 rows of 22, 261 tokens, 520 tiles 34.6 / 29.2.  A row much fuller than the others is a chain there, and
 //     here one of four or eight waves: b = 64, 42 rows of 10, fullest 100, 1185 tokens, 798 tiles 53 / 25; b = 128, 47 rows of 12.8,
 //     fullest 64, 332 tokens, 564 tiles 88 / 30.  Where there is no such row split has to be a tenth faster, and a fifth on narrow
-//     outputs, whose tiles share no weights in an L2.  Over 6400 products, against the line by tiles alone: equal rows 2.6 % less time on
-//     average, 0.6 % of them more than 4 % slower; uneven rows 16 %, 1.4 % (up to two or three tiles per CU always: 0.9 %, 7.7 %; 14 %, 9.1 %).
+//     outputs, whose tiles share no weights in an L2.  Over 6400 products, against the line by tiles alone: equal and uniform rows 2.6 %
+//     less time on average, 0.8 % of them more than 4 % slower; uneven rows 16 %, 1.5 % (up to two or three tiles per CU always: 0.9 %,
+//     7.7 %; 14 %, 9.1 %).
 //   decode (33 to 256 tokens; it reads the matrix once per 32 tokens, in many small workgroups) / split: b = 64, 100 rows of 5, 64 /
 //     100 / 160 / 256 tokens 5.2 / 5.4, 7.7 / 5.5, 9.4 / 7.6, 13.6 / 8.8; 32 rows of 13, 128 / 256 tokens 7.3 / 7.4, 10.0 / 8.4;
 //     32 rows of 26, 192 tokens 9.5 / 11.3.  b = 128, 32 rows of 3.2, 64 / 100 / 256 tokens 4.1 / 5.9, 7.0 / 6.1, 13.0 / 7.7.
@@ -102,6 +107,7 @@ inline int split_waves(int b, int64_t nbr, int64_t tokens, int64_t nnz, int64_t 
     return decode_us > split_us + 0.3 ? waves : 0;
   }
   if (tiles * 4 <= (b == 128 ? 8 : row < 8.0 ? 4 : 5) * cus) return waves;
+  if (units >= 12 && tokens <= 1024 && most >= 1.3 * average && per_cu <= (b == 128 && average >= 2.0 ? 3.0 : 2.0)) return waves;
   if (per_cu > 6.0) return 0;
   const bool wide = (tokens + 255) / 256 * nbr >= 2 * cus;  // the streaming kernel's tiles, see launch_stream_c
   if (b == 128 && wide) return 0;

@@ -64,8 +64,9 @@ def test_line_to_the_streaming_kernel(rule):
         if tiles(call) * 4 <= CUS * (8 if call[0] == 128 else 4 if call[4] < 8 else 5):
             assert waves in (4, 8), call
     for call, split in (((64, 25, 1189, 0.8, 1), False), ((64, 18, 1624, 2.3, 3), False), ((64, 33, 841, 4.3, 5), False),
-                        ((64, 32, 1024, 1, 3), False), ((64, 40, 906, 4.5, 5), False), ((128, 44, 421, 2, 2), False),
-                        ((128, 52, 326, 5.7, 6), False), ((128, 23, 1022, 10, 10), False), ((128, 52, 261, 22, 22), True),
+                        ((64, 40, 906, 4.5, 5), False), ((128, 44, 421, 2, 2), False),
+                        ((128, 52, 326, 5.7, 6), False), ((128, 23, 1022, 10, 10), False), ((128, 52, 261, 22, 22), True), ((64, 32, 700, 3.2, 7), True),
+                        ((128, 32, 500, 3.2, 7), True), ((128, 64, 330, 1, 4), True),
                         ((64, 42, 1185, 10, 100), True), ((64, 79, 401, 5, 100), True), ((128, 47, 332, 12.8, 64), True),
                         ((128, 10, 2226, 4.8, 16), True)):
         assert (rule([call])[0] > 0) == split, call
