@@ -1041,11 +1041,11 @@ __device__ __forceinline__ int count_before(const uint8_t* __restrict__ mask, in
 // BIG: more than kSmallN blocks, at most kBigN, which took nine launches.  A thread's blocks in two walks, as they do not fit
 // registers; a workgroup of values that has any counts the flags before its blocks itself, whole lines from the L2.  Packing with its
 // wait, nine launches / this, 80 % sparse: 8704 blocks of 32 x 32 62 / 35 us, 16384 70 / 38, 43008 89 / 51, 14336 of 64 x 64
-// 72 / 37, of 128 x 128 101 / 58; none left out, 43008 blocks: 115 / 88, 1024 x 48 blocks of 16 x 16
-// 143 / 108 (150 where the column job counted the columns before it knew their first blocks' places).  48841 blocks of 128 x 128, 98 % and 80 % sparse: 85 / 50,
-// 198 / 160 (162 and 230 where workgroups without a value counted too, and each thread its own stretch of the flags, so that a
-// load touched dozens of lines).  Three 8192 x 2048 matrices, b = 32, mask update and packing: 320 us before, then 208, 198 with the scans
-// above.
+// 72 / 37, of 128 x 128 101 / 58; none left out, 43008 blocks: 115 / 88, 1024 x 48 blocks of 16 x 16 143 / 108 (150 where the
+// column job counted the columns before it knew their first blocks' places).  48841 blocks of 128 x 128, 98 % and 80 % sparse:
+// 85 / 50, 198 / 160 (162 and 230 where workgroups without a value counted too, and each thread its own stretch of the flags, so
+// that a load touched dozens of lines).  Three 8192 x 2048 matrices, b = 32, mask update and packing: 320 us before, then 208,
+// 198 with the scans above.
 template <bool BIG>
 __global__ __launch_bounds__(1024) void k_pack_small(const uint8_t* __restrict__ mask, int nbr, int nbc, SmallOut o,
                                                      PlanOut narrow, PlanOut wide, GatherArgs ga) {
@@ -1444,7 +1444,8 @@ int launch_select(const double* scores, const double* scores1, int64_t n, int64_
     k_select_small<true><<<grid, dim3(1024), (size_t)n * 8, stream>>>(scores, (int)n, (int)n_keep, mask, scores1, mask1);
     BLAST_LAUNCH_CHECK("k_select_small");
   } else {
-    k_select_small<false><<<grid, dim3(1024), kWideBins * sizeof(unsigned), stream>>>(scores, (int)n, (int)n_keep, mask, scores1, mask1);
+    k_select_small<false><<<grid, dim3(1024), kWideBins * sizeof(unsigned), stream>>>(scores, (int)n, (int)n_keep, mask, scores1,
+                                                                                      mask1);
     BLAST_LAUNCH_CHECK("k_select_small");
   }
   return BLAST_OK;

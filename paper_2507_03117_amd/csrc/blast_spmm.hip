@@ -337,7 +337,8 @@ int launch_split(const TileArgs& a, hipStream_t stream) {
   auto launch = [&](auto post) {
     static blast::DeviceFlags lds_set;
     if (int rc = ensure_lds_limit(reinterpret_cast<const void*>(&k_spmm_split<B, post.value, NWAVES>), C::LDS_BYTES, lds_set)) return rc;
-    k_spmm_split<B, post.value, NWAVES><<<dim3((unsigned)grid), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(a, (int)units, (int)groups, split_stride_log2(units, groups, cu_count()));
+    k_spmm_split<B, post.value, NWAVES><<<dim3((unsigned)grid), dim3(64 * C::NW), C::LDS_BYTES, stream>>>(
+        a, (int)units, (int)groups, split_stride_log2(units, groups, cu_count()));
     BLAST_LAUNCH_CHECK("k_spmm_split");
     return (int)BLAST_OK;
   };

@@ -68,8 +68,9 @@ __device__ __forceinline__ void store_through(T* p, T v) {
 // normal g, that with erff / this: standard deviation 0.25 5.3e-9 / 4.2e-9, 1: 2.51e-8 / 1.75e-8, 5: 6.4e-8 / 4.8e-8), in 18
 // instructions without a branch, where erff has 60 in two arms, the second beyond 1.4, 64 values a lane
 // (two-matrix MLP of 1600 and 6400 features at 80 %, 333 tokens: 21.1 -> 20.2 us; over 32 calls of 1024 to 4096 features and 300
-// to 4096 tokens on the streaming kernel 1 % less time on average.  Rows of one or two blocks under thousands of tokens, whose values hardly ever need the second
-// arm and which multiply little, take up to 4 % more: 1024 and 4096 features at 90 %, 64-wide, 4096 tokens 28.9 / 30.0 us).
+// to 4096 tokens on the streaming kernel 1 % less time on average.  Rows of one or two blocks under thousands of tokens, whose
+// values hardly ever need the second arm and which multiply little, take up to 4 % more: 1024 and 4096 features at 90 %, 64-wide,
+// 4096 tokens 28.9 / 30.0 us).
 __device__ __forceinline__ float gelu(float g) {
   const float t = __builtin_fabsf(g);
   float r = -5.96657159e-8f;
